@@ -47,23 +47,25 @@ __device__ __forceinline__ int shfl_idx(int v, int src) {
     return __builtin_amdgcn_ds_bpermute(src << 2, v);
 }
 
-// XOR butterfly exchange inside the wavefront. Distances 1 and 2 stay in a
-// quad (DPP quad_perm), 4..16 use ds_swizzle's bit-mask mode inside 32-lane
-// halves, 32 crosses halves through ds_bpermute.
-template <int J>
+// Exchange inside the wavefront with the lane whose number differs in the bits
+// of M. 1, 2 and 3 stay in a quad (DPP quad_perm), 7 and 15 mirror half a row
+// and a row, 8 rotates a row by 8 lanes (all DPP); 4, 16 and 31 use
+// ds_swizzle's bit-mask mode inside 32-lane halves, 32 and 63 cross halves
+// through ds_bpermute.
+template <int M>
 __device__ __forceinline__ int shfl_xor_c(int v) {
-    if constexpr (J == 1) {
-        // quad_perm [1,0,3,2]
-        return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
-    } else if constexpr (J == 2) {
-        // quad_perm [2,3,0,1]
-        return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
-    } else if constexpr (J >= 4 && J <= 16) {
-        // bit-mask mode: and_mask = 0x1f, or_mask = 0, xor_mask = J
-        return __builtin_amdgcn_ds_swizzle(v, (J << 10) | 0x1F);
-    } else {
-        return __builtin_amdgcn_ds_bpermute((lane_id() ^ J) << 2, v);
-    }
+    static_assert(M == 1 || M == 2 || M == 3 || M == 4 || M == 7 || M == 8 || M == 15 || M == 16 ||
+                      M == 31 || M == 32 || M == 63, "exchange masks in use");
+    if constexpr (M == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
+    else if constexpr (M == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
+    else if constexpr (M == 3) return __builtin_amdgcn_mov_dpp(v, 0x1B, 0xF, 0xF, true);
+    else if constexpr (M == 7) return __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);
+    else if constexpr (M == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);
+    else if constexpr (M == 15) return __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true);
+    else if constexpr (M < 32)
+        // bit-mask mode: and_mask = 0x1f, or_mask = 0, xor_mask = M
+        return __builtin_amdgcn_ds_swizzle(v, (M << 10) | 0x1F);
+    else return __builtin_amdgcn_ds_bpermute((lane_id() ^ M) << 2, v);
 }
 
 template <int J>
@@ -74,25 +76,49 @@ __device__ __forceinline__ unsigned long long shfl_xor_c64(unsigned long long v)
     return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
 }
 
-__device__ __forceinline__ int shfl_up1_or(int v, int d, int fill) {
-    int l = lane_id();
-    int t = __builtin_amdgcn_ds_bpermute((l - d) << 2, v);
-    return l >= d ? t : fill;
+// value of the lane below / above (lane 0 / lane 63: `edge`), one DPP move
+__device__ __forceinline__ int wave_shr1(int v, int edge) {
+    return __builtin_amdgcn_update_dpp(edge, v, 0x138, 0xF, 0xF, false);
+}
+__device__ __forceinline__ int wave_shl1(int v, int edge) {
+    return __builtin_amdgcn_update_dpp(edge, v, 0x130, 0xF, 0xF, false);
+}
+__device__ __forceinline__ double wave_shr1_v(double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const int lo = wave_shr1((int)(unsigned)b, 0), hi = wave_shr1((int)(unsigned)(b >> 32), 0);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+__device__ __forceinline__ float wave_shr1_v(float v) {
+    return __int_as_float(wave_shr1(__float_as_int(v), 0));
 }
 
-// inclusive prefix sum over the wavefront
+// Inclusive prefix sum and maximum over the wavefront: four DPP row shifts
+// scan every row of 16 lanes, two row broadcasts carry the rows on. (A scan by
+// LDS permutes waits on the LDS six times.)
 __device__ __forceinline__ int wave_incl_scan(int v) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) v += shfl_up1_or(v, d, 0);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return v;
+}
+__device__ __forceinline__ int wave_incl_max(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));
     return v;
 }
 
 __device__ __forceinline__ int wave_bcast(int v, int src) { return shfl_idx(v, src); }
 
+// the sum over the wavefront, in every lane
 __device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __builtin_amdgcn_ds_bpermute((lane_id() ^ d) << 2, v);
-    return v;
+    return __builtin_amdgcn_readlane(wave_incl_scan(v), 63);
 }
 
 // Exclusive prefix sum over a workgroup of kBlock threads. `tmp` holds

@@ -63,23 +63,6 @@ __device__ __forceinline__ int shfl_up_i(int v, int d) {
     const int l = lane_id();
     return __builtin_amdgcn_ds_bpermute((l >= d ? l - d : l) << 2, v);
 }
-__device__ __forceinline__ double shfl_up_v(double v, int d) {
-    const unsigned long long b = __double_as_longlong(v);
-    const int lo = shfl_up_i((int)(unsigned)b, d), hi = shfl_up_i((int)(unsigned)(b >> 32), d);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-__device__ __forceinline__ float shfl_up_v(float v, int d) {
-    return __int_as_float(shfl_up_i(__float_as_int(v), d));
-}
-
-template <int J>
-__device__ __forceinline__ unsigned kx(unsigned v) {
-    return (unsigned)shfl_xor_c<J>((int)v);
-}
-template <int J>
-__device__ __forceinline__ unsigned long long kx(unsigned long long v) {
-    return shfl_xor_c64<J>(v);
-}
 
 // Median of three unsigned 32-bit values where c is 0 (the smaller of x and
 // y) or all ones (the larger): one v_med3_u32 takes a compare-exchange's side
@@ -92,522 +75,482 @@ __device__ __forceinline__ unsigned med3u(unsigned x, unsigned y, unsigned c) {
     return r;
 }
 
-// one compare-exchange stage between lanes at distance J (J >= 1)
-template <typename K, int KPL, int J, int S>
-__device__ __forceinline__ void lane_stage(K (&key)[KPL], int k, int lane) {
-    const int s0 = lane * KPL;
-    const bool asc = k == S || (s0 & k) == 0;
-    const bool take_min = asc == ((lane & J) == 0);
+// compare-exchange of two registers of one lane
+__device__ __forceinline__ void minmax(unsigned &lo, unsigned &hi) {
+    unsigned a, b;
+    asm("v_min_u32 %0, %2, %3\n\tv_max_u32 %1, %2, %3" : "=&v"(a), "=v"(b) : "v"(lo), "v"(hi));
+    lo = a;
+    hi = b;
+}
+__device__ __forceinline__ void minmax(unsigned long long &lo, unsigned long long &hi) {
+    const bool sw = lo > hi;
+    const unsigned long long a = sw ? hi : lo, b = sw ? lo : hi;
+    lo = a;
+    hi = b;
+}
+
+// Four registers of a cross-lane stage whose exchange is a DPP move: each
+// register takes the median of itself, the other lane's register (its own
+// number, or with `flip` the mirrored one) and c. The moves, the wait that
+// DPP reads need after a VALU write and the medians are one block: the
+// compiler does not see the medians' writes as a hazard for its own moves.
+#define SPG_DPP_BLOCK(CTRL, S0, S1, S2, S3)                                    \
+    asm volatile(                                                              \
+        "s_nop 1\n\t"                                                          \
+        "v_mov_b32_dpp %4, " S0 " " CTRL " row_mask:0xf bank_mask:0xf\n\t"     \
+        "v_mov_b32_dpp %5, " S1 " " CTRL " row_mask:0xf bank_mask:0xf\n\t"     \
+        "v_mov_b32_dpp %6, " S2 " " CTRL " row_mask:0xf bank_mask:0xf\n\t"     \
+        "v_mov_b32_dpp %7, " S3 " " CTRL " row_mask:0xf bank_mask:0xf\n\t"     \
+        "v_med3_u32 %0, %0, %4, %8\n\t"                                        \
+        "v_med3_u32 %1, %1, %5, %8\n\t"                                        \
+        "v_med3_u32 %2, %2, %6, %8\n\t"                                        \
+        "v_med3_u32 %3, %3, %7, %8"                                            \
+        : "+v"(k0), "+v"(k1), "+v"(k2), "+v"(k3), "=&v"(t0), "=&v"(t1),        \
+          "=&v"(t2), "=&v"(t3)                                                 \
+        : "v"(c))
+
+template <int MASK, bool FLIP>
+__device__ __forceinline__ void dpp_block(unsigned &k0, unsigned &k1, unsigned &k2, unsigned &k3,
+                                          unsigned c) {
+    unsigned t0, t1, t2, t3;
+    if constexpr (MASK == 1 && FLIP) SPG_DPP_BLOCK("quad_perm:[1,0,3,2]", "%3", "%2", "%1", "%0");
+    else if constexpr (MASK == 1) SPG_DPP_BLOCK("quad_perm:[1,0,3,2]", "%0", "%1", "%2", "%3");
+    else if constexpr (MASK == 2) SPG_DPP_BLOCK("quad_perm:[2,3,0,1]", "%0", "%1", "%2", "%3");
+    else if constexpr (MASK == 3) SPG_DPP_BLOCK("quad_perm:[3,2,1,0]", "%3", "%2", "%1", "%0");
+    else if constexpr (MASK == 7) SPG_DPP_BLOCK("row_half_mirror", "%3", "%2", "%1", "%0");
+    else if constexpr (MASK == 15) SPG_DPP_BLOCK("row_mirror", "%3", "%2", "%1", "%0");
+    else SPG_DPP_BLOCK("row_ror:8", "%0", "%1", "%2", "%3");  // exchange at distance 8
+}
+#undef SPG_DPP_BLOCK
+
+// One compare-exchange stage across lanes: with the lane whose number differs
+// in the bits of MASK, register r against register r, or (FLIP) KPL - 1 - r.
+// The lane with the highest differing bit clear keeps the smaller keys.
+template <typename K, int KPL, int MASK, bool FLIP>
+__device__ __forceinline__ void lane_stage(K (&key)[KPL], int lane) {
+    constexpr int TOP = FLIP ? (MASK + 1) / 2 : MASK;
     if constexpr (sizeof(K) == 4) {
-        const unsigned c = take_min ? 0u : ~0u;
+        // all ones in the lanes with the bit set, else 0
+        const unsigned c = (unsigned)(((int)((unsigned)lane << (31 - __builtin_ctz(TOP)))) >> 31);
+        if constexpr (MASK <= 3 || MASK == 7 || MASK == 8 || MASK == 15) {
+            static_assert(KPL % 4 == 0, "the exchange blocks take four registers");
 #pragma unroll
-        for (int r = 0; r < KPL; ++r) key[r] = (K)med3u((unsigned)key[r], kx<J>((unsigned)key[r]), c);
-    } else {
+            for (int r = 0; r < KPL / 2; r += 2) {
+                if constexpr (FLIP)
+                    dpp_block<MASK, true>(key[r], key[r + 1], key[KPL - 2 - r], key[KPL - 1 - r], c);
+                else
+                    dpp_block<MASK, false>(key[2 * r], key[2 * r + 1], key[2 * r + 2],
+                                           key[2 * r + 3], c);
+            }
+        } else {
+            unsigned o[KPL];
 #pragma unroll
-        for (int r = 0; r < KPL; ++r) {
-            const K o = kx<J>(key[r]);
-            const K mn = key[r] < o ? key[r] : o;
-            const K mx = key[r] < o ? o : key[r];
-            key[r] = take_min ? mn : mx;
+            for (int r = 0; r < KPL; ++r)
+                o[r] = (unsigned)shfl_xor_c<MASK>((int)key[FLIP ? KPL - 1 - r : r]);
+#pragma unroll
+            for (int r = 0; r < KPL; ++r) key[r] = med3u(key[r], o[r], c);
         }
+    } else {
+        const bool take_max = (lane & TOP) != 0;
+        K o[KPL];
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) o[r] = shfl_xor_c64<MASK>(key[FLIP ? KPL - 1 - r : r]);
+#pragma unroll
+        for (int r = 0; r < KPL; ++r)
+            key[r] = (key[r] < o[r]) != take_max ? key[r] : o[r];
     }
 }
 
-// every aligned segment of S positions sorted ascending (bitonic network of
-// the segment's size; the last merge ascending everywhere)
+// Every aligned segment of S positions sorted ascending, position KPL lane + r
+// in register r. Bitonic merges whose first stage compares a position with
+// its mirror image in the merge (so every merge and every stage is ascending,
+// a register exchange is one min and one max, and the first stage of a merge
+// of 2, 4, 8 or 16 lanes is a DPP move).
 template <typename K, int KPL, int S>
 __device__ __forceinline__ void seg_sort(K (&key)[KPL], int lane_in) {
-    // The direction masks below depend on the lane only: an opaque copy of
-    // the lane number keeps them from being computed once outside the
-    // caller's loop and held in registers for the whole kernel.
+    // The masks below depend on the lane only: an opaque copy of the lane
+    // number keeps them from being computed once outside the caller's loop
+    // and held in registers for the whole kernel.
     int lane = lane_in;
     asm volatile("" : "+v"(lane));
-    const int s0 = lane * KPL;
 #pragma unroll
     for (int k = 2; k <= S; k <<= 1) {
+        if (k <= KPL) {
 #pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            if (j < KPL && sizeof(K) == 4 && k >= KPL && k != S) {
-                // the direction depends on the lane only (r < KPL <= k):
-                // each side of a pair is one median of three
-                const unsigned c = (s0 & k) == 0 ? 0u : ~0u;
+            for (int r = 0; r < KPL; ++r)
+                if ((r & (k - 1)) < k / 2) minmax(key[r], key[r ^ (k - 1)]);
+        } else {
+            switch (k / KPL) {
+                case 2: lane_stage<K, KPL, 1, true>(key, lane); break;
+                case 4: lane_stage<K, KPL, 3, true>(key, lane); break;
+                case 8: lane_stage<K, KPL, 7, true>(key, lane); break;
+                case 16: lane_stage<K, KPL, 15, true>(key, lane); break;
+                case 32: lane_stage<K, KPL, 31, true>(key, lane); break;
+                default: lane_stage<K, KPL, 63, true>(key, lane); break;
+            }
+        }
 #pragma unroll
-                for (int r = 0; r < KPL; ++r) {
-                    if (r & j) continue;
-                    const int rp = r | j;
-                    const unsigned x = (unsigned)key[r], y = (unsigned)key[rp];
-                    key[r] = (K)med3u(x, y, c);
-                    key[rp] = (K)med3u(x, y, ~c);
-                }
-            } else if (j < KPL) {
+        for (int j = k >> 2; j > 0; j >>= 1) {
+            if (j < KPL) {
 #pragma unroll
-                for (int r = 0; r < KPL; ++r) {
-                    if (r & j) continue;
-                    const int rp = r | j;
-                    const bool asc = k == S || ((s0 + r) & k) == 0;
-                    const K x = key[r], y = key[rp];
-                    const bool sw = asc ? (x > y) : (x < y);
-                    key[r] = sw ? y : x;
-                    key[rp] = sw ? x : y;
-                }
+                for (int r = 0; r < KPL; ++r)
+                    if (!(r & j)) minmax(key[r], key[r | j]);
             } else {
                 switch (j / KPL) {
-                    case 1: lane_stage<K, KPL, 1, S>(key, k, lane); break;
-                    case 2: lane_stage<K, KPL, 2, S>(key, k, lane); break;
-                    case 4: lane_stage<K, KPL, 4, S>(key, k, lane); break;
-                    case 8: lane_stage<K, KPL, 8, S>(key, k, lane); break;
-                    case 16: lane_stage<K, KPL, 16, S>(key, k, lane); break;
-                    default: lane_stage<K, KPL, 32, S>(key, k, lane); break;
+                    case 1: lane_stage<K, KPL, 1, false>(key, lane); break;
+                    case 2: lane_stage<K, KPL, 2, false>(key, lane); break;
+                    case 4: lane_stage<K, KPL, 4, false>(key, lane); break;
+                    case 8: lane_stage<K, KPL, 8, false>(key, lane); break;
+                    default: lane_stage<K, KPL, 16, false>(key, lane); break;
                 }
             }
         }
     }
+    // the caller's first move across lanes reads the last register, whose
+    // write (inside an asm block) the compiler does not count as a hazard
+    if constexpr (sizeof(K) == 4) asm volatile("s_nop 1" : "+v"(key[KPL - 1]), "+v"(key[0]));
 }
 
-// LDS of one wavefront: the buffer's keys (heads before the sort, sorted keys
-// after it, staged output rows last) and values (B values of the heads, then
-// the products' values by position, staged output values last)
+// ---------------------------------------------------------------- one buffer
+// LDS of one wavefront: head offsets, then staged output rows (key), and head
+// values, then the products by slot, then staged output values (val).
 template <typename K, typename V, int N, bool FILL>
 struct WaveLds {
     K key[N];
     V val[FILL ? N : 1];
-    int colv[64];          // per column of the item: products, then entries found
-    int seg_out[64];       // per column: output entries (run count)
     int stk[2 * 48];       // window stack (heavy columns)
 };
-
-// ---------------------------------------------------------------- shared steps
-// Forward fill of the heads over the lane's KPL positions and across lanes:
-// qb[r] / bv[r] of every position become those of the last head at or before
-// it. hq[s] = kHeadNone marks a position without a head.
-template <typename V, int KPL, bool FILL>
-__device__ __forceinline__ void fill_heads(int (&qb)[KPL], V (&bb)[KPL], int lane) {
-    bool has = false;
-    int lq = 0;
-    V lb = V(0);
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) {
-        if (qb[r] != kHeadNone) {
-            has = true;
-            lq = qb[r];
-            if (FILL) lb = bb[r];
-        }
-    }
-    // last head of the lanes below (inclusive scan "take the later valid")
-    int hv = has ? 1 : 0, sq = lq;
-    V sb = lb;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int oh = shfl_up_i(hv, d), oq = shfl_up_i(sq, d);
-        V ob = V(0);
-        if (FILL) ob = shfl_up_v(sb, d);
-        if (lane >= d && !hv && oh) {
-            hv = 1;
-            sq = oq;
-            if (FILL) sb = ob;
-        }
-    }
-    // exclusive: the lane below's inclusive result
-    int cq = shfl_up_i(sq, 1), ch = shfl_up_i(hv, 1);
-    V cb = V(0);
-    if (FILL) cb = shfl_up_v(sb, 1);
-    if (lane == 0) ch = 0;
-    int q = ch ? cq : kHeadNone;
-    V b = cb;
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) {
-        if (qb[r] != kHeadNone) {
-            q = qb[r];
-            if (FILL) b = bb[r];
-        }
-        qb[r] = q;
-        if (FILL) bb[r] = b;
-    }
-}
+template <typename V, int N, bool FILL>
+struct GroupLds {
+    int key[N];
+    V val[FILL ? N : 1];
+    int colv[64];          // per column of the item: its place in C (-1: do not write)
+    int seg_out[64];       // per column: output entries (run count)
+};
 
 // Runs of equal rows inside every aligned segment of S positions of the sorted
-// keys: head flags, the run index of every head within its segment, and the
-// segment's run count (valid in every lane of the segment).
+// keys (position KPL lane + r in register r).
+template <int KPL>
+struct Runs {
+    unsigned head;   // bit r: position r starts a run
+    unsigned live;   // bit r: position r holds a product
+    int run;         // run index (inside the segment) of the lane's first run start
+    int total;       // runs of the segment
+    bool first;      // the lane starts a segment
+    bool dups;       // some run of the buffer has more than one product (uniform)
+};
+
 template <typename K, int KPL, int S>
-__device__ __forceinline__ void seg_runs(const K (&key)[KPL], bool (&head)[KPL], int (&run)[KPL],
-                                         int &seg_total, int lane_in) {
+__device__ __forceinline__ Runs<KPL> seg_runs(const K (&key)[KPL], int lane) {
     constexpr K KMAX = KeyTraits<K>::kmax;
-    // opaque lane number: the permute addresses below stay inside the
-    // caller's loop instead of occupying registers for the whole kernel
-    int lane = lane_in;
-    asm volatile("" : "+v"(lane));
-    const int s0 = lane * KPL;
-    // the last key of the lane below (the previous position of this lane's first)
+    constexpr int LPS = S / KPL;  // lanes per segment
+    static_assert(LPS >= 2, "a segment spans lanes");
+    Runs<KPL> o;
+    o.first = (lane & (LPS - 1)) == 0;
+    // the last key of the lane below (the position before this lane's first)
     K prev;
     if constexpr (sizeof(K) == 4) {
-        prev = (K)(unsigned)shfl_up_i((int)key[KPL - 1], 1);
+        prev = (K)(unsigned)wave_shr1((int)key[KPL - 1], 0);
     } else {
-        const int lo = shfl_up_i((int)(unsigned)key[KPL - 1], 1);
-        const int hi = shfl_up_i((int)(unsigned)(key[KPL - 1] >> 32), 1);
+        const int lo = wave_shr1((int)(unsigned)key[KPL - 1], 0);
+        const int hi = wave_shr1((int)(unsigned)(key[KPL - 1] >> 32), 0);
         prev = ((K)(unsigned)hi << 32) | (unsigned)lo;
     }
-    int cnt = 0;
+    o.head = 0;
+    o.live = 0;
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
-        const int s = s0 + r;
         const K p = r == 0 ? prev : key[r - 1];
-        const bool first = (s & (S - 1)) == 0;
-        head[r] = key[r] != KMAX && (first || (key[r] >> kKeyBits) != (p >> kKeyBits));
-        run[r] = cnt;
-        cnt += head[r] ? 1 : 0;
+        const bool lv = key[r] != KMAX;
+        const bool hd = lv && ((r == 0 && o.first) || (key[r] >> kKeyBits) != (p >> kKeyBits));
+        o.live |= lv ? 1u << r : 0u;
+        o.head |= hd ? 1u << r : 0u;
     }
-    // exclusive prefix of the lane counts inside the segment
+    o.dups = ballot(o.live != o.head) != 0;
+    const int cnt = __builtin_popcount(o.head);
     const int inc = wave_incl_scan(cnt);
-    int base = inc - cnt;
-    if constexpr (S > KPL) {
-        constexpr int LPS = S / KPL;  // lanes per segment
-        const int first_lane = lane & ~(LPS - 1);
-        const int seg_base = __builtin_amdgcn_ds_bpermute(first_lane << 2, base);
-        base -= seg_base;
-        const int last_lane = first_lane + LPS - 1;
-        seg_total = __builtin_amdgcn_ds_bpermute(last_lane << 2, inc) - seg_base;
+    if constexpr (LPS == 64) {
+        o.run = inc - cnt;
+        o.total = __builtin_amdgcn_readlane(inc, 63);
     } else {
-        // segments inside one lane's registers (KPL >= S): counted per segment
-        seg_total = 0;  // filled by the caller from run indices
-        base = 0;
+        const int first_lane = lane & ~(LPS - 1);
+        const int base = __builtin_amdgcn_ds_bpermute(first_lane << 2, inc - cnt);
+        o.run = inc - cnt - base;
+        o.total = __builtin_amdgcn_ds_bpermute((first_lane + LPS - 1) << 2, inc) - base;
     }
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) run[r] += base;
+    return o;
 }
 
 // Largest occurrence index of the sorted buffer: a product's distance to the
 // head of its run (its position among the products Algorithm 1 adds into the
 // same entry); raised into the header's later_maxk for the plan's statistics.
-template <typename K, int KPL>
-__device__ __forceinline__ void note_depth(const KArgs &a, const K (&key)[KPL],
-                                           const bool (&head)[KPL], int lane) {
-    constexpr K KMAX = KeyTraits<K>::kmax;
+template <int KPL>
+__device__ __forceinline__ void note_depth(const KArgs &a, const Runs<KPL> &o, int lane) {
+    if (!o.dups) return;
     const int s0 = lane * KPL;
-    int hp[KPL];
-    int last = -1;
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) {
-        if (head[r]) last = s0 + r;
-        hp[r] = last;
-    }
     // the last head of the lanes below (head positions increase with the lane)
-    int inc = last;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int o = shfl_up_i(inc, d);
-        if (lane >= d) inc = max(inc, o);
-    }
-    int carry = shfl_up_i(inc, 1);
-    if (lane == 0) carry = -1;
+    const int last = o.head ? s0 + 31 - __builtin_clz(o.head) : -1;
+    int h = wave_shr1(wave_incl_max(last), -1);
     int k = 0;
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
-        const int h = hp[r] >= 0 ? hp[r] : carry;
-        if (key[r] != KMAX && h >= 0) k = max(k, s0 + r - h);
+        if ((o.head >> r) & 1u) h = s0 + r;
+        if ((o.live >> r) & 1u) k = max(k, s0 + r - h);
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) k = max(k, __builtin_amdgcn_ds_bpermute((lane ^ d) << 2, k));
+    k = __builtin_amdgcn_readlane(wave_incl_max(k), 63);
     if (lane == 0 && k > __atomic_load_n(&a.hdr->later_maxk, __ATOMIC_RELAXED))
         atomicMax(&a.hdr->later_maxk, k);
 }
 
-// LDS slot of sorted position q when every lane stores its KPL consecutive
-// positions: the position's low bits are XORed with bits of its lane, so that
-// the lanes of one store (or of one step of the heads' walks) spread over the
-// banks instead of sharing a few. A permutation inside each lane's KPL slots;
-// with 4 positions per lane the plain layout measured no slower.
-template <int KPL>
-__device__ __forceinline__ int sorted_slot(int q) {
-    return KPL >= 8 ? q ^ ((q >> 5) & (KPL - 1)) : q;
+// The sorted products' values (v[r] of position r) become the running sums of
+// their runs in order, every run starting from zero: the last position of a
+// run holds its sum. A run that crosses lanes hands its partial sum from lane
+// to lane, which keeps the order of the additions.
+template <typename V, int KPL>
+__device__ __forceinline__ void run_sums(V (&v)[KPL], const Runs<KPL> &o) {
+    if (!o.dups) {
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) v[r] = V(0) + v[r];
+        return;
+    }
+    const bool cont = (o.live & 1u) && !(o.head & 1u);  // starts inside a run of the lane below
+    V carry = V(0);
+    if (ballot(cont)) {
+        // the sum of the lane's last run as far as this lane knows it
+        V t = V(0);
+#pragma unroll
+        for (int r = 0; r < KPL; ++r)
+            if ((o.live >> r) & 1u) t = ((o.head >> r) & 1u) ? V(0) + v[r] : t + v[r];
+        // lanes wholly inside a run wait for the lane below, lane after lane
+        int known = (o.head != 0 || !cont) ? 1 : 0;
+        while (ballot(!known)) {
+            const V c = wave_shr1_v(t);
+            const int k = wave_shr1(known, 1);
+            if (!known && k) {
+                t = c;
+#pragma unroll
+                for (int r = 0; r < KPL; ++r)
+                    if ((o.live >> r) & 1u) t = t + v[r];
+                known = 1;
+            }
+        }
+        carry = wave_shr1_v(t);
+    }
+    V t = carry;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        t = ((o.head >> r) & 1u) ? V(0) + v[r] : t + v[r];
+        v[r] = t;
+    }
+}
+
+// Bit r: position r is the last of its run.
+template <int KPL, int S>
+__device__ __forceinline__ unsigned run_tails(const Runs<KPL> &o, int lane) {
+    constexpr int LPS = S / KPL;
+    // the next lane's first position continues this lane's last run
+    const bool next = (o.live & 1u) && !(o.head & 1u);
+    const int go = wave_shl1(next ? 1 : 0, 0);
+    const bool last_lane = (lane & (LPS - 1)) == LPS - 1;
+    const unsigned cont = (o.live & ~o.head) >> 1;  // bit r: position r + 1 continues the run of r
+    const unsigned high = (go && !last_lane) ? 1u << (KPL - 1) : 0u;
+    return o.live & ~(cont | high);
 }
 
 // ---------------------------------------------------------------- one work item
-// A work item: G = N / S columns (global column g[cc], first stored B entry
-// bs[cc], B entries nb[cc], products op[cc]), each in its aligned segment.
+// A work item: up to G = N / S columns of one problem (bin-list entry
+// (global column, first stored B entry, B entries, products) in lane c), each
+// in its segment. Lanes LPS seg .. LPS (seg + 1) - 1 hold segment seg, LPS =
+// S / KPL; product i of a column is gathered in row r = i / LPS of its
+// segment, lane i mod LPS, LDS slot 64 r + lane.
+//
+// What bounds it: the chain bin entry -> B entries -> A gathers -> stores, and
+// between them the instructions of the scans, the sort and the sums. So the
+// cross-lane steps are DPP moves rather than LDS permutes, a product finds its
+// B entry from a ballot of the head flags (no fill over the lanes), the sort
+// starts from the gathered layout (any start order sorts the same), and the
+// runs are summed in registers.
 template <typename K, typename V, int KPL, int S, bool FILL>
-__device__ __forceinline__ void item_sort_compress(const KArgs &a, const Prob &d, int pid,
-                                                   WaveLds<K, V, 64 * KPL, FILL> &L,
-                                                   K (&key)[KPL], int ncol, const int *gcol,
-                                                   int2a ccp_lane, int lane, int &bad) {
-    constexpr int N = 64 * KPL, G = N / S;
+__device__ __forceinline__ void wave_item(const KArgs &a, const Prob &d,
+                                          GroupLds<V, 64 * KPL, FILL> &L, int4 ent, int ncol,
+                                          int lane, int &bad) {
+    constexpr int N = 64 * KPL, G = N / S, LPS = S / KPL;
     constexpr K KMAX = KeyTraits<K>::kmax;
-    seg_sort<K, KPL, S>(key, lane);
-    bool head[KPL];
-    int run[KPL];
-    int seg_total;
-    seg_runs<K, KPL, S>(key, head, run, seg_total, lane);
-    if (!FILL || a.spec_fill) note_depth<K, KPL>(a, key, head, lane);
-    const int s0 = lane * KPL;
-    if constexpr (S <= KPL) {
-        // several segments per lane: count runs per segment in registers
-#pragma unroll
-        for (int r = 0; r < KPL; ++r) {
-            // run index inside the segment: heads before r in the same segment
-            const int seg_first = r & ~(S - 1);
-            int c = 0;
-#pragma unroll
-            for (int q = 0; q < KPL; ++q)
-                if (q >= seg_first && q < r && head[q]) ++c;
-            run[r] = c;
-        }
-    }
-    // run count per column
-    if constexpr (S > KPL) {
-        if ((s0 & (S - 1)) == 0) L.seg_out[s0 / S] = seg_total;
-    } else {
-#pragma unroll
-        for (int r = 0; r < KPL; r += S) {
-            int c = 0;
-#pragma unroll
-            for (int q = 0; q < S; ++q) c += head[r + q] ? 1 : 0;
-            L.seg_out[(s0 + r) / S] = c;
-        }
-    }
-    if constexpr (!FILL) {
-        wsync();
-        if (lane < ncol) a.gnnz[gcol[lane]] = L.seg_out[lane];
-        wsync();
-        return;
-    } else {
-        // sorted keys to LDS (own positions), then every head adds its run
-#pragma unroll
-        for (int r = 0; r < KPL; ++r) L.key[sorted_slot<KPL>(s0 + r)] = key[r];
-        wsync();
-        // A key's position bits index the values inside its segment. Every
-        // head sums its run in order and leaves the sum in its own product's
-        // slot, which no other run reads.
-#pragma unroll
-        for (int r = 0; r < KPL; ++r) {
-            if (!head[r]) continue;
-            const int s = s0 + r, ss = s & ~(S - 1), send = ss + S;
-            const K row = key[r] >> kKeyBits;
-            const int own = ss + (int)(key[r] & (K)(S - 1));
-            V acc = V(0) + L.val[own];
-            for (int q = s + 1; q < send; ++q) {
-                const K kq = L.key[sorted_slot<KPL>(q)];
-                if (kq == KMAX || (kq >> kKeyBits) != row) break;
-                acc = acc + L.val[ss + (int)(kq & (K)(S - 1))];
-            }
-            L.val[own] = acc;
-        }
-        // output start of every column; a count that differs from the
-        // symbolic phase's means other inputs (nothing is written then)
-        if (lane < ncol) {
-            // the column's bounds in C, loaded when the item started
-            const int c0 = ccp_lane.x, clen = ccp_lane.y - c0;
-            L.colv[lane] = L.seg_out[lane] == clen ? c0 : -1;
-            if (a.spec_fill) a.gnnz[gcol[lane]] = L.seg_out[lane];
-        }
-        wsync();
-        // head keys staged at segment start + run index, then written out:
-        // the row from the key, the sum from the slot its position bits name
-#pragma unroll
-        for (int r = 0; r < KPL; ++r) {
-            if (!head[r]) continue;
-            const int ss = (s0 + r) & ~(S - 1);
-            L.key[ss + run[r]] = key[r];
-        }
-        wsync();
-        gmem<int32_t> *cri = to_gmem(d.cri);
-        gmem<V> *cv = to_gmem((V *)d.cv);
-        if constexpr (G == 1) {
-            // one column: 64 consecutive entries per store
-            const int c0 = L.colv[0], nout = L.seg_out[0];
-            if (c0 < 0) {
-                bad = 1;
-            } else {
-                for (int i = lane; i < nout; i += 64) {
-                    const K k = L.key[i];
-                    cri[c0 + i] = (int32_t)(k >> kKeyBits);
-                    cv[c0 + i] = L.val[(int)(k & (K)(S - 1))];
-                }
-            }
-        } else {
-            // several columns: every lane writes its own positions
-#pragma unroll
-            for (int r = 0; r < KPL; ++r) {
-                const int s = s0 + r, cc = s / S, i = s - cc * S;
-                if (cc >= ncol) continue;
-                const int c0 = L.colv[cc];
-                if (c0 < 0) {
-                    bad = 1;
-                    continue;
-                }
-                if (i < L.seg_out[cc]) {
-                    const K k = L.key[s];
-                    cri[c0 + i] = (int32_t)(k >> kKeyBits);
-                    cv[c0 + i] = L.val[cc * S + (int)(k & (K)(S - 1))];
-                }
-            }
-        }
-        wsync();
-    }
-}
-
-// Products of the item's columns into the wave buffer: heads from the stored B
-// entries, forward fill, gathers of A's rows (and values). Returns false when
-// a column's entries do not add up to its product count (inputs changed).
-template <typename K, typename V, int KPL, int S, bool FILL>
-__device__ __forceinline__ bool item_gather(const KArgs &a, const Prob &d,
-                                            WaveLds<K, V, 64 * KPL, FILL> &L, K (&key)[KPL],
-                                            int ncol, const int *bsv, const int *nbv,
-                                            const int *opv, int lane) {
-    constexpr int N = 64 * KPL;
-    constexpr K KMAX = KeyTraits<K>::kmax;
-    const int s0 = lane * KPL;
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) L.key[s0 + r] = (K)(unsigned)kHeadNone;
-    wsync();
+    const int j = ent.x - d.col0;
+    // the filling pass's column bounds in C (known before the kernel) load
+    // with the entries; they are used after the sort
+    int2a ccp = {0, 0};
+    if (FILL && lane < ncol) ccp = load_pair(d.ccp, j);
     const int2 *__restrict__ Ep = a.E + d.ebase;
     const gmem<const V> *__restrict__ bvp = to_gmem((const V *)d.bv);
+    // first entry and first product of every column in the item's list
+    const int einc = wave_incl_scan(ent.z), oinc = wave_incl_scan(ent.w);
+    const int es = einc - ent.z, ob = oinc - ent.w, bsd = ent.y - es;
+    const int tot_entries = __builtin_amdgcn_readlane(einc, 63);
+    const int tot_products = __builtin_amdgcn_readlane(oinc, 63);
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) L.key[r * 64 + lane] = kHeadNone;
+    wsync();
+    // heads: at the slot of a stored B entry's first product (and of its first
+    // product of every further row), A's index less the product's position
     bool ok = true;
-    // the item's stored B entries, flattened column after column
-    int tot_entries = 0;
-    for (int cc = 0; cc < ncol; ++cc) tot_entries += nbv[cc];
-    int cc_cur = 0, cc_first = 0, run = 0;  // running product count of column cc_cur
-    // column of entry x and its column's first entry (columns are few: a
-    // linear walk from a known column)
-    auto locate = [&](int x, int c0, int f0, int &cc, int &cf) {
-        cc = c0;
-        cf = f0;
-        while (cc < ncol - 1 && x >= cf + nbv[cc]) {
-            cf += nbv[cc];
-            ++cc;
-        }
-    };
-    // entries are walked 64 at a time (a chunk may span several columns),
-    // the next chunk's loads in flight while the current one is scanned
-    int ncc, ncf;
-    int2 ne = make_int2(0, 0);
-    V nbval = V(0);
-    locate(lane, 0, 0, ncc, ncf);
-    if (lane < tot_entries) {
-        const int t = bsv[ncc] + (lane - ncf);
-        ne = Ep[t];
-        if (FILL) nbval = bvp[t];
-    }
+    int run = 0;
     for (int x0 = 0; x0 < tot_entries; x0 += 64) {
         const int x = x0 + lane;
-        const int cc = ncc, cf = ncf;
-        const int z = x < tot_entries ? ne.y : 0, as = ne.x;
-        const V bval = nbval;
-        if (x0 + 64 < tot_entries) {
-            locate(x + 64, cc, cf, ncc, ncf);
-            if (x + 64 < tot_entries) {
-                const int t = bsv[ncc] + (x + 64 - ncf);
-                ne = Ep[t];
-                if (FILL) nbval = bvp[t];
-            }
-        }
-        // position inside the column: exclusive prefix of z over the column's
-        // entries (scan over the chunk, restarted at every column start)
-        const bool seg_head = x < tot_entries && (x == cf || x == x0);
-        // segmented inclusive scan: add the value of the lane below while no
-        // segment head lies between
-        int inc = z;
-        bool blocked = seg_head;
+        int cc = 0;
 #pragma unroll
-        for (int dd = 1; dd < 64; dd <<= 1) {
-            const int oi = shfl_up_i(inc, dd);
-            const int ob = shfl_up_i(blocked ? 1 : 0, dd);
-            if (lane >= dd && !blocked) inc += oi;
-            if (lane >= dd && !blocked) blocked = ob != 0;
+        for (int c = 1; c < G; ++c)
+            cc += x >= __builtin_amdgcn_readlane(es, c) ? 1 : 0;
+        const int cbs = G == 1 ? __builtin_amdgcn_readlane(bsd, 0) : shfl_idx(bsd, cc);
+        const int cob = G == 1 ? 0 : shfl_idx(ob, cc);
+        const int ces = G == 1 ? 0 : shfl_idx(es, cc);
+        int2 e = make_int2(0, 0);
+        V bval = V(0);
+        if (x < tot_entries) {
+            e = Ep[cbs + x];
+            if (FILL) bval = bvp[cbs + x];
         }
-        // carry into the chunk: the running count of the column the chunk
-        // starts in, for entries of that column
-        const int carry = (cc == cc_cur) ? run : 0;
-        const int o = carry + inc - z;
-        // the last entry of a column closes it at exactly its product count
-        if (x < tot_entries && x == cf + nbv[cc] - 1 && o + z != opv[cc]) ok = false;
-        if (x < tot_entries && z > 0) {
-            if (o < 0 || o + z > opv[cc]) {
+        const int inc = wave_incl_scan(e.y);
+        // position of the entry's first product inside its column: the
+        // products listed before it less those of the earlier columns
+        const int o = run + inc - e.y - cob;
+        if (x < tot_entries && x == ces && o != 0) ok = false;
+        if (e.y > 0) {
+            if (o < 0 || e.y > S - o) {
                 ok = false;
             } else {
-                L.key[cc * S + o] = (K)(unsigned)(as - o);
-                if (FILL) L.val[cc * S + o] = bval;
+                const int end = o + e.y;
+                int row = o / LPS;
+                int slot = row * 64 + cc * LPS + o % LPS;
+                L.key[slot] = e.x - o;
+                if (FILL) L.val[slot] = bval;
+                for (++row; row * LPS < end; ++row) {
+                    slot = row * 64 + cc * LPS;
+                    L.key[slot] = e.x - o;
+                    if (FILL) L.val[slot] = bval;
+                }
             }
         }
-        // advance: the column and running count after the chunk's last entry
-        const int last = min(63, tot_entries - 1 - x0);
-        const int cc_last = __builtin_amdgcn_ds_bpermute(last << 2, cc);
-        const int cf_last = __builtin_amdgcn_ds_bpermute(last << 2, cf);
-        const int o_last = __builtin_amdgcn_ds_bpermute(last << 2, o + z);
-        cc_cur = cc_last;
-        cc_first = cf_last;
-        run = o_last;
+        run += __builtin_amdgcn_readlane(inc, 63);
     }
-    ok = __builtin_amdgcn_ballot_w64(!ok) == 0;
-    wsync();
-    int qb[KPL];
-    V bb[KPL];
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) {
-        qb[r] = (int)(unsigned)L.key[s0 + r];
-        bb[r] = FILL ? L.val[s0 + r] : V(0);
-    }
-    fill_heads<V, KPL, FILL>(qb, bb, lane);
-    // The filled heads go back to LDS by position, and the gathers take
-    // positions lane-major (position 64 r + lane in register r): consecutive
-    // lanes then read consecutive entries of the same A column, so a load
-    // instruction touches a few cache lines instead of up to 64.
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) {
-        L.key[s0 + r] = (K)(unsigned)qb[r];
-        if (FILL) L.val[s0 + r] = bb[r];
+    if (ballot(!ok) != 0 || run != tot_products) {
+        bad = 1;
+        wsync();
+        return;
     }
     wsync();
+    // every product's head is the last one at or before its lane in its row
+    const int seg = lane / LPS;
+    const int opn = shfl_idx(ent.w, seg);
     const gmem<const int32_t> *__restrict__ ari = to_gmem(d.ari);
     const gmem<const V> *__restrict__ av = to_gmem((const V *)d.av);
-    int row[KPL];
-    bool live[KPL];
-    V x[KPL];
-    // every gather of the lane issued before any is used (the B value of
-    // each position stays in LDS until its product replaces it)
+    const unsigned long long le = mask_lt() | (1ull << lane);
+    int q[KPL], from[KPL];
+    unsigned live = 0;
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
-        const int s = r * 64 + lane, cc = s / S, i = s & (S - 1);
-        const int qs = (int)(unsigned)L.key[s];
-        live[r] = ok && cc < ncol && i < opv[cc] && qs != kHeadNone;
-        const int q = live[r] ? qs + i : 0;
-        row[r] = live[r] ? ari[q] : 0;
-        if (FILL) x[r] = live[r] ? av[q] : V(0);
+        const unsigned long long m = ballot(L.key[r * 64 + lane] != kHeadNone) & le;
+        const int i = r * LPS + (lane & (LPS - 1));
+        const bool lv = i < opn && m != 0;
+        from[r] = r * 64 + 63 - __builtin_clzll(m | 1ull);
+        q[r] = lv ? L.key[from[r]] + i : 0;
+        live |= lv ? 1u << r : 0u;
     }
-    wsync();  // every lane has read the filled heads
+    int row[KPL];
+    V v[KPL];
+    // every gather of the lane issued before any is used
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const bool lv = (live >> r) & 1u;
+        row[r] = lv ? ari[q[r]] : 0;
+        if (FILL) v[r] = lv ? av[q[r]] : V(0);
+    }
+    if (FILL) {
+        // products by slot (a row's heads are read before its products land)
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+            const V b = L.val[from[r]];
+            wsync();
+            L.val[r * 64 + lane] = v[r] * b;
+        }
+    }
+    K key[KPL];
     bool badrow = false;
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
-        const int s = r * 64 + lane, i = s & (S - 1);
+        const bool lv = (live >> r) & 1u;
         // a row outside A's row range is malformed input (reported; the
         // product takes no part)
-        if (live[r] && (row[r] < 0 || row[r] >= d.m)) {
-            badrow = true;
-            live[r] = false;
-        }
-        L.key[s] = live[r] ? (((K)(unsigned)row[r] << kKeyBits) | (K)(unsigned)i) : KMAX;
-        if (FILL && live[r]) L.val[s] = x[r] * L.val[s];
+        const bool in = row[r] >= 0 && row[r] < d.m;
+        badrow |= lv && !in;
+        key[r] = lv && in ? (((K)(unsigned)row[r] << kKeyBits) | (K)(unsigned)(r * 64 + lane)) : KMAX;
     }
     if (ballot(badrow) && lane == 0) atomicOr(&a.hdr->err, ERR_CSC);
-    wsync();
-    // keys back in the sort's layout: positions s0 .. s0 + KPL - 1 per lane;
-    // a buffer that is one segment may start the sort in any order, so its
-    // lanes read position 64 r + lane (consecutive lanes, consecutive banks)
+    seg_sort<K, KPL, S>(key, lane);
+    const Runs<KPL> o = seg_runs<K, KPL, S>(key, lane);
+    if (!FILL || a.spec_fill) note_depth<KPL>(a, o, lane);
+    if constexpr (!FILL) {
+        // run count of every column, from its segment's lanes
+        const int cnt = shfl_idx(o.total, (lane * LPS) & 63);
+        if (lane < ncol) a.gnnz[ent.x] = cnt;
+        wsync();
+    } else {
+        const int cnt = shfl_idx(o.total, (lane * LPS) & 63);
+        if (lane < ncol) {
+            // a count that differs from the symbolic phase's means other
+            // inputs (nothing is written then)
+            const int clen = ccp.y - ccp.x;
+            L.colv[lane] = cnt == clen ? ccp.x : -1;
+            L.seg_out[lane] = cnt;
+            if (a.spec_fill) a.gnnz[ent.x] = cnt;
+        }
+        wsync();
 #pragma unroll
-    for (int r = 0; r < KPL; ++r) key[r] = L.key[S == N ? r * 64 + lane : s0 + r];
-    wsync();
-    return ok;
+        for (int r = 0; r < KPL; ++r)
+            v[r] = (o.live >> r) & 1u ? L.val[(int)(key[r] & (K)(N - 1))] : V(0);
+        run_sums<V, KPL>(v, o);
+        wsync();
+        // a run's row and sum staged at segment start + run index
+        const unsigned tails = run_tails<KPL, S>(o, lane);
+        int at = seg * S + o.run - 1;
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+            at += (o.head >> r) & 1u;
+            if ((tails >> r) & 1u) {
+                L.key[at] = (int)(key[r] >> kKeyBits);
+                L.val[at] = v[r];
+            }
+        }
+        wsync();
+        // consecutive lanes write consecutive entries of a column
+        gmem<int32_t> *cri = to_gmem(d.cri);
+        gmem<V> *cv = to_gmem((V *)d.cv);
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+            const int s = r * 64 + lane, c = s / S, i = s - c * S;
+            if (c >= ncol) continue;
+            const int c0 = L.colv[c];
+            if (c0 < 0) {
+                bad = 1;
+                continue;
+            }
+            if (i < L.seg_out[c]) {
+                cri[c0 + i] = L.key[s];
+                cv[c0 + i] = L.val[s];
+            }
+        }
+        wsync();
+    }
 }
 
 // ---------------------------------------------------------------- wavefront groups
 // Bin `bin` holds columns of at most S products; G = N / S of them per wave.
 // One wavefront per workgroup: waves share nothing.
 template <typename K, typename V, int KPL, int S, bool FILL>
-// The groups of 32 to 128 products are held to 96 VGPRs, 5 waves per SIMD
-// instead of 4 (at the cost of 8 bytes of scratch), which measured 1.5 to 3 us
-// faster each; the groups of 16 lose more to the spill than they gain.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KPL == 4 && S >= 32 && S < 256 ? 5 : 1))) void k_acc_wave(KArgs a, int bin) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KPL == 16 ? 3 : 1))) void k_acc_wave(KArgs a, int bin) {
     constexpr int N = 64 * KPL, G = N / S;
     static_assert(S <= N && (N % S) == 0 && N <= (1 << kKeyBits), "segments tile the buffer");
-    __shared__ WaveLds<K, V, N, FILL> L;
+    __shared__ GroupLds<V, N, FILL> L;
     if (__atomic_load_n(&a.hdr->err, __ATOMIC_RELAXED) |
         (FILL ? __atomic_load_n(&a.hdr->cap_over, __ATOMIC_RELAXED) : 0))
         return;
@@ -617,56 +560,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KPL == 4 && 
     const int cnt = a.hdr->bin_count[bin];
     const int ngroups = ceil_div(cnt, G);
     int bad = 0;
-    __shared__ int s_g[G > 64 ? 64 : G], s_bs[G > 64 ? 64 : G], s_nb[G > 64 ? 64 : G],
-        s_op[G > 64 ? 64 : G];
     for (int gi = blockIdx.x; gi < ngroups; gi += gridDim.x) {
         const int first = start + gi * G, ncol = min(G, cnt - gi * G);
-        if (lane < ncol) {
-            const int4 ent = a.binlist[first + lane];
-            s_g[lane] = ent.x;
-            s_bs[lane] = ent.y;
-            s_nb[lane] = ent.z;
-            s_op[lane] = ent.w;
-            if (ent.w > S) bad = 1;  // cannot happen for unchanged inputs
-        }
-        wsync();
-        if (__builtin_amdgcn_ballot_w64(bad != 0)) break;
-        // every column of a group belongs to one problem (bins are filled per
-        // problem tile, but a group may cross problems): split by problem
         int c0 = 0;
         while (c0 < ncol) {
-            const int pid = find_prob(a, s_g[c0]);
-            const Prob d = get_prob(a, pid);
-            int c1 = c0 + 1;
-            while (c1 < ncol && s_g[c1] >= d.col0 && s_g[c1] < d.col0 + d.n) ++c1;
-            K key[KPL];
-            // the filling pass's column bounds in C (known before the kernel)
-            // load now; they are used after the sort
-            int2a ccp_lane = {0, 0};
-            if (FILL && lane < c1 - c0) ccp_lane = load_pair(d.ccp, s_g[c0 + lane] - d.col0);
-            if (c0 == 0 && c1 == ncol) {
-                if (!item_gather<K, V, KPL, S, FILL>(a, d, L, key, ncol, s_bs, s_nb, s_op, lane))
-                    bad = 1;
-                else
-                    item_sort_compress<K, V, KPL, S, FILL>(a, d, pid, L, key, ncol, s_g, ccp_lane,
-                                                           lane, bad);
-            } else {
-                // a group spanning problems: each problem's columns as an item
-                // of their own (at the front of the buffer)
-                if (!item_gather<K, V, KPL, S, FILL>(a, d, L, key, c1 - c0, s_bs + c0, s_nb + c0,
-                                                     s_op + c0, lane))
-                    bad = 1;
-                else
-                    item_sort_compress<K, V, KPL, S, FILL>(a, d, pid, L, key, c1 - c0, s_g + c0,
-                                                           ccp_lane, lane, bad);
+            // the columns from c0 on, lane c holding column c0 + c
+            const int4 ent = lane < ncol - c0 ? a.binlist[first + c0 + lane] : make_int4(0, 0, 0, 0);
+            if (ballot(ent.w > S || ent.z > N)) {  // cannot happen for unchanged inputs
+                bad = 1;
+                break;
             }
-            c0 = c1;
+            // a group may cross problems (bins are filled problem by problem):
+            // the columns of the first one's problem are an item of their own
+            int nc = ncol - c0;
+            const int pid = find_prob(a, __builtin_amdgcn_readfirstlane(ent.x));
+            const Prob d = get_prob(a, pid);
+            if (a.nprob > 1) {
+                const unsigned long long other =
+                    ballot(lane < nc && (ent.x < d.col0 || ent.x >= d.col0 + d.n));
+                if (other) nc = __builtin_ctzll(other);
+            }
+            int4 mine = ent;
+            if (lane >= nc) mine = make_int4(0, 0, 0, 0);
+            wave_item<K, V, KPL, S, FILL>(a, d, L, mine, nc, lane, bad);
+            c0 += nc;
         }
-        wsync();
     }
     // an output count other than the planned one: other inputs, or (a
     // numeric phase run at a previous structure's positions) a redo
-    if (__builtin_amdgcn_ballot_w64(bad != 0) && lane == 0)
+    if (ballot(bad != 0) && lane == 0)
         atomicOr(&a.hdr->err, a.spec_fill ? ERR_RETRY : ERR_GROUP);
 }
 
@@ -1223,34 +1145,27 @@ __global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
             }
             wsync();
             seg_sort<K, KPL, N>(key, lane);
-            bool head[KPL];
-            int run[KPL];
-            int runs;
-            seg_runs<K, KPL, N>(key, head, run, runs, lane);
-            if (!FILL || a.spec_fill) note_depth<K, KPL>(a, key, head, lane);
-            if (FILL) {
-#pragma unroll
-                for (int r = 0; r < KPL; ++r) L.key[sorted_slot<KPL>(s0 + r)] = key[r];
-                wsync();
-                // every head sums its run in order into its own product's
-                // slot, then its key is staged at its run index
-#pragma unroll
-                for (int r = 0; r < KPL; ++r) {
-                    if (!head[r]) continue;
-                    const K row = key[r] >> kKeyBits;
-                    const int own = (int)(key[r] & (K)(N - 1));
-                    V acc = V(0) + L.val[own];
-                    for (int q = s0 + r + 1; q < N; ++q) {
-                        const K kq = L.key[sorted_slot<KPL>(q)];
-                        if (kq == KMAX || (kq >> kKeyBits) != row) break;
-                        acc = acc + L.val[(int)(kq & (K)(N - 1))];
-                    }
-                    L.val[own] = acc;
-                }
-                wsync();
+            const Runs<KPL> o = seg_runs<K, KPL, N>(key, lane);
+            const int runs = o.total;
+            if (!FILL || a.spec_fill) note_depth<KPL>(a, o, lane);
+            if constexpr (FILL) {
+                V v[KPL];
 #pragma unroll
                 for (int r = 0; r < KPL; ++r)
-                    if (head[r]) L.key[run[r]] = key[r];
+                    v[r] = (o.live >> r) & 1u ? L.val[(int)(key[r] & (K)(N - 1))] : V(0);
+                run_sums<V, KPL>(v, o);
+                wsync();
+                // a run's row and sum staged at its run index
+                const unsigned tails = run_tails<KPL, N>(o, lane);
+                int at = o.run - 1;
+#pragma unroll
+                for (int r = 0; r < KPL; ++r) {
+                    at += (o.head >> r) & 1u;
+                    if ((tails >> r) & 1u) {
+                        L.key[at] = key[r] >> kKeyBits;
+                        L.val[at] = v[r];
+                    }
+                }
                 wsync();
                 const int clen = d.ccp[j + 1] - c0;
                 if (out + total + runs > clen) {
@@ -1259,9 +1174,8 @@ __global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
                     gmem<int32_t> *cri = to_gmem(d.cri);
                     gmem<V> *cv = to_gmem((V *)d.cv);
                     for (int i = lane; i < runs; i += 64) {
-                        const K k = L.key[i];
-                        cri[c0 + out + total + i] = (int32_t)(k >> kKeyBits);
-                        cv[c0 + out + total + i] = L.val[(int)(k & (K)(N - 1))];
+                        cri[c0 + out + total + i] = (int32_t)L.key[i];
+                        cv[c0 + out + total + i] = L.val[i];
                     }
                 }
                 wsync();

@@ -1,0 +1,96 @@
+"""Wavefront accumulators at the edges of their segments, against the oracle.
+
+Columns whose product counts stand at, just below and just above every segment
+size, formed so that stored B entries cross the rows of a segment, runs of
+equal rows cross lanes (up to a whole segment in one run), and A columns
+without entries stand between the others. Equal means the same structure and
+the same bits: the kernels add in Algorithm 1's order.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2303_02471_amd import inputs as gen
+from helpers import HAVE_GPU, assert_same_structure, assert_values_exact
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not HAVE_GPU, reason="needs an MI355X GPU")]
+
+if HAVE_GPU:
+    import torch
+    from paper_2303_02471_amd import api
+
+COUNTS = sorted({c for s in (4, 8, 16, 32, 64, 128, 256, 512, 1024)
+                 for c in (s // 2 + 1, s - 1, s, s + 1)} | {1, 2, 3})
+
+
+def _columns(style, m, seed):
+    """(A, B): several columns of B for every count in COUNTS."""
+    rng = np.random.default_rng(seed)
+    acols, bcols = [], []
+
+    def acol(rows):
+        acols.append(np.asarray(rows, np.int64))
+        return len(acols) - 1
+
+    empty = acol([])
+    for c in COUNTS:
+        for rep in range(3):
+            if style == "one_entry":  # one A column of c rows
+                b = [acol(rng.permutation(np.arange(c) + (m - c if rep else 0)))]
+            elif style == "one_row":  # c stored entries, one row: a single run
+                b = [acol([(0, m - 1, m // 2)[rep]]) for _ in range(c)]
+            else:  # entries of 0 to 9 rows out of few rows: many short runs
+                b, left, span = [], c, max(10, c // 3)
+                while left:
+                    z = min(left, int(rng.integers(1, 10)))
+                    b.append(acol(rng.choice(span, z, replace=False) + (m - span if rep else 0)))
+                    left -= z
+                    if rep == 2 and len(b) % 3 == 0 and len(b) < c // 2:
+                        b.append(empty)
+            bcols.append(b)
+    # an A column stands at most once in a column of B
+    used = [np.asarray(list(dict.fromkeys(b)), np.int64) for b in bcols]
+    acp = np.concatenate([[0], np.cumsum([len(r) for r in acols])]).astype(np.int32)
+    bcp = np.concatenate([[0], np.cumsum([len(b) for b in used])]).astype(np.int32)
+    ari = np.concatenate(acols).astype(np.int32)
+    bri = np.concatenate(used).astype(np.int32)
+    A = gen.CSC(m, len(acols), acp, ari, rng.standard_normal(len(ari)))
+    B = gen.CSC(len(acols), len(used), bcp, bri, rng.standard_normal(len(bri)))
+    B.val[::7] = -0.0
+    return A, B
+
+
+@pytest.mark.parametrize("m", [1100, 1 << 21], ids=["keys32", "keys64"])
+@pytest.mark.parametrize("style", ["one_entry", "one_row", "mixed"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_segment_edges(style, m, dtype):
+    print(f"[case] segment edges {style} m={m} {dtype}", flush=True)
+    np_t = np.float64 if dtype == "f64" else np.float32
+    A, B = (x.astype(np_t) for x in _columns(style, m, 5))
+    ocp, ori, ov = oracle.spgemm(A, B, dtype)
+    At, Bt = api.CscTensor.from_host(A), api.CscTensor.from_host(B)
+    cp, ri, v = api.matmul(At, Bt).to_host()
+    assert_same_structure(cp, ri, ocp, ori, style)
+    assert_values_exact(v, ov, style)
+    # the one-call product on a kept plan fills at the previous positions
+    plan, cpt, rit, vt, nnz = api.multiply(At, Bt)
+    for _ in range(2):
+        plan, cpt, rit, vt, nnz = api.multiply(At, Bt, plan=plan, out=(cpt, rit, vt))
+        torch.cuda.synchronize()
+        assert_same_structure(cpt.cpu().numpy(), rit[:nnz].cpu().numpy(), ocp, ori, style)
+        assert_values_exact(vt[:nnz].cpu().numpy(), ov, style)
+    assert plan.stats()["later_max"] == _depth(A, B)
+    plan.close()
+
+
+def _depth(A, B):
+    """Most products adding into one entry of C, less one."""
+    deep = 0
+    for j in range(B.ncols):
+        rows = [A.rowidx[A.colptr[k]:A.colptr[k + 1]]
+                for k in B.rowidx[B.colptr[j]:B.colptr[j + 1]]]
+        rows = np.concatenate(rows) if rows else np.zeros(0, np.int32)
+        if len(rows):
+            deep = max(deep, int(np.unique(rows, return_counts=True)[1].max()) - 1)
+    return deep
