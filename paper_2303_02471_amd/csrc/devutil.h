@@ -116,6 +116,24 @@ __device__ __forceinline__ int wave_incl_max(int v) {
 
 __device__ __forceinline__ int wave_bcast(int v, int src) { return shfl_idx(v, src); }
 
+// 64-bit prefix sum (values and sums of 0 .. 2^63 - 1) over the wavefront, and
+// its last value: three scans of 21-bit pieces, whose sums stay below 2^27
+__device__ __forceinline__ long long wave_incl_scan64(long long v) {
+    constexpr int B = 21, M = (1 << B) - 1;
+    const long long a = wave_incl_scan((int)v & M), b = wave_incl_scan((int)(v >> B) & M),
+                    c = wave_incl_scan((int)(v >> (2 * B)) & M);
+    return a + (b << B) + (c << (2 * B));
+}
+__device__ __forceinline__ long long wave_last64(long long v) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
+    const unsigned hi =
+        (unsigned)__builtin_amdgcn_readlane((int)(unsigned)((unsigned long long)v >> 32), 63);
+    return (long long)(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ long long wave_sum64(long long v) {
+    return wave_last64(wave_incl_scan64(v));
+}
+
 // the sum over the wavefront, in every lane
 __device__ __forceinline__ int wave_sum(int v) {
     return __builtin_amdgcn_readlane(wave_incl_scan(v), 63);
@@ -165,6 +183,29 @@ __device__ __forceinline__ int wg_excl_scan(int v, int *tmp, int &total) {
     }
     __syncthreads();
     int ex = tmp[w] + inc - v;
+    total = tmp[T / 64];
+    __syncthreads();
+    return ex;
+}
+
+// the same for 64-bit values (`tmp` holds T / 64 + 1 of them)
+template <int T>
+__device__ __forceinline__ long long wg_excl_scan64(long long v, long long *tmp, long long &total) {
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const long long inc = wave_incl_scan64(v);
+    if (l == 63) tmp[w] = inc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        long long run = 0;
+        for (int i = 0; i < T / 64; ++i) {
+            const long long x = tmp[i];
+            tmp[i] = run;
+            run += x;
+        }
+        tmp[T / 64] = run;
+    }
+    __syncthreads();
+    const long long ex = tmp[w] + inc - v;
     total = tmp[T / 64];
     __syncthreads();
     return ex;

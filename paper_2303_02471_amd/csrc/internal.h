@@ -53,8 +53,25 @@ __host__ __device__ constexpr int blk_class(int op) {
     return op <= 512 ? 0 : (op <= 1024 ? 1 : (op <= 2048 ? 2 : (op <= 4096 ? 3 : 4)));
 }
 constexpr int kBlock = 256;
-// columns per classification tile
+// Columns per classification tile: the largest, and the tile of a launch over
+// ncols columns, the smallest power of two that gives at most 1024 tiles (more
+// tiles than compute units by a factor of four, so that the longest tile's
+// chain of passes is short; with 8 columns of 1600 products in 4096 the
+// classification took 76 us in 8 tiles of 512).
 constexpr int kTile = 512;
+constexpr int kTileMin = 8;
+// tiles up to which the place kernel combines the tiles' records itself
+constexpr int kSelfTiles = 1280;
+inline int plan_tile(long long ncols) {
+    int t = kTileMin;
+    while (t < kTile && ncols > 1024ll * t) t *= 2;
+    return t;
+}
+constexpr int kHeavyBins = 3;  // bins of the heavy columns: SORT2, SORT3, WSORT
+constexpr int kWinKpl = 16;    // positions per lane of a heavy row window's buffer
+// planned products per window: 15/16 of the buffer (measured: 7/8 leaves more
+// windows and rescans, 1000 of 1024 more windows that overflow and are halved)
+constexpr int kWinTarget = 64 * kWinKpl * 15 / 16;
 
 // error bits gathered on the device
 enum ErrBits : int {
@@ -93,6 +110,9 @@ struct Hdr {
     int32_t pad_;
 };
 
+// words of the header before the per-problem totals, which follow it
+constexpr int kHdrWords = (int)((sizeof(Hdr) + 63) / 64 * 16);
+
 // binw[g] = bin | (window flags << 8); the workgroup accumulator records how
 // it accumulated the column's row windows
 enum WinFlags : int { WF_DIRECT = 1, WF_HASH = 2, WF_SPLIT = 4 };
@@ -119,12 +139,21 @@ struct KArgs {
     int32_t ncols;          // total columns over all problems
     int32_t ntiles;
     const int4 *tiles;      // (pid, j0, j1, 0) when nprob > 1
-    // per classification tile: the tile's column count of every bin (then the
-    // tile's first position inside the bin), its products and the most
-    // chunks of one of its columns above t_split
-    int32_t *th;            // [ntiles * NBINS]
+    int32_t tile;           // columns per classification tile
+    int32_t tpitch;         // tiles per row of the records below (a multiple of 8)
+    int32_t direct;         // direct-gather accumulators (no product space)
+    // Records per classification tile: its column count of every bin and its
+    // error bits, its products, the most chunks of one of its columns above
+    // t_split, and per heavy bin its products and planned windows. With more
+    // than kSelfTiles tiles k_tally turns them into positions before the tile.
+    uint16_t *th;           // [(NBINS + 1) tpitch]
     long long *ttot;        // [ntiles]
     int32_t *tmax;          // [ntiles]
+    long long *tprod;       // [kHeavyBins tpitch]
+    int32_t *twin;          // [kHeavyBins tpitch]
+    int32_t *tbase;         // [NBINS tpitch] first position inside the bin
+    long long *tpbase;      // [kHeavyBins tpitch] products of the heavy columns before
+    int32_t *twbase;        // [kHeavyBins tpitch] windows of the heavy columns before
     Tune tune;
     // A symbolic launch planned before the sizes are read back (from the
     // previous call on the plan) covers the bins in spec_mask with product
@@ -172,8 +201,8 @@ struct KArgs {
     // Heavy columns of the direct-gather accumulators (bins SORT3 and WSORT,
     // adjacent in the bin list, position li among them): first product in the
     // heavy scratch, first row window, and the scratch itself.
-    long long *hoff;        // [heavy columns + 1]
-    int32_t *wbase;         // [heavy columns + 1]
+    long long *hoff;        // [heavy columns]
+    int32_t *wbase;         // [heavy columns]
     int32_t *wcnt;          // [windows] output entries of every window (symbolic phase)
     int32_t *winmap;        // [windows] heavy column (position li) of every window
     int32_t *hrow;          // [heavy products] row of every product of a heavy column
@@ -212,8 +241,8 @@ __device__ __forceinline__ Prob get_prob(const KArgs &a, int pid) {
 // ---------------------------------------------------------------- launchers
 // Each returns hipSuccess or the launch error.
 hipError_t launch_classify(const KArgs &a, hipStream_t s);
-// bin counts, product total and largest chunk count from the tile tallies;
-// per-tile positions inside every bin
+// positions before every tile and the totals, when the place kernel does not
+// combine the tiles' records itself
 hipError_t launch_tally(const KArgs &a, hipStream_t s);
 hipError_t launch_place(const KArgs &a, hipStream_t s);
 // wavefront groups of ESC sub-bin `sub`; wide: 64-bit keys (rows of 2^24 - 1 and more)
@@ -231,8 +260,15 @@ hipError_t launch_wsort(const KArgs &a, bool wide, int grid, hipStream_t s);
 // workgroup hash accumulator of block class `cls` (columns and their bin-list
 // positions from the device header; any grid covers them)
 hipError_t launch_block(const KArgs &a, int cls, int grid, hipStream_t s);
+// C's column pointers from the per-column counts; of a single problem also
+// the publication of the header and total to the host (pub.dst, may be NULL)
+struct PubArgs {
+    unsigned long long *dst;  // mapped host memory: (word, seq) pairs
+    int32_t nwords;           // header words, then the totals' words
+    uint32_t seq;
+};
 hipError_t launch_scan(const KArgs &a, long long *gcp, long long *bsum, int nblk,
-                       long long *totals, hipStream_t s);
+                       long long *totals, const PubArgs &pub, hipStream_t s);
 // first product of every global column (colprod) and first column of every
 // product-balanced tile (tilestart); bsum holds nbsum scan partials
 hipError_t launch_prod_offsets(const KArgs &a, long long *bsum, int nbsum, hipStream_t s);
@@ -257,8 +293,6 @@ hipError_t launch_later_runs(const KArgs &a, bool f64, long long n, hipStream_t 
 int wave_bin_items(int bin, int ncols);
 hipError_t launch_acc_wave(const KArgs &a, int bin, int items, bool wide, bool fill, bool f64,
                            hipStream_t s);
-// offsets and windows of the heavy columns; totals to the header
-hipError_t launch_heavy_plan(const KArgs &a, hipStream_t s);
 // global ESC with radix sort over groups of heavy columns (after the heavy
 // expansion); rowbits: bits of the largest row index
 hipError_t launch_esc_radix(const KArgs &a, long long heavy_products, int rowbits, bool fill,
@@ -287,9 +321,9 @@ hipError_t launch_lane_blocked(const KArgs &a, const LbArgs &lb, int ncols_hint,
 // heavy columns: windows, or (radix) the global radix ESC; heavy_products and
 // rowbits size the radix launch
 // part 0 .. heavy_parts(radix) - 1 of the heavy columns' launches, in order;
-// a launch whose heavy plan ran in it (planned) starts at heavy_first_part
+// a launch whose windows are mapped already starts at heavy_first_part
 int heavy_parts(bool radix);
-int heavy_first_part(bool radix, bool planned);
+int heavy_first_part(bool radix, bool mapped);
 hipError_t launch_heavy(const KArgs &a, int ncols, int nwin, bool wide, bool fill, bool f64,
                         hipStream_t s, bool radix, long long heavy_products, int rowbits,
                         int part);
@@ -338,7 +372,7 @@ hipError_t launch_backward(const Prob &p, const BwView &w, bool f64, const void 
                            hipStream_t s);
 // nwords 32-bit words from src to mapped host memory dst, as 8-byte pairs
 // (word, seq)
-hipError_t launch_publish(const void *src, int nwords, void *dst, uint32_t seq, hipStream_t s);
+hipError_t launch_publish(const void *src, const PubArgs &pub, hipStream_t s);
 // exclusive scans of n int32 values (bsum: nbsum partials, in place allowed
 // for the int32 output)
 hipError_t launch_scan_i32(const int32_t *in, int n, long long *bsum, int nbsum, int32_t *out,

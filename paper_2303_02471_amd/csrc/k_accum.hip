@@ -767,106 +767,18 @@ __global__ __launch_bounds__(64) void k_acc_lane(KArgs a, int bin) {
 }
 
 // ---------------------------------------------------------------- heavy columns
-// Plan of the heavy columns (bins SORT2, SORT3 and WSORT: more than 1024
-// products; contiguous in the bin list): per column its first product in the heavy scratch (hoff) and its
-// first window (wbase), W = ceil(Op / kWinTarget) windows of equal row span;
-// in a planned launch also the map of windows to columns.
-// One workgroup; the totals go to the header (the host sizes the scratch from
-// them). A planned launch whose scratch is too small is redone.
-constexpr int kWinKpl = 16;                     // positions per lane of a window's buffer
-// planned products per window: 15/16 of the buffer (measured: 7/8 leaves more
-// windows and rescans, 1000 of 1024 more windows that overflow and are halved)
-constexpr int kWinTarget = 64 * kWinKpl * 15 / 16;
-
-__global__ __launch_bounds__(1024) void k_heavy_plan(KArgs a) {
-    constexpr int T = 1024, PT = 4;
-    __shared__ int tmp[T / 64 + 1];
-    __shared__ long long s_tmp[T / 64 + 1];
-    if (__syncthreads_or(__atomic_load_n(&a.hdr->err, __ATOMIC_RELAXED) != 0)) return;
-    int first = 0;
-    for (int b = 0; b < kHeavyBin; ++b) first += a.hdr->bin_count[b];
-    int n = 0;
-    for (int b = kHeavyBin; b <= BIN_WSORT; ++b) n += a.hdr->bin_count[b];
-    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
-    long long pcarry = 0;
-    int wcarry = 0;
-    // PT consecutive columns per thread: one scan step covers T PT columns
-    for (int i0 = 0; i0 < n; i0 += T * PT) {
-        const int ib = i0 + tid * PT;
-        int op[PT], nw[PT];
-        int wsum = 0;
-        long long v = 0;
-#pragma unroll
-        for (int u = 0; u < PT; ++u) {
-            const int i = ib + u;
-            op[u] = i < n ? a.binlist[first + i].w : 0;
-            nw[u] = i < n ? max(1, ceil_div(op[u], kWinTarget)) : 0;
-            wsum += nw[u];
-            v += op[u];
-        }
-        int wt;
-        const int wex = wg_excl_scan<T>(wsum, tmp, wt);
-        // 64-bit prefix of the products
-        long long inc = v;
-#pragma unroll
-        for (int dd = 1; dd < 64; dd <<= 1) {
-            const int lo = shfl_up_i((int)(unsigned)inc, dd);
-            const int hi = shfl_up_i((int)(unsigned)((unsigned long long)inc >> 32), dd);
-            const long long o = (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-            if (l >= dd) inc += o;
-        }
-        if (l == 63) s_tmp[w] = inc;
-        __syncthreads();
-        if (tid == 0) {
-            long long run = 0;
-            for (int q = 0; q < T / 64; ++q) {
-                const long long x = s_tmp[q];
-                s_tmp[q] = run;
-                run += x;
-            }
-            s_tmp[T / 64] = run;
-        }
-        __syncthreads();
-        long long pr = pcarry + s_tmp[w] + inc - v;
-        int wr = wcarry + wex;
-#pragma unroll
-        for (int u = 0; u < PT; ++u) {
-            const int i = ib + u;
-            if (i < n) {
-                a.hoff[i] = pr;
-                a.wbase[i] = wr;
-                // a planned launch has its window scratch already: the
-                // column's windows are mapped here (as far as it holds them;
-                // more windows than it holds ask for a redo below)
-                if (a.spec_total >= 0)
-                    for (int q = wr; q < wr + nw[u] && q < a.win_cap; ++q) a.winmap[q] = i;
-            }
-            pr += op[u];
-            wr += nw[u];
-        }
-        pcarry += s_tmp[T / 64];
-        wcarry += wt;
-        __syncthreads();
-    }
-    if (tid == 0) {
-        a.hoff[n] = pcarry;
-        a.wbase[n] = wcarry;
-        a.hdr->heavy_prod = (unsigned long long)pcarry;
-        a.hdr->heavy_win = wcarry;
-        if (a.spec_total >= 0 && (pcarry > a.heavy_cap || wcarry > a.win_cap))
-            atomicOr(&a.hdr->err, ERR_RETRY);
-    }
-}
-
 // The heavy column of every window (one thread per heavy column), written
 // once the window scratch is in place; a launch planned with too small a
 // scratch has been flagged for a redo and writes nothing.
 __global__ __launch_bounds__(kBlock) void k_win_map(KArgs a) {
     if (__atomic_load_n(&a.hdr->err, __ATOMIC_RELAXED)) return;
+    int first = 0;
+    for (int b = 0; b < kHeavyBin; ++b) first += a.hdr->bin_count[b];
     int n = 0;
     for (int b = kHeavyBin; b <= BIN_WSORT; ++b) n += a.hdr->bin_count[b];
     for (int li = blockIdx.x * kBlock + threadIdx.x; li < n; li += gridDim.x * kBlock) {
-        const int w0 = a.wbase[li], w1 = a.wbase[li + 1];
+        const int w0 = a.wbase[li];
+        const int w1 = w0 + (a.binlist[first + li].w - 1) / kWinTarget + 1;
         for (int w = w0; w < w1 && w < a.win_cap; ++w) a.winmap[w] = li;
     }
 }
@@ -895,7 +807,7 @@ __global__ __launch_bounds__(kBlock) void k_heavy_expand(KArgs a) {
         const int g = ent.x, bs = ent.y, nb = ent.z;
         const int pid = find_prob(a, g);
         const Prob d = get_prob(a, pid);
-        const long long base0 = a.hoff[li], end = a.hoff[li + 1];
+        const long long base0 = a.hoff[li], end = base0 + ent.w;
         const int2 *__restrict__ Ep = a.E + d.ebase;
         const gmem<const int32_t> *__restrict__ ari = to_gmem(d.ari);
         const gmem<const V> *__restrict__ av = to_gmem((const V *)d.av);
@@ -990,9 +902,7 @@ __global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
     const int lane = threadIdx.x;
     int first = 0;
     for (int b = 0; b < kHeavyBin; ++b) first += a.hdr->bin_count[b];
-    int n = 0;
-    for (int b = kHeavyBin; b <= BIN_WSORT; ++b) n += a.hdr->bin_count[b];
-    const int nwin = a.wbase[n];
+    const int nwin = a.hdr->heavy_win;
     int bad = 0;
     // windows of the largest columns (the longest scans) first; workgroups go
     // to the 8 XCDs in turn and each XCD has its own L2, so every run of kRun
@@ -1007,13 +917,13 @@ __global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
         const int wj = b >= full ? b : b - rb + (rb % kXcd) * kRun + rb / kXcd;
         const int wi = nwin - 1 - wj;
         const int li = a.winmap[wi];
-        const int wb = a.wbase[li], w = wi - wb, W = a.wbase[li + 1] - wb;
-        const int g = a.binlist[first + li].x;
+        const int4 ent = a.binlist[first + li];
+        const int g = ent.x, op = ent.w;
+        const int wb = a.wbase[li], w = wi - wb, W = (op - 1) / kWinTarget + 1;
         const int pid = find_prob(a, g);
         const Prob d = get_prob(a, pid);
         const int j = g - d.col0;
         const long long hb = a.hoff[li];
-        const int op = (int)(a.hoff[li + 1] - hb);
         const int *__restrict__ prow = a.hrow + hb;
         const V *__restrict__ pval = FILL ? (const V *)a.hval + hb : nullptr;
         // output position of the window: the entries of the earlier windows
@@ -1244,18 +1154,14 @@ hipError_t launch_acc_wave(const KArgs &a, int bin, int items, bool wide, bool f
                 : launch_wave_bin<unsigned, float, true>(a, bin, items, s);
 }
 
-hipError_t launch_heavy_plan(const KArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(k_heavy_plan, dim3(1), dim3(1024), 0, s, a);
-    return hipGetLastError();
-}
-
 // The heavy columns' launches one part at a time (the caller interleaves them
 // with other streams' launches): windows take the map of windows, the
 // expansion and the windowed sort; the radix ESC the expansion and the sort.
 int heavy_parts(bool radix) { return radix ? 2 : 3; }
-// the first part a launch needs: the windows' map is written by the heavy
-// plan of a planned launch
-int heavy_first_part(bool radix, bool planned) { return !radix && planned ? 1 : 0; }
+// the first part a launch needs: the windows' map is written by the place
+// kernel of a planned launch, and stays from the counting launch to the
+// filling ones that follow it
+int heavy_first_part(bool radix, bool mapped) { return !radix && mapped ? 1 : 0; }
 
 hipError_t launch_heavy(const KArgs &a, int ncols, int nwin, bool wide, bool fill, bool f64,
                         hipStream_t s, bool radix, long long heavy_products, int rowbits,

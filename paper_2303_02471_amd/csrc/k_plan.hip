@@ -1,31 +1,91 @@
 // Planning kernels: per-column product count Op_j (Section 3.1), accumulator
 // choice (the role of the paper's sort + hybrid switch, Sections 3.1-3.3),
 // placement of columns into per-accumulator lists, and the column-pointer scan.
+#include <cstddef>
+
 #include "devutil.h"
 
 namespace spg {
 
+// the tile's problem and columns [j0, j1)
+__device__ __forceinline__ void tile_columns(const KArgs &a, int &pid, int &j0, int &j1) {
+    if (a.nprob == 1) {
+        pid = 0;
+        j0 = blockIdx.x * a.tile;
+        j1 = min(a.single.n, j0 + a.tile);
+    } else {
+        const int4 tl = a.tiles[blockIdx.x];
+        pid = tl.x;
+        j0 = tl.y;
+        j1 = tl.z;
+    }
+}
+
+// row windows planned for a heavy column of op products
+__device__ __forceinline__ int heavy_windows(int op) { return max(1, (op - 1) / kWinTarget + 1); }
+
+// Totals of the heavy columns into the header; a planned launch whose scratch
+// holds fewer products or windows is redone (set_err: the bit goes straight to
+// the header, else it is returned).
+__device__ __forceinline__ int heavy_totals(const KArgs &a, long long prod, long long win,
+                                            bool set_err) {
+    a.hdr->heavy_prod = (unsigned long long)prod;
+    a.hdr->heavy_win = (int)min(win, 0x7fffffffll);
+    const int err = a.direct && a.spec_total >= 0 && (prod > a.heavy_cap || win > a.win_cap) ? ERR_RETRY : 0;
+    if (set_err && err) atomicOr(&a.hdr->err, err);
+    return err;
+}
+
+// The whole header of a launch whose place kernel combines the tiles itself
+// (one thread). With the product-space accumulators the header was cleared
+// before and another stream may already raise error bits in it.
+__device__ __forceinline__ void place_header(const KArgs &a, int err, const int *counts,
+                                             unsigned long long total, int maxch, long long hprod,
+                                             long long hwin) {
+    Hdr *h = a.hdr;
+    err &= ERR_CSC | ERR_OPOVF;
+#pragma unroll 1
+    for (int b = 0; b < NBINS; ++b) {
+        h->bin_count[b] = counts[b];
+        // a planned launch that does not cover a non-empty bin is redone
+        if (a.spec_total >= 0 && counts[b] > 0 && !((a.spec_mask >> b) & 1u)) err |= ERR_RETRY;
+    }
+    // a planned launch sized for another product count is redone
+    if (a.spec_total >= 0 && total != (unsigned long long)a.spec_total) err |= ERR_RETRY;
+    h->total_op = total;
+    h->big_chunks = maxch;
+    if (a.direct) {
+        err |= heavy_totals(a, hprod, hwin, false);
+        h->later_maxk = 0;
+        h->cap_over = 0;
+        h->err = err;
+    } else if (err) {
+        atomicOr(&h->err, err);
+    }
+}
+
 // ---------------------------------------------------------------- classify
-// One workgroup per tile of at most kTile columns of one problem. The tile's
+// One workgroup per tile of at most a.tile columns of one problem. The tile's
 // stored B entries are contiguous; threads walk them flat (coalesced reads of
 // B.rowidx, gathers of A.colptr), and add Z^A_k to the owning column's count.
 // Every index read here is checked before it is used as an address.
+//
+// What bounds it: the chain of dependent loads (B's row, A's column pointers)
+// of the tile with the most entries, so the tiles are cut fine (plan_tile) and
+// a pass's gathers are in flight together with the next pass's row loads.
+// 4096 columns of 40 entries: 76.5 us in 8 tiles of 512 columns, 8.5 us in 512
+// tiles of 8; 1000 columns of 5: 15.5 -> 7.3 us. A million power-law columns
+// stay at 70 us: 5 M gathers of A.colptr in tiles of 512.
 __global__ __launch_bounds__(kBlock) void k_classify(KArgs a) {
     __shared__ int s_bcp[kTile + 1];
     __shared__ unsigned long long s_op[kTile];
     __shared__ int s_hist[NBINS];
     __shared__ int s_err, s_maxch;
-    __shared__ unsigned long long s_tot;
+    __shared__ unsigned long long s_tot, s_hp[kHeavyBins];
+    __shared__ int s_hw[kHeavyBins];
 
     int pid, j0, j1;
-    if (a.nprob == 1) {
-        pid = 0;
-        j0 = blockIdx.x * kTile;
-        j1 = min(a.single.n, j0 + kTile);
-    } else {
-        int4 tl = a.tiles[blockIdx.x];
-        pid = tl.x; j0 = tl.y; j1 = tl.z;
-    }
+    tile_columns(a, pid, j0, j1);
     const Prob d = get_prob(a, pid);
     const int nt = j1 - j0;
     const int tid = threadIdx.x;
@@ -33,6 +93,7 @@ __global__ __launch_bounds__(kBlock) void k_classify(KArgs a) {
     for (int c = tid; c <= nt; c += kBlock) s_bcp[c] = d.bcp[j0 + c];
     for (int c = tid; c < nt; c += kBlock) s_op[c] = 0;
     if (tid < NBINS) s_hist[tid] = 0;
+    if (tid < kHeavyBins) { s_hp[tid] = 0; s_hw[tid] = 0; }
     if (tid == 0) { s_err = 0; s_tot = 0; s_maxch = 0; }
     __syncthreads();
 
@@ -50,102 +111,117 @@ __global__ __launch_bounds__(kBlock) void k_classify(KArgs a) {
     }
     if (err) atomicOr(&s_err, err);
     __syncthreads();
-    if (s_err) {
-        if (tid == 0) atomicOr(&a.hdr->err, s_err);
-        return;
-    }
 
     const int pb = s_bcp[0], pe = s_bcp[nt];
     const gmem<const int32_t> *__restrict__ bri = to_gmem(d.bri);
     err = 0;
     // with no A columns every stored B entry is out of range (and A.colptr
     // holds one entry: the pair loads below need two)
-    const int pe_ok = d.k > 0 ? pe : pb;
     if (d.k == 0 && pe > pb) err = ERR_CSC;
-    for (int p0 = pb; p0 < pe_ok; p0 += 4 * kBlock) {
-        // Every load of the pass is issued before any is used: a slot past
-        // the tile's end reads its last entry, an index out of range reads
-        // A's first column pointers; neither result is used.
-        int kk[4], x0[4], x1[4];
+    if (!s_err && d.k > 0 && pe > pb) {
+        // Passes of 4 kBlock entries. A slot past the tile's end reads its last
+        // entry, an index out of range reads A's first column pointers; neither
+        // result is used. Both column pointers come in one 8-byte load (4-byte
+        // alignment is enough for a global load): kc < k, so kc + 1 <= k.
+        constexpr int U = 4, STEP = U * kBlock;
+        int kk[U], kn[U];
+        int2a x[U];
+        auto rows_at = [&](int p0, int (&k)[U]) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) kk[u] = bri[min(p0 + u * kBlock + tid, pe - 1)];
+            for (int u = 0; u < U; ++u) k[u] = bri[min(p0 + u * kBlock + tid, pe - 1)];
+        };
+        auto pairs_of = [&](const int (&k)[U], int2a (&v)[U]) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            // both column pointers in one 8-byte load (4-byte alignment is
-            // enough for a global load): kc < k, so kc + 1 <= k stays inside
-            const int kc = (kk[u] < 0 || kk[u] >= d.k) ? 0 : kk[u];
-            const int2a x = load_pair(d.acp, kc);
-            x0[u] = x.x;
-            x1[u] = x.y;
-        }
+            for (int u = 0; u < U; ++u)
+                v[u] = load_pair(d.acp, (k[u] < 0 || k[u] >= d.k) ? 0 : k[u]);
+        };
+        rows_at(pb, kk);
+        for (int p0 = pb; p0 < pe; p0 += STEP) {
+            pairs_of(kk, x);
+            if (p0 + STEP < pe) rows_at(p0 + STEP, kn);  // in flight beside the gathers
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int p = p0 + u * kBlock + tid;
-            const int k = kk[u];
-            const bool in = p < pe;
-            const bool ok = k >= 0 && k < d.k && x0[u] >= 0 && x1[u] >= x0[u] && x1[u] <= d.nnza;
-            const int s0 = ok ? x0[u] : 0, z = (in && ok) ? x1[u] - x0[u] : 0;
-            if (in && !ok) err = ERR_CSC;
-            // the A column each stored B entry selects, for the accumulators
-            if (in) a.E[d.ebase + p] = make_int2(s0, z);
-            if (z > 0) atomicAdd(&s_op[last_le(s_bcp, nt + 1, p)], (unsigned long long)z);
+            for (int u = 0; u < U; ++u) {
+                const int p = p0 + u * kBlock + tid;
+                const int k = kk[u];
+                const bool in = p < pe;
+                const bool ok = k >= 0 && k < d.k && x[u].x >= 0 && x[u].y >= x[u].x && x[u].y <= d.nnza;
+                const int s0 = ok ? x[u].x : 0, z = (in && ok) ? x[u].y - x[u].x : 0;
+                if (in && !ok) err = ERR_CSC;
+                // the A column each stored B entry selects, for the accumulators
+                if (in) a.E[d.ebase + p] = make_int2(s0, z);
+                if (z > 0) atomicAdd(&s_op[last_le(s_bcp, nt + 1, p)], (unsigned long long)z);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) kk[u] = kn[u];
         }
     }
     if (err) atomicOr(&s_err, err);
     __syncthreads();
-    if (s_err) {
-        if (tid == 0) atomicOr(&a.hdr->err, s_err);
-        return;
-    }
 
     const int esc_max = 4 << (a.tune.esc_bins - 1);
     unsigned long long tot = 0;
     int maxch = 0;
     err = 0;
-    for (int c = tid; c < nt; c += kBlock) {
-        const int g = d.col0 + j0 + c;
-        unsigned long long op64 = s_op[c];
-        if (op64 > 0x7fffffffull) { err = ERR_OPOVF; op64 = 0x7fffffffull; }
-        tot += op64;
-        const int op = (int)op64;
-        // the sort-merge bins take a column by its products or its stored B
-        // entries, whichever is more (a work item holds both)
-        const int size = max(op, s_bcp[c + 1] - s_bcp[c]);
-        int bin;
-        if (op == 0) bin = BIN_EMPTY;
-        else if (size <= esc_max) bin = BIN_ESC0 + max(ceil_log2(size), 2) - 2;
-        else if (op > a.tune.t_block) bin = BIN_BLK0 + blk_class(op);
-        else if (size <= kSortMax) bin = BIN_SORT0 + max(ceil_log2(size), 9) - 9;
-        else bin = BIN_WSORT;
-        if (op > a.tune.t_split) maxch = max(maxch, ceil_div(s_bcp[c + 1] - s_bcp[c], kChunkB));
-        a.op[g] = op;
-        a.binw[g] = bin;
-        a.gnnz[g] = 0;
-        atomicAdd(&s_hist[bin], 1);
+    if (!s_err) {
+        for (int c = tid; c < nt; c += kBlock) {
+            const int g = d.col0 + j0 + c;
+            unsigned long long op64 = s_op[c];
+            if (op64 > 0x7fffffffull) { err = ERR_OPOVF; op64 = 0x7fffffffull; }
+            tot += op64;
+            const int op = (int)op64;
+            // the sort-merge bins take a column by its products or its stored B
+            // entries, whichever is more (a work item holds both)
+            const int size = max(op, s_bcp[c + 1] - s_bcp[c]);
+            int bin;
+            if (op == 0) bin = BIN_EMPTY;
+            else if (size <= esc_max) bin = BIN_ESC0 + max(ceil_log2(size), 2) - 2;
+            else if (op > a.tune.t_block) bin = BIN_BLK0 + blk_class(op);
+            else if (size <= kSortMax) bin = BIN_SORT0 + max(ceil_log2(size), 9) - 9;
+            else bin = BIN_WSORT;
+            if (op > a.tune.t_split) maxch = max(maxch, ceil_div(s_bcp[c + 1] - s_bcp[c], kChunkB));
+            a.op[g] = op;
+            a.binw[g] = bin;
+            a.gnnz[g] = 0;
+            atomicAdd(&s_hist[bin], 1);
+            if (bin >= BIN_SORT2 && bin <= BIN_WSORT) {
+                atomicAdd(&s_hp[bin - BIN_SORT2], (unsigned long long)op);
+                atomicAdd(&s_hw[bin - BIN_SORT2], heavy_windows(op));
+            }
+        }
     }
-    if (err) atomicOr(&s_err, err);
     // tile total of products
+    if (err) atomicOr(&s_err, err);
     atomicAdd(&s_tot, tot);
     if (maxch) atomicMax(&s_maxch, maxch);
     __syncthreads();
-    // the tile's tallies (no device atomics: k_tally combines the tiles)
-    if (tid < NBINS) a.th[blockIdx.x * NBINS + tid] = s_hist[tid];
+    // the tile's tallies (no device atomics: k_place or k_tally combine them),
+    // counts of at most kTile columns and the tile's error bits
+    const int t = blockIdx.x;
+    if (tid < NBINS) a.th[tid * a.tpitch + t] = (uint16_t)s_hist[tid];
+    if (tid == NBINS) a.th[NBINS * a.tpitch + t] = (uint16_t)s_err;
+    if (tid < kHeavyBins) {
+        a.tprod[tid * a.tpitch + t] = (long long)s_hp[tid];
+        a.twin[tid * a.tpitch + t] = s_hw[tid];
+    }
     if (tid == 0) {
-        a.ttot[blockIdx.x] = (long long)s_tot;
-        a.tmax[blockIdx.x] = s_maxch;
+        a.ttot[t] = (long long)s_tot;
+        a.tmax[t] = s_maxch;
         if (s_err) atomicOr(&a.hdr->err, s_err);
     }
 }
 
 // ---------------------------------------------------------------- tally
-// Workgroup b < NBINS: exclusive scan of bin b's per-tile counts (in place:
-// each tile's first position inside the bin) and the bin's total. Workgroup
-// NBINS: the product total and the largest chunk count.
+// With more than kSelfTiles tiles: workgroup b < NBINS scans bin b's per-tile
+// counts (each tile's first position inside the bin) and writes the bin's
+// total; workgroup NBINS the product total, the largest chunk count and the
+// error bits; the kHeavyBins after it the heavy columns' products and windows
+// per tile, over the heavy bins in bin-list order.
 __global__ __launch_bounds__(256) void k_tally(KArgs a) {
     constexpr int T = 256, PT = 8;  // threads, consecutive tiles per thread
     __shared__ int tmp[T / 64 + 1];
+    __shared__ long long tmp64[T / 64 + 1];
     __shared__ unsigned long long s_tot;
-    __shared__ int s_max;
+    __shared__ int s_max, s_err;
     const int tid = threadIdx.x, b = blockIdx.x, nt = a.ntiles;
     if (b < NBINS) {
         int carry = 0;
@@ -154,14 +230,14 @@ __global__ __launch_bounds__(256) void k_tally(KArgs a) {
             int v[PT], sum = 0;
 #pragma unroll
             for (int u = 0; u < PT; ++u) {
-                v[u] = tb + u < nt ? a.th[(tb + u) * NBINS + b] : 0;
+                v[u] = tb + u < nt ? a.th[b * a.tpitch + tb + u] : 0;
                 sum += v[u];
             }
             int total;
             int run = carry + wg_excl_scan<T>(sum, tmp, total);
 #pragma unroll
             for (int u = 0; u < PT; ++u) {
-                if (tb + u < nt) a.th[(tb + u) * NBINS + b] = run;
+                if (tb + u < nt) a.tbase[b * a.tpitch + tb + u] = run;
                 run += v[u];
             }
             carry += total;
@@ -172,117 +248,353 @@ __global__ __launch_bounds__(256) void k_tally(KArgs a) {
             if (a.spec_total >= 0 && carry > 0 && !((a.spec_mask >> b) & 1u))
                 atomicOr(&a.hdr->err, ERR_RETRY);
         }
-    } else {
+    } else if (b == NBINS) {
         if (tid == 0) {
             s_tot = 0;
             s_max = 0;
+            s_err = 0;
         }
         __syncthreads();
         unsigned long long tot = 0;
-        int mx = 0;
-        for (int t0 = 0; t0 < nt; t0 += T * PT) {
-#pragma unroll
-            for (int u = 0; u < PT; ++u) {
-                const int t = t0 + u * T + tid;
-                if (t < nt) {
-                    tot += (unsigned long long)a.ttot[t];
-                    mx = max(mx, a.tmax[t]);
-                }
-            }
+        int mx = 0, err = 0;
+        for (int t = tid; t < nt; t += T) {
+            tot += (unsigned long long)a.ttot[t];
+            mx = max(mx, a.tmax[t]);
+            err |= a.th[NBINS * a.tpitch + t];
         }
         atomicAdd(&s_tot, tot);
         atomicMax(&s_max, mx);
+        if (err) atomicOr(&s_err, err);
         __syncthreads();
         if (tid == 0) {
             a.hdr->total_op = s_tot;
             a.hdr->big_chunks = s_max;
             // a planned launch sized for another product count is redone
-            if (a.spec_total >= 0 && s_tot != (unsigned long long)a.spec_total)
-                atomicOr(&a.hdr->err, ERR_RETRY);
+            if (a.spec_total >= 0 && s_tot != (unsigned long long)a.spec_total) s_err |= ERR_RETRY;
+            if (s_err) atomicOr(&a.hdr->err, s_err);
         }
+    } else {
+        // heavy bin c: its windows and products start after those of the
+        // heavy bins before it
+        const int c = b - NBINS - 1;
+        long long pcarry = 0, wcarry = 0;
+        for (int q = 0; q <= c; ++q) {
+            for (int t0 = 0; t0 < nt; t0 += T * PT) {
+                const int tb = t0 + tid * PT;
+                long long pv[PT], wv[PT], psum = 0, wsum = 0;
+#pragma unroll
+                for (int u = 0; u < PT; ++u) {
+                    const bool in = tb + u < nt;
+                    pv[u] = in ? a.tprod[q * a.tpitch + tb + u] : 0;
+                    wv[u] = in ? a.twin[q * a.tpitch + tb + u] : 0;
+                    psum += pv[u];
+                    wsum += wv[u];
+                }
+                long long ptot, wtot;
+                long long prun = pcarry + wg_excl_scan64<T>(psum, tmp64, ptot);
+                long long wrun = wcarry + wg_excl_scan64<T>(wsum, tmp64, wtot);
+                if (q == c) {
+#pragma unroll
+                    for (int u = 0; u < PT; ++u) {
+                        if (tb + u < nt) {
+                            a.tpbase[c * a.tpitch + tb + u] = prun;
+                            a.twbase[c * a.tpitch + tb + u] = (int)wrun;
+                        }
+                        prun += pv[u];
+                        wrun += wv[u];
+                    }
+                }
+                pcarry += ptot;
+                wcarry += wtot;
+            }
+        }
+        if (c == kHeavyBins - 1 && tid == 0) heavy_totals(a, pcarry, wcarry, true);
     }
 }
 
 hipError_t launch_tally(const KArgs &a, hipStream_t s) {
-    if (a.ntiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tally, dim3(NBINS + 1), dim3(256), 0, s, a);
+    if (a.ntiles <= kSelfTiles) return hipSuccess;
+    hipLaunchKernelGGL(k_tally, dim3(NBINS + 1 + kHeavyBins), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- place
-// Same tiling. Each tile writes its columns to its range of every bin list
-// (the tally's per-tile positions) in column order, so the columns that one
-// wavefront of an accumulator takes lie close together (their per-column
-// data and their output in C share cache lines). The rank of a column inside
-// its bin is counted with wavefront ballots per bin, then the counts of the
-// waves before it.
-__global__ __launch_bounds__(kBlock) void k_place(KArgs a) {
-    constexpr int PER = kTile / kBlock, NW = kBlock / 64;
-    __shared__ int s_start[NBINS];
-    __shared__ int s_cnt[PER * NW][NBINS];  // columns of every bin per (pass, wave), then prefix
+// Same tiling. Each tile writes its columns to its range of every bin list in
+// column order, so the columns that one wavefront of an accumulator takes lie
+// close together (their per-column data and their output in C share cache
+// lines). The rank of a column inside its bin is counted with wavefront
+// ballots per bin, then the counts of the waves before it. The heavy columns
+// (more than 1024 products) also get their first product in the heavy scratch
+// (hoff), their first row window (wbase; windows of about kWinTarget products)
+// and, in a planned launch, the map of windows to columns as far as its
+// scratch holds them (more windows than it holds ask for a redo).
+//
+// SELF (at most kSelfTiles tiles): every workgroup adds up the tiles before
+// its own from the tiles' records (38 bytes a tile, in the L2), which takes
+// less than a tally launch before this one; a workgroup of its own writes the
+// header. With the header's clearing, a tally, this kernel and a one-workgroup
+// plan of the heavy columns as four launches: 6.2 + 5.0 + 2.7 us and the
+// clearing for 1000 columns, 9.1 us now; 6.2 + 5.0 + 10.4 us for 4096 columns
+// of 1600 products, 15 us now. With more tiles each workgroup would read too
+// much and k_tally scans the records first.
+template <bool SELF>
+__global__ __launch_bounds__(kTile) void k_place(KArgs a) {
+    constexpr int T = kTile, NW = T / 64, ROWS = NBINS + 1;  // one column per thread
+    __shared__ int s_base[ROWS], s_total[ROWS], s_start[NBINS];
+    __shared__ int s_cnt[NW][NBINS];  // columns of every bin per wave, then prefix
+    __shared__ int s_w[NW][kHeavyBins];         // windows, then prefix
+    __shared__ long long s_p[NW][kHeavyBins];   // products, then prefix
+    __shared__ long long s_hpb[kHeavyBins], s_hpt[kHeavyBins];
+    __shared__ long long s_hwb[kHeavyBins], s_hwt[kHeavyBins];
+    __shared__ unsigned long long s_tot;
+    __shared__ int s_max;
 
-    if (__syncthreads_or((__atomic_load_n(&a.hdr->err, __ATOMIC_RELAXED) & (ERR_CSC | ERR_OPOVF)) != 0))
-        return;  // every thread takes the same branch
-    int pid, j0, j1;
-    if (a.nprob == 1) {
-        pid = 0;
-        j0 = blockIdx.x * kTile;
-        j1 = min(a.single.n, j0 + kTile);
-    } else {
-        int4 tl = a.tiles[blockIdx.x];
-        pid = tl.x; j0 = tl.y; j1 = tl.z;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, mt = blockIdx.x;
+    if (!SELF) {
+        if (__syncthreads_or((__atomic_load_n(&a.hdr->err, __ATOMIC_RELAXED) & (ERR_CSC | ERR_OPOVF)) != 0))
+            return;  // every thread takes the same branch
     }
+    // one workgroup past the tiles (SELF) has no columns and writes the header
+    const bool header = SELF && mt == a.ntiles;
+    int pid = 0, j0 = 0, j1 = 0;
+    if (!header) tile_columns(a, pid, j0, j1);
     const int col0 = a.nprob == 1 ? 0 : a.table[pid].col0;
     const int nt = j1 - j0;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (tid == 0) {
-        int run = 0;
-        for (int b = 0; b < NBINS; ++b) {
-            s_start[b] = run;
-            run += a.hdr->bin_count[b];
-        }
-    }
-    // column c = 64 (NW u + w) + lane: passes and waves in column order; the
-    // column's entries and product count load together with its bin
+    // column tid of the tile: its entries and product count load with its bin
     const int32_t *bcp = a.nprob == 1 ? a.single.bcp : a.table[pid].bcp;
-    int rank[PER], binv[PER], opv[PER];
-    int2a bse[PER];
+    const bool in = tid < nt;
+    const int bin = in ? a.binw[col0 + j0 + tid] : -1;
+    const int2a bse = in ? load_pair(bcp, j0 + tid) : int2a{0, 0};
+    const int op = in ? a.op[col0 + j0 + tid] : 0;
+    unsigned long long ptot = 0;  // the header's product total and largest chunk count
+    int pmax = 0;
+    if (SELF) {
+        // row r of the records: bin r's columns per tile; the last row error
+        // bits. Every load is issued before any is used.
+        constexpr int RW = (ROWS + NW - 1) / NW, CH = (kSelfTiles + 8 * 64 - 1) / (8 * 64);
+        uint4 v[RW][CH];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int c = 64 * (NW * u + w) + lane;
-        const bool in = c < nt;
-        binv[u] = in ? a.binw[col0 + j0 + c] : -1;
-        bse[u] = in ? load_pair(bcp, j0 + c) : int2a{0, 0};
-        opv[u] = in ? a.op[col0 + j0 + c] : 0;
-    }
+        for (int i = 0; i < RW; ++i) {
+            const int r = min(w + i * NW, ROWS - 1);
+            const uint4 *row = (const uint4 *)(a.th + (size_t)r * a.tpitch);
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        rank[u] = 0;
-        for (int b = 0; b < NBINS; ++b) {
-            const unsigned long long m = ballot(binv[u] == b);
-            if (binv[u] == b) rank[u] = popc64(m & mask_lt());
-            if (lane == 0) s_cnt[NW * u + w][b] = popc64(m);
+            for (int c = 0; c < CH; ++c) {
+                const int q = c * 64 + lane;
+                v[i][c] = 8 * q < a.tpitch ? row[q] : make_uint4(0, 0, 0, 0);
+            }
         }
+        if (header) {
+#pragma unroll
+            for (int c = 0; c < (kSelfTiles + T - 1) / T; ++c) {
+                const int t = c * T + tid;
+                ptot += t < a.ntiles ? (unsigned long long)a.ttot[t] : 0ull;
+                pmax = max(pmax, t < a.ntiles ? a.tmax[t] : 0);
+            }
+        }
+        // a word holds two tiles' counts, summed as pairs of 16 bits (a lane
+        // adds at most 24 tiles of kTile columns): all tiles, and those before
+        // this one by a mask per word
+        static_assert(8 * CH * kTile < 65536, "a lane's counts fit 16 bits");
+        unsigned tot[RW], bef[RW];
+#pragma unroll
+        for (int i = 0; i < RW; ++i) tot[i] = bef[i] = 0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int t0 = 8 * (c * 64 + lane);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int left = mt - (t0 + 2 * q), live = a.ntiles - (t0 + 2 * q);
+                const unsigned mb = left >= 2 ? ~0u : (left == 1 ? 0xffffu : 0u);
+                const unsigned ml = live >= 2 ? ~0u : (live == 1 ? 0xffffu : 0u);
+#pragma unroll
+                for (int i = 0; i < RW; ++i) {
+                    const unsigned x = (&v[i][c].x)[q] & ml;
+                    tot[i] = i == RW - 1 && w == NBINS % NW ? tot[i] | x : tot[i] + x;
+                    bef[i] += x & mb;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int r = w + i * NW;
+            int total = (int)((tot[i] & 0xffffu) + (tot[i] >> 16));
+            if (i == RW - 1 && r == NBINS) {
+                const unsigned bits = (tot[i] | (tot[i] >> 16)) & 0xffffu;
+                total = (ballot((bits & ERR_CSC) != 0) ? ERR_CSC : 0) |
+                        (ballot((bits & ERR_OPOVF) != 0) ? ERR_OPOVF : 0);
+            } else {
+                total = wave_sum(total);
+            }
+            const int before = wave_sum((int)((bef[i] & 0xffffu) + (bef[i] >> 16)));
+            if (lane == 0 && r < ROWS) {
+                s_base[r] = before;
+                s_total[r] = total;
+            }
+        }
+        __syncthreads();
+    } else if (tid < NBINS) {
+        s_base[tid] = a.tbase[tid * a.tpitch + mt];
+        s_total[tid] = a.hdr->bin_count[tid];
+    }
+    const int terr = SELF ? s_total[NBINS] : 0;
+    if (SELF && (terr & (ERR_CSC | ERR_OPOVF))) {
+        if (header && tid == 0) place_header(a, terr, s_total, 0, 0, 0, 0);
+        return;  // every thread takes the same branch
+    }
+    int rank = 0;
+    if (64 * w < nt) {
+#pragma unroll 1
+        for (int b = 0; b < NBINS; ++b) {
+            const unsigned long long m = ballot(bin == b);
+            if (bin == b) rank = popc64(m & mask_lt());
+            if (lane == 0) s_cnt[w][b] = popc64(m);
+        }
+    } else if (lane < NBINS) {
+        s_cnt[w][lane] = 0;
     }
     __syncthreads();
-    // exclusive prefix over (pass, wave) per bin, from the tile's first
+    int heavy = 0, nheavy = 0;
+    for (int b = BIN_SORT2; b <= BIN_WSORT; ++b) nheavy += s_total[b];
+    if (a.direct && nheavy > 0)
+        for (int b = BIN_SORT2; b <= BIN_WSORT; ++b)
+#pragma unroll
+            for (int x = 0; x < NW; ++x) heavy += s_cnt[x][b];
+    __syncthreads();
+    // exclusive prefix over the waves per bin, from the tile's first
     // position in the bin
     if (tid < NBINS) {
-        int run = s_start[tid] + a.th[blockIdx.x * NBINS + tid];
-        for (int x = 0; x < PER * NW; ++x) {
-            const int v = s_cnt[x][tid];
+        int start = 0, v[NW];
+#pragma unroll
+        for (int b = 0; b < NBINS; ++b) start += b < tid ? s_total[b] : 0;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) v[x] = s_cnt[x][tid];
+        s_start[tid] = start;
+        int run = start + s_base[tid];
+#pragma unroll
+        for (int x = 0; x < NW; ++x) {
             s_cnt[x][tid] = run;
-            run += v;
+            run += v[x];
+        }
+    }
+    if (header) {
+        if (tid == 0) {
+            s_tot = 0;
+            s_max = 0;
+        }
+        __syncthreads();
+        atomicAdd(&s_tot, ptot);
+        atomicMax(&s_max, pmax);
+    }
+    // the heavy columns' products and windows before the tile
+    const bool heavy_sums = a.direct && nheavy > 0 && (heavy || header);
+    if (heavy_sums) {
+        if (SELF) {
+            // one wave per heavy bin and kind of sum, every load issued first
+            constexpr int PT = kSelfTiles / 64;
+            const int q = w >> 1;
+            if (q < kHeavyBins && (w & 1)) {
+                int x[PT], before = 0, total = 0;
+#pragma unroll
+                for (int c = 0; c < PT; ++c)
+                    x[c] = c * 64 + lane < a.ntiles ? a.twin[q * a.tpitch + c * 64 + lane] : 0;
+#pragma unroll
+                for (int c = 0; c < PT; ++c) {
+                    total += x[c];
+                    before += c * 64 + lane < mt ? x[c] : 0;
+                }
+                const long long wt = wave_sum64(total), wb = wave_sum64(before);
+                if (lane == 0) {
+                    s_hwt[q] = wt;
+                    s_hwb[q] = wb;
+                }
+            } else if (q < kHeavyBins) {
+                long long x[PT], before = 0, total = 0;
+#pragma unroll
+                for (int c = 0; c < PT; ++c)
+                    x[c] = c * 64 + lane < a.ntiles ? a.tprod[q * a.tpitch + c * 64 + lane] : 0;
+#pragma unroll
+                for (int c = 0; c < PT; ++c) {
+                    total += x[c];
+                    before += c * 64 + lane < mt ? x[c] : 0;
+                }
+                const long long pt = wave_sum64(total), pb = wave_sum64(before);
+                if (lane == 0) {
+                    s_hpt[q] = pt;
+                    s_hpb[q] = pb;
+                }
+            }
+        } else if (tid < kHeavyBins) {
+            s_hpb[tid] = a.tpbase[tid * a.tpitch + mt];
+            s_hwb[tid] = a.twbase[tid * a.tpitch + mt];
+            s_hpt[tid] = 0;
+            s_hwt[tid] = 0;
+        }
+    }
+    int wex = 0;
+    long long pex = 0;
+    if (heavy) {
+        // prefix inside the wave over the columns of the same heavy bin
+#pragma unroll 1
+        for (int c = 0; c < kHeavyBins; ++c) {
+            const bool mine = bin == BIN_SORT2 + c;
+            int wt = 0;
+            long long pt = 0;
+            if (ballot(mine)) {
+                const int nw = mine ? heavy_windows(op) : 0;
+                const long long p = mine ? op : 0;
+                const int wi = wave_incl_scan(nw);
+                const long long pi = wave_incl_scan64(p);
+                if (mine) {
+                    wex = wi - nw;
+                    pex = pi - p;
+                }
+                wt = __builtin_amdgcn_readlane(wi, 63);
+                pt = wave_last64(pi);
+            }
+            if (lane == 0) {
+                s_w[w][c] = wt;
+                s_p[w][c] = pt;
+            }
         }
     }
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int c = 64 * (NW * u + w) + lane;
-        if (c >= nt) continue;
-        const int g = col0 + j0 + c;
-        a.binlist[s_cnt[NW * u + w][binv[u]] + rank[u]] =
-            make_int4(g, bse[u].x, bse[u].y - bse[u].x, opv[u]);
+    if (header && tid == 0) {
+        long long p = 0, q = 0;
+        if (heavy_sums)
+            for (int c = 0; c < kHeavyBins; ++c) {
+                p += s_hpt[c];
+                q += s_hwt[c];
+            }
+        place_header(a, terr, s_total, s_tot, s_max, p, q);
+    }
+    if (heavy && tid < kHeavyBins) {
+        long long p = s_hpb[tid], q = s_hwb[tid];
+        if (SELF)
+            for (int c = 0; c < tid; ++c) {  // the heavy bins before this one
+                p += s_hpt[c];
+                q += s_hwt[c];
+            }
+#pragma unroll 1
+        for (int x = 0; x < NW; ++x) {
+            const long long pv = s_p[x][tid];
+            const int wv = s_w[x][tid];
+            s_p[x][tid] = p;
+            s_w[x][tid] = (int)q;
+            p += pv;
+            q += wv;
+        }
+    }
+    __syncthreads();
+    if (!in) return;
+    const int g = col0 + j0 + tid, at = s_cnt[w][bin] + rank;
+    a.binlist[at] = make_int4(g, bse.x, bse.y - bse.x, op);
+    if (heavy && bin >= BIN_SORT2 && bin <= BIN_WSORT) {
+        const int h = bin - BIN_SORT2, li = at - s_start[BIN_SORT2];
+        const int wr = s_w[w][h] + wex, we = wr + heavy_windows(op);
+        a.hoff[li] = s_p[w][h] + pex;
+        a.wbase[li] = wr;
+        if (a.spec_total >= 0)
+            for (int q = wr; q < we && q < a.win_cap; ++q) a.winmap[q] = li;
     }
 }
 
@@ -301,13 +613,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_reduce(const int32_t *__restric
         int i = base + u * kBlock + threadIdx.x;
         if (i < n) v += in[i];
     }
-    // wave reduction through 32-bit halves
-    for (int d = 32; d >= 1; d >>= 1) {
-        int lo = (int)(unsigned)v, hi = (int)(unsigned)((unsigned long long)v >> 32);
-        lo = __builtin_amdgcn_ds_bpermute((lane_id() ^ d) << 2, lo);
-        hi = __builtin_amdgcn_ds_bpermute((lane_id() ^ d) << 2, hi);
-        v += (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-    }
+    v = wave_sum64(v);
     if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -330,43 +636,102 @@ struct ScanOut {
 __device__ __forceinline__ void block_scan_down(const int32_t *__restrict__ in, int n,
                                                 const long long *__restrict__ bsum,
                                                 long long *s, ScanOut &o) {
-    constexpr int PER = ScanOut::PER;
-    const int base = blockIdx.x * kScanBlock;
+    constexpr int PER = ScanOut::PER, NW = kBlock / 64;
+    const int base = blockIdx.x * kScanBlock + threadIdx.x * PER;
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    int v[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) v[u] = base + u < n ? in[base + u] : 0;
     // sums of the earlier blocks
     long long before = 0;
     for (int b = threadIdx.x; b < (int)blockIdx.x; b += kBlock) before += bsum[b];
-    s[threadIdx.x] = before;
-    __syncthreads();
-    for (int d = kBlock / 2; d >= 1; d >>= 1) {
-        if ((int)threadIdx.x < d) s[threadIdx.x] += s[threadIdx.x + d];
-        __syncthreads();
-    }
-    before = s[0];
-    __syncthreads();
-    for (int u = 0; u < PER; ++u) {
-        int i = base + u * kBlock + threadIdx.x;
-        s[u * kBlock + threadIdx.x] = i < n ? in[i] : 0;
-    }
-    __syncthreads();
+    before = wave_sum64(before);
     long long run = 0;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         o.pre[u] = run;
-        run += s[threadIdx.x * PER + u];
+        run += v[u];
+    }
+    const long long inc = wave_incl_scan64(run);
+    if (l == 63) {
+        s[w] = inc;
+        s[NW + w] = before;
     }
     __syncthreads();
-    s[threadIdx.x] = run;
-    __syncthreads();
-    for (int d = 1; d < kBlock; d <<= 1) {
-        long long t = threadIdx.x >= d ? s[threadIdx.x - d] : 0;
-        __syncthreads();
-        s[threadIdx.x] += t;
-        __syncthreads();
-    }
-    const long long off = before + s[threadIdx.x] - run;
+    long long off = 0, all = 0, own = 0;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) o.pre[u] += off;
-    o.block_end = before + s[kBlock - 1];
+    for (int q = 0; q < NW; ++q) {
+        off += s[NW + q];
+        if (q < w) own += s[q];
+        all += s[q];
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) o.pre[u] += off + own + inc - run;
+    o.block_end = off + all;
+}
+
+// (word, sequence number) pairs of the header and totals to mapped host
+// memory: see k_publish. Words the launch itself has set come from the caller.
+__device__ __forceinline__ void publish_words(const uint32_t *src, const PubArgs &pub, int tid,
+                                              int nthreads, int err, int cap_over,
+                                              long long total) {
+    constexpr int W_ERR = offsetof(Hdr, err) / 4, W_CAP = offsetof(Hdr, cap_over) / 4;
+    constexpr int W_TOT = kHdrWords;
+    for (int i = tid; i < pub.nwords; i += nthreads) {
+        uint32_t v = src[i];
+        if (i == W_ERR) v |= (uint32_t)err;
+        if (i == W_CAP) v |= (uint32_t)cap_over;
+        if (i == W_TOT) v = (uint32_t)total;
+        if (i == W_TOT + 1) v = (uint32_t)((unsigned long long)total >> 32);
+        __hip_atomic_store(&pub.dst[i], (unsigned long long)v | ((unsigned long long)pub.seq << 32),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// end of a single problem's scan (one thread): total, capacity and overflow
+// flags, for the device's header and the published copy
+__device__ __forceinline__ void scan_total(const KArgs &a, long long total, long long *totals,
+                                           int &err, int &cap) {
+    err = total > 0x7fffffffll ? ERR_NNZOVF : 0;
+    a.single.ccp[a.ncols] = (int32_t)total;
+    totals[0] = total;
+    // a numeric phase queued behind this scan must not write past the
+    // caller's arrays
+    cap = total > a.out_cap ? 1 : 0;
+    if (cap) a.hdr->cap_over = 1;
+    if (err) atomicOr(&a.hdr->err, err);
+}
+
+// A single problem of at most kScanSmall columns: column pointers, total and
+// publication in one workgroup of one launch (three launches of 4 to 5 us
+// each, and the gaps between them, otherwise).
+constexpr int kScanSmallT = 1024, kScanSmallPer = 16;
+constexpr int kScanSmall = kScanSmallT * kScanSmallPer;
+__global__ __launch_bounds__(kScanSmallT) void k_scan_small(KArgs a, long long *totals,
+                                                            PubArgs pub) {
+    constexpr int PER = kScanSmallPer;
+    __shared__ long long tmp[kScanSmallT / 64 + 1];
+    __shared__ int s_err, s_cap;
+    const int n = a.ncols, per = (n + kScanSmallT - 1) / kScanSmallT;
+    const int base = threadIdx.x * per;
+    int v[PER];
+    long long sum = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        v[u] = u < per && base + u < n ? a.gnnz[base + u] : 0;
+        sum += v[u];
+    }
+    long long total;
+    long long run = wg_excl_scan64<kScanSmallT>(sum, tmp, total);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (u < per && base + u < n) a.single.ccp[base + u] = (int32_t)run;
+        run += v[u];
+    }
+    if (threadIdx.x == 0) scan_total(a, total, totals, s_err, s_cap);
+    if (!pub.dst) return;
+    __syncthreads();
+    publish_words((const uint32_t *)a.hdr, pub, threadIdx.x, kScanSmallT, s_err, s_cap, total);
 }
 
 // C column pointers from the per-column counts. For one problem the int32 column pointers are written
@@ -374,38 +739,28 @@ __device__ __forceinline__ void block_scan_down(const int32_t *__restrict__ in, 
 // prefix is kept in gcp and k_scan_finish cuts it per problem.
 __global__ __launch_bounds__(kBlock) void k_scan_down(KArgs a, long long *__restrict__ gcp,
                                                       const long long *__restrict__ bsum,
-                                                      long long *__restrict__ totals) {
-    __shared__ long long s[kScanBlock];
+                                                      long long *totals, PubArgs pub) {
+    __shared__ long long s[2 * kBlock / 64];
+    __shared__ int s_err, s_cap;
     const int n = a.ncols;
     ScanOut o;
     block_scan_down(a.gnnz, n, bsum, s, o);
-    int err = 0;
 #pragma unroll
     for (int u = 0; u < ScanOut::PER; ++u) {
         const int i = blockIdx.x * kScanBlock + threadIdx.x * ScanOut::PER + u;
         if (i >= n) break;
-        const long long v = o.pre[u];
-        if (a.nprob == 1) {
-            if (v > 0x7fffffffll) err = ERR_NNZOVF;
-            a.single.ccp[i] = (int32_t)v;
-        } else {
-            gcp[i] = v;
-        }
+        if (a.nprob == 1) a.single.ccp[i] = (int32_t)o.pre[u];  // the total is checked below
+        else gcp[i] = o.pre[u];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        const long long total = o.block_end;
-        if (a.nprob == 1) {
-            if (total > 0x7fffffffll) err = ERR_NNZOVF;
-            a.single.ccp[n] = (int32_t)total;
-            totals[0] = total;
-            // a numeric phase queued behind this scan must not write past the
-            // caller's arrays
-            if (total > a.out_cap) a.hdr->cap_over = 1;
-        } else {
-            gcp[n] = total;
-        }
+    if (blockIdx.x != gridDim.x - 1) return;
+    if (a.nprob > 1) {
+        if (threadIdx.x == 0) gcp[n] = o.block_end;
+        return;
     }
-    if (err) atomicOr(&a.hdr->err, err);
+    if (threadIdx.x == 0) scan_total(a, o.block_end, totals, s_err, s_cap);
+    if (!pub.dst) return;
+    __syncthreads();
+    publish_words((const uint32_t *)a.hdr, pub, threadIdx.x, kBlock, s_err, s_cap, o.block_end);
 }
 
 __global__ __launch_bounds__(kBlock) void k_scan_finish(KArgs a, const long long *__restrict__ gcp,
@@ -431,7 +786,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_finish(KArgs a, const long long
 // P(g - 1) < t * kProdTile <= P(g); the tiles after the last column's first
 // product are empty.
 __global__ __launch_bounds__(kBlock) void k_prod_down(KArgs a, const long long *__restrict__ bsum) {
-    __shared__ long long s[kScanBlock];
+    __shared__ long long s[2 * kBlock / 64];
     if (__syncthreads_or(__atomic_load_n(&a.hdr->err, __ATOMIC_RELAXED) != 0))
         return;  // every thread takes the same branch
     const int n = a.ncols;
@@ -463,7 +818,7 @@ __global__ __launch_bounds__(kBlock) void k_prod_down(KArgs a, const long long *
 __global__ __launch_bounds__(kBlock) void k_scan_down_i32(const int32_t *in, int n,
                                                           const long long *__restrict__ bsum,
                                                           int32_t *out) {
-    __shared__ long long s[kScanBlock];
+    __shared__ long long s[2 * kBlock / 64];
     ScanOut o;
     block_scan_down(in, n, bsum, s, o);
     __syncthreads();  // every block element is read before any is written (in place)
@@ -477,7 +832,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_down_i32(const int32_t *in, int
 __global__ __launch_bounds__(kBlock) void k_scan_down_i64(const int32_t *in, int n,
                                                           const long long *__restrict__ bsum,
                                                           long long *out) {
-    __shared__ long long s[kScanBlock];
+    __shared__ long long s[2 * kBlock / 64];
     ScanOut o;
     block_scan_down(in, n, bsum, s, o);
 #pragma unroll
@@ -528,17 +883,24 @@ hipError_t launch_classify(const KArgs &a, hipStream_t s) {
 
 hipError_t launch_place(const KArgs &a, hipStream_t s) {
     if (a.ntiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_place, dim3(a.ntiles), dim3(kBlock), 0, s, a);
+    if (a.ntiles <= kSelfTiles)
+        hipLaunchKernelGGL(k_place<true>, dim3(a.ntiles + 1), dim3(kTile), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_place<false>, dim3(a.ntiles), dim3(kTile), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_scan(const KArgs &a, long long *gcp, long long *bsum, int nblk,
-                       long long *totals, hipStream_t s) {
+                       long long *totals, const PubArgs &pub, hipStream_t s) {
+    if (a.nprob == 1 && a.ncols > 0 && a.ncols <= kScanSmall) {
+        hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kScanSmallT), 0, s, a, totals, pub);
+        return hipGetLastError();
+    }
     if (a.ncols > 0) {
         hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(kBlock), 0, s,
                            (const int32_t *)a.gnnz, a.ncols, bsum);
         hipLaunchKernelGGL(k_scan_down, dim3(nblk), dim3(kBlock), 0, s, a, gcp,
-                           (const long long *)bsum, totals);
+                           (const long long *)bsum, totals, pub);
     }
     if (a.nprob > 1) {
         int n = a.ncols > a.nprob ? a.ncols : a.nprob;
@@ -553,17 +915,16 @@ hipError_t launch_scan(const KArgs &a, long long *gcp, long long *bsum, int nblk
 // host memory, each word beside the call's sequence number in one 8-byte
 // store, so the host can read them as soon as the symbolic phase ends while
 // later work stays queued behind it. A word is current when its pair carries
-// the current number: no fence or cache write-back is needed.
-__global__ __launch_bounds__(64) void k_publish(const uint32_t *__restrict__ src, int nwords,
-                                                unsigned long long *dst, uint32_t seq) {
-    for (int i = threadIdx.x; i < nwords; i += 64)
-        __hip_atomic_store(&dst[i], (unsigned long long)src[i] | ((unsigned long long)seq << 32),
+// the current number: no fence or cache write-back is needed. (A single
+// problem's scan publishes by itself.)
+__global__ __launch_bounds__(64) void k_publish(const uint32_t *__restrict__ src, PubArgs pub) {
+    for (int i = threadIdx.x; i < pub.nwords; i += 64)
+        __hip_atomic_store(&pub.dst[i], (unsigned long long)src[i] | ((unsigned long long)pub.seq << 32),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-hipError_t launch_publish(const void *src, int nwords, void *dst, uint32_t seq, hipStream_t s) {
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, (const uint32_t *)src, nwords,
-                       (unsigned long long *)dst, seq);
+hipError_t launch_publish(const void *src, const PubArgs &pub, hipStream_t s) {
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, (const uint32_t *)src, pub);
     return hipGetLastError();
 }
 

@@ -47,7 +47,9 @@ __global__ __launch_bounds__(kRadixT) void k_esc_radix(KArgs a, int rowbits) {
     for (int b = 0; b < BIN_SORT2; ++b) first += a.hdr->bin_count[b];
     int n = 0;
     for (int b = BIN_SORT2; b <= BIN_WSORT; ++b) n += a.hdr->bin_count[b];
-    const long long total = a.hoff[n];
+    const long long total = (long long)a.hdr->heavy_prod;
+    // first product of heavy column x (of none: the end of the scratch)
+    auto first_of = [&](int x) { return x < n ? a.hoff[x] : total; };
     const int nid = (int)(total / kRadixGroup) + 1;
     const int tid = threadIdx.x;
     int bad = 0, depth = 0;
@@ -71,10 +73,10 @@ __global__ __launch_bounds__(kRadixT) void k_esc_radix(KArgs a, int rowbits) {
             bad = 1;
             break;
         }
-        const long long base = a.hoff[l0];
-        const int np = (int)(a.hoff[l1] - base);
+        const long long base = first_of(l0);
+        const int np = (int)(first_of(l1) - base);
         for (int c = tid; c <= nc; c += T) {
-            s_cs[c] = (int)(a.hoff[l0 + c] - base);
+            s_cs[c] = (int)(first_of(l0 + c) - base);
             if (c < nc) s_cn[c] = 0;
         }
         __syncthreads();

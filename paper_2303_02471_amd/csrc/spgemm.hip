@@ -86,8 +86,10 @@ struct spgemm_plan_s {
     long long *gcp = nullptr, *bsum = nullptr, *totals = nullptr;
     Prob *table = nullptr;
     int4 *tiles = nullptr;
-    int32_t *th = nullptr, *tmax = nullptr;
-    long long *ttot = nullptr;
+    uint16_t *th = nullptr;
+    int32_t *tmax = nullptr, *twin = nullptr, *tbase = nullptr, *twbase = nullptr;
+    long long *ttot = nullptr, *tprod = nullptr, *tpbase = nullptr;
+    int tile = kTile, tpitch = 8;
     int nbsum = 0;
 
     // pinned host mirror of the header and totals (raw, then as published
@@ -139,6 +141,7 @@ struct spgemm_plan_s {
     // one-call product may run its numeric phase at these positions first
     int32_t *saved_cp = nullptr;
     bool saved_ok = false;
+    int saved_n = 0;
     long long saved_total = 0;
 
     hipStream_t last_stream = nullptr;
@@ -188,19 +191,19 @@ struct ProfScope {
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-constexpr size_t kHdrBytes = (sizeof(Hdr) + 63) / 64 * 64;  // header, then the totals
+constexpr size_t kHdrBytes = 4 * (size_t)kHdrWords;  // header, then the totals
 // The host mirror: the raw header and totals (pin bytes, read back by copies)
 // and then the same words as published pairs (word, sequence number).
 unsigned long long *pub_pairs_host(spgemm_plan p) {
     return (unsigned long long *)((char *)p->pinned + p->pinned_bytes);
 }
 
-// Queues the publication of the header and totals, tagged with the next
-// sequence number; later work queued on s runs on behind it.
-hipError_t publish(spgemm_plan p, hipStream_t s) {
-    const uint32_t seq = ++p->pub_seq;
-    return launch_publish(p->hdr, (int)((kHdrBytes + 8 * (size_t)p->nprob) / 4),
-                          (char *)p->pinned_dev + p->pinned_bytes, seq, s);
+// The next publication of the header and totals, tagged with the next sequence
+// number (nothing to publish to in a plan of the allocation-free entry point).
+PubArgs next_publication(spgemm_plan p) {
+    if (p->use_arena) return PubArgs{nullptr, 0, 0};
+    return PubArgs{(unsigned long long *)((char *)p->pinned_dev + p->pinned_bytes),
+                   (int32_t)((kHdrBytes + 8 * (size_t)p->nprob) / 4), ++p->pub_seq};
 }
 
 // Waits until every published pair carries the last sequence number and
@@ -388,13 +391,21 @@ spgemm_status ensure_workspace(spgemm_plan p, hipStream_t s) {
     const size_t o_op = take(4 * n), o_binw = take(4 * n), o_binlist = take(16 * n),
                  o_gnnz = take(4 * n);
     const size_t o_E = take(8 * (size_t)std::max(p->total_nnzb, 1ll));
-    const size_t o_colprod = take(8 * (n + 1));
-    const size_t o_gcp = take(8 * (n + 1));
+    // the product space's offsets, and the pointers over all problems
+    const size_t o_colprod = take(p->direct ? 0 : 8 * (n + 1));
+    const size_t o_gcp = take(p->nprob > 1 ? 8 * (n + 1) : 0);
     const size_t o_bsum = take(8 * (size_t)p->nbsum);
     const size_t o_tab = take(sizeof(Prob) * (size_t)std::max(p->nprob, 1));
     const size_t o_c0 = take(4 * ((size_t)p->nprob + 1));
     const size_t o_tiles = take(sizeof(int4) * (size_t)std::max(p->ntiles, 1));
-    const size_t o_th = take(4 * (size_t)NBINS * std::max(p->ntiles, 1));
+    const size_t pitch = align_up((size_t)std::max(p->ntiles, 1), 8);
+    const bool tally = p->ntiles > kSelfTiles;
+    const size_t o_th = take(2 * (size_t)(NBINS + 1) * pitch);
+    const size_t o_tprod = take(8 * (size_t)kHeavyBins * pitch);
+    const size_t o_twin = take(4 * (size_t)kHeavyBins * pitch);
+    const size_t o_tbase = take(tally ? 4 * (size_t)NBINS * pitch : 0);
+    const size_t o_tpbase = take(tally ? 8 * (size_t)kHeavyBins * pitch : 0);
+    const size_t o_twbase = take(tally ? 4 * (size_t)kHeavyBins * pitch : 0);
     const size_t o_ttot = take(8 * (size_t)std::max(p->ntiles, 1));
     const size_t o_tmax = take(4 * (size_t)std::max(p->ntiles, 1));
     const size_t o_hoff = take(8 * (n + 1)), o_wbase = take(4 * (n + 1));
@@ -419,7 +430,13 @@ spgemm_status ensure_workspace(spgemm_plan p, hipStream_t s) {
     p->table = (Prob *)(b + o_tab);
     p->col0s = (int32_t *)(b + o_c0);
     p->tiles = (int4 *)(b + o_tiles);
-    p->th = (int32_t *)(b + o_th);
+    p->tpitch = (int)pitch;
+    p->th = (uint16_t *)(b + o_th);
+    p->tprod = (long long *)(b + o_tprod);
+    p->twin = (int32_t *)(b + o_twin);
+    p->tbase = (int32_t *)(b + o_tbase);
+    p->tpbase = (long long *)(b + o_tpbase);
+    p->twbase = (int32_t *)(b + o_twbase);
     p->ttot = (long long *)(b + o_ttot);
     p->tmax = (int32_t *)(b + o_tmax);
     p->hoff = (long long *)(b + o_hoff);
@@ -456,7 +473,15 @@ KArgs make_args(spgemm_plan p) {
     a.ncols = p->ncols;
     a.ntiles = p->ntiles;
     a.tiles = p->tiles;
+    a.tile = p->tile;
+    a.tpitch = p->tpitch;
+    a.direct = p->direct ? 1 : 0;
     a.th = p->th;
+    a.tprod = p->tprod;
+    a.twin = p->twin;
+    a.tbase = p->tbase;
+    a.tpbase = p->tpbase;
+    a.twbase = p->twbase;
     a.ttot = p->ttot;
     a.tmax = p->tmax;
     a.tune = p->tune;
@@ -725,10 +750,8 @@ spgemm_status ensure_lblock(spgemm_plan p, hipStream_t s) {
 // up to 256 and the one-column waves (up to 1024 products) on another, the
 // heavy columns (above 1024 products) on the caller's. The host takes
 // several microseconds per launch, so the order of the launches matters:
-// first the heavy columns' plan when plan_heavy asks for it (a single
-// workgroup that then runs before the accumulators fill the chip) and every
-// launch of the heavy chain but its last, then one launch per stream in turn
-// (each stream's first kernel early).
+// first every launch of the heavy chain but its last, then one launch per
+// stream in turn (each stream's first kernel early).
 struct LaunchQueue {
     const char *name;
     hipStream_t st;
@@ -737,8 +760,7 @@ struct LaunchQueue {
     std::optional<ProfScope> ps;
 };
 
-hipError_t launch_direct_accumulators(spgemm_plan p, const KArgs &a, hipStream_t s, bool fill,
-                                      bool plan_heavy) {
+hipError_t launch_direct_accumulators(spgemm_plan p, const KArgs &a, hipStream_t s, bool fill) {
     const Hdr &h = p->hdr_host;
     const bool f64 = p->dt == SPGEMM_F64;
     const bool wide = p->wide_acc;
@@ -755,10 +777,6 @@ hipError_t launch_direct_accumulators(spgemm_plan p, const KArgs &a, hipStream_t
             if (h.bin_count[BIN_SORT0 + c]) used |= 2u;
     }
     if ((e = fork(p, s, used))) return e;
-    if (plan_heavy) {
-        ProfScope ps("heavy_plan", s);
-        if ((e = launch_heavy_plan(a, s))) return e;
-    }
     LaunchQueue q[3] = {{fill ? "esc_numeric" : "esc_symbolic", on(0), {}},
                         {fill ? "heavy_numeric" : "heavy_symbolic", s, {}},
                         {fill ? "wave_numeric" : "wave_symbolic", on(1), {}}};
@@ -790,7 +808,7 @@ hipError_t launch_direct_accumulators(spgemm_plan p, const KArgs &a, hipStream_t
         const bool radix = (p->flags & SPGEMM_RADIX_ESC) != 0;
         const int nwin = h.heavy_win, rowbits = p->rowbits;
         const long long hp = (long long)h.heavy_prod;
-        for (int part = heavy_first_part(radix, plan_heavy && a.spec_total >= 0);
+        for (int part = heavy_first_part(radix, fill || a.spec_total >= 0);
              part < heavy_parts(radix); ++part)
             q[1].l.push_back([=, &a] {
                 return launch_heavy(a, nheavy, nwin, wide, fill, f64, s, radix, hp, rowbits, part);
@@ -879,7 +897,7 @@ NumLaunch numeric_launch(spgemm_plan p) {
 }
 
 hipError_t launch_numeric_phase(spgemm_plan p, const KArgs &a, hipStream_t s) {
-    if (p->direct) return launch_direct_accumulators(p, a, s, true, false);
+    if (p->direct) return launch_direct_accumulators(p, a, s, true);
     const bool f64 = p->dt == SPGEMM_F64;
     const NumLaunch L = numeric_launch(p);
     hipError_t e;
@@ -950,7 +968,9 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
         SPG_TRY(hipStreamSynchronize(s));
         p->table_dev_copy = p->probs;
     }
-    SPG_TRY(hipMemsetAsync(p->hdr, 0, sizeof(Hdr), s));
+    // a place kernel that combines the tiles itself writes the whole header
+    if (!p->direct || p->ntiles == 0 || p->ntiles > kSelfTiles)
+        SPG_TRY(hipMemsetAsync(p->hdr, 0, sizeof(Hdr), s));
     // launches are planned from hdr_host: the previous call's sizes (spec) or
     // this call's, read back after the placement
     unsigned mask = 0;
@@ -975,12 +995,6 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
         hipStream_t sp = overlap ? p->side[0] : s;
         { ProfScope ps("tally", sp); SPG_TRY(launch_tally(a, sp)); }
         { ProfScope ps("place", sp); SPG_TRY(launch_place(a, sp)); }
-        // a planned launch queues the heavy columns' plan behind the fork of
-        // the accumulator streams; a first launch reads its totals back here
-        if (p->direct && p->ncols > 0 && !spec) {
-            ProfScope ps("heavy_plan", s);
-            SPG_TRY(launch_heavy_plan(a, s));
-        }
     }
     if (!spec) {
         // the bin sizes fix the grids and the product count the allocation
@@ -1002,7 +1016,8 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
     // every column's entries as it goes; the scan then builds this call's
     // column pointers from those counts. A count that differs asks for a redo.
     const bool speculate = p->direct && spec && fo && p->nprob == 1 && p->saved_ok &&
-                           p->saved_total <= fo->cap && p->ncols > 0;
+                           p->saved_n == p->ncols && p->saved_total <= fo->cap && p->ncols > 0;
+    PubArgs pub{nullptr, 0, 0};
     if (p->ncols > 0 && p->direct) {
         if ((st = ensure_lblock(p, s))) return st;
         const KArgs al = args();
@@ -1012,14 +1027,15 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
             af.single.cv = fo->cv;
             af.single.ccp = p->saved_cp;
             af.spec_fill = 1;
-            SPG_TRY(launch_direct_accumulators(p, af, s, true, true));
+            SPG_TRY(launch_direct_accumulators(p, af, s, true));
             fo->queued = true;
             fo->used = numeric_launch(p);
         } else {
-            SPG_TRY(launch_direct_accumulators(p, al, s, false, spec));
+            SPG_TRY(launch_direct_accumulators(p, al, s, false));
         }
         ProfScope ps("scan", s);
-        SPG_TRY(launch_scan(al, p->gcp, p->bsum, p->nblk, p->totals, s));
+        pub = next_publication(p);
+        SPG_TRY(launch_scan(al, p->gcp, p->bsum, p->nblk, p->totals, pub, s));
     } else if (p->ncols > 0) {
         const KArgs al = args();
         {
@@ -1031,7 +1047,8 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
         if (overlap) SPG_TRY(join(p, s, 1u));
         SPG_TRY(launch_symbolic_accumulators(p, al, s));
         ProfScope ps("scan", s);
-        SPG_TRY(launch_scan(al, p->gcp, p->bsum, p->nblk, p->totals, s));
+        pub = next_publication(p);
+        SPG_TRY(launch_scan(al, p->gcp, p->bsum, p->nblk, p->totals, pub, s));
     }
     if (p->use_arena) {
         // no mapped host memory: a plain copy of the header and totals to the
@@ -1039,8 +1056,10 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
         SPG_TRY(hipMemcpyAsync(p->pinned, p->hdr, kHdrBytes + 8 * (size_t)p->nprob,
                                hipMemcpyDeviceToHost, s));
         SPG_TRY(hipStreamSynchronize(s));
-    } else {
-        SPG_TRY(publish(p, s));
+    } else if (p->nprob != 1 || p->ncols == 0) {
+        // (a single problem's scan has published them)
+        if (!pub.dst) pub = next_publication(p);
+        SPG_TRY(launch_publish(p->hdr, pub, s));
     }
     if (fo && spec && p->ncols > 0 && p->nprob == 1 && !speculate) {
         // the numeric phase from the previous sizes; it stands down on an
@@ -1085,6 +1104,7 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
             SPG_TRY(hipMemcpyAsync(p->saved_cp, p->probs[0].ccp, 4 * ((size_t)p->ncols + 1),
                                    hipMemcpyDeviceToDevice, s));
             p->saved_total = p->totals_host[0];
+            p->saved_n = p->ncols;
             p->saved_ok = true;
         }
         if (p->ncols == 0) {
@@ -1196,6 +1216,9 @@ static spgemm_status symbolic_common(int32_t count, const spgemm_csc *A, const s
     long long ncols = 0, nnzb_total = 0;
     std::vector<Prob> probs(count);
     std::vector<int4> tiles;
+    long long all_cols = 0;
+    for (int i = 0; i < count; ++i) all_cols += std::max(B[i].ncols, 0);
+    const int tile = plan_tile(all_cols);
     for (int i = 0; i < count; ++i) {
         if ((st = check_desc(&A[i], false)) || (st = check_desc(&B[i], false))) return st;
         if (!C_colptr[i]) return SPGEMM_ERR_NULL;
@@ -1213,8 +1236,8 @@ static spgemm_status symbolic_common(int32_t count, const spgemm_csc *A, const s
         q.acp = A[i].colptr; q.ari = A[i].rowidx; q.av = A[i].val;
         q.bcp = B[i].colptr; q.bri = B[i].rowidx; q.bv = B[i].val;
         q.ccp = C_colptr[i];
-        for (int j0 = 0; j0 < q.n; j0 += kTile)
-            tiles.push_back(make_int4(i, j0, std::min(q.n, j0 + kTile), 0));
+        for (int j0 = 0; j0 < q.n; j0 += tile)
+            tiles.push_back(make_int4(i, j0, std::min(q.n, j0 + tile), 0));
         ncols += q.n;
         if (ncols > 0x7fffffffll) return SPGEMM_ERR_INDEX_OVERFLOW;
     }
@@ -1250,6 +1273,7 @@ static spgemm_status symbolic_common(int32_t count, const spgemm_csc *A, const s
     p->direct = direct;
     p->ncols = (int)ncols;
     p->total_nnzb = nnzb_total;
+    p->tile = tile;
     p->ntiles = (int)tiles.size();
     p->symbolic_ok = false;
     p->bt_ready = false;
@@ -1673,7 +1697,8 @@ extern "C" spgemm_status spgemm_multiply_noalloc(const spgemm_csc *A, const spge
     p->win_cap = 0;
     p->ncols = q.n;
     p->total_nnzb = q.nnzb;
-    p->ntiles = ceil_div(q.n, kTile);
+    p->tile = plan_tile(q.n);
+    p->ntiles = ceil_div(q.n, p->tile);
     p->symbolic_ok = false;
     p->spec_ready = false;
     p->bt_ready = false;
