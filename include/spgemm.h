@@ -370,6 +370,11 @@ void spgemm_plan_destroy(spgemm_plan plan);
 /* Frees a plan made by spgemm_batched (the same as spgemm_plan_destroy). */
 void spgemm_batch_plan_destroy(spgemm_batch_plan plan);
 
+/* Frees the idle side streams, events and pinned buffers that destroyed plans
+ * have handed back for later plans (a few of each are kept). Host only;
+ * thread-safe. */
+void spgemm_release_pool(void);
+
 /* Static text for a status code. */
 const char *spgemm_status_string(spgemm_status s);
 

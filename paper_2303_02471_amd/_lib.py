@@ -33,7 +33,7 @@ EXPORTS = (
     "spgemm_plan_get_stats", "spgemm_plan_destroy", "spgemm_status_string", "spgemm_version",
     "spgemm_profile_enable", "spgemm_profile_read", "spgemm_profile_select",
     "spgemm_autotune", "spgemm_tune_key", "spgemm_tune_cache_load", "spgemm_tune_cache_store",
-    "spgemm_set_allocator", "spgemm_batch_plan_destroy", "spgemm_multiply_noalloc",
+    "spgemm_set_allocator", "spgemm_batch_plan_destroy", "spgemm_release_pool", "spgemm_multiply_noalloc",
 )
 
 # device memory callbacks of spgemm_set_allocator
@@ -114,6 +114,8 @@ def lib() -> C.CDLL:
     L.spgemm_plan_destroy.restype = None
     L.spgemm_batch_plan_destroy.argtypes = [vp]
     L.spgemm_batch_plan_destroy.restype = None
+    L.spgemm_release_pool.argtypes = []
+    L.spgemm_release_pool.restype = None
     L.spgemm_set_allocator.argtypes = [ALLOC_FN, FREE_FN, vp]
     L.spgemm_set_allocator.restype = C.c_int
     L.spgemm_status_string.argtypes = [C.c_int]

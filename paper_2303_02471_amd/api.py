@@ -68,12 +68,15 @@ def _ensure_allocator():
 
 @atexit.register
 def _close_plans():
-    # plans hand their memory back to torch while torch is still alive
+    # plans hand their memory back to torch while torch is still alive, then
+    # the library frees the streams and host buffers it kept for later plans
     for p in list(_plans):
         try:
             p.close()
         except Exception:
             pass
+    if _installed is not None:
+        _lib.lib().spgemm_release_pool()
 
 
 def profile_enable(on: bool = True) -> None:

@@ -215,6 +215,7 @@ struct KArgs {
     // also records every column's entry count, and a count that differs
     // from the previous structure asks for a redo (ERR_RETRY).
     int32_t spec_fill;
+    int32_t *save;          // second copy of a single problem's column pointers (NULL: none)
 };
 
 // Destination code of a product: the rank of its output row inside its
@@ -244,7 +245,14 @@ hipError_t launch_classify(const KArgs &a, hipStream_t s);
 // positions before every tile and the totals, when the place kernel does not
 // combine the tiles' records itself
 hipError_t launch_tally(const KArgs &a, hipStream_t s);
-hipError_t launch_place(const KArgs &a, hipStream_t s);
+// Publication of the device header (and the totals behind it) to the host
+struct PubArgs {
+    unsigned long long *dst;  // mapped host memory: (word, seq) pairs (NULL: none)
+    int32_t nwords;           // header words, then the totals' words
+    uint32_t seq;
+};
+// pub: the header's publication, when the place kernel writes the header
+hipError_t launch_place(const KArgs &a, const PubArgs &pub, hipStream_t s);
 // wavefront groups of ESC sub-bin `sub`; wide: 64-bit keys (rows of 2^24 - 1 and more)
 hipError_t launch_esc(const KArgs &a, bool wide, int sub, int groups, hipStream_t s);
 // every sub-bin in one launch; groups[i] wavefront groups of sub-bin i (0: none)
@@ -261,12 +269,7 @@ hipError_t launch_wsort(const KArgs &a, bool wide, int grid, hipStream_t s);
 // positions from the device header; any grid covers them)
 hipError_t launch_block(const KArgs &a, int cls, int grid, hipStream_t s);
 // C's column pointers from the per-column counts; of a single problem also
-// the publication of the header and total to the host (pub.dst, may be NULL)
-struct PubArgs {
-    unsigned long long *dst;  // mapped host memory: (word, seq) pairs
-    int32_t nwords;           // header words, then the totals' words
-    uint32_t seq;
-};
+// the publication of the header and total to the host
 hipError_t launch_scan(const KArgs &a, long long *gcp, long long *bsum, int nblk,
                        long long *totals, const PubArgs &pub, hipStream_t s);
 // first product of every global column (colprod) and first column of every

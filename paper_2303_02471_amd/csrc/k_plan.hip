@@ -64,6 +64,18 @@ __device__ __forceinline__ void place_header(const KArgs &a, int err, const int 
     }
 }
 
+// The header as (word, sequence number) pairs in mapped host memory, by the
+// workgroup whose thread has just written it (see k_publish).
+__device__ __forceinline__ void publish_header(const KArgs &a, const PubArgs &pub, int tid,
+                                               int nthreads) {
+    if (!pub.dst) return;
+    __syncthreads();
+    const uint32_t *src = (const uint32_t *)a.hdr;
+    for (int i = tid; i < pub.nwords; i += nthreads)
+        __hip_atomic_store(&pub.dst[i], (unsigned long long)src[i] | ((unsigned long long)pub.seq << 32),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---------------------------------------------------------------- classify
 // One workgroup per tile of at most a.tile columns of one problem. The tile's
 // stored B entries are contiguous; threads walk them flat (coalesced reads of
@@ -338,7 +350,7 @@ hipError_t launch_tally(const KArgs &a, hipStream_t s) {
 // of 1600 products, 15 us now. With more tiles each workgroup would read too
 // much and k_tally scans the records first.
 template <bool SELF>
-__global__ __launch_bounds__(kTile) void k_place(KArgs a) {
+__global__ __launch_bounds__(kTile) void k_place(KArgs a, PubArgs pub) {
     constexpr int T = kTile, NW = T / 64, ROWS = NBINS + 1;  // one column per thread
     __shared__ int s_base[ROWS], s_total[ROWS], s_start[NBINS];
     __shared__ int s_cnt[NW][NBINS];  // columns of every bin per wave, then prefix
@@ -438,7 +450,10 @@ __global__ __launch_bounds__(kTile) void k_place(KArgs a) {
     }
     const int terr = SELF ? s_total[NBINS] : 0;
     if (SELF && (terr & (ERR_CSC | ERR_OPOVF))) {
-        if (header && tid == 0) place_header(a, terr, s_total, 0, 0, 0, 0);
+        if (header) {
+            if (tid == 0) place_header(a, terr, s_total, 0, 0, 0, 0);
+            publish_header(a, pub, tid, T);
+        }
         return;  // every thread takes the same branch
     }
     int rank = 0;
@@ -567,6 +582,10 @@ __global__ __launch_bounds__(kTile) void k_place(KArgs a) {
             }
         place_header(a, terr, s_total, s_tot, s_max, p, q);
     }
+    if (header) {
+        publish_header(a, pub, tid, T);
+        return;
+    }
     if (heavy && tid < kHeavyBins) {
         long long p = s_hpb[tid], q = s_hwb[tid];
         if (SELF)
@@ -694,6 +713,7 @@ __device__ __forceinline__ void scan_total(const KArgs &a, long long total, long
                                            int &err, int &cap) {
     err = total > 0x7fffffffll ? ERR_NNZOVF : 0;
     a.single.ccp[a.ncols] = (int32_t)total;
+    if (a.save) a.save[a.ncols] = (int32_t)total;
     totals[0] = total;
     // a numeric phase queued behind this scan must not write past the
     // caller's arrays
@@ -725,7 +745,10 @@ __global__ __launch_bounds__(kScanSmallT) void k_scan_small(KArgs a, long long *
     long long run = wg_excl_scan64<kScanSmallT>(sum, tmp, total);
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        if (u < per && base + u < n) a.single.ccp[base + u] = (int32_t)run;
+        if (u < per && base + u < n) {
+            a.single.ccp[base + u] = (int32_t)run;
+            if (a.save) a.save[base + u] = (int32_t)run;
+        }
         run += v[u];
     }
     if (threadIdx.x == 0) scan_total(a, total, totals, s_err, s_cap);
@@ -749,8 +772,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(KArgs a, long long *__rest
     for (int u = 0; u < ScanOut::PER; ++u) {
         const int i = blockIdx.x * kScanBlock + threadIdx.x * ScanOut::PER + u;
         if (i >= n) break;
-        if (a.nprob == 1) a.single.ccp[i] = (int32_t)o.pre[u];  // the total is checked below
-        else gcp[i] = o.pre[u];
+        if (a.nprob == 1) {
+            a.single.ccp[i] = (int32_t)o.pre[u];  // the total is checked below
+            if (a.save) a.save[i] = (int32_t)o.pre[u];
+        } else {
+            gcp[i] = o.pre[u];
+        }
     }
     if (blockIdx.x != gridDim.x - 1) return;
     if (a.nprob > 1) {
@@ -881,12 +908,12 @@ hipError_t launch_classify(const KArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_place(const KArgs &a, hipStream_t s) {
+hipError_t launch_place(const KArgs &a, const PubArgs &pub, hipStream_t s) {
     if (a.ntiles == 0) return hipSuccess;
     if (a.ntiles <= kSelfTiles)
-        hipLaunchKernelGGL(k_place<true>, dim3(a.ntiles + 1), dim3(kTile), 0, s, a);
+        hipLaunchKernelGGL(k_place<true>, dim3(a.ntiles + 1), dim3(kTile), 0, s, a, pub);
     else
-        hipLaunchKernelGGL(k_place<false>, dim3(a.ntiles), dim3(kTile), 0, s, a);
+        hipLaunchKernelGGL(k_place<false>, dim3(a.ntiles), dim3(kTile), 0, s, a, pub);
     return hipGetLastError();
 }
 

@@ -42,6 +42,31 @@ struct DevBuf {
     hipStream_t stream = nullptr;
 };
 
+// Host-side objects that cost tens of microseconds each to make: a plan takes
+// them from a process-wide pool when it first needs them and hands them back,
+// idle, when it is destroyed.
+// Side streams (default priority) with the events of their fork and join.
+struct SideSet {
+    static constexpr int kSide = 3;
+    int device = -1;
+    hipStream_t side[kSide] = {nullptr, nullptr, nullptr};
+    hipEvent_t fork_ev = nullptr, join_ev[kSide] = {nullptr, nullptr, nullptr};
+};
+// Mapped, coherent host memory: pairs[words] (word, sequence number) written by
+// the device, raw words[words], upload room. The pairs keep their place and the
+// sequence runs on for the memory's life, so no pair an earlier plan left can
+// look current to a later one.
+struct HostMirror {
+    int device = -1;
+    char *base = nullptr;
+    void *dev = nullptr;
+    size_t words = 0, upload = 0;
+    uint32_t seq = 0;
+    unsigned long long *pairs() const { return (unsigned long long *)base; }
+    char *raw() const { return base + 8 * words; }
+    char *room() const { return base + 12 * words; }
+};
+
 struct spgemm_plan_s {
     int device = -1;
     DevAllocator allocator;
@@ -92,23 +117,24 @@ struct spgemm_plan_s {
     int tile = kTile, tpitch = 8;
     int nbsum = 0;
 
-    // pinned host mirror of the header and totals (raw, then as published
-    // pairs), mapped for the device
-    void *pinned = nullptr, *pinned_dev = nullptr;
-    size_t pinned_bytes = 0;
-    uint32_t pub_seq = 0;
+    // mapped host memory from the pool: the header and totals as published
+    // pairs, their raw words (`pinned`; the allocation-free entry point has
+    // only these), and room for uploads
+    HostMirror mirror;
+    void *pinned = nullptr;
+    bool upload_pending = false;  // a copy from the upload room may still run
     Hdr hdr_host{};
     std::vector<long long> totals_host;
 
     // table currently on the device (batched numeric uploads when it changes)
     std::vector<Prob> table_dev_copy;
     hipEvent_t upload_done = nullptr;
+    size_t o_table = 0, table_bytes = 0;  // the table, column offsets and tiles in the workspace
 
-    // side streams (default priority) on which the accumulator kinds run
-    // concurrently with the caller's stream; fork/join through events
-    static constexpr int kSide = 3;
-    hipStream_t side[kSide] = {nullptr, nullptr, nullptr};
-    hipEvent_t fork_ev = nullptr, join_ev[kSide] = {nullptr, nullptr, nullptr};
+    // side streams on which the accumulator kinds run concurrently with the
+    // caller's stream, and the events of the fork and join, from the pool
+    static constexpr int kSide = SideSet::kSide;
+    SideSet sides;
 
     // backward: row view of B
     DevBuf bt;
@@ -141,7 +167,7 @@ struct spgemm_plan_s {
     // one-call product may run its numeric phase at these positions first
     int32_t *saved_cp = nullptr;
     bool saved_ok = false;
-    int saved_n = 0;
+    int saved_n = 0;  // columns of that structure
     long long saved_total = 0;
 
     hipStream_t last_stream = nullptr;
@@ -190,34 +216,149 @@ struct ProfScope {
     ProfScope &operator=(const ProfScope &) = delete;
 };
 
+// ---------------------------------------------------------------- pool
+// At most kPoolSets idle stream sets and kPoolMirrors idle mirrors of at most
+// kPoolBytes are kept (first products in a loop, from a few threads, reuse
+// them); spgemm_release_pool frees them. Every access holds the mutex; an
+// object belongs to one plan at a time.
+constexpr size_t kPoolSets = 4, kPoolMirrors = 4, kPoolBytes = 1u << 20;
+struct HostPool {
+    std::mutex mu;
+    std::vector<SideSet> sets;
+    std::vector<HostMirror> mirrors;
+};
+HostPool &host_pool() {
+    static HostPool *pool = new HostPool;  // outlives every static destructor
+    return *pool;
+}
+
+void destroy_sides(SideSet &x) {
+    for (int i = 0; i < SideSet::kSide; ++i) {
+        if (x.side[i]) (void)hipStreamDestroy(x.side[i]);
+        if (x.join_ev[i]) (void)hipEventDestroy(x.join_ev[i]);
+    }
+    if (x.fork_ev) (void)hipEventDestroy(x.fork_ev);
+    x = SideSet{};
+}
+
+// The streams are drained first: nothing of the plan runs on after this.
+void release_sides(SideSet &x) {
+    if (!x.fork_ev) {
+        destroy_sides(x);
+        return;
+    }
+    bool ok = true;
+    for (int i = 0; i < SideSet::kSide; ++i) ok &= hipStreamSynchronize(x.side[i]) == hipSuccess;
+    if (ok) {
+        HostPool &hp = host_pool();
+        std::lock_guard<std::mutex> lk(hp.mu);
+        if (hp.sets.size() < kPoolSets) {
+            hp.sets.push_back(x);
+            x = SideSet{};
+            return;
+        }
+    }
+    destroy_sides(x);
+}
+
+hipError_t acquire_sides(SideSet &x, int device) {
+    {
+        HostPool &hp = host_pool();
+        std::lock_guard<std::mutex> lk(hp.mu);
+        for (size_t i = 0; i < hp.sets.size(); ++i)
+            if (hp.sets[i].device == device) {
+                x = hp.sets[i];
+                hp.sets.erase(hp.sets.begin() + (long)i);
+                return hipSuccess;
+            }
+    }
+    hipError_t e;
+    // the fork and join events only order streams of this device: a
+    // device-scope release is enough (no write-back for the host's view)
+    const unsigned ef = hipEventDisableTiming | hipEventReleaseToDevice;
+    x.device = device;
+    for (int i = 0; i < SideSet::kSide; ++i) {
+        if ((e = hipStreamCreateWithFlags(&x.side[i], hipStreamNonBlocking))) return e;
+        if ((e = hipEventCreateWithFlags(&x.join_ev[i], ef))) return e;
+    }
+    return hipEventCreateWithFlags(&x.fork_ev, ef);
+}
+
+// The device writes no more to it and no copy reads it.
+void release_mirror(HostMirror &m) {
+    if (!m.base) return;
+    if (12 * m.words + m.upload <= kPoolBytes) {
+        HostPool &hp = host_pool();
+        std::lock_guard<std::mutex> lk(hp.mu);
+        if (hp.mirrors.size() < kPoolMirrors) {
+            hp.mirrors.push_back(m);
+            m = HostMirror{};
+            return;
+        }
+    }
+    (void)hipHostFree(m.base);
+    m = HostMirror{};
+}
+
+spgemm_status acquire_mirror(HostMirror &m, int device, size_t words, size_t upload) {
+    {
+        HostPool &hp = host_pool();
+        std::lock_guard<std::mutex> lk(hp.mu);
+        for (size_t i = 0; i < hp.mirrors.size(); ++i) {
+            const HostMirror &x = hp.mirrors[i];
+            if (x.device == device && x.words >= words && x.upload >= upload) {
+                m = x;
+                hp.mirrors.erase(hp.mirrors.begin() + (long)i);
+                return SPGEMM_OK;
+            }
+        }
+    }
+    auto up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
+    m = HostMirror{};
+    m.device = device;
+    m.words = up(words, 512);
+    m.upload = up(upload, 4096);
+    const size_t bytes = 12 * m.words + m.upload;
+    void *ptr = nullptr;
+    // coherent: the device's stores reach host memory without a copy
+    if (hipHostMalloc(&ptr, bytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        m = HostMirror{};
+        return SPGEMM_ERR_NO_MEMORY;
+    }
+    m.base = (char *)ptr;
+    if (hipHostGetDevicePointer(&m.dev, ptr, 0) != hipSuccess) {
+        (void)hipHostFree(ptr);
+        m = HostMirror{};
+        return SPGEMM_ERR_HIP;
+    }
+    std::memset(ptr, 0, bytes);  // no pair carries the next number
+    return SPGEMM_OK;
+}
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 constexpr size_t kHdrBytes = 4 * (size_t)kHdrWords;  // header, then the totals
-// The host mirror: the raw header and totals (pin bytes, read back by copies)
-// and then the same words as published pairs (word, sequence number).
-unsigned long long *pub_pairs_host(spgemm_plan p) {
-    return (unsigned long long *)((char *)p->pinned + p->pinned_bytes);
-}
-
-// The next publication of the header and totals, tagged with the next sequence
-// number (nothing to publish to in a plan of the allocation-free entry point).
-PubArgs next_publication(spgemm_plan p) {
+// The next publication of `words` words of the header (and totals behind it),
+// tagged with the next sequence number (nothing to publish to in a plan of the
+// allocation-free entry point).
+PubArgs next_publication(spgemm_plan p, size_t words) {
     if (p->use_arena) return PubArgs{nullptr, 0, 0};
-    return PubArgs{(unsigned long long *)((char *)p->pinned_dev + p->pinned_bytes),
-                   (int32_t)((kHdrBytes + 8 * (size_t)p->nprob) / 4), ++p->pub_seq};
+    return PubArgs{(unsigned long long *)p->mirror.dev, (int32_t)words, ++p->mirror.seq};
 }
+size_t all_words(spgemm_plan p) { return (kHdrBytes + 8 * (size_t)p->nprob) / 4; }
 
-// Waits until every published pair carries the last sequence number and
-// copies the words to the raw mirror. The stream is polled now and then, so a
+// Waits until the first `words` published pairs carry the last sequence number
+// and copies them to the raw mirror. The stream is polled now and then, so a
 // failed or finished stream ends the wait.
-spgemm_status wait_published(spgemm_plan p, hipStream_t s) {
-    const int nwords = (int)((kHdrBytes + 8 * (size_t)p->nprob) / 4);
-    const unsigned long long *pairs = pub_pairs_host(p);
+spgemm_status wait_published(spgemm_plan p, hipStream_t s, size_t words) {
+    const unsigned long long *pairs = p->mirror.pairs();
+    const uint32_t seq = p->mirror.seq;
     uint32_t *raw = (uint32_t *)p->pinned;
     unsigned spin = 0;
-    for (int i = 0; i < nwords; ++i) {
+    for (size_t i = 0; i < words; ++i) {
         for (;;) {
             const unsigned long long v = __atomic_load_n(&pairs[i], __ATOMIC_ACQUIRE);
-            if ((uint32_t)(v >> 32) == p->pub_seq) {
+            if ((uint32_t)(v >> 32) == seq) {
                 raw[i] = (uint32_t)v;
                 break;
             }
@@ -226,7 +367,7 @@ spgemm_status wait_published(spgemm_plan p, hipStream_t s) {
                 // all queued work has ended: the pairs are written by now
                 if (q == hipSuccess) {
                     const unsigned long long w = __atomic_load_n(&pairs[i], __ATOMIC_ACQUIRE);
-                    if ((uint32_t)(w >> 32) != p->pub_seq) return SPGEMM_ERR_HIP;
+                    if ((uint32_t)(w >> 32) != seq) return SPGEMM_ERR_HIP;
                     raw[i] = (uint32_t)w;
                     break;
                 }
@@ -375,6 +516,24 @@ spgemm_status validate_host(const spgemm_csc *m) {
     return SPGEMM_OK;
 }
 
+// A copy from the plan's upload room has ended (the room may be written again).
+spgemm_status wait_upload(spgemm_plan p) {
+    if (!p->upload_pending) return SPGEMM_OK;
+    SPG_TRY(hipEventSynchronize(p->upload_done));
+    p->upload_pending = false;
+    return SPGEMM_OK;
+}
+
+// `bytes` from the start of the upload room to the problem table on `s`.
+spgemm_status upload_table(spgemm_plan p, size_t bytes, hipStream_t s) {
+    if (!p->upload_done)
+        SPG_TRY(hipEventCreateWithFlags(&p->upload_done, hipEventDisableTiming));
+    SPG_TRY(hipMemcpyAsync(p->table, p->mirror.room(), bytes, hipMemcpyHostToDevice, s));
+    SPG_TRY(hipEventRecord(p->upload_done, s));
+    p->upload_pending = true;
+    return SPGEMM_OK;
+}
+
 // carve the workspace for the plan's current sizes; grows the allocation
 spgemm_status ensure_workspace(spgemm_plan p, hipStream_t s) {
     const size_t n = (size_t)std::max(p->ncols, 1);
@@ -390,6 +549,8 @@ spgemm_status ensure_workspace(spgemm_plan p, hipStream_t s) {
     const size_t o_hdr = take(kHdrBytes + 8 * (size_t)std::max(p->nprob, 1));
     const size_t o_op = take(4 * n), o_binw = take(4 * n), o_binlist = take(16 * n),
                  o_gnnz = take(4 * n);
+    // (at an offset that depends on the column count alone: see saved_n)
+    const size_t o_saved = take(4 * (n + 1));
     const size_t o_E = take(8 * (size_t)std::max(p->total_nnzb, 1ll));
     // the product space's offsets, and the pointers over all problems
     const size_t o_colprod = take(p->direct ? 0 : 8 * (n + 1));
@@ -409,7 +570,6 @@ spgemm_status ensure_workspace(spgemm_plan p, hipStream_t s) {
     const size_t o_ttot = take(8 * (size_t)std::max(p->ntiles, 1));
     const size_t o_tmax = take(4 * (size_t)std::max(p->ntiles, 1));
     const size_t o_hoff = take(8 * (n + 1)), o_wbase = take(4 * (n + 1));
-    const size_t o_saved = take(4 * (n + 1));
     const size_t need = off;
     if (need > p->ws.bytes) {
         if (spgemm_status st = dev_alloc(p, p->ws, need, s)) return st;
@@ -443,23 +603,19 @@ spgemm_status ensure_workspace(spgemm_plan p, hipStream_t s) {
     p->wbase = (int32_t *)(b + o_wbase);
     p->saved_cp = (int32_t *)(b + o_saved);
 
-    const size_t pin = kHdrBytes + 8 * (size_t)std::max(p->nprob, 1);
-    if (pin > p->pinned_bytes && !p->use_arena) {
-        if (p->pinned) (void)hipHostFree(p->pinned);
-        p->pinned = p->pinned_dev = nullptr;
-        p->pinned_bytes = 0;
-        // coherent: the device's stores reach host memory without a copy
-        if (hipHostMalloc(&p->pinned, 3 * pin, hipHostMallocMapped | hipHostMallocCoherent) !=
-            hipSuccess)
-            return SPGEMM_ERR_NO_MEMORY;
-        if (hipHostGetDevicePointer(&p->pinned_dev, p->pinned, 0) != hipSuccess) {
-            (void)hipHostFree(p->pinned);
-            p->pinned = p->pinned_dev = nullptr;
-            return SPGEMM_ERR_HIP;
+    p->o_table = o_tab;
+    p->table_bytes = o_tiles + sizeof(int4) * (size_t)std::max(p->ntiles, 1) - o_tab;
+    if (!p->use_arena) {
+        const size_t words = (kHdrBytes + 8 * (size_t)std::max(p->nprob, 1)) / 4;
+        const size_t room = p->nprob > 1 ? p->table_bytes : 0;
+        if (words > p->mirror.words || room > p->mirror.upload) {
+            if (spgemm_status st = wait_upload(p)) return st;
+            // nothing queued may still publish to the old one
+            if (p->mirror.base) SPG_TRY(hipStreamSynchronize(s));
+            release_mirror(p->mirror);
+            if (spgemm_status st = acquire_mirror(p->mirror, p->device, words, room)) return st;
         }
-        p->pinned_bytes = pin;
-        std::memset(p->pinned, 0, 3 * pin);
-        p->pub_seq = 0;  // no pair carries the next number
+        p->pinned = p->mirror.raw();
     }
     return SPGEMM_OK;
 }
@@ -540,22 +696,12 @@ int device_cus() {
 // one workgroup (dense, hash) per work item; the grids come from the bin sizes
 // on the host.
 hipError_t ensure_side_streams(spgemm_plan p) {
-    if (p->fork_ev) return hipSuccess;
-    hipError_t e;
-    // the fork and join events only order streams of this device: a
-    // device-scope release is enough (no write-back for the host's view)
-    const unsigned ef = hipEventDisableTiming | hipEventReleaseToDevice;
-    for (int i = 0; i < spgemm_plan_s::kSide; ++i) {
-        if ((e = hipStreamCreateWithFlags(&p->side[i], hipStreamNonBlocking))) return e;
-        if ((e = hipEventCreateWithFlags(&p->join_ev[i], ef))) return e;
-    }
-    return hipEventCreateWithFlags(&p->fork_ev, ef);
+    return p->sides.fork_ev ? hipSuccess : acquire_sides(p->sides, p->device);
 }
-
 
 // side stream i, or the caller's stream when every kind runs on it
 hipStream_t side(spgemm_plan p, int i, hipStream_t s) {
-    return (p->flags & SPGEMM_ONE_STREAM) ? s : p->side[i];
+    return (p->flags & SPGEMM_ONE_STREAM) ? s : p->sides.side[i];
 }
 
 // the side streams in `used` (bit i: side stream i) wait for the caller's
@@ -563,10 +709,10 @@ hipStream_t side(spgemm_plan p, int i, hipStream_t s) {
 hipError_t fork(spgemm_plan p, hipStream_t s, unsigned used) {
     if ((p->flags & SPGEMM_ONE_STREAM) || !used) return hipSuccess;
     hipError_t e;
-    if ((e = hipEventRecord(p->fork_ev, s))) return e;
+    if ((e = hipEventRecord(p->sides.fork_ev, s))) return e;
     for (int i = 0; i < spgemm_plan_s::kSide; ++i)
         if ((used >> i) & 1u)
-            if ((e = hipStreamWaitEvent(p->side[i], p->fork_ev, 0))) return e;
+            if ((e = hipStreamWaitEvent(p->sides.side[i], p->sides.fork_ev, 0))) return e;
     return hipSuccess;
 }
 
@@ -579,11 +725,11 @@ hipError_t join(spgemm_plan p, hipStream_t s, unsigned used) {
     int prev = -1;
     for (int i = 0; i < spgemm_plan_s::kSide; ++i) {
         if (!((used >> i) & 1u)) continue;
-        if (prev >= 0 && (e = hipStreamWaitEvent(p->side[i], p->join_ev[prev], 0))) return e;
-        if ((e = hipEventRecord(p->join_ev[i], p->side[i]))) return e;
+        if (prev >= 0 && (e = hipStreamWaitEvent(p->sides.side[i], p->sides.join_ev[prev], 0))) return e;
+        if ((e = hipEventRecord(p->sides.join_ev[i], p->sides.side[i]))) return e;
         prev = i;
     }
-    return hipStreamWaitEvent(s, p->join_ev[prev], 0);
+    return hipStreamWaitEvent(s, p->sides.join_ev[prev], 0);
 }
 
 // first bin-list position of bin b
@@ -768,6 +914,7 @@ hipError_t launch_direct_accumulators(spgemm_plan p, const KArgs &a, hipStream_t
     // a small product runs on the caller's stream alone: the events of a
     // fork and join cost more than the overlap gains
     const bool one = (p->flags & SPGEMM_ONE_STREAM) || h.total_op < kSmallProducts;
+    if (!one && (e = ensure_side_streams(p))) return e;
     auto on = [&](int i) { return one ? s : side(p, i, s); };
     unsigned used = 0;
     if (!one) {
@@ -956,16 +1103,17 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
     spgemm_status st = ensure_workspace(p, s);
     if (st) return st;
     if (p->nprob > 1) {
-        std::vector<int32_t> c0(p->nprob + 1);
+        // table, column offsets and tiles in one copy from pinned memory, laid
+        // out as in the workspace (three pageable copies and a wait before)
+        if ((st = wait_upload(p))) return st;
+        char *room = p->mirror.room();
+        std::memcpy(room, p->probs.data(), sizeof(Prob) * p->nprob);
+        int32_t *c0 = (int32_t *)(room + ((char *)p->col0s - (char *)p->table));
         for (int i = 0; i < p->nprob; ++i) c0[i] = p->probs[i].col0;
         c0[p->nprob] = p->ncols;
-        SPG_TRY(hipMemcpyAsync(p->table, p->probs.data(), sizeof(Prob) * p->nprob,
-                               hipMemcpyHostToDevice, s));
-        SPG_TRY(hipMemcpyAsync(p->col0s, c0.data(), 4 * c0.size(), hipMemcpyHostToDevice, s));
-        SPG_TRY(hipMemcpyAsync(p->tiles, tiles_host.data(), sizeof(int4) * tiles_host.size(),
-                               hipMemcpyHostToDevice, s));
-        // the pageable sources may change after return: wait for the copies
-        SPG_TRY(hipStreamSynchronize(s));
+        std::memcpy(room + ((char *)p->tiles - (char *)p->table), tiles_host.data(),
+                    sizeof(int4) * tiles_host.size());
+        if ((st = upload_table(p, p->table_bytes, s))) return st;
         p->table_dev_copy = p->probs;
     }
     // a place kernel that combines the tiles itself writes the whole header
@@ -987,19 +1135,31 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
     // expansion run on the caller's; the offsets kernel stops the expansion if
     // the products outgrow the planned product space.
     // (The direct-gather accumulators have nothing to overlap them with.)
+    if (p->nprob != 1) p->saved_ok = false;
+    PubArgs mid{nullptr, 0, 0};  // publication of the header before the accumulators
     const bool overlap = spec && !p->direct && p->ncols > 0 && !(p->flags & SPGEMM_ONE_STREAM);
     {
         const KArgs a = args();
         { ProfScope ps("classify", s); SPG_TRY(launch_classify(a, s)); }
         if (overlap) SPG_TRY(fork(p, s, 1u));
-        hipStream_t sp = overlap ? p->side[0] : s;
+        hipStream_t sp = overlap ? p->sides.side[0] : s;
         { ProfScope ps("tally", sp); SPG_TRY(launch_tally(a, sp)); }
-        { ProfScope ps("place", sp); SPG_TRY(launch_place(a, sp)); }
+        if (!spec && p->direct) mid = next_publication(p, kHdrWords);
+        { ProfScope ps("place", sp); SPG_TRY(launch_place(a, mid, sp)); }
     }
     if (!spec) {
-        // the bin sizes fix the grids and the product count the allocation
-        SPG_TRY(hipMemcpyAsync(p->pinned, p->hdr, sizeof(Hdr), hipMemcpyDeviceToHost, s));
-        SPG_TRY(hipStreamSynchronize(s));
+        // the bin sizes fix the grids and the product count the allocation:
+        // the place kernel's workgroup that writes the header publishes it
+        if (p->use_arena) {
+            SPG_TRY(hipMemcpyAsync(p->pinned, p->hdr, sizeof(Hdr), hipMemcpyDeviceToHost, s));
+            SPG_TRY(hipStreamSynchronize(s));
+        } else {
+            if (!mid.dst || p->ntiles == 0 || p->ntiles > kSelfTiles) {
+                if (!mid.dst) mid = next_publication(p, kHdrWords);
+                SPG_TRY(launch_publish(p->hdr, mid, s));
+            }
+            if ((st = wait_published(p, s, kHdrWords))) return st;
+        }
         std::memcpy(&p->hdr_host, p->pinned, sizeof(Hdr));
         const int err = p->hdr_host.err;
         if (err & ERR_CSC) return SPGEMM_ERR_CSC;
@@ -1020,7 +1180,13 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
     PubArgs pub{nullptr, 0, 0};
     if (p->ncols > 0 && p->direct) {
         if ((st = ensure_lblock(p, s))) return st;
-        const KArgs al = args();
+        KArgs al = args();
+        if (p->nprob == 1 && !speculate) {
+            // the structure a later one-call product may start from: the scan
+            // writes it beside the caller's pointers
+            al.save = p->saved_cp;
+            p->saved_ok = false;
+        }
         if (speculate) {
             KArgs af = al;
             af.single.cri = fo->cri;
@@ -1034,7 +1200,7 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
             SPG_TRY(launch_direct_accumulators(p, al, s, false));
         }
         ProfScope ps("scan", s);
-        pub = next_publication(p);
+        pub = next_publication(p, all_words(p));
         SPG_TRY(launch_scan(al, p->gcp, p->bsum, p->nblk, p->totals, pub, s));
     } else if (p->ncols > 0) {
         const KArgs al = args();
@@ -1047,7 +1213,7 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
         if (overlap) SPG_TRY(join(p, s, 1u));
         SPG_TRY(launch_symbolic_accumulators(p, al, s));
         ProfScope ps("scan", s);
-        pub = next_publication(p);
+        pub = next_publication(p, all_words(p));
         SPG_TRY(launch_scan(al, p->gcp, p->bsum, p->nblk, p->totals, pub, s));
     }
     if (p->use_arena) {
@@ -1058,7 +1224,7 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
         SPG_TRY(hipStreamSynchronize(s));
     } else if (p->nprob != 1 || p->ncols == 0) {
         // (a single problem's scan has published them)
-        if (!pub.dst) pub = next_publication(p);
+        if (!pub.dst) pub = next_publication(p, all_words(p));
         SPG_TRY(launch_publish(p->hdr, pub, s));
     }
     if (fo && spec && p->ncols > 0 && p->nprob == 1 && !speculate) {
@@ -1074,7 +1240,7 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
         SPG_TRY(launch_numeric_phase(p, an, s));
     }
     if (!p->use_arena) {
-        const spgemm_status w = wait_published(p, s);
+        const spgemm_status w = wait_published(p, s, all_words(p));
         if (w != SPGEMM_OK) return w;
     }
     std::memcpy(&p->hdr_host, p->pinned, sizeof(Hdr));
@@ -1100,9 +1266,6 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
         // a later planned pass compares its product total with this one
         p->prod_total = (long long)p->hdr_host.total_op;
         if (p->nprob == 1 && p->ncols > 0 && !speculate) {
-            // the structure a later one-call product may start from
-            SPG_TRY(hipMemcpyAsync(p->saved_cp, p->probs[0].ccp, 4 * ((size_t)p->ncols + 1),
-                                   hipMemcpyDeviceToDevice, s));
             p->saved_total = p->totals_host[0];
             p->saved_n = p->ncols;
             p->saved_ok = true;
@@ -1285,7 +1448,8 @@ static spgemm_status symbolic_common(int32_t count, const spgemm_csc *A, const s
         p->hdr_host = Hdr{};
         return SPGEMM_OK;
     }
-    if (hipError_t e = ensure_side_streams(p)) {
+    // (the direct-gather accumulators take theirs when they first overlap)
+    if (hipError_t e = p->direct ? hipSuccess : ensure_side_streams(p)) {
         if (fresh) spgemm_plan_destroy(p);
         return hip_status(e);
     }
@@ -1400,10 +1564,9 @@ spgemm_status spgemm_batched(int32_t count, const spgemm_csc *A_host, const spge
                     std::memcmp(p->table_dev_copy.data(), p->probs.data(),
                                 sizeof(Prob) * p->probs.size()) == 0;
         if (!same) {
-            SPG_TRY(hipMemcpyAsync(p->table, p->probs.data(), sizeof(Prob) * p->nprob,
-                                   hipMemcpyHostToDevice, s));
-            // the pageable source may be reused by the caller: wait for the copy
-            SPG_TRY(hipStreamSynchronize(s));
+            if (spgemm_status st = wait_upload(p)) return st;
+            std::memcpy(p->mirror.room(), p->probs.data(), sizeof(Prob) * p->nprob);
+            if (spgemm_status st = upload_table(p, sizeof(Prob) * p->nprob, s)) return st;
             p->table_dev_copy = p->probs;
         }
     }
@@ -1582,20 +1745,24 @@ void spgemm_plan_destroy(spgemm_plan p) {
     dev_free(p, p->bt, s);
     dev_free(p, p->lbuf, s);
     (void)hipStreamSynchronize(s);
-    for (int i = 0; i < spgemm_plan_s::kSide; ++i) {
-        if (p->side[i]) {
-            (void)hipStreamSynchronize(p->side[i]);
-            (void)hipStreamDestroy(p->side[i]);
-        }
-        if (p->join_ev[i]) (void)hipEventDestroy(p->join_ev[i]);
-    }
-    if (p->fork_ev) (void)hipEventDestroy(p->fork_ev);
+    release_sides(p->sides);
+    (void)wait_upload(p);
+    release_mirror(p->mirror);
     if (p->order_ev) (void)hipEventDestroy(p->order_ev);
-    if (p->pinned) (void)hipHostFree(p->pinned);
+    if (p->upload_done) (void)hipEventDestroy(p->upload_done);
     delete p;
 }
 
 void spgemm_batch_plan_destroy(spgemm_batch_plan p) { spgemm_plan_destroy(p); }
+
+void spgemm_release_pool(void) {
+    HostPool &hp = host_pool();
+    std::lock_guard<std::mutex> lk(hp.mu);
+    for (SideSet &x : hp.sets) destroy_sides(x);
+    for (HostMirror &m : hp.mirrors) (void)hipHostFree(m.base);
+    hp.sets.clear();
+    hp.mirrors.clear();
+}
 
 }  // extern "C"
 
@@ -1672,8 +1839,6 @@ extern "C" spgemm_status spgemm_multiply_noalloc(const spgemm_csc *A, const spge
     p->arena_off = 0;
     p->ws = p->prod = p->stage = p->bt = p->lbuf = DevBuf{};
     p->pinned = sl.host;
-    p->pinned_dev = nullptr;
-    p->pinned_bytes = sizeof(sl.host);
     p->dt = dt;
     p->batched = false;
     p->nprob = 1;
