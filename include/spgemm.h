@@ -309,10 +309,12 @@ spgemm_status spgemm_multiply_noalloc(const spgemm_csc *A, const spgemm_csc *B, 
  * that gradient. Every term is added in the stated order without FMA, so the
  * result equals the sequential sums bit for bit. Single-problem plans only.
  * The first call builds and caches a view of the two patterns inside the plan
- * (per stored entry: its first product and C column start; a row view of B)
- * and may allocate; later calls on the plan are stream-ordered, allocate
- * nothing and queue only kernels (they may be captured in a HIP graph together
- * with spgemm_numeric on the same plan).
+ * (per product its place in C; per stored entry its products and terms) and
+ * takes space for one value per product (the terms of dA; without that space
+ * dA gathers G a second time). It may allocate; later calls on the plan are
+ * stream-ordered, allocate nothing and queue only kernels (they may be captured
+ * in a HIP graph together with spgemm_numeric on the same plan; a replay uses
+ * the plan's workspace, so it must not overlap other work on the plan).
  */
 spgemm_status spgemm_backward(spgemm_plan plan, const void *A_val, const void *B_val,
                               const int32_t *C_rowidx, const void *G_val,

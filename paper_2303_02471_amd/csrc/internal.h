@@ -331,58 +331,41 @@ hipError_t launch_heavy(const KArgs &a, int ncols, int nwin, bool wide, bool fil
                         hipStream_t s, bool radix, long long heavy_products, int rowbits,
                         int part);
 inline int row_bits(int m) { return m <= 1 ? 0 : 32 - __builtin_clz((unsigned)(m - 1)); }
-// rank of every product's row in its C column (binary search of C's sorted
-// rows), for the backward view
-hipError_t launch_bw_dst(const Prob &p, const int2 *E, const long long *pofs, const int32_t *bcol,
-                         const int32_t *cri, uint32_t *dst, int *err, hipStream_t s);
-
-// Backward view, built once per single-problem plan: per stored B entry its
-// first product (pofs) and its column's first C entry (cb); per stored A entry
-// (column, offset in the column); a row view of B (rowptr over B's rows,
-// entries by ascending column) holding (B entry, cb) and the first product.
+// Backward view, built once per single-problem plan (see k_backward.hip).
 struct BwView {
     const int2 *E;            // the plan's (A column start, length) per stored B entry
-    const uint32_t *dst;      // rank of every product's row in its C column
+    const uint32_t *gpos;     // [products] place of every product's row among C's entries
     long long nnzc;           // stored entries of C
-    const long long *pofs;    // [nnz(B)]
-    const int32_t *cb;        // [nnz(B)]
-    const int2 *aview;        // [nnz(A)]
+    const long long *pofs;    // [nnz(B)] first product of every stored B entry
+    const long long *woff;    // [nnz(B)] its first term of dA
+    const int4 *aview;        // [nnz(A)] (first term: 64 bits, terms, their distance)
     const int32_t *rowptr;    // [rows of B + 1]
-    const int2 *rv;           // [nnz(B)]
-    const long long *rvp;     // [nnz(B)]
+    const int32_t *rowent;    // [nnz(B)] every row's stored B entries by ascending column
 };
 // writable arrays of the view and its construction temporaries
 struct BwBuild {
-    long long *pofs;
-    int32_t *cb;
-    int2 *aview;
-    int32_t *rowptr;
-    int2 *rv;
-    long long *rvp;
-    int32_t *fill, *colj, *pos, *bcol, *len;
-    long long *scratch;  // scan partials of the row counts (nscratch)
-    int nscratch;
-    long long *scratch2;  // scan partials of the product counts (nscratch2)
-    int nscratch2;
-    uint32_t *dst;        // [products] rank of every product's row in its C column
+    uint32_t *gpos;
+    long long *pofs, *woff;
+    int4 *aview;
+    int32_t *rowptr, *rowent;
+    int32_t *cnt;          // [rows of B], cleared with the error word behind it
+    size_t clear_bytes;
+    int32_t *arrival, *pos;
+    long long *wbase;      // [rows of B] terms of dA before every row
+    long long *bsum, *bsum2;  // [bw_scan_blocks]
 };
-hipError_t launch_bw_view(const Prob &p, const int2 *E, const BwBuild &b, BwView &w,
-                          hipStream_t s);
-// dA (if da) and dB (if db) of one problem through the view; err collects
-// ERR_CSC for a destination outside C (an inconsistent plan)
-hipError_t launch_backward(const Prob &p, const BwView &w, bool f64, const void *av,
+int bw_scan_blocks(int nnzb, int nrows);
+hipError_t launch_bw_view(const Prob &p, const BwView &v, const BwBuild &b, const int32_t *cri,
+                          int *err, hipStream_t s);
+// dA (if da) and dB (if db) of one problem through the view; terms: space of
+// one value per product, or NULL; err collects ERR_CSC for a place outside C
+// (an inconsistent plan)
+hipError_t launch_backward(const Prob &p, const BwView &v, void *terms, bool f64, const void *av,
                            const void *bv, const void *gv, void *da, void *db, int *err,
                            hipStream_t s);
 // nwords 32-bit words from src to mapped host memory dst, as 8-byte pairs
 // (word, seq)
 hipError_t launch_publish(const void *src, const PubArgs &pub, hipStream_t s);
-// exclusive scans of n int32 values (bsum: nbsum partials, in place allowed
-// for the int32 output)
-hipError_t launch_scan_i32(const int32_t *in, int n, long long *bsum, int nbsum, int32_t *out,
-                           hipStream_t s);
-hipError_t launch_scan_i64(const int32_t *in, int n, long long *bsum, int nbsum, long long *out,
-                           hipStream_t s);
-
 constexpr int kScanBlock = 1024;  // elements per scan block
 
 }  // namespace spg

@@ -3,21 +3,30 @@
 // sparse products over the same product space as the forward pass:
 //   dB(k,j) = sum over stored A(i,k), in A's storage order, of A(i,k) G(i,j)
 //   dA(i,k) = sum over stored B(k,j), j ascending,          of G(i,j) B(k,j)
-// One thread owns one output entry and adds its terms sequentially in the
+// Every term is rounded on its own and the terms of one entry are added in the
 // stated order (no fused multiply-add), so the result is reproducible and
 // matches a plain sequential loop bit for bit.
 //
 // Every term is one product of the forward pass: stored B entry t of column j
 // times the u-th entry of A's column bri[t]. A view built once per plan
-// records that product's rank among the entries of C's column j (dst, by a
-// binary search of C's sorted rows), so G(i,j) sits at ccp[j] + rank; it also
-// holds, per stored B entry, its first product (pofs) and its column's first C
-// entry (cb); per stored A entry, its column and offset in it; and a row view
-// of B (entries of each row by ascending column) with the same two values per
-// entry, so the dA loop reads them without an indirection.
+// records, in product order, the place of every product's G(i,j) among C's
+// entries (gpos, by binary search of C's sorted rows); per stored B entry its
+// first product (pofs) and the first of its terms of dA (woff); per stored A
+// entry its terms of dA.
+//
+// Two passes over the products. The first walks them in product order, where
+// a column's G values lie together: it loads G once, adds up dB and writes the
+// terms G(i,j) B(k,j) of dA grouped by A's column, entry after entry of B's
+// row k in ascending j. The second adds up dA from contiguous blocks. One pass
+// gathering G twice, once in A's order all over C, with a thread per entry
+// walking its list alone, took 87 us for 6.4 M float products (8 per entry) and
+// 324 us for 5 M double products of power-law columns, where the longest list
+// set the time; the two passes take 31 + 8 us and 88 + 11 us.
 #include "devutil.h"
 
 namespace spg {
+
+namespace {
 
 // largest j in [0, n) with cp[j] <= t (columns may be empty)
 __device__ __forceinline__ int column_of(const int32_t *cp, int n, int t) {
@@ -30,261 +39,507 @@ __device__ __forceinline__ int column_of(const int32_t *cp, int n, int t) {
     return lo;
 }
 
-constexpr int kBwUnroll = 4;  // terms whose loads are issued together
+// A wavefront's 64 consecutive stored B entries and their products, which are
+// consecutive too, kBwN at a time: lane l takes positions 64 r + l. Each entry
+// with products in the chunk gets a rank; bit p of `bits` set means that a new
+// entry starts at position p + 1, so the bits below a position count its
+// entry's rank.
+constexpr int kBwKpl = 8, kBwN = 64 * kBwKpl;
 
-template <typename V>
-__device__ __forceinline__ V g_at(const V *__restrict__ gv, long long nnzc, int cb, uint32_t d,
-                                  int &bad) {
-    const long long gp = (long long)cb + (long long)(d & ~kDstLater);
-    if (gp >= nnzc) { bad = 1; return V(0); }
-    return gv[gp];
+__device__ __forceinline__ void bw_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <typename V>
-__device__ __forceinline__ void grad_b(const BwView &w, int t, const V *__restrict__ av,
-                                       const V *__restrict__ gv, V *__restrict__ db, int *err) {
-    const int2 e = w.E[t];  // A column start and length of the entry's row of B
-    const long long base = w.pofs[t];
-    const int cb = w.cb[t];
-    const V *__restrict__ ap = av + e.x;
-    const uint32_t *__restrict__ dp = w.dst + base;
-    V acc = V(0);
-    int bad = 0, u = 0;
-    for (; u + kBwUnroll <= e.y; u += kBwUnroll) {
-        V a[kBwUnroll], g[kBwUnroll];
-        uint32_t d[kBwUnroll];
+struct Chunk {
+    int lo, hi;  // the lane's entry holds positions [lo, hi) of the chunk
+    int rank;    // its rank (where hi > lo)
+    int n;       // products in the chunk
+};
+
+__device__ __forceinline__ Chunk chunk_of(long long c0, long long total, long long o, int z,
+                                          unsigned *bits, int lane) {
+    Chunk c;
+    c.n = (int)max(0ll, min((long long)kBwN, total - c0));
+    c.lo = (int)min(max(o - c0, 0ll), (long long)kBwN);
+    c.hi = (int)min(max(o + z - c0, 0ll), (long long)kBwN);
+    const unsigned long long has = ballot(c.hi > c.lo);
+    c.rank = popc64(has & mask_lt());
+    if (lane < kBwN / 32) bits[lane] = 0;
+    bw_sync();
+    if (c.hi > c.lo && c.lo > 0) atomicOr(&bits[(c.lo - 1) >> 5], 1u << ((c.lo - 1) & 31));
+    bw_sync();
+    return c;
+}
+
+// ranks of the lane's positions
+__device__ __forceinline__ void ranks_of(const unsigned *bits, int (&rk)[kBwKpl]) {
+    int cum = 0;
 #pragma unroll
-        for (int v = 0; v < kBwUnroll; ++v) {
-            a[v] = ap[u + v];
-            d[v] = dp[u + v];
-        }
-#pragma unroll
-        for (int v = 0; v < kBwUnroll; ++v) g[v] = g_at(gv, w.nnzc, cb, d[v], bad);
-#pragma unroll
-        for (int v = 0; v < kBwUnroll; ++v) acc = acc + a[v] * g[v];
+    for (int r = 0; r < kBwKpl; ++r) {
+        const unsigned lo = __builtin_amdgcn_readfirstlane(bits[2 * r]);
+        const unsigned hi = __builtin_amdgcn_readfirstlane(bits[2 * r + 1]);
+        rk[r] = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, (unsigned)cum));
+        cum += __builtin_popcount(lo) + __builtin_popcount(hi);
     }
-    for (; u < e.y; ++u) acc = acc + ap[u] * g_at(gv, w.nnzc, cb, dp[u], bad);
-    db[t] = acc;
+}
+
+// ---------------------------------------------------------------- first pass
+// dB (if db), and the terms of dA (if w). Bound by the loads of gpos, A's
+// columns and G (all contiguous per entry) and the stores of the terms; where
+// long A columns meet in one wavefront (7 chunks among 1 M entries of a power
+// law), by its chain of chunks, so a chunk's loads are in flight while the one
+// before it is summed.
+template <typename V>
+__global__ __launch_bounds__(64) void k_grad_b(BwView v, int nnzb, const V *__restrict__ av,
+                                               const V *__restrict__ bv,
+                                               const V *__restrict__ gv, V *__restrict__ db,
+                                               V *__restrict__ w, int *err) {
+    __shared__ unsigned bits[2][kBwN / 32];  // of this chunk and the next
+    __shared__ int s_q[2][64];
+    __shared__ long long s_w[2][64];
+    __shared__ V s_b[2][64];
+    __shared__ V val[kBwN];
+    const int lane = threadIdx.x;
+    int bad = 0;
+    const int t = blockIdx.x * 64 + lane;
+    int2 e = make_int2(0, 0);
+    long long wo = 0;
+    V bval = V(0);
+    const uint32_t *gpos = v.gpos + v.pofs[blockIdx.x * 64];
+    if (t < nnzb) {
+        e = v.E[t];
+        if (w) {
+            wo = v.woff[t];
+            bval = bv[t];
+        }
+    }
+    const long long inc = wave_incl_scan64(e.y), o = inc - e.y, total = wave_last64(inc);
+    uint32_t gp[kBwKpl];  // the places of a chunk's products, loaded a chunk ahead
+    V a[kBwKpl], g[kBwKpl];
+    Chunk c;
+    auto places = [&](long long c0) {
+#pragma unroll
+        for (int r = 0; r < kBwKpl; ++r) {
+            const long long p = c0 + r * 64 + lane;
+            gp[r] = p < total ? gpos[p] : 0u;
+        }
+    };
+    auto load = [&](long long c0, int x) {
+        c = chunk_of(c0, total, o, e.y, bits[x], lane);
+        if (c.hi > c.lo) {
+            s_q[x][c.rank] = e.x + (int)(c0 - o);
+            if (w) {
+                s_w[x][c.rank] = wo + (c0 - o);
+                s_b[x][c.rank] = bval;
+            }
+        }
+        bw_sync();
+        int rk[kBwKpl];
+        ranks_of(bits[x], rk);
+#pragma unroll
+        for (int r = 0; r < kBwKpl; ++r) {
+            const int p = r * 64 + lane;
+            const bool in = p < c.n;
+            const bool ok = (long long)gp[r] < v.nnzc;
+            bad |= in && !ok;
+            a[r] = in && db ? av[s_q[x][rk[r]] + p] : V(0);
+            g[r] = in && ok ? gv[gp[r]] : V(0);
+        }
+        places(c0 + kBwN);
+    };
+    V acc = V(0);
+    places(0);
+    load(0, 0);
+    int x = 0;
+    for (long long c0 = 0; c0 < total; c0 += kBwN, x ^= 1) {
+        const Chunk d = c;
+        int rk[kBwKpl];
+        ranks_of(bits[x], rk);
+#pragma unroll
+        for (int r = 0; r < kBwKpl; ++r) {
+            const int p = r * 64 + lane;
+            if (p < d.n) {
+                if (w) w[s_w[x][rk[r]] + p] = g[r] * s_b[x][rk[r]];
+                if (db) val[p] = a[r] * g[r];
+            }
+        }
+        if (c0 + kBwN < total) load(c0 + kBwN, x ^ 1);
+        bw_sync();
+        if (db) {
+            // the entry's terms in order; a long list waits neither on a read
+            // (the next U are in flight beside the adds) nor on masks
+            constexpr int U = 8;
+            int i = d.lo;
+            V q[2][U];
+            auto read = [&](V (&y)[U], int at) {
+                const V *n = &val[min(at, kBwN - U)];
+#pragma unroll
+                for (int u = 0; u < U; ++u) y[u] = n[u];
+            };
+            auto add = [&](const V (&y)[U]) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) acc = acc + y[u];
+            };
+            if (i + 2 * U <= d.hi) {
+                read(q[0], i);
+                read(q[1], i + U);
+                for (; i + 2 * U <= d.hi; i += 2 * U) {
+                    add(q[0]);
+                    read(q[0], i + 2 * U);
+                    add(q[1]);
+                    read(q[1], i + 3 * U);
+                }
+            }
+            for (; i < d.hi; i += U) {
+                read(q[0], i);
+                const int skip = i - min(i, kBwN - U);  // read at the buffer's end: shifted
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (u >= skip && i + u - skip < d.hi) acc = acc + q[0][u];
+            }
+        }
+        bw_sync();
+    }
+    if (db && t < nnzb) db[t] = acc;
     if (bad) atomicOr(err, ERR_CSC);
 }
 
+// ---------------------------------------------------------------- second pass
+// dA: one thread per stored A entry; entries of one A column read consecutive
+// terms.
 template <typename V>
-__device__ __forceinline__ void grad_a(const BwView &w, int q, const V *__restrict__ bv,
-                                       const V *__restrict__ gv, V *__restrict__ da, int *err) {
-    const int2 ku = w.aview[q];  // column of A (= row of B) and offset in that column
-    const int r0 = w.rowptr[ku.x], r1 = w.rowptr[ku.x + 1];
+__global__ __launch_bounds__(kBlock) void k_grad_a(const int4 *__restrict__ aview, int nnza,
+                                                   const V *__restrict__ w, V *__restrict__ da) {
+    constexpr int U = 8;  // terms whose loads are issued together
+    const int q = blockIdx.x * kBlock + threadIdx.x;
+    if (q >= nnza) return;
+    const int4 x = aview[q];
+    const V *p = w + (long long)(((unsigned long long)(unsigned)x.y << 32) | (unsigned)x.x);
+    const int deg = x.z, z = x.w;
     V acc = V(0);
-    int bad = 0, r = r0;
-    for (; r + kBwUnroll <= r1; r += kBwUnroll) {
-        int2 tc[kBwUnroll];
-        long long pf[kBwUnroll];
+    int r = 0;
+    for (; r + U <= deg; r += U) {
+        V t[U];
 #pragma unroll
-        for (int v = 0; v < kBwUnroll; ++v) {
-            tc[v] = w.rv[r + v];
-            pf[v] = w.rvp[r + v];
-        }
-        uint32_t d[kBwUnroll];
-        V b[kBwUnroll], g[kBwUnroll];
+        for (int u = 0; u < U; ++u) t[u] = p[(long long)(r + u) * z];
 #pragma unroll
-        for (int v = 0; v < kBwUnroll; ++v) {
-            d[v] = w.dst[pf[v] + ku.y];
-            b[v] = bv[tc[v].x];
-        }
-#pragma unroll
-        for (int v = 0; v < kBwUnroll; ++v) g[v] = g_at(gv, w.nnzc, tc[v].y, d[v], bad);
-#pragma unroll
-        for (int v = 0; v < kBwUnroll; ++v) acc = acc + g[v] * b[v];
+        for (int u = 0; u < U; ++u) acc = acc + t[u];
     }
-    for (; r < r1; ++r) {
-        const int2 tc = w.rv[r];
-        const uint32_t d = w.dst[w.rvp[r] + ku.y];
-        acc = acc + g_at(gv, w.nnzc, tc.y, d, bad) * bv[tc.x];
+    if (r < deg) {
+        V t[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) t[u] = r + u < deg ? p[(long long)(r + u) * z] : V(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (r + u < deg) acc = acc + t[u];
+    }
+    da[q] = acc;
+}
+
+// dA without the terms in memory (a plan that could not get their space): one
+// thread per stored A entry walks B's row and gathers G.
+template <typename V>
+__global__ __launch_bounds__(kBlock) void k_grad_a_gather(BwView v, Prob p, int nnza,
+                                                          const V *__restrict__ bv,
+                                                          const V *__restrict__ gv,
+                                                          V *__restrict__ da, int *err) {
+    const int q = blockIdx.x * kBlock + threadIdx.x;
+    if (q >= nnza) return;
+    const int k = column_of(p.acp, p.k, q), u = q - p.acp[k];
+    V acc = V(0);
+    int bad = 0;
+    for (int r = v.rowptr[k]; r < v.rowptr[k + 1]; ++r) {
+        const int t = v.rowent[r];
+        const uint32_t gp = v.gpos[v.pofs[t] + u];
+        if ((long long)gp >= v.nnzc) {
+            bad = 1;
+            continue;
+        }
+        acc = acc + gv[gp] * bv[t];
     }
     da[q] = acc;
     if (bad) atomicOr(err, ERR_CSC);
 }
 
-// Both gradients in one launch: workgroups [0, nbw) take dB (one thread per
-// stored B entry), the rest dA (one thread per stored A entry).
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_grad(BwView w, int nnza, int nnzb, int nbw,
-                                                 const V *__restrict__ av,
-                                                 const V *__restrict__ bv,
-                                                 const V *__restrict__ gv, V *__restrict__ da,
-                                                 V *__restrict__ db, int *err) {
-    if ((int)blockIdx.x < nbw) {
-        const int t = blockIdx.x * kBlock + threadIdx.x;
-        if (t < nnzb) grad_b<V>(w, t, av, gv, db, err);
-    } else {
-        const int q = (blockIdx.x - nbw) * kBlock + threadIdx.x;
-        if (q < nnza) grad_a<V>(w, q, bv, gv, da, err);
-    }
-}
-
 // ---------------------------------------------------------------- view construction
-// per stored B entry: its column, its column's first C entry, the length of
-// the A column it selects, and the count of its row
-__global__ __launch_bounds__(kBlock) void k_bv_bent(Prob p, const int2 *__restrict__ E,
-                                                    int32_t *bcol, int32_t *cb, int32_t *len,
-                                                    int32_t *cnt) {
+// per stored B entry: its arrival among its row's entries; counts per row
+__global__ __launch_bounds__(kBlock) void k_bv_count(Prob p, int32_t *cnt, int32_t *arrival) {
     const int t = blockIdx.x * kBlock + threadIdx.x;
-    if (t >= p.nnzb) return;
-    const int j = column_of(p.bcp, p.n, t);
-    bcol[t] = j;
-    cb[t] = p.ccp[j];
-    len[t] = E[t].y;
-    atomicAdd(&cnt[p.bri[t]], 1);
+    if (t < p.nnzb) arrival[t] = atomicAdd(&cnt[p.bri[t]], 1);
 }
 
-// per stored A entry: its column and its offset in the column
-__global__ __launch_bounds__(kBlock) void k_bv_aent(Prob p, int2 *aview) {
-    const int q = blockIdx.x * kBlock + threadIdx.x;
-    if (q >= p.nnza) return;
-    const int k = column_of(p.acp, p.k, q);
-    aview[q] = make_int2(k, q - p.acp[k]);
-}
+// Prefix sums in two launches. Blocks [0, nbt): the lengths of the A columns
+// that the stored B entries select (pofs); the others, over B's rows k: the
+// entries before (rowptr) and the terms of dA before (wbase, deg_k z_k each).
+struct BvScan {
+    const int2 *E;
+    int nnzb, nrows, nbt;
+    const int32_t *cnt, *acp;
+    long long *bsum, *bsum2;  // per block: pofs or wbase sums; rowptr sums
+    long long *pofs, *wbase;
+    int32_t *rowptr;
+};
+constexpr int kBvPer = 4, kBvBlock = kBvPer * kBlock;
 
-__global__ __launch_bounds__(kBlock) void k_bv_fill(Prob p, const int32_t *rowptr,
-                                                    const int32_t *bcol, int32_t *fill,
-                                                    int32_t *colj, int32_t *pos) {
-    const int t = blockIdx.x * kBlock + threadIdx.x;
-    if (t >= p.nnzb) return;
-    const int k = p.bri[t];
-    const int slot = rowptr[k] + atomicAdd(&fill[k], 1);
-    colj[slot] = bcol[t];
-    pos[slot] = t;
-}
-
-// each row's entries by ascending column (Shell sort with Ciura's gaps)
-__global__ __launch_bounds__(kBlock) void k_bv_sort(int nrows, const int32_t *rowptr,
-                                                    int32_t *colj, int32_t *pos) {
-    const int k = blockIdx.x * kBlock + threadIdx.x;
-    if (k >= nrows) return;
-    const int b = rowptr[k], e = rowptr[k + 1], len = e - b;
-    const int gaps[8] = {701, 301, 132, 57, 23, 10, 4, 1};
-    for (int gi = 0; gi < 8; ++gi) {
-        const int gap = gaps[gi];
-        if (gap >= len) continue;
-        for (int u = b + gap; u < e; ++u) {
-            const int cj = colj[u], cp = pos[u];
-            int v = u;
-            while (v - gap >= b && colj[v - gap] > cj) {
-                colj[v] = colj[v - gap];
-                pos[v] = pos[v - gap];
-                v -= gap;
+__device__ __forceinline__ void bv_items(const BvScan &a, int b, long long (&x)[kBvPer],
+                                         long long (&y)[kBvPer]) {
+#pragma unroll
+    for (int u = 0; u < kBvPer; ++u) {
+        x[u] = y[u] = 0;
+        if (b < a.nbt) {
+            const int t = b * kBvBlock + threadIdx.x * kBvPer + u;
+            if (t < a.nnzb) x[u] = a.E[t].y;
+        } else {
+            const int k = (b - a.nbt) * kBvBlock + threadIdx.x * kBvPer + u;
+            if (k < a.nrows) {
+                y[u] = a.cnt[k];
+                x[u] = y[u] * (a.acp[k + 1] - a.acp[k]);
             }
-            colj[v] = cj;
-            pos[v] = cp;
         }
     }
 }
 
-// the row view's per-entry values: (B entry, C column start) and first product
-__global__ __launch_bounds__(kBlock) void k_bv_pack(int nnzb, const int32_t *pos,
-                                                    const int32_t *cb, const long long *pofs,
-                                                    int2 *rv, long long *rvp) {
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= nnzb) return;
-    const int t = pos[r];
-    rv[r] = make_int2(t, cb[t]);
-    rvp[r] = pofs[t];
+__global__ __launch_bounds__(kBlock) void k_bv_sums(BvScan a) {
+    __shared__ long long s[2][kBlock / 64];
+    long long x[kBvPer], y[kBvPer], sx = 0, sy = 0;
+    bv_items(a, blockIdx.x, x, y);
+#pragma unroll
+    for (int u = 0; u < kBvPer; ++u) {
+        sx += x[u];
+        sy += y[u];
+    }
+    sx = wave_sum64(sx);
+    sy = wave_sum64(sy);
+    if ((threadIdx.x & 63) == 0) {
+        s[0][threadIdx.x >> 6] = sx;
+        s[1][threadIdx.x >> 6] = sy;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sx = sy = 0;
+        for (int q = 0; q < kBlock / 64; ++q) {
+            sx += s[0][q];
+            sy += s[1][q];
+        }
+        a.bsum[blockIdx.x] = sx;
+        a.bsum2[blockIdx.x] = sy;
+    }
 }
 
-// rank of every product's row inside its C column (C's rows are ascending:
-// a binary search), thread per stored B entry walking its A column
-__global__ __launch_bounds__(kBlock) void k_bv_dst(Prob p, const int2 *__restrict__ E,
-                                                   const long long *__restrict__ pofs,
-                                                   const int32_t *__restrict__ bcol,
-                                                   const int32_t *__restrict__ cri,
-                                                   uint32_t *__restrict__ dst, int *err) {
-    const int t = blockIdx.x * kBlock + threadIdx.x;
-    if (t >= p.nnzb) return;
-    const int j = bcol[t];
-    const int c0 = p.ccp[j], c1 = p.ccp[j + 1];
-    const int2 e = E[t];
-    const long long base = pofs[t];
-    int bad = 0;
-    for (int u = 0; u < e.y; ++u) {
-        const int row = p.ari[e.x + u];
-        int lo = c0, hi = c1;  // first position whose row is not below `row`
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (cri[mid] < row) lo = mid + 1;
-            else hi = mid;
-        }
-        if (lo >= c1 || cri[lo] != row) {  // C does not hold the product's row
-            bad = 1;
-            dst[base + u] = 0;
+__global__ __launch_bounds__(kBlock) void k_bv_scan(BvScan a) {
+    __shared__ long long tmp[kBlock / 64 + 1];
+    const int b = blockIdx.x, first = b < a.nbt ? 0 : a.nbt;
+    long long bx = 0, by = 0;  // sums of the earlier blocks of the same list
+    for (int q = first + threadIdx.x; q < b; q += kBlock) {
+        bx += a.bsum[q];
+        by += a.bsum2[q];
+    }
+    long long x[kBvPer], y[kBvPer], sx = 0, sy = 0, tx, ty;
+    bv_items(a, b, x, y);
+#pragma unroll
+    for (int u = 0; u < kBvPer; ++u) {
+        sx += x[u];
+        sy += y[u];
+    }
+    (void)wg_excl_scan64<kBlock>(bx, tmp, tx);
+    (void)wg_excl_scan64<kBlock>(by, tmp, ty);
+    long long tot;
+    long long rx = tx + wg_excl_scan64<kBlock>(sx, tmp, tot);
+    long long ry = ty + wg_excl_scan64<kBlock>(sy, tmp, tot);
+#pragma unroll
+    for (int u = 0; u < kBvPer; ++u) {
+        if (b < a.nbt) {
+            const int t = b * kBvBlock + threadIdx.x * kBvPer + u;
+            if (t < a.nnzb) a.pofs[t] = rx;
         } else {
-            dst[base + u] = (uint32_t)(lo - c0);
+            const int k = (b - a.nbt) * kBvBlock + threadIdx.x * kBvPer + u;
+            if (k < a.nrows) {
+                a.wbase[k] = rx;
+                a.rowptr[k] = (int32_t)ry;
+                if (k == a.nrows - 1) a.rowptr[a.nrows] = (int32_t)(ry + y[u]);
+            }
         }
+        rx += x[u];
+        ry += y[u];
+    }
+}
+
+// each row's entries in arrival order
+__global__ __launch_bounds__(kBlock) void k_bv_fill(Prob p, const int32_t *rowptr,
+                                                    const int32_t *arrival, int32_t *pos) {
+    const int t = blockIdx.x * kBlock + threadIdx.x;
+    if (t < p.nnzb) pos[rowptr[p.bri[t]] + arrival[t]] = t;
+}
+
+// Blocks [0, nbt): every B entry's rank in its row by ascending column (the
+// entries before it in B's storage, counted in the row's list: by its thread,
+// or for rows above kBvCount entries by the whole wavefront), the row's sorted
+// entries and the entry's terms of dA. The others: every A entry's terms.
+constexpr int kBvCount = 64;
+__global__ __launch_bounds__(kBlock) void k_bv_rank(Prob p, const int32_t *rowptr,
+                                                    const int32_t *pos, const long long *wbase,
+                                                    int nbt, int32_t *rowent, long long *woff,
+                                                    int4 *aview) {
+    if ((int)blockIdx.x < nbt) {
+        const int t = blockIdx.x * kBlock + threadIdx.x;
+        const int k = t < p.nnzb ? p.bri[t] : -1;
+        const int b = k >= 0 ? rowptr[k] : 0, e = k >= 0 ? rowptr[k + 1] : 0;
+        int rank = 0;
+        if (e - b <= kBvCount)
+            for (int r = b; r < e; ++r) rank += pos[r] < t ? 1 : 0;
+        for (unsigned long long m = ballot(e - b > kBvCount); m; m &= m - 1) {
+            const int src = __builtin_ctzll(m);
+            const int bt = __builtin_amdgcn_readlane(t, src);
+            const int bb = __builtin_amdgcn_readlane(b, src);
+            const int be = __builtin_amdgcn_readlane(e, src);
+            int n = 0;
+            for (int r = bb + lane_id(); r < be; r += 64) n += pos[r] < bt ? 1 : 0;
+            n = wave_sum(n);
+            if (lane_id() == src) rank = n;
+        }
+        if (k < 0) return;
+        rowent[b + rank] = t;
+        woff[t] = wbase[k] + (long long)rank * (p.acp[k + 1] - p.acp[k]);
+    } else {
+        const int q = (blockIdx.x - nbt) * kBlock + threadIdx.x;
+        if (q >= p.nnza) return;
+        const int k = column_of(p.acp, p.k, q);
+        const long long base = wbase[k] + (q - p.acp[k]);
+        aview[q] = make_int4((int)(unsigned)base, (int)(unsigned)((unsigned long long)base >> 32),
+                             rowptr[k + 1] - rowptr[k], p.acp[k + 1] - p.acp[k]);
+    }
+}
+
+// the place of every product's row among C's entries (C's columns ascend: a
+// binary search), products taken as in the first pass
+__global__ __launch_bounds__(64) void k_bv_gpos(Prob p, const int2 *__restrict__ E,
+                                                const long long *__restrict__ pofs,
+                                                const int32_t *__restrict__ cri, long long nnzc,
+                                                uint32_t *__restrict__ gpos, int *err) {
+    __shared__ unsigned bits[kBwN / 32];
+    __shared__ int s_q[64], s_lo[64], s_hi[64];
+    const int lane = threadIdx.x;
+    const int t = blockIdx.x * 64 + lane;
+    const long long p0 = pofs[blockIdx.x * 64];
+    int2 e = make_int2(0, 0);
+    int c0 = 0, c1 = 0;
+    if (t < p.nnzb) {
+        e = E[t];
+        const int j = column_of(p.bcp, p.n, t);
+        c0 = p.ccp[j];
+        c1 = p.ccp[j + 1];
+        if (c0 < 0 || c1 < c0 || c1 > nnzc) c0 = c1 = 0;
+    }
+    const long long inc = wave_incl_scan64(e.y), o = inc - e.y, total = wave_last64(inc);
+    int bad = 0;
+    for (long long b0 = 0; b0 < total; b0 += kBwN) {
+        const Chunk c = chunk_of(b0, total, o, e.y, bits, lane);
+        if (c.hi > c.lo) {
+            s_q[c.rank] = e.x + (int)(b0 - o);
+            s_lo[c.rank] = c0;
+            s_hi[c.rank] = c1;
+        }
+        bw_sync();
+        int rk[kBwKpl], row[kBwKpl], lo[kBwKpl], hi[kBwKpl], end[kBwKpl];
+        ranks_of(bits, rk);
+#pragma unroll
+        for (int r = 0; r < kBwKpl; ++r) {
+            const int q = r * 64 + lane;
+            const bool in = q < c.n;
+            row[r] = in ? p.ari[s_q[rk[r]] + q] : 0;
+            lo[r] = in ? s_lo[rk[r]] : 0;
+            hi[r] = end[r] = in ? s_hi[rk[r]] : 0;
+        }
+        for (bool more = true; more;) {  // first position whose row is not below `row`
+            int mid[kBwKpl], x[kBwKpl];
+#pragma unroll
+            for (int r = 0; r < kBwKpl; ++r) {
+                mid[r] = lo[r] + ((hi[r] - lo[r]) >> 1);
+                x[r] = lo[r] < hi[r] ? cri[mid[r]] : 0;
+            }
+            bool any = false;
+#pragma unroll
+            for (int r = 0; r < kBwKpl; ++r) {
+                if (lo[r] < hi[r]) {
+                    if (x[r] < row[r]) lo[r] = mid[r] + 1;
+                    else hi[r] = mid[r];
+                }
+                any |= lo[r] < hi[r];
+            }
+            more = ballot(any) != 0;
+        }
+#pragma unroll
+        for (int r = 0; r < kBwKpl; ++r) {
+            const int q = r * 64 + lane;
+            if (q >= c.n) continue;
+            const bool ok = lo[r] < end[r] && cri[lo[r]] == row[r];
+            bad |= !ok;  // C does not hold the product's row
+            gpos[p0 + b0 + q] = ok ? (uint32_t)lo[r] : 0u;
+        }
+        bw_sync();
     }
     if (bad) atomicOr(err, ERR_CSC);
 }
 
-hipError_t launch_bw_dst(const Prob &p, const int2 *E, const long long *pofs, const int32_t *bcol,
-                         const int32_t *cri, uint32_t *dst, int *err, hipStream_t s) {
-    if (p.nnzb <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bv_dst, dim3(ceil_div(p.nnzb, kBlock)), dim3(kBlock), 0, s, p, E, pofs,
-                       bcol, cri, dst, err);
-    return hipGetLastError();
-}
+}  // namespace
 
 // ---------------------------------------------------------------- launchers
-hipError_t launch_bw_view(const Prob &p, const int2 *E, const BwBuild &b, BwView &w,
-                          hipStream_t s) {
+int bw_scan_blocks(int nnzb, int nrows) { return ceil_div(nnzb, kBvBlock) + ceil_div(nrows, kBvBlock); }
+
+hipError_t launch_bw_view(const Prob &p, const BwView &v, const BwBuild &b, const int32_t *cri,
+                          int *err, hipStream_t s) {
     const int nrows = p.k;  // rows of B
-    hipError_t e = hipMemsetAsync(b.rowptr, 0, sizeof(int32_t) * (size_t)(nrows + 1), s);
-    if (e != hipSuccess) return e;
-    e = hipMemsetAsync(b.fill, 0, sizeof(int32_t) * (size_t)(nrows > 0 ? nrows : 1), s);
-    if (e != hipSuccess) return e;
-    const int gb = ceil_div(p.nnzb, kBlock);
-    if (gb > 0)
-        hipLaunchKernelGGL(k_bv_bent, dim3(gb), dim3(kBlock), 0, s, p, E, b.bcol, b.cb, b.len,
-                           b.rowptr);
-    if (p.nnza > 0)
-        hipLaunchKernelGGL(k_bv_aent, dim3(ceil_div(p.nnza, kBlock)), dim3(kBlock), 0, s, p,
-                           b.aview);
-    e = launch_scan_i32(b.rowptr, nrows + 1, b.scratch, b.nscratch, b.rowptr, s);
-    if (e != hipSuccess) return e;
-    e = launch_scan_i64(b.len, p.nnzb, b.scratch2, b.nscratch2, b.pofs, s);
-    if (e != hipSuccess) return e;
-    if (gb > 0)
-        hipLaunchKernelGGL(k_bv_fill, dim3(gb), dim3(kBlock), 0, s, p, (const int32_t *)b.rowptr,
-                           (const int32_t *)b.bcol, b.fill, b.colj, b.pos);
-    if (nrows > 0)
-        hipLaunchKernelGGL(k_bv_sort, dim3(ceil_div(nrows, kBlock)), dim3(kBlock), 0, s, nrows,
-                           (const int32_t *)b.rowptr, b.colj, b.pos);
-    if (gb > 0)
-        hipLaunchKernelGGL(k_bv_pack, dim3(gb), dim3(kBlock), 0, s, p.nnzb,
-                           (const int32_t *)b.pos, (const int32_t *)b.cb,
-                           (const long long *)b.pofs, b.rv, b.rvp);
-    w.E = E;
-    w.dst = b.dst;
-    w.pofs = b.pofs;
-    w.cb = b.cb;
-    w.aview = b.aview;
-    w.rowptr = b.rowptr;
-    w.rv = b.rv;
-    w.rvp = b.rvp;
+    hipError_t e;
+    // counts and the error word lie together
+    if ((e = hipMemsetAsync(b.cnt, 0, b.clear_bytes, s))) return e;
+    const int gt = ceil_div(p.nnzb, kBlock), ga = ceil_div(p.nnza, kBlock);
+    if (gt > 0) hipLaunchKernelGGL(k_bv_count, dim3(gt), dim3(kBlock), 0, s, p, b.cnt, b.arrival);
+    BvScan sc{v.E, p.nnzb, nrows, ceil_div(p.nnzb, kBvBlock), b.cnt, p.acp,
+              b.bsum, b.bsum2, b.pofs, b.wbase, b.rowptr};
+    if (const int nb = bw_scan_blocks(p.nnzb, nrows)) {
+        hipLaunchKernelGGL(k_bv_sums, dim3(nb), dim3(kBlock), 0, s, sc);
+        hipLaunchKernelGGL(k_bv_scan, dim3(nb), dim3(kBlock), 0, s, sc);
+    }
+    if (gt > 0)
+        hipLaunchKernelGGL(k_bv_fill, dim3(gt), dim3(kBlock), 0, s, p, (const int32_t *)b.rowptr,
+                           (const int32_t *)b.arrival, b.pos);
+    if (gt + ga > 0)
+        hipLaunchKernelGGL(k_bv_rank, dim3(gt + ga), dim3(kBlock), 0, s, p,
+                           (const int32_t *)b.rowptr, (const int32_t *)b.pos,
+                           (const long long *)b.wbase, gt, b.rowent, b.woff, b.aview);
+    if (p.nnzb > 0)
+        hipLaunchKernelGGL(k_bv_gpos, dim3(ceil_div(p.nnzb, 64)), dim3(64), 0, s, p, v.E,
+                           (const long long *)b.pofs, cri, v.nnzc, b.gpos, err);
     return hipGetLastError();
 }
 
-hipError_t launch_backward(const Prob &p, const BwView &w, bool f64, const void *av,
+template <typename V>
+static hipError_t run_backward(const Prob &p, const BwView &v, void *terms, const V *av,
+                               const V *bv, const V *gv, V *da, V *db, int *err, hipStream_t s) {
+    V *w = da ? (V *)terms : nullptr;
+    if (p.nnzb > 0 && (db || w))
+        hipLaunchKernelGGL(k_grad_b<V>, dim3(ceil_div(p.nnzb, 64)), dim3(64), 0, s, v, p.nnzb, av,
+                           bv, gv, db, w, err);
+    if (da && p.nnza > 0) {
+        const dim3 g(ceil_div(p.nnza, kBlock)), t(kBlock);
+        if (terms)
+            hipLaunchKernelGGL(k_grad_a<V>, g, t, 0, s, v.aview, p.nnza, (const V *)w, da);
+        else
+            hipLaunchKernelGGL(k_grad_a_gather<V>, g, t, 0, s, v, p, p.nnza, bv, gv, da, err);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_backward(const Prob &p, const BwView &v, void *terms, bool f64, const void *av,
                            const void *bv, const void *gv, void *da, void *db, int *err,
                            hipStream_t s) {
-    const int nbw = (db && p.nnzb > 0) ? ceil_div(p.nnzb, kBlock) : 0;
-    const int naw = (da && p.nnza > 0) ? ceil_div(p.nnza, kBlock) : 0;
-    if (nbw + naw == 0) return hipSuccess;
     if (f64)
-        hipLaunchKernelGGL(k_grad<double>, dim3(nbw + naw), dim3(kBlock), 0, s, w, p.nnza, p.nnzb,
-                           nbw, (const double *)av, (const double *)bv, (const double *)gv,
-                           (double *)da, (double *)db, err);
-    else
-        hipLaunchKernelGGL(k_grad<float>, dim3(nbw + naw), dim3(kBlock), 0, s, w, p.nnza, p.nnzb,
-                           nbw, (const float *)av, (const float *)bv, (const float *)gv,
-                           (float *)da, (float *)db, err);
-    return hipGetLastError();
+        return run_backward<double>(p, v, terms, (const double *)av, (const double *)bv,
+                                    (const double *)gv, (double *)da, (double *)db, err, s);
+    return run_backward<float>(p, v, terms, (const float *)av, (const float *)bv,
+                               (const float *)gv, (float *)da, (float *)db, err, s);
 }
 
 }  // namespace spg

@@ -841,57 +841,7 @@ __global__ __launch_bounds__(kBlock) void k_prod_down(KArgs a, const long long *
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) a.colprod[n] = o.block_end;
 }
 
-// generic exclusive scan of int32 values into int32 (in place allowed)
-__global__ __launch_bounds__(kBlock) void k_scan_down_i32(const int32_t *in, int n,
-                                                          const long long *__restrict__ bsum,
-                                                          int32_t *out) {
-    __shared__ long long s[2 * kBlock / 64];
-    ScanOut o;
-    block_scan_down(in, n, bsum, s, o);
-    __syncthreads();  // every block element is read before any is written (in place)
-#pragma unroll
-    for (int u = 0; u < ScanOut::PER; ++u) {
-        const int i = blockIdx.x * kScanBlock + threadIdx.x * ScanOut::PER + u;
-        if (i < n) out[i] = (int32_t)o.pre[u];
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_scan_down_i64(const int32_t *in, int n,
-                                                          const long long *__restrict__ bsum,
-                                                          long long *out) {
-    __shared__ long long s[2 * kBlock / 64];
-    ScanOut o;
-    block_scan_down(in, n, bsum, s, o);
-#pragma unroll
-    for (int u = 0; u < ScanOut::PER; ++u) {
-        const int i = blockIdx.x * kScanBlock + threadIdx.x * ScanOut::PER + u;
-        if (i < n) out[i] = o.pre[u];
-    }
-}
-
 // ---------------------------------------------------------------- launchers
-hipError_t launch_scan_i32(const int32_t *in, int n, long long *bsum, int nbsum, int32_t *out,
-                           hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int nblk = ceil_div(n, kScanBlock);
-    if (nblk > nbsum) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(kBlock), 0, s, in, n, bsum);
-    hipLaunchKernelGGL(k_scan_down_i32, dim3(nblk), dim3(kBlock), 0, s, in, n,
-                       (const long long *)bsum, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_scan_i64(const int32_t *in, int n, long long *bsum, int nbsum, long long *out,
-                           hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int nblk = ceil_div(n, kScanBlock);
-    if (nblk > nbsum) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(kBlock), 0, s, in, n, bsum);
-    hipLaunchKernelGGL(k_scan_down_i64, dim3(nblk), dim3(kBlock), 0, s, in, n,
-                       (const long long *)bsum, out);
-    return hipGetLastError();
-}
-
 hipError_t launch_prod_offsets(const KArgs &a, long long *bsum, int nbsum, hipStream_t s) {
     if (a.ncols <= 0) return hipSuccess;
     const int nblk = ceil_div(a.ncols, kScanBlock);

@@ -136,8 +136,8 @@ struct spgemm_plan_s {
     static constexpr int kSide = SideSet::kSide;
     SideSet sides;
 
-    // backward: row view of B
-    DevBuf bt;
+    // backward: the view, and one value per product (the terms of dA)
+    DevBuf bt, terms;
     bool bt_ready = false;
     int *bt_err = nullptr;
 
@@ -409,6 +409,17 @@ hipError_t order_after(spgemm_plan p, hipStream_t later, hipStream_t earlier) {
     hipError_t e = hipEventRecord(p->order_ev, earlier);
     if (e != hipSuccess) return e;
     return hipStreamWaitEvent(later, p->order_ev, 0);
+}
+
+// Work queued on s from now on comes after the plan's earlier work. (A stream
+// being captured cannot wait for work outside its graph: there the caller
+// keeps the plan's other work apart from the graph's replays.)
+hipError_t order_plan(spgemm_plan p, hipStream_t s) {
+    if (p->last_stream == s) return hipSuccess;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(s, &st);
+    if (e != hipSuccess || st != hipStreamCaptureStatusNone) return e;
+    return order_after(p, s, p->last_stream);
 }
 
 // Releases b (its last use is ordered before the end of stream `s`).
@@ -1328,6 +1339,7 @@ spgemm_status run_symbolic(spgemm_plan p, hipStream_t s, const std::vector<int4>
 }
 
 spgemm_status run_numeric(spgemm_plan p, hipStream_t s) {
+    if (!p->use_arena) SPG_TRY(order_plan(p, s));
     const KArgs a = make_args(p);
     SPG_TRY(launch_numeric_phase(p, a, s));
     p->last_stream = s;
@@ -1587,72 +1599,63 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
     q.av = A_val;
     q.bv = B_val;
     const bool f64 = p->dt == SPGEMM_F64;
-    // the backward view (per B entry, per A entry, row view of B), its
+    // the view and the terms' space belong to the plan: its earlier work,
+    // possibly on another stream, comes first
+    SPG_TRY(order_plan(p, s));
+    // the backward view (per B entry, per A entry, rows of B), its
     // construction temporaries, scan partials and an error word
-    const size_t k = (size_t)q.k, nb = (size_t)std::max(q.nnzb, 1),
+    const size_t k = (size_t)std::max(q.k, 1), nb = (size_t)std::max(q.nnzb, 1),
                  na = (size_t)std::max(q.nnza, 1);
-    const int nbs = ceil_div((int)k + 1, kScanBlock) + 2;
-    const int nbs2 = ceil_div((int)nb, kScanBlock) + 2;
+    const size_t products = (size_t)std::max<unsigned long long>(p->hdr_host.total_op, 1);
+    const size_t blocks = (size_t)std::max(bw_scan_blocks(q.nnzb, q.k), 1);
     size_t off = 0;
     auto carve = [&](size_t bytes) {
         const size_t o = off;
         off += align_up(bytes, 256);
         return o;
     };
-    const size_t o_pofs = carve(8 * nb), o_cb = carve(4 * nb), o_aview = carve(8 * na),
-                 o_rowptr = carve(4 * (k + 1)), o_rv = carve(8 * nb), o_rvp = carve(8 * nb),
-                 o_fill = carve(4 * std::max<size_t>(k, 1)), o_colj = carve(4 * nb),
-                 o_pos = carve(4 * nb), o_bcol = carve(4 * nb), o_len = carve(4 * nb),
-                 o_scr = carve(8 * (size_t)nbs), o_scr2 = carve(8 * (size_t)nbs2),
-                 o_err = carve(sizeof(int)),
-                 o_dst = carve(4 * (size_t)std::max<unsigned long long>(p->hdr_host.total_op, 1));
-    const size_t need = off;
+    const size_t o_pofs = carve(8 * nb), o_woff = carve(8 * nb), o_aview = carve(16 * na),
+                 o_rowptr = carve(4 * (k + 1)), o_rowent = carve(4 * nb),
+                 o_cnt = carve(4 * (k + 1)), o_arrival = carve(4 * nb), o_pos = carve(4 * nb),
+                 o_wbase = carve(8 * k), o_bsum = carve(8 * blocks), o_bsum2 = carve(8 * blocks),
+                 o_gpos = carve(4 * products);
+    const size_t need = off, terms_need = (f64 ? 8 : 4) * products;
     if (need > p->bt.bytes) {
         p->bt_ready = false;
-        SPG_TRY(order_after(p, s, p->last_stream));
         if (spgemm_status st = dev_alloc(p, p->bt, need, s)) return st;
     }
+    // without this space dA gathers G a second time
+    if (!p->bt_ready && terms_need > p->terms.bytes) (void)dev_alloc(p, p->terms, terms_need, s);
+    void *terms = p->terms.bytes >= terms_need ? p->terms.ptr : nullptr;
     char *b = (char *)p->bt.ptr;
     BwBuild bb{};
     bb.pofs = (long long *)(b + o_pofs);
-    bb.cb = (int32_t *)(b + o_cb);
-    bb.aview = (int2 *)(b + o_aview);
+    bb.woff = (long long *)(b + o_woff);
+    bb.aview = (int4 *)(b + o_aview);
     bb.rowptr = (int32_t *)(b + o_rowptr);
-    bb.rv = (int2 *)(b + o_rv);
-    bb.rvp = (long long *)(b + o_rvp);
-    bb.fill = (int32_t *)(b + o_fill);
-    bb.colj = (int32_t *)(b + o_colj);
+    bb.rowent = (int32_t *)(b + o_rowent);
+    bb.cnt = (int32_t *)(b + o_cnt);
+    bb.clear_bytes = 4 * (k + 1);
+    bb.arrival = (int32_t *)(b + o_arrival);
     bb.pos = (int32_t *)(b + o_pos);
-    bb.bcol = (int32_t *)(b + o_bcol);
-    bb.len = (int32_t *)(b + o_len);
-    bb.scratch = (long long *)(b + o_scr);
-    bb.nscratch = nbs;
-    bb.scratch2 = (long long *)(b + o_scr2);
-    bb.nscratch2 = nbs2;
-    bb.dst = (uint32_t *)(b + o_dst);
-    p->bt_err = (int *)(b + o_err);
-    BwView w{};
-    w.E = p->E;
-    w.dst = bb.dst;
-    w.nnzc = p->totals_host[0];
-    w.pofs = bb.pofs;
-    w.cb = bb.cb;
-    w.aview = bb.aview;
-    w.rowptr = bb.rowptr;
-    w.rv = bb.rv;
-    w.rvp = bb.rvp;
+    bb.wbase = (long long *)(b + o_wbase);
+    bb.bsum = (long long *)(b + o_bsum);
+    bb.bsum2 = (long long *)(b + o_bsum2);
+    bb.gpos = (uint32_t *)(b + o_gpos);
+    p->bt_err = (int *)(b + o_cnt) + k;
+    const BwView w{p->E, bb.gpos, p->totals_host[0], bb.pofs, bb.woff, bb.aview, bb.rowptr,
+                   bb.rowent};
     if (!p->bt_ready) {
         // the error word is cleared with the view only: later calls queue no
         // memset, so they can be captured in a HIP graph
-        SPG_TRY(hipMemsetAsync(p->bt_err, 0, sizeof(int), s));
         ProfScope ps("bw_view", s);
-        SPG_TRY(launch_bw_view(q, p->E, bb, w, s));
-        SPG_TRY(launch_bw_dst(q, p->E, bb.pofs, bb.bcol, C_rowidx, bb.dst, p->bt_err, s));
+        SPG_TRY(launch_bw_view(q, w, bb, C_rowidx, p->bt_err, s));
         p->bt_ready = true;
     }
     {
         ProfScope ps("gradients", s);
-        SPG_TRY(launch_backward(q, w, f64, A_val, B_val, G_val, dA_val, dB_val, p->bt_err, s));
+        SPG_TRY(launch_backward(q, w, terms, f64, A_val, B_val, G_val, dA_val, dB_val, p->bt_err,
+                                s));
     }
     p->last_stream = s;
     return SPGEMM_OK;
@@ -1743,6 +1746,7 @@ void spgemm_plan_destroy(spgemm_plan p) {
     dev_free(p, p->stage, s);
     dev_free(p, p->ws, s);
     dev_free(p, p->bt, s);
+    dev_free(p, p->terms, s);
     dev_free(p, p->lbuf, s);
     (void)hipStreamSynchronize(s);
     release_sides(p->sides);
