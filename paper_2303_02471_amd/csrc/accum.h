@@ -1,0 +1,1208 @@
+// Direct-gather accumulators (kernels and their launchers, for one problem
+// or, MULTI, a batch): expand-sort-compress (Section 4) of every output
+// column, with the column's products gathered straight from A through its
+// stored B entries, in two modes sharing one code path:
+//   COUNT  (symbolic phase): the number of distinct rows of every column;
+//   FILL   (numeric phase):  the rows in ascending order and their values,
+//          each summed in Algorithm 1's order (B's stored order, starting from
+//          zero, every product and sum rounded on its own), written
+//          contiguously at the column's place in C.
+// Nothing per product is kept between the phases.
+//
+// Wave buffer. A wavefront holds N = 64 KPL positions, KPL consecutive
+// positions per lane (position s = KPL lane + r in register r). The columns of
+// a work item occupy aligned segments of S positions; a column's products fill
+// its segment in the order Algorithm 1 meets them (stored B entries in storage
+// order, then the rows of the selected A column in storage order), the rest of
+// the segment is padding that sorts last.
+//
+// Gather. A product's address in A is (start of its entry's A column) +
+// (its position) - (the entry's first position). The wave writes, at the first
+// position of every stored B entry, that difference and the entry's B value
+// (a "head"); every other position takes the head before it (a forward fill,
+// first inside each lane's registers, then across lanes by a shuffle scan).
+// All of a lane's loads of A are then independent and issued together.
+//
+// Sort and compress. Keys (row << 11 | position) are sorted inside every
+// segment by a bitonic network on registers (distances below KPL) and lanes
+// (DPP, ds_swizzle, ds_bpermute). Equal rows form runs whose positions are in
+// Algorithm 1's order; a run's head adds the run's values in that order.
+//
+// Heavy columns (more products than a wave buffer holds) are cut into row
+// windows of equal span, each an independent wave work item that compacts the
+// window's products (from a per-column expansion into a scratch area) into its
+// buffer; a window that still overflows is halved in row span.
+#pragma once
+
+#include <climits>
+
+#include "devutil.h"
+
+namespace spg {
+
+constexpr int kKeyBits = 11;          // position bits of a key (N <= 2048)
+constexpr int kHeavyBin = BIN_SORT2;  // first bin of the heavy columns (above 1024 products)
+constexpr int kHeadNone = INT_MIN;    // no head at this position
+
+// Device memory that no launch changes while this one runs (the header's bin
+// positions, the problem table): read through the scalar cache, one load for
+// the wavefront. The header's error words sit beside the positions; a flag
+// raised while a kernel runs stops the kernels after it.
+template <typename T>
+using cmem = const __attribute__((address_space(4))) T;
+
+struct BinRange {
+    int first, count;  // positions in the bin list
+    bool stop;         // an error (or, filling, too small a C): nothing to do
+};
+template <bool FILL>
+__device__ __forceinline__ BinRange bin_range(const KArgs &a, int b0, int b1) {
+    cmem<Hdr> *h = (cmem<Hdr> *)a.hdr;
+    const int first = h->bin_start[b0], last = h->bin_start[b1] + h->bin_count[b1];
+    return {first, last - first, (h->err | (FILL ? h->cap_over : 0)) != 0};
+}
+
+// Problem of global column g (the same in every lane): a single problem's
+// arguments lie in scalar registers, a batch's in the device table.
+template <bool MULTI>
+__device__ __forceinline__ Prob prob_of(const KArgs &a, int g) {
+    if constexpr (!MULTI) {
+        return a.single;
+    } else {
+        cmem<int32_t> *c = (cmem<int32_t> *)a.col0s;
+        const int gu = __builtin_amdgcn_readfirstlane(g);
+        int lo = 0, hi = a.nprob;  // last problem that starts at or before g
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (c[mid] <= gu) lo = mid;
+            else hi = mid;
+        }
+        cmem<Prob> *t = (cmem<Prob> *)a.table + lo;
+        Prob d;
+        d.m = t->m; d.k = t->k; d.n = t->n; d.col0 = t->col0;
+        d.nnza = t->nnza; d.nnzb = t->nnzb; d.ebase = t->ebase;
+        d.acp = t->acp; d.ari = t->ari; d.av = t->av;
+        d.bcp = t->bcp; d.bri = t->bri; d.bv = t->bv;
+        d.ccp = t->ccp; d.cri = t->cri; d.cv = t->cv;
+        return d;
+    }
+}
+
+__device__ __forceinline__ void wsync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <typename K>
+struct KeyTraits;
+template <>
+struct KeyTraits<unsigned> {
+    static constexpr unsigned kmax = ~0u;
+};
+template <>
+struct KeyTraits<unsigned long long> {
+    static constexpr unsigned long long kmax = ~0ull;
+};
+
+// value of `v` in the lane `d` below (lanes below d read their own)
+__device__ __forceinline__ int shfl_up_i(int v, int d) {
+    const int l = lane_id();
+    return __builtin_amdgcn_ds_bpermute((l >= d ? l - d : l) << 2, v);
+}
+
+// Median of three unsigned 32-bit values where c is 0 (the smaller of x and
+// y) or all ones (the larger): one v_med3_u32 takes a compare-exchange's side
+// chosen per lane.
+// (Written as the instruction itself: spelled as min and max, the network's
+// chains of them send the compiler's combiner into a very long search.)
+__device__ __forceinline__ unsigned med3u(unsigned x, unsigned y, unsigned c) {
+    unsigned r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(c));
+    return r;
+}
+
+// compare-exchange of two registers of one lane
+__device__ __forceinline__ void minmax(unsigned &lo, unsigned &hi) {
+    unsigned a, b;
+    asm("v_min_u32 %0, %2, %3\n\tv_max_u32 %1, %2, %3" : "=&v"(a), "=v"(b) : "v"(lo), "v"(hi));
+    lo = a;
+    hi = b;
+}
+__device__ __forceinline__ void minmax(unsigned long long &lo, unsigned long long &hi) {
+    const bool sw = lo > hi;
+    const unsigned long long a = sw ? hi : lo, b = sw ? lo : hi;
+    lo = a;
+    hi = b;
+}
+
+// Four registers of a cross-lane stage whose exchange is a DPP move: each
+// register takes the median of itself, the other lane's register (its own
+// number, or with `flip` the mirrored one) and c. The moves, the wait that
+// DPP reads need after a VALU write and the medians are one block: the
+// compiler does not see the medians' writes as a hazard for its own moves.
+#define SPG_DPP_BLOCK(CTRL, S0, S1, S2, S3)                                    \
+    asm volatile(                                                              \
+        "s_nop 1\n\t"                                                          \
+        "v_mov_b32_dpp %4, " S0 " " CTRL " row_mask:0xf bank_mask:0xf\n\t"     \
+        "v_mov_b32_dpp %5, " S1 " " CTRL " row_mask:0xf bank_mask:0xf\n\t"     \
+        "v_mov_b32_dpp %6, " S2 " " CTRL " row_mask:0xf bank_mask:0xf\n\t"     \
+        "v_mov_b32_dpp %7, " S3 " " CTRL " row_mask:0xf bank_mask:0xf\n\t"     \
+        "v_med3_u32 %0, %0, %4, %8\n\t"                                        \
+        "v_med3_u32 %1, %1, %5, %8\n\t"                                        \
+        "v_med3_u32 %2, %2, %6, %8\n\t"                                        \
+        "v_med3_u32 %3, %3, %7, %8"                                            \
+        : "+v"(k0), "+v"(k1), "+v"(k2), "+v"(k3), "=&v"(t0), "=&v"(t1),        \
+          "=&v"(t2), "=&v"(t3)                                                 \
+        : "v"(c))
+
+template <int MASK, bool FLIP>
+__device__ __forceinline__ void dpp_block(unsigned &k0, unsigned &k1, unsigned &k2, unsigned &k3,
+                                          unsigned c) {
+    unsigned t0, t1, t2, t3;
+    if constexpr (MASK == 1 && FLIP) SPG_DPP_BLOCK("quad_perm:[1,0,3,2]", "%3", "%2", "%1", "%0");
+    else if constexpr (MASK == 1) SPG_DPP_BLOCK("quad_perm:[1,0,3,2]", "%0", "%1", "%2", "%3");
+    else if constexpr (MASK == 2) SPG_DPP_BLOCK("quad_perm:[2,3,0,1]", "%0", "%1", "%2", "%3");
+    else if constexpr (MASK == 3) SPG_DPP_BLOCK("quad_perm:[3,2,1,0]", "%3", "%2", "%1", "%0");
+    else if constexpr (MASK == 7) SPG_DPP_BLOCK("row_half_mirror", "%3", "%2", "%1", "%0");
+    else if constexpr (MASK == 15) SPG_DPP_BLOCK("row_mirror", "%3", "%2", "%1", "%0");
+    else SPG_DPP_BLOCK("row_ror:8", "%0", "%1", "%2", "%3");  // exchange at distance 8
+}
+#undef SPG_DPP_BLOCK
+
+// One compare-exchange stage across lanes: with the lane whose number differs
+// in the bits of MASK, register r against register r, or (FLIP) KPL - 1 - r.
+// The lane with the highest differing bit clear keeps the smaller keys.
+template <typename K, int KPL, int MASK, bool FLIP>
+__device__ __forceinline__ void lane_stage(K (&key)[KPL], int lane) {
+    constexpr int TOP = FLIP ? (MASK + 1) / 2 : MASK;
+    if constexpr (sizeof(K) == 4) {
+        // all ones in the lanes with the bit set, else 0
+        const unsigned c = (unsigned)(((int)((unsigned)lane << (31 - __builtin_ctz(TOP)))) >> 31);
+        if constexpr (MASK <= 3 || MASK == 7 || MASK == 8 || MASK == 15) {
+            static_assert(KPL % 4 == 0, "the exchange blocks take four registers");
+#pragma unroll
+            for (int r = 0; r < KPL / 2; r += 2) {
+                if constexpr (FLIP)
+                    dpp_block<MASK, true>(key[r], key[r + 1], key[KPL - 2 - r], key[KPL - 1 - r], c);
+                else
+                    dpp_block<MASK, false>(key[2 * r], key[2 * r + 1], key[2 * r + 2],
+                                           key[2 * r + 3], c);
+            }
+        } else {
+            unsigned o[KPL];
+#pragma unroll
+            for (int r = 0; r < KPL; ++r)
+                o[r] = (unsigned)shfl_xor_c<MASK>((int)key[FLIP ? KPL - 1 - r : r]);
+#pragma unroll
+            for (int r = 0; r < KPL; ++r) key[r] = med3u(key[r], o[r], c);
+        }
+    } else {
+        const bool take_max = (lane & TOP) != 0;
+        K o[KPL];
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) o[r] = shfl_xor_c64<MASK>(key[FLIP ? KPL - 1 - r : r]);
+#pragma unroll
+        for (int r = 0; r < KPL; ++r)
+            key[r] = (key[r] < o[r]) != take_max ? key[r] : o[r];
+    }
+}
+
+// Every aligned segment of S positions sorted ascending, position KPL lane + r
+// in register r. Bitonic merges whose first stage compares a position with
+// its mirror image in the merge (so every merge and every stage is ascending,
+// a register exchange is one min and one max, and the first stage of a merge
+// of 2, 4, 8 or 16 lanes is a DPP move).
+template <typename K, int KPL, int S>
+__device__ __forceinline__ void seg_sort(K (&key)[KPL], int lane_in) {
+    // The masks below depend on the lane only: an opaque copy of the lane
+    // number keeps them from being computed once outside the caller's loop
+    // and held in registers for the whole kernel.
+    int lane = lane_in;
+    asm volatile("" : "+v"(lane));
+#pragma unroll
+    for (int k = 2; k <= S; k <<= 1) {
+        if (k <= KPL) {
+#pragma unroll
+            for (int r = 0; r < KPL; ++r)
+                if ((r & (k - 1)) < k / 2) minmax(key[r], key[r ^ (k - 1)]);
+        } else {
+            switch (k / KPL) {
+                case 2: lane_stage<K, KPL, 1, true>(key, lane); break;
+                case 4: lane_stage<K, KPL, 3, true>(key, lane); break;
+                case 8: lane_stage<K, KPL, 7, true>(key, lane); break;
+                case 16: lane_stage<K, KPL, 15, true>(key, lane); break;
+                case 32: lane_stage<K, KPL, 31, true>(key, lane); break;
+                default: lane_stage<K, KPL, 63, true>(key, lane); break;
+            }
+        }
+#pragma unroll
+        for (int j = k >> 2; j > 0; j >>= 1) {
+            if (j < KPL) {
+#pragma unroll
+                for (int r = 0; r < KPL; ++r)
+                    if (!(r & j)) minmax(key[r], key[r | j]);
+            } else {
+                switch (j / KPL) {
+                    case 1: lane_stage<K, KPL, 1, false>(key, lane); break;
+                    case 2: lane_stage<K, KPL, 2, false>(key, lane); break;
+                    case 4: lane_stage<K, KPL, 4, false>(key, lane); break;
+                    case 8: lane_stage<K, KPL, 8, false>(key, lane); break;
+                    default: lane_stage<K, KPL, 16, false>(key, lane); break;
+                }
+            }
+        }
+    }
+    // the caller's first move across lanes reads the last register, whose
+    // write (inside an asm block) the compiler does not count as a hazard
+    if constexpr (sizeof(K) == 4) asm volatile("s_nop 1" : "+v"(key[KPL - 1]), "+v"(key[0]));
+}
+
+// ---------------------------------------------------------------- one buffer
+// LDS of one wavefront: head offsets, then staged output rows (key), and head
+// values, then the products by slot, then staged output values (val).
+template <typename K, typename V, int N, bool FILL>
+struct WaveLds {
+    K key[N];
+    V val[FILL ? N : 1];
+    int stk[2 * 48];       // window stack (heavy columns)
+};
+template <typename V, int N, bool FILL>
+struct GroupLds {
+    int key[N];
+    V val[FILL ? N : 1];
+    int colv[64];          // per column of the item: its place in C (-1: do not write)
+    int seg_out[64];       // per column: output entries (run count)
+};
+
+// Runs of equal rows inside every aligned segment of S positions of the sorted
+// keys (position KPL lane + r in register r).
+template <int KPL>
+struct Runs {
+    unsigned head;   // bit r: position r starts a run
+    unsigned live;   // bit r: position r holds a product
+    int run;         // run index (inside the segment) of the lane's first run start
+    int total;       // runs of the segment
+    bool first;      // the lane starts a segment
+    bool dups;       // some run of the buffer has more than one product (uniform)
+};
+
+template <typename K, int KPL, int S>
+__device__ __forceinline__ Runs<KPL> seg_runs(const K (&key)[KPL], int lane) {
+    constexpr K KMAX = KeyTraits<K>::kmax;
+    constexpr int LPS = S / KPL;  // lanes per segment
+    static_assert(LPS >= 2, "a segment spans lanes");
+    Runs<KPL> o;
+    o.first = (lane & (LPS - 1)) == 0;
+    // the last key of the lane below (the position before this lane's first)
+    K prev;
+    if constexpr (sizeof(K) == 4) {
+        prev = (K)(unsigned)wave_shr1((int)key[KPL - 1], 0);
+    } else {
+        const int lo = wave_shr1((int)(unsigned)key[KPL - 1], 0);
+        const int hi = wave_shr1((int)(unsigned)(key[KPL - 1] >> 32), 0);
+        prev = ((K)(unsigned)hi << 32) | (unsigned)lo;
+    }
+    o.head = 0;
+    o.live = 0;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const K p = r == 0 ? prev : key[r - 1];
+        const bool lv = key[r] != KMAX;
+        const bool hd = lv && ((r == 0 && o.first) || (key[r] >> kKeyBits) != (p >> kKeyBits));
+        o.live |= lv ? 1u << r : 0u;
+        o.head |= hd ? 1u << r : 0u;
+    }
+    o.dups = ballot(o.live != o.head) != 0;
+    const int cnt = __builtin_popcount(o.head);
+    const int inc = wave_incl_scan(cnt);
+    if constexpr (LPS == 64) {
+        o.run = inc - cnt;
+        o.total = __builtin_amdgcn_readlane(inc, 63);
+    } else {
+        const int first_lane = lane & ~(LPS - 1);
+        const int base = __builtin_amdgcn_ds_bpermute(first_lane << 2, inc - cnt);
+        o.run = inc - cnt - base;
+        o.total = __builtin_amdgcn_ds_bpermute((first_lane + LPS - 1) << 2, inc) - base;
+    }
+    return o;
+}
+
+// Largest occurrence index of the sorted buffer: a product's distance to the
+// head of its run (its position among the products Algorithm 1 adds into the
+// same entry); raised into the header's later_maxk for the plan's statistics.
+template <int KPL>
+__device__ __forceinline__ void note_depth(const KArgs &a, const Runs<KPL> &o, int lane) {
+    if (!o.dups) return;
+    const int s0 = lane * KPL;
+    // the last head of the lanes below (head positions increase with the lane)
+    const int last = o.head ? s0 + 31 - __builtin_clz(o.head) : -1;
+    int h = wave_shr1(wave_incl_max(last), -1);
+    int k = 0;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        if ((o.head >> r) & 1u) h = s0 + r;
+        if ((o.live >> r) & 1u) k = max(k, s0 + r - h);
+    }
+    k = __builtin_amdgcn_readlane(wave_incl_max(k), 63);
+    if (lane == 0 && k > __atomic_load_n(&a.hdr->later_maxk, __ATOMIC_RELAXED))
+        atomicMax(&a.hdr->later_maxk, k);
+}
+
+// The sorted products' values (v[r] of position r) become the running sums of
+// their runs in order, every run starting from zero: the last position of a
+// run holds its sum. A run that crosses lanes hands its partial sum from lane
+// to lane, which keeps the order of the additions.
+template <typename V, int KPL>
+__device__ __forceinline__ void run_sums(V (&v)[KPL], const Runs<KPL> &o) {
+    if (!o.dups) {
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) v[r] = V(0) + v[r];
+        return;
+    }
+    const bool cont = (o.live & 1u) && !(o.head & 1u);  // starts inside a run of the lane below
+    V carry = V(0);
+    if (ballot(cont)) {
+        // the sum of the lane's last run as far as this lane knows it
+        V t = V(0);
+#pragma unroll
+        for (int r = 0; r < KPL; ++r)
+            if ((o.live >> r) & 1u) t = ((o.head >> r) & 1u) ? V(0) + v[r] : t + v[r];
+        // lanes wholly inside a run wait for the lane below, lane after lane
+        int known = (o.head != 0 || !cont) ? 1 : 0;
+        while (ballot(!known)) {
+            const V c = wave_shr1_v(t);
+            const int k = wave_shr1(known, 1);
+            if (!known && k) {
+                t = c;
+#pragma unroll
+                for (int r = 0; r < KPL; ++r)
+                    if ((o.live >> r) & 1u) t = t + v[r];
+                known = 1;
+            }
+        }
+        carry = wave_shr1_v(t);
+    }
+    V t = carry;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        t = ((o.head >> r) & 1u) ? V(0) + v[r] : t + v[r];
+        v[r] = t;
+    }
+}
+
+// Bit r: position r is the last of its run.
+template <int KPL, int S>
+__device__ __forceinline__ unsigned run_tails(const Runs<KPL> &o, int lane) {
+    constexpr int LPS = S / KPL;
+    // the next lane's first position continues this lane's last run
+    const bool next = (o.live & 1u) && !(o.head & 1u);
+    const int go = wave_shl1(next ? 1 : 0, 0);
+    const bool last_lane = (lane & (LPS - 1)) == LPS - 1;
+    const unsigned cont = (o.live & ~o.head) >> 1;  // bit r: position r + 1 continues the run of r
+    const unsigned high = (go && !last_lane) ? 1u << (KPL - 1) : 0u;
+    return o.live & ~(cont | high);
+}
+
+// ---------------------------------------------------------------- one work item
+// A work item: up to G = N / S columns of one problem (bin-list entry
+// (global column, first stored B entry, B entries, products) in lane c), each
+// in its segment. Lanes LPS seg .. LPS (seg + 1) - 1 hold segment seg, LPS =
+// S / KPL; product i of a column is gathered in row r = i / LPS of its
+// segment, lane i mod LPS, LDS slot 64 r + lane.
+//
+// What bounds it: the chain bin entry -> B entries -> A gathers -> stores, and
+// between them the instructions of the scans, the sort and the sums. So the
+// cross-lane steps are DPP moves rather than LDS permutes, a product finds its
+// B entry from a ballot of the head flags (no fill over the lanes), the sort
+// starts from the gathered layout (any start order sorts the same), and the
+// runs are summed in registers.
+template <typename K, typename V, int KPL, int S, bool FILL>
+__device__ __forceinline__ void wave_item(const KArgs &a, const Prob &d,
+                                          GroupLds<V, 64 * KPL, FILL> &L, int4 ent, int ncol,
+                                          int lane, int &bad) {
+    constexpr int N = 64 * KPL, G = N / S, LPS = S / KPL;
+    constexpr K KMAX = KeyTraits<K>::kmax;
+    const int j = ent.x - d.col0;
+    // the filling pass's column bounds in C (known before the kernel) load
+    // with the entries; they are used after the sort
+    int2a ccp = {0, 0};
+    if (FILL && lane < ncol) ccp = load_pair(d.ccp, j);
+    const int2 *__restrict__ Ep = a.E + d.ebase;
+    const gmem<const V> *__restrict__ bvp = to_gmem((const V *)d.bv);
+    // first entry and first product of every column in the item's list
+    const int einc = wave_incl_scan(ent.z), oinc = wave_incl_scan(ent.w);
+    const int es = einc - ent.z, ob = oinc - ent.w, bsd = ent.y - es;
+    const int tot_entries = __builtin_amdgcn_readlane(einc, 63);
+    const int tot_products = __builtin_amdgcn_readlane(oinc, 63);
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) L.key[r * 64 + lane] = kHeadNone;
+    wsync();
+    // heads: at the slot of a stored B entry's first product (and of its first
+    // product of every further row), A's index less the product's position
+    bool ok = true;
+    int run = 0;
+    for (int x0 = 0; x0 < tot_entries; x0 += 64) {
+        const int x = x0 + lane;
+        int cc = 0;
+#pragma unroll
+        for (int c = 1; c < G; ++c)
+            cc += x >= __builtin_amdgcn_readlane(es, c) ? 1 : 0;
+        const int cbs = G == 1 ? __builtin_amdgcn_readlane(bsd, 0) : shfl_idx(bsd, cc);
+        const int cob = G == 1 ? 0 : shfl_idx(ob, cc);
+        const int ces = G == 1 ? 0 : shfl_idx(es, cc);
+        int2 e = make_int2(0, 0);
+        V bval = V(0);
+        if (x < tot_entries) {
+            e = Ep[cbs + x];
+            if (FILL) bval = bvp[cbs + x];
+        }
+        const int inc = wave_incl_scan(e.y);
+        // position of the entry's first product inside its column: the
+        // products listed before it less those of the earlier columns
+        const int o = run + inc - e.y - cob;
+        if (x < tot_entries && x == ces && o != 0) ok = false;
+        if (e.y > 0) {
+            if (o < 0 || e.y > S - o) {
+                ok = false;
+            } else {
+                const int end = o + e.y;
+                int row = o / LPS;
+                int slot = row * 64 + cc * LPS + o % LPS;
+                L.key[slot] = e.x - o;
+                if (FILL) L.val[slot] = bval;
+                for (++row; row * LPS < end; ++row) {
+                    slot = row * 64 + cc * LPS;
+                    L.key[slot] = e.x - o;
+                    if (FILL) L.val[slot] = bval;
+                }
+            }
+        }
+        run += __builtin_amdgcn_readlane(inc, 63);
+    }
+    if (ballot(!ok) != 0 || run != tot_products) {
+        bad = 1;
+        wsync();
+        return;
+    }
+    wsync();
+    // every product's head is the last one at or before its lane in its row
+    const int seg = lane / LPS;
+    const int opn = shfl_idx(ent.w, seg);
+    const gmem<const int32_t> *__restrict__ ari = to_gmem(d.ari);
+    const gmem<const V> *__restrict__ av = to_gmem((const V *)d.av);
+    const unsigned long long le = mask_lt() | (1ull << lane);
+    int q[KPL], from[KPL];
+    unsigned live = 0;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const unsigned long long m = ballot(L.key[r * 64 + lane] != kHeadNone) & le;
+        const int i = r * LPS + (lane & (LPS - 1));
+        const bool lv = i < opn && m != 0;
+        from[r] = r * 64 + 63 - __builtin_clzll(m | 1ull);
+        const int h = L.key[from[r]];
+        q[r] = lv ? h + i : 0;  // (a product exists, so A's first entry does)
+        live |= lv ? 1u << r : 0u;
+    }
+    int row[KPL];
+    V v[KPL];
+    // every gather of the lane issued before any is used
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        row[r] = ari[q[r]];
+        if (FILL) v[r] = av[q[r]];
+    }
+    if (FILL) {
+        // products by slot (a row's heads are read before its products land)
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+            const V b = L.val[from[r]];
+            wsync();
+            L.val[r * 64 + lane] = v[r] * b;
+        }
+    }
+    K key[KPL];
+    bool badrow = false;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const bool lv = (live >> r) & 1u;
+        // a row outside A's row range is malformed input (reported; the
+        // product takes no part)
+        const bool in = row[r] >= 0 && row[r] < d.m;
+        badrow |= lv && !in;
+        key[r] = lv && in ? (((K)(unsigned)row[r] << kKeyBits) | (K)(unsigned)(r * 64 + lane)) : KMAX;
+    }
+    if (ballot(badrow) && lane == 0) atomicOr(&a.hdr->err, ERR_CSC);
+    seg_sort<K, KPL, S>(key, lane);
+    const Runs<KPL> o = seg_runs<K, KPL, S>(key, lane);
+    if (!FILL || a.spec_fill) note_depth<KPL>(a, o, lane);
+    if constexpr (!FILL) {
+        // run count of every column, from its segment's lanes
+        const int cnt = shfl_idx(o.total, (lane * LPS) & 63);
+        if (lane < ncol) a.gnnz[ent.x] = cnt;
+        wsync();
+    } else {
+        const int cnt = shfl_idx(o.total, (lane * LPS) & 63);
+        if (lane < ncol) {
+            // a count that differs from the symbolic phase's means other
+            // inputs (nothing is written then)
+            const int clen = ccp.y - ccp.x;
+            L.colv[lane] = cnt == clen ? ccp.x : -1;
+            L.seg_out[lane] = cnt;
+            if (a.spec_fill) a.gnnz[ent.x] = cnt;
+        }
+        wsync();
+#pragma unroll
+        for (int r = 0; r < KPL; ++r)
+            v[r] = L.val[(int)(key[r] & (K)(N - 1))];  // (of padding: any value)
+        run_sums<V, KPL>(v, o);
+        wsync();
+        // a run's row and sum staged at segment start + run index
+        const unsigned tails = run_tails<KPL, S>(o, lane);
+        int at = seg * S + o.run - 1;
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+            at += (o.head >> r) & 1u;
+            if ((tails >> r) & 1u) {
+                L.key[at] = (int)(key[r] >> kKeyBits);
+                L.val[at] = v[r];
+            }
+        }
+        wsync();
+        // consecutive lanes write consecutive entries of a column
+        gmem<int32_t> *cri = to_gmem(d.cri);
+        gmem<V> *cv = to_gmem((V *)d.cv);
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+            const int s = r * 64 + lane, c = s / S, i = s - c * S;
+            if (c >= ncol) continue;
+            const int c0 = L.colv[c];
+            if (c0 < 0) {
+                bad = 1;
+                continue;
+            }
+            if (i < L.seg_out[c]) {
+                cri[c0 + i] = L.key[s];
+                cv[c0 + i] = L.val[s];
+            }
+        }
+        wsync();
+    }
+}
+
+// ---------------------------------------------------------------- wavefront groups
+// Bin `bin` holds columns of at most S products; G = N / S of them per wave.
+// One wavefront per workgroup: waves share nothing.
+template <typename K, typename V, int KPL, int S, bool FILL, bool MULTI>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KPL == 16 ? 3 : 1))) void k_acc_wave(KArgs a, int bin) {
+    constexpr int N = 64 * KPL, G = N / S;
+    static_assert(S <= N && (N % S) == 0 && N <= (1 << kKeyBits), "segments tile the buffer");
+    __shared__ GroupLds<V, N, FILL> L;
+    const BinRange br = bin_range<FILL>(a, bin, bin);
+    if (br.stop) return;
+    const int lane = threadIdx.x;
+    const int ngroups = ceil_div(br.count, G);
+    int bad = 0;
+    for (int gi = blockIdx.x; gi < ngroups; gi += gridDim.x) {
+        const int first = br.first + gi * G, ncol = min(G, br.count - gi * G);
+        int c0 = 0;
+        do {
+            // the columns from c0 on, lane c holding column c0 + c
+            int4 ent = lane < ncol - c0 ? a.binlist[first + c0 + lane] : make_int4(0, 0, 0, 0);
+            if (ballot(ent.w > S || ent.z > N)) {  // cannot happen for unchanged inputs
+                bad = 1;
+                break;
+            }
+            int nc = ncol - c0;
+            const Prob d = prob_of<MULTI>(a, ent.x);
+            if constexpr (MULTI) {
+                // a group may cross problems (bins are filled problem by
+                // problem): the columns of the first one's are an item
+                const unsigned long long other =
+                    ballot(lane < nc && (ent.x < d.col0 || ent.x >= d.col0 + d.n));
+                if (other) nc = __builtin_ctzll(other);
+                if (lane >= nc) ent = make_int4(0, 0, 0, 0);
+            }
+            wave_item<K, V, KPL, S, FILL>(a, d, L, ent, nc, lane, bad);
+            c0 += nc;
+        } while (MULTI && c0 < ncol);
+    }
+    // an output count other than the planned one: other inputs, or (a
+    // numeric phase run at a previous structure's positions) a redo
+    if (ballot(bad != 0) && lane == 0)
+        atomicOr(&a.hdr->err, a.spec_fill ? ERR_RETRY : ERR_GROUP);
+}
+
+// ---------------------------------------------------------------- one column per lane
+// Columns of at most L products and L stored B entries: every lane takes one
+// column whole, in its own registers -- the paper's mapping of one column to
+// one vector element (Section 3.1), with a sort-merge in place of its
+// accumulator. No lane talks to another; each lane's values sit in its own
+// LDS slots. Keys (row << LB | position) are 32-bit while rows stay below
+// 2^(32 - LB) - 1.
+template <typename K, typename V, int L, bool FILL, bool MULTI>
+__global__ __launch_bounds__(64) void k_acc_lane(KArgs a, int bin) {
+    constexpr int LB = L <= 4 ? 2 : (L <= 8 ? 3 : 4);
+    static_assert((1 << LB) == L, "L is 4, 8 or 16");
+    constexpr K KMAX = KeyTraits<K>::kmax;
+    __shared__ V sval[FILL ? 64 * L : 1];
+    const BinRange br = bin_range<FILL>(a, bin, bin);
+    if (br.stop) return;
+    const int lane = threadIdx.x, start = br.first, cnt = br.count;
+    int bad = 0, badrow = 0, kmax = 0;
+    for (int ci = blockIdx.x * 64 + lane; ci < cnt; ci += gridDim.x * 64) {
+        const int4 ent = a.binlist[start + ci];
+        const int g = ent.x, bs = ent.y, nb = ent.z, op = ent.w;
+        if (op > L || nb > L) {  // cannot happen for unchanged inputs
+            bad = 1;
+            continue;
+        }
+        // (the lanes' columns may belong to several problems)
+        const Prob d = MULTI ? a.table[find_prob(a, g)] : a.single;
+        // the C column's bounds (numeric phase) load together with the entries
+        int c0 = 0, clen = 0;
+        if (FILL) {
+            const int j = g - d.col0;
+            const int2a cp = load_pair(d.ccp, j);
+            c0 = cp.x;
+            clen = cp.y - c0;
+        }
+        const int2 *__restrict__ Ep = a.E + d.ebase;
+        const gmem<const V> *__restrict__ bvp = to_gmem((const V *)d.bv);
+        // the column's stored B entries: A column start, length, B value
+        int as_[L], zs[L], oo[L];
+        V bv_[L];
+#pragma unroll
+        for (int t = 0; t < L; ++t) {
+            as_[t] = 0;
+            zs[t] = 0;
+            bv_[t] = V(0);
+            if (t < nb) {
+                const int2 e = Ep[bs + t];
+                as_[t] = e.x;
+                zs[t] = e.y;
+                if (FILL) bv_[t] = bvp[bs + t];
+            }
+        }
+        int run = 0;
+#pragma unroll
+        for (int t = 0; t < L; ++t) {
+            oo[t] = run;
+            run += zs[t];
+        }
+        if (run != op) {  // entries do not add up to the product count
+            bad = 1;
+            continue;
+        }
+        // product p belongs to the entry after the ones ending at or before p
+        int q[L];
+        V bb[L];
+#pragma unroll
+        for (int p = 0; p < L; ++p) {
+            int tp = 0;
+#pragma unroll
+            for (int t = 0; t < L; ++t) tp += (oo[t] + zs[t] <= p) ? 1 : 0;
+            int qa = 0, qo = 0;
+            V qv = V(0);
+#pragma unroll
+            for (int t = 0; t < L; ++t) {
+                if (t == tp) {
+                    qa = as_[t];
+                    qo = oo[t];
+                    if (FILL) qv = bv_[t];
+                }
+            }
+            q[p] = qa + p - qo;
+            bb[p] = qv;
+        }
+        const gmem<const int32_t> *__restrict__ ari = to_gmem(d.ari);
+        const gmem<const V> *__restrict__ av = to_gmem((const V *)d.av);
+        int row[L];
+        V x[L];
+#pragma unroll
+        for (int p = 0; p < L; ++p) {
+            row[p] = p < op ? ari[q[p]] : 0;
+            if (FILL) x[p] = p < op ? av[q[p]] : V(0);
+        }
+        K key[L];
+#pragma unroll
+        for (int p = 0; p < L; ++p) {
+            key[p] = KMAX;
+            if (p < op) {
+                if (row[p] < 0 || row[p] >= d.m) {
+                    badrow = 1;
+                } else {
+                    key[p] = ((K)(unsigned)row[p] << LB) | (K)(unsigned)p;
+                    if (FILL) sval[lane * L + p] = x[p] * bb[p];
+                }
+            }
+        }
+        // bitonic network over the lane's L keys
+#pragma unroll
+        for (int k = 2; k <= L; k <<= 1) {
+#pragma unroll
+            for (int jj = k >> 1; jj > 0; jj >>= 1) {
+#pragma unroll
+                for (int r = 0; r < L; ++r) {
+                    if (r & jj) continue;
+                    const int rp = r | jj;
+                    const bool asc = (r & k) == 0;
+                    const K u = key[r], w = key[rp];
+                    const bool sw = asc ? (u > w) : (u < w);
+                    key[r] = sw ? w : u;
+                    key[rp] = sw ? u : w;
+                }
+            }
+        }
+        // runs of equal rows, each summed in position order (Algorithm 1's)
+        int nd = 0, depth = 0, dcur = 0;
+#pragma unroll
+        for (int p = 0; p < L; ++p) {
+            if (key[p] == KMAX) continue;
+            const bool head = p == 0 || (key[p] >> LB) != (key[p - 1] >> LB);
+            dcur = head ? 0 : dcur + 1;
+            depth = max(depth, dcur);
+            nd += head ? 1 : 0;
+        }
+        kmax = max(kmax, depth);
+        if (!FILL || a.spec_fill) a.gnnz[g] = nd;
+        if (FILL) {
+            if (nd != clen) {
+                bad = 1;
+                continue;
+            }
+            gmem<int32_t> *cri = to_gmem(d.cri);
+            gmem<V> *cv = to_gmem((V *)d.cv);
+            int u = 0;
+            V acc = V(0);
+#pragma unroll
+            for (int p = 0; p < L; ++p) {
+                if (key[p] == KMAX) continue;
+                const V v = sval[lane * L + (int)(key[p] & (K)(L - 1))];
+                const bool head = p == 0 || (key[p] >> LB) != (key[p - 1] >> LB);
+                acc = head ? V(0) + v : acc + v;
+                const bool last = p == L - 1 || key[p + 1 < L ? p + 1 : p] == KMAX ||
+                                  (key[p + 1 < L ? p + 1 : p] >> LB) != (key[p] >> LB);
+                if (last) {
+                    cri[c0 + u] = (int32_t)(key[p] >> LB);
+                    cv[c0 + u] = acc;
+                    ++u;
+                }
+            }
+        }
+    }
+    if (ballot(badrow) && lane == 0) atomicOr(&a.hdr->err, ERR_CSC);
+    if (ballot(bad != 0) && lane == 0)
+        atomicOr(&a.hdr->err, FILL && a.spec_fill ? ERR_RETRY : ERR_GROUP);
+    if (!FILL || a.spec_fill) {
+#pragma unroll
+        for (int dd = 32; dd >= 1; dd >>= 1)
+            kmax = max(kmax, __builtin_amdgcn_ds_bpermute((lane ^ dd) << 2, kmax));
+        if (lane == 0 && kmax > __atomic_load_n(&a.hdr->later_maxk, __ATOMIC_RELAXED))
+            atomicMax(&a.hdr->later_maxk, kmax);
+    }
+}
+
+// ---------------------------------------------------------------- heavy columns
+// The heavy column of every window (one thread per heavy column), written
+// once the window scratch is in place; a launch planned with too small a
+// scratch has been flagged for a redo and writes nothing.
+template <bool MULTI>
+__global__ __launch_bounds__(kBlock) void k_win_map(KArgs a) {
+    const BinRange br = bin_range<false>(a, kHeavyBin, BIN_WSORT);
+    if (br.stop) return;
+    const int first = br.first, n = br.count;
+    for (int li = blockIdx.x * kBlock + threadIdx.x; li < n; li += gridDim.x * kBlock) {
+        const int w0 = a.wbase[li];
+        const int w1 = w0 + (a.binlist[first + li].w - 1) / kWinTarget + 1;
+        for (int w = w0; w < w1 && w < a.win_cap; ++w) a.winmap[w] = li;
+    }
+}
+
+// Expansion of the heavy columns into the scratch: the row (and in FILL the
+// value A(i,k) B(k,j)) of every product, in Algorithm 1's order. One workgroup
+// per heavy column (grid-stride), its stored B entries 256 at a time.
+template <typename V, bool FILL, bool MULTI>
+__global__ __launch_bounds__(kBlock) void k_heavy_expand(KArgs a) {
+    __shared__ int s_acp[kBlock], s_eoff[kBlock], scan_tmp[kBlock / 64 + 1];
+    __shared__ V s_bv[FILL ? kBlock : 1];
+    const BinRange br = bin_range<FILL>(a, kHeavyBin, BIN_WSORT);
+    if (br.stop) return;  // the same in every thread
+    const int first = br.first, n = br.count;
+    const int tid = threadIdx.x;
+    int bad = 0, rowbad = 0;
+    // largest columns first (the heavy list runs from small to large bins):
+    // the longest workgroups start before the short ones
+    for (int lj = blockIdx.x; lj < n; lj += gridDim.x) {
+        const int li = n - 1 - lj;
+        const int4 ent = a.binlist[first + li];
+        const int bs = ent.y, nb = ent.z;
+        const Prob d = prob_of<MULTI>(a, ent.x);
+        const long long base0 = a.hoff[li], end = base0 + ent.w;
+        const int2 *__restrict__ Ep = a.E + d.ebase;
+        const gmem<const int32_t> *__restrict__ ari = to_gmem(d.ari);
+        const gmem<const V> *__restrict__ av = to_gmem((const V *)d.av);
+        const gmem<const V> *__restrict__ bvp = to_gmem((const V *)d.bv);
+        long long base = base0;
+        for (int bw = 0; bw < nb; bw += kBlock) {
+            const int t = bw + tid;
+            int z = 0, as = 0;
+            V bval = V(0);
+            if (t < nb) {
+                const int2 e = Ep[bs + t];
+                as = e.x;
+                z = e.y;
+                if (FILL) bval = bvp[bs + t];
+            }
+            int Ew;
+            const int ex = block_excl_scan(z, scan_tmp, Ew);
+            s_acp[tid] = as;
+            s_eoff[tid] = ex;
+            if (FILL) s_bv[tid] = bval;
+            __syncthreads();
+            const int nbw = min(kBlock, nb - bw);
+            if (base + Ew > end) {  // more products than planned: inputs changed
+                bad = 1;
+                __syncthreads();
+                break;
+            }
+            for (int e0 = 0; e0 < Ew; e0 += 4 * kBlock) {
+                int rr[4];
+                V xv[4];
+                int tt[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int e = e0 + u * kBlock + tid;
+                    const int ee = min(e, Ew - 1);
+                    tt[u] = last_le(s_eoff, nbw, ee);
+                    const int q = s_acp[tt[u]] + ee - s_eoff[tt[u]];
+                    rr[u] = ari[q];
+                    if (FILL) xv[u] = av[q];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int e = e0 + u * kBlock + tid;
+                    if (e >= Ew) continue;
+                    if (rr[u] < 0 || rr[u] >= d.m) {  // malformed input
+                        rowbad = 1;
+                        rr[u] = 0;
+                    }
+                    a.hrow[base + e] = rr[u];
+                    if (FILL) ((V *)a.hval)[base + e] = xv[u] * s_bv[tt[u]];
+                }
+            }
+            base += Ew;
+            __syncthreads();
+        }
+    }
+    if (bad && tid == 0) atomicOr(&a.hdr->err, ERR_GROUP);
+    if (rowbad) atomicOr(&a.hdr->err, ERR_CSC);
+}
+
+// A product index kept in a value slot of the wave buffer (its first 4 bytes)
+// until the value replaces it.
+template <typename V>
+__device__ __forceinline__ void put_index(V &slot, int e) {
+    __builtin_memcpy(&slot, &e, 4);
+}
+template <typename V>
+__device__ __forceinline__ int get_index(const V &slot) {
+    int e;
+    __builtin_memcpy(&e, &slot, 4);
+    return e;
+}
+
+// One window of a heavy column per wavefront (grid-stride over all windows):
+// rows [m w / W, m (w + 1) / W) of the column's products, compacted in product
+// order into the buffer, sorted, compressed. A window holding more products
+// than the buffer is halved in row span (a stack, left half first); a window
+// of a single row with more products than the buffer is one output entry,
+// summed in product order by one lane.
+template <typename K, typename V, bool FILL, bool MULTI>
+__global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
+    constexpr int KPL = kWinKpl, N = 64 * KPL;
+    constexpr K KMAX = KeyTraits<K>::kmax;
+    // Values gathered after the scan (one batch, one memory round trip per
+    // scan step fewer) where the registers it takes cost no occupancy: 32-bit
+    // keys with 8-byte values, whose wave buffer already allows 3 waves per SIMD
+    constexpr bool kDefer = sizeof(K) == 4 && sizeof(V) == 8;
+    __shared__ WaveLds<K, V, N, FILL> L;
+    const BinRange br = bin_range<FILL>(a, kHeavyBin, BIN_WSORT);
+    if (br.stop) return;
+    const int lane = threadIdx.x, first = br.first;
+    const int nwin = ((cmem<Hdr> *)a.hdr)->heavy_win;
+    int bad = 0;
+    // windows of the largest columns (the longest scans) first; workgroups go
+    // to the 8 XCDs in turn and each XCD has its own L2, so every run of kRun
+    // consecutive windows (mostly one column's, which all scan that column)
+    // goes to one XCD: inside each block of kXcd kRun workgroups, XCD x takes
+    // windows kRun x .. kRun x + kRun - 1 of the block (the ragged last block
+    // keeps its order)
+    constexpr int kXcd = 8, kRun = 16, kBlk = kXcd * kRun;
+    const int full = nwin / kBlk * kBlk;
+    for (int b = blockIdx.x; b < nwin; b += gridDim.x) {
+        const int rb = b % kBlk;
+        const int wj = b >= full ? b : b - rb + (rb % kXcd) * kRun + rb / kXcd;
+        const int wi = nwin - 1 - wj;
+        const int li = a.winmap[wi];
+        const int4 ent = a.binlist[first + li];
+        const int g = ent.x, op = ent.w;
+        const int wb = a.wbase[li], w = wi - wb, W = (op - 1) / kWinTarget + 1;
+        const Prob d = prob_of<MULTI>(a, g);
+        const int j = g - d.col0;
+        const long long hb = a.hoff[li];
+        const int *__restrict__ prow = a.hrow + hb;
+        const V *__restrict__ pval = FILL ? (const V *)a.hval + hb : nullptr;
+        // output position of the window: the entries of the earlier windows
+        int out = 0;
+        if (FILL) {
+            for (int q = lane; q < w; q += 64) out += a.wcnt[wb + q];
+            out = wave_sum(out);
+        }
+        int c0 = 0;
+        if (FILL) c0 = d.ccp[j];
+        const int m = d.m;
+        int sp = 0;
+        if (lane == 0) {
+            L.stk[0] = (int)((long long)m * w / W);
+            L.stk[1] = (int)((long long)m * (w + 1) / W);
+        }
+        sp = 1;
+        wsync();
+        int total = 0;
+        while (sp > 0) {
+            --sp;
+            const int x = L.stk[2 * sp], y = L.stk[2 * sp + 1];
+            wsync();
+            // compact the window's products (product order) into the buffer,
+            // 8 rows per lane loaded before any is tested
+            constexpr int U = 8;
+            int cnt = 0;
+            for (int e0 = 0; e0 < op; e0 += 64 * U) {
+                int r[U], pos[U];
+                bool in[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int e = e0 + u * 64 + lane;
+                    r[u] = e < op ? prow[e] : -1;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    in[u] = r[u] >= x && r[u] < y;
+                    const unsigned long long bm = ballot(in[u]);
+                    pos[u] = cnt + popc64(bm & mask_lt());
+                    cnt += popc64(bm);
+                }
+                // deferred: the value slot holds the product's index until
+                // the scan ends; else the values are gathered here
+                V vv[kDefer ? 1 : U];
+                if constexpr (FILL && !kDefer) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        vv[u] = in[u] && pos[u] < N ? pval[e0 + u * 64 + lane] : V(0);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (in[u] && pos[u] < N) {
+                        L.key[pos[u]] = ((K)(unsigned)r[u] << kKeyBits) | (K)(unsigned)pos[u];
+                        if constexpr (FILL && kDefer) put_index(L.val[pos[u]], e0 + u * 64 + lane);
+                        if constexpr (FILL && !kDefer) L.val[pos[u]] = vv[u];
+                    }
+                }
+            }
+            wsync();
+            if (cnt > N && y - x > 1) {
+                if (sp + 2 > 48) {  // cannot happen: the span halves every time
+                    bad = 1;
+                    break;
+                }
+                const int mid = x + (y - x) / 2;
+                if (lane == 0) {
+                    L.stk[2 * sp] = mid;
+                    L.stk[2 * sp + 1] = y;
+                    L.stk[2 * sp + 2] = x;
+                    L.stk[2 * sp + 3] = mid;
+                }
+                sp += 2;
+                wsync();
+                continue;
+            }
+            if (cnt > N) {
+                // one row, more products than the buffer: one entry
+                if ((!FILL || a.spec_fill) && lane == 0 &&
+                    cnt - 1 > __atomic_load_n(&a.hdr->later_maxk, __ATOMIC_RELAXED))
+                    atomicMax(&a.hdr->later_maxk, cnt - 1);
+                if (FILL && lane == 0) {
+                    V acc = V(0);
+                    bool firstp = true;
+                    for (int e = 0; e < op; ++e) {
+                        if (prow[e] != x) continue;
+                        acc = firstp ? V(0) + pval[e] : acc + pval[e];
+                        firstp = false;
+                    }
+                    if (out + total >= d.ccp[j + 1] - c0) bad = 1;
+                    else {
+                        d.cri[c0 + out + total] = x;
+                        ((V *)d.cv)[c0 + out + total] = acc;
+                    }
+                }
+                total += 1;
+                wsync();
+                continue;
+            }
+            if constexpr (FILL && kDefer) {
+                // the values of the window's products, one batch of gathers
+                // (the scan above waited on its rows only)
+                constexpr int H = KPL / 2;  // half the slots per batch (registers)
+#pragma unroll
+                for (int h = 0; h < KPL; h += H) {
+                    V vv[H];
+#pragma unroll
+                    for (int r = 0; r < H; ++r) {
+                        const int s = (h + r) * 64 + lane;
+                        vv[r] = s < cnt ? pval[get_index(L.val[s])] : V(0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < H; ++r) {
+                        const int s = (h + r) * 64 + lane;
+                        if (s < cnt) L.val[s] = vv[r];
+                    }
+                    wsync();
+                }
+            }
+            // sort and compress the buffer as one segment
+            K key[KPL];
+            const int s0 = lane * KPL;
+#pragma unroll
+            for (int r = 0; r < KPL; ++r) {
+                // any start order sorts the same: position 64 r + lane, so
+                // that consecutive lanes read consecutive banks
+                const int s = r * 64 + lane;
+                key[r] = s < cnt ? L.key[s] : KMAX;
+            }
+            wsync();
+            seg_sort<K, KPL, N>(key, lane);
+            const Runs<KPL> o = seg_runs<K, KPL, N>(key, lane);
+            const int runs = o.total;
+            if (!FILL || a.spec_fill) note_depth<KPL>(a, o, lane);
+            if constexpr (FILL) {
+                V v[KPL];
+#pragma unroll
+                for (int r = 0; r < KPL; ++r)
+                    v[r] = L.val[(int)(key[r] & (K)(N - 1))];  // (of padding: any value)
+                run_sums<V, KPL>(v, o);
+                wsync();
+                // a run's row and sum staged at its run index
+                const unsigned tails = run_tails<KPL, N>(o, lane);
+                int at = o.run - 1;
+#pragma unroll
+                for (int r = 0; r < KPL; ++r) {
+                    at += (o.head >> r) & 1u;
+                    if ((tails >> r) & 1u) {
+                        L.key[at] = key[r] >> kKeyBits;
+                        L.val[at] = v[r];
+                    }
+                }
+                wsync();
+                const int clen = d.ccp[j + 1] - c0;
+                if (out + total + runs > clen) {
+                    bad = 1;
+                } else {
+                    gmem<int32_t> *cri = to_gmem(d.cri);
+                    gmem<V> *cv = to_gmem((V *)d.cv);
+                    for (int i = lane; i < runs; i += 64) {
+                        cri[c0 + out + total + i] = (int32_t)L.key[i];
+                        cv[c0 + out + total + i] = L.val[i];
+                    }
+                }
+                wsync();
+            }
+            total += runs;
+        }
+        if (!FILL && lane == 0) {
+            a.wcnt[wb + w] = total;
+            atomicAdd(&a.gnnz[g], total);
+        }
+        if (FILL && a.spec_fill && lane == 0) {
+            // at a previous structure's positions: the window must have kept
+            // its count
+            if (total != a.wcnt[wb + w]) bad = 1;
+            atomicAdd(&a.gnnz[g], total);
+        }
+        wsync();
+    }
+    if (__builtin_amdgcn_ballot_w64(bad != 0) && lane == 0)
+        atomicOr(&a.hdr->err, FILL && a.spec_fill ? ERR_RETRY : ERR_GROUP);
+}
+
+// ---------------------------------------------------------------- launchers
+// ESC sub-bins 0 and 1 (at most 4, 8 products): one column per lane. ESC
+// sub-bin i >= 2 (at most 4 << i products): KPL = 4 (256 positions), segments
+// of 4 << i (measured: segments of 16 beat a lane per column by 16%, segments
+// of 8 lose by 14%). Sort bins 0 and 1 (at most 512, 1024 products): one
+// column per wave, KPL = 8, 16. Larger columns are heavy.
+template <bool MULTI, typename K, typename V, bool FILL>
+static hipError_t launch_wave_bin(const KArgs &a, int bin, int grid, hipStream_t s) {
+    const dim3 g(grid), t(64);
+    switch (bin) {
+        case BIN_ESC0 + 0: hipLaunchKernelGGL((k_acc_lane<K, V, 4, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_ESC0 + 1: hipLaunchKernelGGL((k_acc_lane<K, V, 8, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_ESC0 + 2: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 16, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_ESC0 + 3: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 32, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_ESC0 + 4: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 64, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_ESC0 + 5: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 128, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_ESC0 + 6: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 256, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_SORT0 + 0: hipLaunchKernelGGL((k_acc_wave<K, V, 8, 512, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_SORT0 + 1: hipLaunchKernelGGL((k_acc_wave<K, V, 16, 1024, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <bool MULTI>
+hipError_t launch_acc_wave_t(const KArgs &a, int bin, int items, bool wide, bool fill, bool f64,
+                           hipStream_t s) {
+    if (items <= 0) return hipSuccess;
+    if (!fill) {
+        return wide ? launch_wave_bin<MULTI, unsigned long long, float, false>(a, bin, items, s)
+                    : launch_wave_bin<MULTI, unsigned, float, false>(a, bin, items, s);
+    }
+    if (f64)
+        return wide ? launch_wave_bin<MULTI, unsigned long long, double, true>(a, bin, items, s)
+                    : launch_wave_bin<MULTI, unsigned, double, true>(a, bin, items, s);
+    return wide ? launch_wave_bin<MULTI, unsigned long long, float, true>(a, bin, items, s)
+                : launch_wave_bin<MULTI, unsigned, float, true>(a, bin, items, s);
+}
+
+template <bool MULTI>
+hipError_t launch_heavy_t(const KArgs &a, int ncols, int nwin, bool wide, bool fill, bool f64,
+                        hipStream_t s, bool radix, long long heavy_products, int rowbits,
+                        int part) {
+    if (ncols <= 0) return hipSuccess;
+    const bool expand = radix ? part == 0 : part == 1;
+    if (expand) {
+        if (!fill) hipLaunchKernelGGL((k_heavy_expand<float, false, MULTI>), dim3(ncols), dim3(kBlock), 0, s, a);
+        else if (f64) hipLaunchKernelGGL((k_heavy_expand<double, true, MULTI>), dim3(ncols), dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((k_heavy_expand<float, true, MULTI>), dim3(ncols), dim3(kBlock), 0, s, a);
+        return hipGetLastError();
+    }
+    if (radix) return part == 1 ? launch_esc_radix(a, heavy_products, rowbits, fill, f64, s) : hipSuccess;
+    if (part == 0) {
+        hipLaunchKernelGGL(k_win_map<MULTI>, dim3(ceil_div(ncols, kBlock)), dim3(kBlock), 0, s, a);
+        return hipGetLastError();
+    }
+    if (part != 2 || nwin <= 0) return hipSuccess;
+    if (!fill) {
+        if (wide) hipLaunchKernelGGL((k_acc_window<unsigned long long, float, false, MULTI>), dim3(nwin), dim3(64), 0, s, a);
+        else hipLaunchKernelGGL((k_acc_window<unsigned, float, false, MULTI>), dim3(nwin), dim3(64), 0, s, a);
+    } else if (f64) {
+        if (wide) hipLaunchKernelGGL((k_acc_window<unsigned long long, double, true, MULTI>), dim3(nwin), dim3(64), 0, s, a);
+        else hipLaunchKernelGGL((k_acc_window<unsigned, double, true, MULTI>), dim3(nwin), dim3(64), 0, s, a);
+    } else {
+        if (wide) hipLaunchKernelGGL((k_acc_window<unsigned long long, float, true, MULTI>), dim3(nwin), dim3(64), 0, s, a);
+        else hipLaunchKernelGGL((k_acc_window<unsigned, float, true, MULTI>), dim3(nwin), dim3(64), 0, s, a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace spg

@@ -100,6 +100,7 @@ struct Prob {
 // Device header written by the planning kernels.
 struct Hdr {
     int32_t bin_count[NBINS];
+    int32_t bin_start[NBINS];          // first bin-list position of every bin
     int32_t err;
     int32_t later_maxk;                // largest occurrence index k of any product
     int32_t big_chunks;                // most kChunkB-entry chunks of a column above t_split
@@ -294,8 +295,14 @@ hipError_t launch_later_runs(const KArgs &a, bool f64, long long n, hipStream_t 
 // columns); fill = true: rows and values of C. wide: 64-bit keys (rows of
 // 2^21 - 1 and more).
 int wave_bin_items(int bin, int ncols);
-hipError_t launch_acc_wave(const KArgs &a, int bin, int items, bool wide, bool fill, bool f64,
-                           hipStream_t s);
+template <bool MULTI>
+hipError_t launch_acc_wave_t(const KArgs &a, int bin, int items, bool wide, bool fill, bool f64,
+                             hipStream_t s);
+inline hipError_t launch_acc_wave(const KArgs &a, int bin, int items, bool wide, bool fill,
+                                  bool f64, hipStream_t s) {
+    return a.nprob == 1 ? launch_acc_wave_t<false>(a, bin, items, wide, fill, f64, s)
+                        : launch_acc_wave_t<true>(a, bin, items, wide, fill, f64, s);
+}
 // global ESC with radix sort over groups of heavy columns (after the heavy
 // expansion); rowbits: bits of the largest row index
 hipError_t launch_esc_radix(const KArgs &a, long long heavy_products, int rowbits, bool fill,
@@ -327,9 +334,19 @@ hipError_t launch_lane_blocked(const KArgs &a, const LbArgs &lb, int ncols_hint,
 // a launch whose windows are mapped already starts at heavy_first_part
 int heavy_parts(bool radix);
 int heavy_first_part(bool radix, bool mapped);
-hipError_t launch_heavy(const KArgs &a, int ncols, int nwin, bool wide, bool fill, bool f64,
-                        hipStream_t s, bool radix, long long heavy_products, int rowbits,
-                        int part);
+template <bool MULTI>
+hipError_t launch_heavy_t(const KArgs &a, int ncols, int nwin, bool wide, bool fill, bool f64,
+                          hipStream_t s, bool radix, long long heavy_products, int rowbits,
+                          int part);
+inline hipError_t launch_heavy(const KArgs &a, int ncols, int nwin, bool wide, bool fill, bool f64,
+                               hipStream_t s, bool radix, long long heavy_products, int rowbits,
+                               int part) {
+    return a.nprob == 1
+               ? launch_heavy_t<false>(a, ncols, nwin, wide, fill, f64, s, radix, heavy_products,
+                                       rowbits, part)
+               : launch_heavy_t<true>(a, ncols, nwin, wide, fill, f64, s, radix, heavy_products,
+                                      rowbits, part);
+}
 inline int row_bits(int m) { return m <= 1 ? 0 : 32 - __builtin_clz((unsigned)(m - 1)); }
 // Backward view, built once per single-problem plan (see k_backward.hip).
 struct BwView {

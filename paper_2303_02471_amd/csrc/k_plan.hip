@@ -44,9 +44,12 @@ __device__ __forceinline__ void place_header(const KArgs &a, int err, const int 
                                              long long hwin) {
     Hdr *h = a.hdr;
     err &= ERR_CSC | ERR_OPOVF;
+    int start = 0;
 #pragma unroll 1
     for (int b = 0; b < NBINS; ++b) {
         h->bin_count[b] = counts[b];
+        h->bin_start[b] = start;
+        start += counts[b];
         // a planned launch that does not cover a non-empty bin is redone
         if (a.spec_total >= 0 && counts[b] > 0 && !((a.spec_mask >> b) & 1u)) err |= ERR_RETRY;
     }
@@ -484,6 +487,7 @@ __global__ __launch_bounds__(kTile) void k_place(KArgs a, PubArgs pub) {
 #pragma unroll
         for (int x = 0; x < NW; ++x) v[x] = s_cnt[x][tid];
         s_start[tid] = start;
+        if (!SELF && mt == 0) a.hdr->bin_start[tid] = start;
         int run = start + s_base[tid];
 #pragma unroll
         for (int x = 0; x < NW; ++x) {
