@@ -258,21 +258,138 @@ __device__ __forceinline__ void seg_sort(K (&key)[KPL], int lane_in) {
     if constexpr (sizeof(K) == 4) asm volatile("s_nop 1" : "+v"(key[KPL - 1]), "+v"(key[0]));
 }
 
+// A buffer that is one segment, 32-bit keys: sorted by an order-preserving
+// spread of the rows over as many buckets as the buffer has positions (counts
+// by LDS atomics, their prefix sums, every key to its bucket), then as many
+// odd-even exchanges of neighbours as the fullest bucket holds keys. For rows
+// spread evenly over their span the fullest of 1024 buckets holds 5 or 6 keys,
+// about 390 vector instructions against the 1216 of the bitonic network; a
+// fuller bucket than kBucketMax (rows in a few clusters, or many products per
+// row) leaves the keys as they were, for the network. The waves were bound by
+// the network's vector instructions: 1024-product waves of a batch 384 -> 357
+// us, counting 214 -> 172 us (with the smaller buffer below 341 and 140 us).
+//   key: all ones where there is none; rows in [lo, lo + span); buf: 64 KPL
+//   words.
+constexpr int kBucketMax = 12;
+template <int KPL>
+__device__ __forceinline__ bool bucket_sort(unsigned (&key)[KPL], unsigned lo, unsigned span,
+                                            int *buf, int lane) {
+    constexpr int N = 64 * KPL;
+    constexpr unsigned KMAX = ~0u;
+    // (a float product rounds monotonically: larger rows, no smaller bucket)
+    const float scale = (float)N * __builtin_amdgcn_rcpf((float)span);
+#pragma unroll
+    for (int r = 0; r < KPL; r += 4)
+        *(int4 *)(buf + lane * KPL + r) = make_int4(0, 0, 0, 0);
+    wsync();
+    int b[KPL], at[KPL];
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        at[r] = 0;
+        b[r] = min((int)((float)((key[r] >> kKeyBits) - lo) * scale), N - 1);
+        if (key[r] != KMAX) at[r] = atomicAdd(&buf[b[r]], 1);
+    }
+    wsync();
+    int cnt[KPL], sum = 0, most = 0;
+#pragma unroll
+    for (int r = 0; r < KPL; r += 4) {
+        const int4 x = *(const int4 *)(buf + lane * KPL + r);
+        cnt[r] = x.x;
+        cnt[r + 1] = x.y;
+        cnt[r + 2] = x.z;
+        cnt[r + 3] = x.w;
+    }
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        sum += cnt[r];
+        most = max(most, cnt[r]);
+    }
+    const int inc = wave_incl_scan(sum);
+    const int total = __builtin_amdgcn_readlane(inc, 63);
+    const int fullest = __builtin_amdgcn_readlane(wave_incl_max(most), 63);
+    if (fullest > kBucketMax) {
+        wsync();
+        return false;
+    }
+    int run = inc - sum;
+#pragma unroll
+    for (int r = 0; r < KPL; r += 4) {
+        int4 x;
+        x.x = run;
+        x.y = x.x + cnt[r];
+        x.z = x.y + cnt[r + 1];
+        x.w = x.z + cnt[r + 2];
+        run = x.w + cnt[r + 3];
+        *(int4 *)(buf + lane * KPL + r) = x;
+    }
+    wsync();
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) at[r] += buf[b[r]];
+    wsync();  // every base is read before any key lands
+#pragma unroll
+    for (int r = 0; r < KPL; ++r)
+        if (key[r] != KMAX) buf[at[r]] = (int)key[r];
+    wsync();
+#pragma unroll
+    for (int r = 0; r < KPL; r += 4) {
+        const int4 x = *(const int4 *)(buf + lane * KPL + r);
+        key[r] = lane * KPL + r < total ? (unsigned)x.x : KMAX;
+        key[r + 1] = lane * KPL + r + 1 < total ? (unsigned)x.y : KMAX;
+        key[r + 2] = lane * KPL + r + 2 < total ? (unsigned)x.z : KMAX;
+        key[r + 3] = lane * KPL + r + 3 < total ? (unsigned)x.w : KMAX;
+    }
+    wsync();
+    // (b neighbours need b alternating rounds of exchanges, whichever pairs start)
+    for (int p = fullest > 1 ? 0 : fullest; p < fullest; p += 2) {
+#pragma unroll
+        for (int r = 0; r < KPL; r += 2) minmax(key[r], key[r + 1]);
+        // (the moves below read what the asm blocks above wrote)
+        asm volatile("s_nop 1" : "+v"(key[0]), "+v"(key[KPL - 1]));
+        const unsigned next = (unsigned)wave_shl1((int)key[0], -1);
+        const unsigned prev = (unsigned)wave_shr1((int)key[KPL - 1], 0);
+#pragma unroll
+        for (int r = 1; r + 1 < KPL; r += 2) minmax(key[r], key[r + 1]);
+        key[0] = max(key[0], prev);
+        key[KPL - 1] = min(key[KPL - 1], next);
+    }
+    return true;
+}
+
+// Smallest and largest row of the keys (positions below n) of a buffer.
+template <int KPL>
+__device__ __forceinline__ void row_span(const unsigned (&key)[KPL], unsigned &lo, unsigned &span) {
+    unsigned mn = ~0u, mx = 0;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        mn = min(mn, key[r]);
+        mx = max(mx, key[r] == ~0u ? 0u : key[r]);
+    }
+    // rows have 21 bits: signed comparisons order them
+    const int l = -__builtin_amdgcn_readlane(wave_incl_max(-(int)(mn >> kKeyBits)), 63);
+    const int h = __builtin_amdgcn_readlane(wave_incl_max((int)(mx >> kKeyBits)), 63);
+    lo = (unsigned)l;
+    span = (unsigned)(h - l + 1);
+}
+
 // ---------------------------------------------------------------- one buffer
-// LDS of one wavefront: head offsets, then staged output rows (key), and head
-// values, then the products by slot, then staged output values (val).
-template <typename K, typename V, int N, bool FILL>
-struct WaveLds {
-    K key[N];
-    V val[FILL ? N : 1];
-    int stk[2 * 48];       // window stack (heavy columns)
-};
+// LDS of one wavefront. Groups: head offsets, then staged output rows (key),
+// and head values, then the products by slot, then staged output values (val).
 template <typename V, int N, bool FILL>
 struct GroupLds {
-    int key[N];
+    alignas(16) int key[N];
     V val[FILL ? N : 1];
     int colv[64];          // per column of the item: its place in C (-1: do not write)
     int seg_out[64];       // per column: output entries (run count)
+};
+// A buffer that is one segment holds in turn, in the same 8 bytes a position
+// (4 counting): heads or compacted rows with their entries' or products'
+// indices; the sort's buckets; the products by slot; the staged sums; the
+// staged rows. Between those the products wait in registers: 8 KB for 1024
+// positions let 4 waves per SIMD stand side by side (12 KB: 3).
+template <int N, bool FILL>
+struct OneLds {
+    alignas(16) int mem[FILL ? 2 * N : N];
+    int stk[2 * 48];       // window stack (heavy columns)
 };
 
 // Runs of equal rows inside every aligned segment of S positions of the sorted
@@ -420,9 +537,11 @@ __device__ __forceinline__ unsigned run_tails(const Runs<KPL> &o, int lane) {
 template <typename K, typename V, int KPL, int S, bool FILL>
 __device__ __forceinline__ void wave_item(const KArgs &a, const Prob &d,
                                           GroupLds<V, 64 * KPL, FILL> &L, int4 ent, int ncol,
-                                          int lane, int &bad) {
+                                          int lane_in, int &bad) {
     constexpr int N = 64 * KPL, G = N / S, LPS = S / KPL;
     constexpr K KMAX = KeyTraits<K>::kmax;
+    int lane = lane_in;  // (opaque: see one_item)
+    asm volatile("" : "+v"(lane));
     const int j = ent.x - d.col0;
     // the filling pass's column bounds in C (known before the kernel) load
     // with the entries; they are used after the sort
@@ -590,11 +709,194 @@ __device__ __forceinline__ void wave_item(const KArgs &a, const Prob &d,
     }
 }
 
+// ---------------------------------------------------------------- one segment
+// Sorts a buffer that is one segment (key: slot 64 r + lane in register r, all
+// ones where there is none; rows in [lo, lo + span) when span > 0, else found
+// here) and finds its runs.
+template <typename K, int KPL, bool FILL>
+__device__ __forceinline__ Runs<KPL> one_sort(const KArgs &a, K (&key)[KPL], unsigned lo,
+                                              unsigned span, int *mem, int lane) {
+    constexpr int N = 64 * KPL;
+    bool sorted = false;
+    if constexpr (sizeof(K) == 4) {
+        if (span == 0) row_span<KPL>(key, lo, span);
+        sorted = bucket_sort<KPL>(key, lo, span, mem, lane);
+    }
+    if (!sorted) seg_sort<K, KPL, N>(key, lane);
+    const Runs<KPL> o = seg_runs<K, KPL, N>(key, lane);
+    if (!FILL || a.spec_fill) note_depth<KPL>(a, o, lane);
+    return o;
+}
+
+// The sorted buffer's runs to C at `at`: v holds the products by slot. The
+// sums and then the rows pass through the LDS, so that consecutive lanes write
+// consecutive entries.
+template <typename K, typename V, int KPL>
+__device__ __forceinline__ void one_emit(const Prob &d, const K (&key)[KPL], V (&v)[KPL],
+                                         const Runs<KPL> &o, long long at, int *mem, int lane) {
+    constexpr int N = 64 * KPL;
+    V *val = (V *)mem;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) val[r * 64 + lane] = v[r];
+    wsync();
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) v[r] = val[(int)(key[r] & (K)(N - 1))];  // (of padding: any value)
+    run_sums<V, KPL>(v, o);
+    wsync();
+    const unsigned tails = run_tails<KPL, N>(o, lane);
+    int to = o.run - 1;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        to += (o.head >> r) & 1u;
+        if ((tails >> r) & 1u) val[to] = v[r];
+    }
+    wsync();
+    gmem<V> *cv = to_gmem((V *)d.cv) + at;
+    for (int i = lane; i < o.total; i += 64) cv[i] = val[i];
+    wsync();
+    to = o.run - 1;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        to += (o.head >> r) & 1u;
+        if ((tails >> r) & 1u) mem[to] = (int)(key[r] >> kKeyBits);
+    }
+    wsync();
+    gmem<int32_t> *cri = to_gmem(d.cri) + at;
+    for (int i = lane; i < o.total; i += 64) cri[i] = mem[i];
+    wsync();
+}
+
+// One column per wavefront (`ent`: its bin-list entry, the same in every lane),
+// its products gathered as in wave_item with one row of 64 slots per register.
+template <typename K, typename V, int KPL, bool FILL>
+__device__ __forceinline__ void one_item(const KArgs &a, const Prob &d,
+                                         OneLds<64 * KPL, FILL> &L, int4 ent, int lane_in,
+                                         int &bad) {
+    constexpr int N = 64 * KPL;
+    constexpr K KMAX = KeyTraits<K>::kmax;
+    // opaque lane number: the slots' addresses are not kept in registers
+    // outside the item
+    int lane = lane_in;
+    asm volatile("" : "+v"(lane));
+    const int g = ent.x, bs = ent.y, nb = ent.z, op = ent.w;
+    int2a ccp = {0, 0};
+    if (FILL) ccp = load_pair(d.ccp, g - d.col0);
+    const int2 *__restrict__ Ep = a.E + d.ebase + bs;
+    int2 *head2 = (int2 *)L.mem;  // (A's index less the position, B entry); counting: the first only
+    int *head1 = L.mem;
+    int2 e = lane < nb ? Ep[lane] : make_int2(0, 0);
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        if (FILL) head2[r * 64 + lane] = make_int2(kHeadNone, 0);
+        else head1[r * 64 + lane] = kHeadNone;
+    }
+    wsync();
+    bool ok = true;
+    int run = 0;
+    for (int x0 = 0; x0 < nb; x0 += 64) {
+        // the next entries load while these are placed
+        const int2 next = x0 + 64 + lane < nb ? Ep[x0 + 64 + lane] : make_int2(0, 0);
+        const int inc = wave_incl_scan(e.y), o = run + inc - e.y;
+        if (e.y > 0) {
+            if (o < 0 || e.y > N - o) {
+                ok = false;
+            } else {
+                const int2 h = make_int2(e.x - o, bs + x0 + lane);
+                int slot = o;
+                do {  // its first product, and its first of every further row
+                    if (FILL) head2[slot] = h;
+                    else head1[slot] = h.x;
+                    slot = (slot | 63) + 1;
+                } while (slot < o + e.y);
+            }
+        }
+        run += __builtin_amdgcn_readlane(inc, 63);
+        e = next;
+    }
+    if (ballot(!ok) != 0 || run != op) {
+        bad = 1;
+        wsync();
+        return;
+    }
+    wsync();
+    const gmem<const int32_t> *__restrict__ ari = to_gmem(d.ari);
+    const gmem<const V> *__restrict__ av = to_gmem((const V *)d.av);
+    const gmem<const V> *__restrict__ bvp = to_gmem((const V *)d.bv);
+    const unsigned long long le = mask_lt() | (1ull << lane);
+    int row[KPL];
+    V v[KPL];
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const int h = FILL ? head2[r * 64 + lane].x : head1[r * 64 + lane];
+        const unsigned long long m = ballot(h != kHeadNone) & le;
+        const int from = r * 64 + 63 - __builtin_clzll(m | 1ull);
+        const bool lv = r * 64 + lane < op;  // (row r then starts with a head)
+        int2 x = FILL ? head2[from] : make_int2(head1[from], 0);
+        // a padding position reads A's and B's first entries
+        const int q = lv ? x.x + r * 64 + lane : 0;
+        row[r] = ari[q];
+        if (FILL) v[r] = av[q] * bvp[lv ? x.y : 0];
+    }
+    // (the products are formed here: left to the compiler, both factors wait in
+    // registers until the sort is over)
+    if (FILL)
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) asm volatile("" : "+v"(v[r]));
+    K key[KPL];
+    bool badrow = false;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const bool lv = r * 64 + lane < op;
+        // a row outside A's row range is malformed input (reported; the
+        // product takes no part)
+        const bool in = row[r] >= 0 && row[r] < d.m;
+        badrow |= lv && !in;
+        key[r] = lv && in ? (((K)(unsigned)row[r] << kKeyBits) | (K)(unsigned)(r * 64 + lane)) : KMAX;
+    }
+    if (ballot(badrow)) {
+        if (lane == 0) atomicOr(&a.hdr->err, ERR_CSC);
+        return;
+    }
+    wsync();
+    const Runs<KPL> o = one_sort<K, KPL, FILL>(a, key, 0u, 0u, L.mem, lane);
+    if ((!FILL || a.spec_fill) && lane == 0) a.gnnz[g] = o.total;
+    if constexpr (FILL) {
+        // a count that differs from the symbolic phase's means other inputs
+        // (nothing is written then)
+        if (o.total != ccp.y - ccp.x) bad = 1;
+        else one_emit<K, V, KPL>(d, key, v, o, ccp.x, L.mem, lane);
+    }
+    wsync();
+}
+
+template <typename K, typename V, int KPL, bool FILL, bool MULTI>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KPL == 16 ? 4 : 1))) void k_acc_one(KArgs a, int bin) {
+    __shared__ OneLds<64 * KPL, FILL> L;
+    const BinRange br = bin_range<FILL>(a, bin, bin);
+    if (br.stop) return;
+    const int lane = threadIdx.x;
+    int bad = 0;
+    for (int i = blockIdx.x; i < br.count; i += gridDim.x) {
+        const int4 e = a.binlist[br.first + i];
+        const int4 ent = make_int4(
+            __builtin_amdgcn_readfirstlane(e.x), __builtin_amdgcn_readfirstlane(e.y),
+            __builtin_amdgcn_readfirstlane(e.z), __builtin_amdgcn_readfirstlane(e.w));
+        if (ent.w > 64 * KPL || ent.z > 64 * KPL) {  // cannot happen for unchanged inputs
+            bad = 1;
+            break;
+        }
+        const Prob d = prob_of<MULTI>(a, ent.x);
+        one_item<K, V, KPL, FILL>(a, d, L, ent, lane, bad);
+    }
+    if (ballot(bad != 0) && lane == 0)
+        atomicOr(&a.hdr->err, a.spec_fill ? ERR_RETRY : ERR_GROUP);
+}
+
 // ---------------------------------------------------------------- wavefront groups
 // Bin `bin` holds columns of at most S products; G = N / S of them per wave.
 // One wavefront per workgroup: waves share nothing.
 template <typename K, typename V, int KPL, int S, bool FILL, bool MULTI>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KPL == 16 ? 3 : 1))) void k_acc_wave(KArgs a, int bin) {
+__global__ __launch_bounds__(64) void k_acc_wave(KArgs a, int bin) {
     constexpr int N = 64 * KPL, G = N / S;
     static_assert(S <= N && (N % S) == 0 && N <= (1 << kKeyBits), "segments tile the buffer");
     __shared__ GroupLds<V, N, FILL> L;
@@ -899,19 +1201,6 @@ __global__ __launch_bounds__(kBlock) void k_heavy_expand(KArgs a) {
     if (rowbad) atomicOr(&a.hdr->err, ERR_CSC);
 }
 
-// A product index kept in a value slot of the wave buffer (its first 4 bytes)
-// until the value replaces it.
-template <typename V>
-__device__ __forceinline__ void put_index(V &slot, int e) {
-    __builtin_memcpy(&slot, &e, 4);
-}
-template <typename V>
-__device__ __forceinline__ int get_index(const V &slot) {
-    int e;
-    __builtin_memcpy(&e, &slot, 4);
-    return e;
-}
-
 // One window of a heavy column per wavefront (grid-stride over all windows):
 // rows [m w / W, m (w + 1) / W) of the column's products, compacted in product
 // order into the buffer, sorted, compressed. A window holding more products
@@ -919,17 +1208,14 @@ __device__ __forceinline__ int get_index(const V &slot) {
 // of a single row with more products than the buffer is one output entry,
 // summed in product order by one lane.
 template <typename K, typename V, bool FILL, bool MULTI>
-__global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_acc_window(KArgs a) {
     constexpr int KPL = kWinKpl, N = 64 * KPL;
     constexpr K KMAX = KeyTraits<K>::kmax;
-    // Values gathered after the scan (one batch, one memory round trip per
-    // scan step fewer) where the registers it takes cost no occupancy: 32-bit
-    // keys with 8-byte values, whose wave buffer already allows 3 waves per SIMD
-    constexpr bool kDefer = sizeof(K) == 4 && sizeof(V) == 8;
-    __shared__ WaveLds<K, V, N, FILL> L;
+    __shared__ OneLds<N, FILL> L;
+    int *const prows = L.mem, *const pidx = L.mem + (FILL ? N : 0);  // compacted rows, indices
     const BinRange br = bin_range<FILL>(a, kHeavyBin, BIN_WSORT);
     if (br.stop) return;
-    const int lane = threadIdx.x, first = br.first;
+    const int first = br.first;
     const int nwin = ((cmem<Hdr> *)a.hdr)->heavy_win;
     int bad = 0;
     // windows of the largest columns (the longest scans) first; workgroups go
@@ -941,6 +1227,8 @@ __global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
     constexpr int kXcd = 8, kRun = 16, kBlk = kXcd * kRun;
     const int full = nwin / kBlk * kBlk;
     for (int b = blockIdx.x; b < nwin; b += gridDim.x) {
+        int lane = threadIdx.x;  // (opaque: see one_item)
+        asm volatile("" : "+v"(lane));
         const int rb = b % kBlk;
         const int wj = b >= full ? b : b - rb + (rb % kXcd) * kRun + rb / kXcd;
         const int wi = nwin - 1 - wj;
@@ -993,20 +1281,11 @@ __global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
                     pos[u] = cnt + popc64(bm & mask_lt());
                     cnt += popc64(bm);
                 }
-                // deferred: the value slot holds the product's index until
-                // the scan ends; else the values are gathered here
-                V vv[kDefer ? 1 : U];
-                if constexpr (FILL && !kDefer) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        vv[u] = in[u] && pos[u] < N ? pval[e0 + u * 64 + lane] : V(0);
-                }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     if (in[u] && pos[u] < N) {
-                        L.key[pos[u]] = ((K)(unsigned)r[u] << kKeyBits) | (K)(unsigned)pos[u];
-                        if constexpr (FILL && kDefer) put_index(L.val[pos[u]], e0 + u * 64 + lane);
-                        if constexpr (FILL && !kDefer) L.val[pos[u]] = vv[u];
+                        prows[pos[u]] = r[u];
+                        if constexpr (FILL) pidx[pos[u]] = e0 + u * 64 + lane;
                     }
                 }
             }
@@ -1050,72 +1329,25 @@ __global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
                 wsync();
                 continue;
             }
-            if constexpr (FILL && kDefer) {
-                // the values of the window's products, one batch of gathers
-                // (the scan above waited on its rows only)
-                constexpr int H = KPL / 2;  // half the slots per batch (registers)
-#pragma unroll
-                for (int h = 0; h < KPL; h += H) {
-                    V vv[H];
-#pragma unroll
-                    for (int r = 0; r < H; ++r) {
-                        const int s = (h + r) * 64 + lane;
-                        vv[r] = s < cnt ? pval[get_index(L.val[s])] : V(0);
-                    }
-#pragma unroll
-                    for (int r = 0; r < H; ++r) {
-                        const int s = (h + r) * 64 + lane;
-                        if (s < cnt) L.val[s] = vv[r];
-                    }
-                    wsync();
-                }
-            }
-            // sort and compress the buffer as one segment
+            // keys by slot, and the values of the window's products in one batch
+            // of gathers (the scan above waited on its rows only)
             K key[KPL];
-            const int s0 = lane * KPL;
+            V v[KPL];
 #pragma unroll
             for (int r = 0; r < KPL; ++r) {
-                // any start order sorts the same: position 64 r + lane, so
-                // that consecutive lanes read consecutive banks
                 const int s = r * 64 + lane;
-                key[r] = s < cnt ? L.key[s] : KMAX;
+                const bool lv = s < cnt;
+                key[r] = lv ? (((K)(unsigned)prows[s] << kKeyBits) | (K)(unsigned)s) : KMAX;
+                if constexpr (FILL) v[r] = pval[lv ? pidx[s] : 0];
             }
             wsync();
-            seg_sort<K, KPL, N>(key, lane);
-            const Runs<KPL> o = seg_runs<K, KPL, N>(key, lane);
+            const Runs<KPL> o = one_sort<K, KPL, FILL>(a, key, (unsigned)x, (unsigned)(y - x),
+                                                       L.mem, lane);
             const int runs = o.total;
-            if (!FILL || a.spec_fill) note_depth<KPL>(a, o, lane);
             if constexpr (FILL) {
-                V v[KPL];
-#pragma unroll
-                for (int r = 0; r < KPL; ++r)
-                    v[r] = L.val[(int)(key[r] & (K)(N - 1))];  // (of padding: any value)
-                run_sums<V, KPL>(v, o);
-                wsync();
-                // a run's row and sum staged at its run index
-                const unsigned tails = run_tails<KPL, N>(o, lane);
-                int at = o.run - 1;
-#pragma unroll
-                for (int r = 0; r < KPL; ++r) {
-                    at += (o.head >> r) & 1u;
-                    if ((tails >> r) & 1u) {
-                        L.key[at] = key[r] >> kKeyBits;
-                        L.val[at] = v[r];
-                    }
-                }
-                wsync();
                 const int clen = d.ccp[j + 1] - c0;
-                if (out + total + runs > clen) {
-                    bad = 1;
-                } else {
-                    gmem<int32_t> *cri = to_gmem(d.cri);
-                    gmem<V> *cv = to_gmem((V *)d.cv);
-                    for (int i = lane; i < runs; i += 64) {
-                        cri[c0 + out + total + i] = (int32_t)L.key[i];
-                        cv[c0 + out + total + i] = L.val[i];
-                    }
-                }
-                wsync();
+                if (out + total + runs > clen) bad = 1;
+                else one_emit<K, V, KPL>(d, key, v, o, (long long)c0 + out + total, L.mem, lane);
             }
             total += runs;
         }
@@ -1131,7 +1363,7 @@ __global__ __launch_bounds__(64) void k_acc_window(KArgs a) {
         }
         wsync();
     }
-    if (__builtin_amdgcn_ballot_w64(bad != 0) && lane == 0)
+    if (__builtin_amdgcn_ballot_w64(bad != 0) && threadIdx.x == 0)
         atomicOr(&a.hdr->err, FILL && a.spec_fill ? ERR_RETRY : ERR_GROUP);
 }
 
@@ -1152,8 +1384,8 @@ static hipError_t launch_wave_bin(const KArgs &a, int bin, int grid, hipStream_t
         case BIN_ESC0 + 4: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 64, FILL, MULTI>), g, t, 0, s, a, bin); break;
         case BIN_ESC0 + 5: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 128, FILL, MULTI>), g, t, 0, s, a, bin); break;
         case BIN_ESC0 + 6: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 256, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_SORT0 + 0: hipLaunchKernelGGL((k_acc_wave<K, V, 8, 512, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_SORT0 + 1: hipLaunchKernelGGL((k_acc_wave<K, V, 16, 1024, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_SORT0 + 0: hipLaunchKernelGGL((k_acc_one<K, V, 8, FILL, MULTI>), g, t, 0, s, a, bin); break;
+        case BIN_SORT0 + 1: hipLaunchKernelGGL((k_acc_one<K, V, 16, FILL, MULTI>), g, t, 0, s, a, bin); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

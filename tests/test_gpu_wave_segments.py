@@ -94,3 +94,36 @@ def _depth(A, B):
         if len(rows):
             deep = max(deep, int(np.unique(rows, return_counts=True)[1].max()) - 1)
     return deep
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_row_clusters(dtype):
+    """Long columns whose rows stand in clusters of 1 to 14 neighbours, far
+    apart: the bucket sort's fullest bucket holds as many keys, up to above the
+    limit from which the sorting network takes over; in descending, ascending
+    and mixed order, with and without a second product on every row."""
+    print(f"[case] row clusters {dtype}", flush=True)
+    np_t = np.float64 if dtype == "f64" else np.float32
+    rng = np.random.default_rng(9)
+    m = 1 << 20
+    acols, bcols = [], []
+    for size in range(1, 15):
+        for total in (300, 512, 700, 1024, 2500):
+            starts = np.arange(total // size) * (m // (total // size + 1))
+            rows = (starts[:, None] + np.arange(size)).ravel()
+            for order in ("down", "up", "mixed"):
+                r = rows[::-1] if order == "down" else rows if order == "up" else rng.permutation(rows)
+                half = len(r) // 2
+                acols += [r[:half], r[half:], r[:half:2]]
+                k = len(acols)
+                bcols.append([k - 3, k - 2] if order != "mixed" else [k - 1, k - 3, k - 2])
+    acp = np.concatenate([[0], np.cumsum([len(r) for r in acols])]).astype(np.int32)
+    bcp = np.concatenate([[0], np.cumsum([len(b) for b in bcols])]).astype(np.int32)
+    ari = np.concatenate(acols).astype(np.int32)
+    bri = np.concatenate(bcols).astype(np.int32)
+    A = gen.CSC(m, len(acols), acp, ari, rng.standard_normal(len(ari)).astype(np_t))
+    B = gen.CSC(len(acols), len(bcols), bcp, bri, rng.standard_normal(len(bri)).astype(np_t))
+    ocp, ori, ov = oracle.spgemm(A, B, dtype)
+    cp, ri, v = api.matmul(api.CscTensor.from_host(A), api.CscTensor.from_host(B)).to_host()
+    assert_same_structure(cp, ri, ocp, ori, "clusters")
+    assert_values_exact(v, ov, "clusters")
