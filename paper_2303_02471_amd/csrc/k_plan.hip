@@ -87,13 +87,19 @@ __device__ __forceinline__ void publish_header(const KArgs &a, const PubArgs &pu
 //
 // What bounds it: the chain of dependent loads (B's row, A's column pointers)
 // of the tile with the most entries, so the tiles are cut fine (plan_tile) and
-// a pass's gathers are in flight together with the next pass's row loads.
-// 4096 columns of 40 entries: 76.5 us in 8 tiles of 512 columns, 8.5 us in 512
-// tiles of 8; 1000 columns of 5: 15.5 -> 7.3 us. A million power-law columns
-// stay at 70 us: 5 M gathers of A.colptr in tiles of 512.
+// a pass's gathers are in flight together with the next pass's row loads; then
+// the work per entry, so a column's count is a difference of two prefix sums
+// (an LDS search and a 64-bit LDS atomic per entry before). 4096 columns of 40
+// entries: 76.5 us in 8 tiles of 512 columns, 6.1 us in 512 tiles of 8; 1000
+// columns of 5: 15.5 -> 5.4 us; a million power-law columns (5 M gathers of
+// A.colptr): 70 -> 62 us with the prefix sums, a squared grid operator of
+// 250,000 columns 16.8 -> 12.0 us. (512 and 1024 threads per workgroup: 69 and
+// 78 us before the prefix sums; the loads in flight set the rest.)
 __global__ __launch_bounds__(kBlock) void k_classify(KArgs a) {
+    constexpr int U = 4, STEP = U * kBlock, PER = kTile / kBlock;
     __shared__ int s_bcp[kTile + 1];
-    __shared__ unsigned long long s_op[kTile];
+    __shared__ long long s_pre[STEP + 1];  // products before every entry of the pass
+    __shared__ long long s_wave[kBlock / 64];
     __shared__ int s_hist[NBINS];
     __shared__ int s_err, s_maxch;
     __shared__ unsigned long long s_tot, s_hp[kHeavyBins];
@@ -106,7 +112,6 @@ __global__ __launch_bounds__(kBlock) void k_classify(KArgs a) {
     const int tid = threadIdx.x;
 
     for (int c = tid; c <= nt; c += kBlock) s_bcp[c] = d.bcp[j0 + c];
-    for (int c = tid; c < nt; c += kBlock) s_op[c] = 0;
     if (tid < NBINS) s_hist[tid] = 0;
     if (tid < kHeavyBins) { s_hp[tid] = 0; s_hw[tid] = 0; }
     if (tid == 0) { s_err = 0; s_tot = 0; s_maxch = 0; }
@@ -133,38 +138,81 @@ __global__ __launch_bounds__(kBlock) void k_classify(KArgs a) {
     // with no A columns every stored B entry is out of range (and A.colptr
     // holds one entry: the pair loads below need two)
     if (d.k == 0 && pe > pb) err = ERR_CSC;
-    if (!s_err && d.k > 0 && pe > pb) {
-        // Passes of 4 kBlock entries. A slot past the tile's end reads its last
-        // entry, an index out of range reads A's first column pointers; neither
-        // result is used. Both column pointers come in one 8-byte load (4-byte
-        // alignment is enough for a global load): kc < k, so kc + 1 <= k.
-        constexpr int U = 4, STEP = U * kBlock;
+    unsigned long long op64[PER];  // products of column tid + kBlock v
+#pragma unroll
+    for (int v = 0; v < PER; ++v) op64[v] = 0;
+    const bool sound = s_err == 0;
+    __syncthreads();
+    if (sound && d.k > 0 && pe > pb) {
+        // Passes of STEP entries, U consecutive ones per thread. A slot past
+        // the tile's end reads its last entry, an index out of range reads A's
+        // first column pointers; neither result is used. Both column pointers
+        // come in one 8-byte load (4-byte alignment is enough for a global
+        // load): kc < k, so kc + 1 <= k.
+        typedef int int4a __attribute__((ext_vector_type(4), aligned(4)));
+        typedef int int4b __attribute__((ext_vector_type(4), aligned(8)));
         int kk[U], kn[U];
         int2a x[U];
         auto rows_at = [&](int p0, int (&k)[U]) {
+            const int p = p0 + U * tid;
+            if (p + U <= pe) {
+                const int4a r = *(const gmem<const int4a> *)(bri + p);
 #pragma unroll
-            for (int u = 0; u < U; ++u) k[u] = bri[min(p0 + u * kBlock + tid, pe - 1)];
-        };
-        auto pairs_of = [&](const int (&k)[U], int2a (&v)[U]) {
+                for (int u = 0; u < U; ++u) k[u] = r[u];
+            } else {
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                v[u] = load_pair(d.acp, (k[u] < 0 || k[u] >= d.k) ? 0 : k[u]);
+                for (int u = 0; u < U; ++u) k[u] = bri[min(p + u, pe - 1)];
+            }
         };
         rows_at(pb, kk);
         for (int p0 = pb; p0 < pe; p0 += STEP) {
-            pairs_of(kk, x);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                x[u] = load_pair(d.acp, (kk[u] < 0 || kk[u] >= d.k) ? 0 : kk[u]);
             if (p0 + STEP < pe) rows_at(p0 + STEP, kn);  // in flight beside the gathers
+            const int p = p0 + U * tid;
+            int s0[U], z[U];
+            long long sum = 0;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int p = p0 + u * kBlock + tid;
                 const int k = kk[u];
-                const bool in = p < pe;
+                const bool in = p + u < pe;
                 const bool ok = k >= 0 && k < d.k && x[u].x >= 0 && x[u].y >= x[u].x && x[u].y <= d.nnza;
-                const int s0 = ok ? x[u].x : 0, z = (in && ok) ? x[u].y - x[u].x : 0;
+                s0[u] = ok ? x[u].x : 0;
+                z[u] = (in && ok) ? x[u].y - x[u].x : 0;
                 if (in && !ok) err = ERR_CSC;
-                // the A column each stored B entry selects, for the accumulators
-                if (in) a.E[d.ebase + p] = make_int2(s0, z);
-                if (z > 0) atomicAdd(&s_op[last_le(s_bcp, nt + 1, p)], (unsigned long long)z);
+                sum += z[u];
+            }
+            // the A column each stored B entry selects, for the accumulators
+            int2 *E = a.E + d.ebase + p;
+            if (p + U <= pe) {
+                *(int4b *)(E) = int4b{s0[0], z[0], s0[1], z[1]};
+                *(int4b *)(E + 2) = int4b{s0[2], z[2], s0[3], z[3]};
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (p + u < pe) E[u] = make_int2(s0[u], z[u]);
+            }
+            const long long inc = wave_incl_scan64(sum);
+            if ((tid & 63) == 63) s_wave[tid >> 6] = inc;
+            __syncthreads();
+            long long run = inc - sum;
+            for (int w = 0; w < tid >> 6; ++w) run += s_wave[w];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                s_pre[U * tid + u] = run;
+                run += z[u];
+            }
+            if (tid == kBlock - 1) s_pre[STEP] = run;
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < PER; ++v) {
+                const int c = tid + kBlock * v;
+                if (c < nt) {
+                    const int b = min(max(s_bcp[c] - p0, 0), STEP);
+                    const int e = min(max(s_bcp[c + 1] - p0, 0), STEP);
+                    op64[v] += (unsigned long long)(s_pre[e] - s_pre[b]);
+                }
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) kk[u] = kn[u];
@@ -178,12 +226,14 @@ __global__ __launch_bounds__(kBlock) void k_classify(KArgs a) {
     int maxch = 0;
     err = 0;
     if (!s_err) {
-        for (int c = tid; c < nt; c += kBlock) {
+#pragma unroll
+        for (int v = 0; v < PER; ++v) {
+            const int c = tid + kBlock * v;
+            if (c >= nt) continue;
             const int g = d.col0 + j0 + c;
-            unsigned long long op64 = s_op[c];
-            if (op64 > 0x7fffffffull) { err = ERR_OPOVF; op64 = 0x7fffffffull; }
-            tot += op64;
-            const int op = (int)op64;
+            if (op64[v] > 0x7fffffffull) { err = ERR_OPOVF; op64[v] = 0x7fffffffull; }
+            tot += op64[v];
+            const int op = (int)op64[v];
             // the sort-merge bins take a column by its products or its stored B
             // entries, whichever is more (a work item holds both)
             const int size = max(op, s_bcp[c + 1] - s_bcp[c]);
@@ -206,7 +256,8 @@ __global__ __launch_bounds__(kBlock) void k_classify(KArgs a) {
     }
     // tile total of products
     if (err) atomicOr(&s_err, err);
-    atomicAdd(&s_tot, tot);
+    const long long wtot = wave_sum64((long long)tot);
+    if ((tid & 63) == 0) atomicAdd(&s_tot, (unsigned long long)wtot);
     if (maxch) atomicMax(&s_maxch, maxch);
     __syncthreads();
     // the tile's tallies (no device atomics: k_place or k_tally combine them),
