@@ -37,24 +37,25 @@ __device__ __forceinline__ int heavy_totals(const KArgs &a, long long prod, long
 }
 
 // The whole header of a launch whose place kernel combines the tiles itself
-// (one thread). With the product-space accumulators the header was cleared
-// before and another stream may already raise error bits in it.
+// (one wavefront, lane b with bin b). With the product-space accumulators the
+// header was cleared before and another stream may already raise error bits.
 __device__ __forceinline__ void place_header(const KArgs &a, int err, const int *counts,
                                              unsigned long long total, int maxch, long long hprod,
                                              long long hwin) {
     Hdr *h = a.hdr;
-    err &= ERR_CSC | ERR_OPOVF;
-    int start = 0;
-#pragma unroll 1
-    for (int b = 0; b < NBINS; ++b) {
-        h->bin_count[b] = counts[b];
+    const int b = lane_id();
+    const int n = b < NBINS ? counts[b] : 0;
+    const int start = wave_incl_scan(n) - n;
+    if (b < NBINS) {
+        h->bin_count[b] = n;
         h->bin_start[b] = start;
-        start += counts[b];
-        // a planned launch that does not cover a non-empty bin is redone
-        if (a.spec_total >= 0 && counts[b] > 0 && !((a.spec_mask >> b) & 1u)) err |= ERR_RETRY;
     }
-    // a planned launch sized for another product count is redone
+    err &= ERR_CSC | ERR_OPOVF;
+    // a planned launch that does not cover a non-empty bin is redone
+    if (ballot(n > 0 && !((a.spec_mask >> (b & 31)) & 1u)) && a.spec_total >= 0) err |= ERR_RETRY;
+    // and one sized for another product count
     if (a.spec_total >= 0 && total != (unsigned long long)a.spec_total) err |= ERR_RETRY;
+    if (b != 0) return;
     h->total_op = total;
     h->big_chunks = maxch;
     if (a.direct) {
@@ -263,8 +264,11 @@ __global__ __launch_bounds__(kBlock) void k_classify(KArgs a) {
     // the tile's tallies (no device atomics: k_place or k_tally combine them),
     // counts of at most kTile columns and the tile's error bits
     const int t = blockIdx.x;
-    if (tid < NBINS) a.th[tid * a.tpitch + t] = (uint16_t)s_hist[tid];
-    if (tid == NBINS) a.th[NBINS * a.tpitch + t] = (uint16_t)s_err;
+    if (tid <= NBINS) {
+        a.th[tid * a.tpitch + t] = (uint16_t)(tid < NBINS ? s_hist[tid] : s_err);
+        if (t == a.ntiles - 1)  // zeros up to the pitch
+            for (int x = a.ntiles; x < a.tpitch; ++x) a.th[tid * a.tpitch + x] = 0;
+    }
     if (tid < kHeavyBins) {
         a.tprod[tid * a.tpitch + t] = (long long)s_hp[tid];
         a.twin[tid * a.tpitch + t] = s_hw[tid];
@@ -400,14 +404,16 @@ hipError_t launch_tally(const KArgs &a, hipStream_t s) {
 // less than a tally launch before this one; a workgroup of its own writes the
 // header. With the header's clearing, a tally, this kernel and a one-workgroup
 // plan of the heavy columns as four launches: 6.2 + 5.0 + 2.7 us and the
-// clearing for 1000 columns, 9.1 us now; 6.2 + 5.0 + 10.4 us for 4096 columns
-// of 1600 products, 15 us now. With more tiles each workgroup would read too
-// much and k_tally scans the records first.
+// clearing for 1000 columns, 4.5 us now; 6.2 + 5.0 + 10.4 us for 4096 columns
+// of 1600 products, 9.7 us now. What bounds it is the header's workgroup (one
+// thread walking the bins took 5 us) and the chain of its loads. With more
+// tiles each workgroup would read too much and k_tally scans the records first.
 template <bool SELF>
 __global__ __launch_bounds__(kTile) void k_place(KArgs a, PubArgs pub) {
     constexpr int T = kTile, NW = T / 64, ROWS = NBINS + 1;  // one column per thread
     __shared__ int s_base[ROWS], s_total[ROWS], s_start[NBINS];
-    __shared__ int s_cnt[NW][NBINS];  // columns of every bin per wave, then prefix
+    __shared__ int s_cnt[NW][NBINS];  // columns of every bin per wave
+    __shared__ int s_at[NW][NBINS];   // the wave's first position in every bin
     __shared__ int s_w[NW][kHeavyBins];         // windows, then prefix
     __shared__ long long s_p[NW][kHeavyBins];   // products, then prefix
     __shared__ long long s_hpb[kHeavyBins], s_hpt[kHeavyBins];
@@ -432,13 +438,13 @@ __global__ __launch_bounds__(kTile) void k_place(KArgs a, PubArgs pub) {
     const int bin = in ? a.binw[col0 + j0 + tid] : -1;
     const int2a bse = in ? load_pair(bcp, j0 + tid) : int2a{0, 0};
     const int op = in ? a.op[col0 + j0 + tid] : 0;
+    // row r of the records: bin r's columns per tile; the last row error bits.
+    // Every load is issued before any is used.
+    constexpr int RW = (ROWS + NW - 1) / NW, CH = (kSelfTiles + 8 * 64 - 1) / (8 * 64);
+    uint4 v[SELF ? RW : 1][CH];
     unsigned long long ptot = 0;  // the header's product total and largest chunk count
     int pmax = 0;
     if (SELF) {
-        // row r of the records: bin r's columns per tile; the last row error
-        // bits. Every load is issued before any is used.
-        constexpr int RW = (ROWS + NW - 1) / NW, CH = (kSelfTiles + 8 * 64 - 1) / (8 * 64);
-        uint4 v[RW][CH];
 #pragma unroll
         for (int i = 0; i < RW; ++i) {
             const int r = min(w + i * NW, ROWS - 1);
@@ -450,6 +456,10 @@ __global__ __launch_bounds__(kTile) void k_place(KArgs a, PubArgs pub) {
             }
         }
         if (header) {
+            if (tid == 0) {
+                s_tot = 0;
+                s_max = 0;
+            }
 #pragma unroll
             for (int c = 0; c < (kSelfTiles + T - 1) / T; ++c) {
                 const int t = c * T + tid;
@@ -457,25 +467,39 @@ __global__ __launch_bounds__(kTile) void k_place(KArgs a, PubArgs pub) {
                 pmax = max(pmax, t < a.ntiles ? a.tmax[t] : 0);
             }
         }
+    } else if (tid < NBINS) {
+        s_base[tid] = a.tbase[tid * a.tpitch + mt];
+        s_total[tid] = a.hdr->bin_count[tid];
+    }
+    // ranks inside the wave, one ballot per bin that occurs in it
+    if (lane < NBINS) s_cnt[w][lane] = 0;
+    int rank = 0;
+    for (unsigned long long todo = ballot(in); todo;) {
+        const int b = __builtin_amdgcn_readlane(bin, __builtin_ctzll(todo));
+        const unsigned long long m = ballot(bin == b);
+        if (bin == b) rank = popc64(m & mask_lt());
+        if (lane == 0) s_cnt[w][b] = popc64(m);
+        todo &= ~m;
+    }
+    if (SELF) {
         // a word holds two tiles' counts, summed as pairs of 16 bits (a lane
-        // adds at most 24 tiles of kTile columns): all tiles, and those before
-        // this one by a mask per word
+        // adds at most 24 tiles of kTile columns): all tiles (the pitch is
+        // padded with zeros), and those before this one by a mask per word
         static_assert(8 * CH * kTile < 65536, "a lane's counts fit 16 bits");
         unsigned tot[RW], bef[RW];
 #pragma unroll
         for (int i = 0; i < RW; ++i) tot[i] = bef[i] = 0;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const int t0 = 8 * (c * 64 + lane);
+            const int left = mt - 8 * (c * 64 + lane);  // the lane's tiles before this one
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int left = mt - (t0 + 2 * q), live = a.ntiles - (t0 + 2 * q);
-                const unsigned mb = left >= 2 ? ~0u : (left == 1 ? 0xffffu : 0u);
-                const unsigned ml = live >= 2 ? ~0u : (live == 1 ? 0xffffu : 0u);
+                const unsigned mb = left >= 2 * q + 2 ? ~0u : (left == 2 * q + 1 ? 0xffffu : 0u);
 #pragma unroll
                 for (int i = 0; i < RW; ++i) {
-                    const unsigned x = (&v[i][c].x)[q] & ml;
-                    tot[i] = i == RW - 1 && w == NBINS % NW ? tot[i] | x : tot[i] + x;
+                    const unsigned x = (&v[i][c].x)[q];
+                    // (a tile's error bits repeat at most 24 times in a lane's sum)
+                    tot[i] += x;
                     bef[i] += x & mb;
                 }
             }
@@ -483,80 +507,63 @@ __global__ __launch_bounds__(kTile) void k_place(KArgs a, PubArgs pub) {
 #pragma unroll
         for (int i = 0; i < RW; ++i) {
             const int r = w + i * NW;
-            int total = (int)((tot[i] & 0xffffu) + (tot[i] >> 16));
-            if (i == RW - 1 && r == NBINS) {
-                const unsigned bits = (tot[i] | (tot[i] >> 16)) & 0xffffu;
-                total = (ballot((bits & ERR_CSC) != 0) ? ERR_CSC : 0) |
-                        (ballot((bits & ERR_OPOVF) != 0) ? ERR_OPOVF : 0);
-            } else {
-                total = wave_sum(total);
-            }
+            const int total = wave_sum((int)((tot[i] & 0xffffu) + (tot[i] >> 16)));
             const int before = wave_sum((int)((bef[i] & 0xffffu) + (bef[i] >> 16)));
             if (lane == 0 && r < ROWS) {
                 s_base[r] = before;
                 s_total[r] = total;
             }
         }
-        __syncthreads();
-    } else if (tid < NBINS) {
-        s_base[tid] = a.tbase[tid * a.tpitch + mt];
-        s_total[tid] = a.hdr->bin_count[tid];
     }
-    const int terr = SELF ? s_total[NBINS] : 0;
-    if (SELF && (terr & (ERR_CSC | ERR_OPOVF))) {
+    __syncthreads();
+    if (header) {
+        const unsigned long long p = (unsigned long long)wave_sum64((long long)ptot);
+        const int m = __builtin_amdgcn_readlane(wave_incl_max(pmax), 63);
+        if (lane == 0) {
+            atomicAdd(&s_tot, p);
+            atomicMax(&s_max, m);
+        }
+    }
+    if (SELF && s_total[NBINS] != 0) {
+        // some tile has found an error: which one, tile by tile
+        __shared__ int s_err;
+        if (tid == 0) s_err = 0;
+        __syncthreads();
+        int e = 0;
+        for (int t = tid; t < a.ntiles; t += T) e |= a.th[NBINS * a.tpitch + t];
+        if (e) atomicOr(&s_err, e);
+        __syncthreads();
         if (header) {
-            if (tid == 0) place_header(a, terr, s_total, 0, 0, 0, 0);
+            if (w == 0) place_header(a, s_err, s_total, 0, 0, 0, 0);
             publish_header(a, pub, tid, T);
         }
         return;  // every thread takes the same branch
     }
-    int rank = 0;
-    if (64 * w < nt) {
-#pragma unroll 1
-        for (int b = 0; b < NBINS; ++b) {
-            const unsigned long long m = ballot(bin == b);
-            if (bin == b) rank = popc64(m & mask_lt());
-            if (lane == 0) s_cnt[w][b] = popc64(m);
+    // exclusive prefix over the waves per bin, from the tile's first
+    // position in the bin
+    if (tid < NBINS) {
+        int start = 0;
+#pragma unroll
+        for (int b = 0; b < NBINS; ++b) start += b < tid ? s_total[b] : 0;
+        s_start[tid] = start;
+        if (!SELF && mt == 0) a.hdr->bin_start[tid] = start;
+        int run = start + s_base[tid];
+#pragma unroll
+        for (int x = 0; x < NW; ++x) {
+            s_at[x][tid] = run;
+            run += s_cnt[x][tid];
         }
-    } else if (lane < NBINS) {
-        s_cnt[w][lane] = 0;
     }
-    __syncthreads();
     int heavy = 0, nheavy = 0;
     for (int b = BIN_SORT2; b <= BIN_WSORT; ++b) nheavy += s_total[b];
     if (a.direct && nheavy > 0)
         for (int b = BIN_SORT2; b <= BIN_WSORT; ++b)
 #pragma unroll
             for (int x = 0; x < NW; ++x) heavy += s_cnt[x][b];
-    __syncthreads();
-    // exclusive prefix over the waves per bin, from the tile's first
-    // position in the bin
-    if (tid < NBINS) {
-        int start = 0, v[NW];
-#pragma unroll
-        for (int b = 0; b < NBINS; ++b) start += b < tid ? s_total[b] : 0;
-#pragma unroll
-        for (int x = 0; x < NW; ++x) v[x] = s_cnt[x][tid];
-        s_start[tid] = start;
-        if (!SELF && mt == 0) a.hdr->bin_start[tid] = start;
-        int run = start + s_base[tid];
-#pragma unroll
-        for (int x = 0; x < NW; ++x) {
-            s_cnt[x][tid] = run;
-            run += v[x];
-        }
-    }
-    if (header) {
-        if (tid == 0) {
-            s_tot = 0;
-            s_max = 0;
-        }
-        __syncthreads();
-        atomicAdd(&s_tot, ptot);
-        atomicMax(&s_max, pmax);
-    }
     // the heavy columns' products and windows before the tile
     const bool heavy_sums = a.direct && nheavy > 0 && (heavy || header);
+    int wex = 0;
+    long long pex = 0;
     if (heavy_sums) {
         if (SELF) {
             // one wave per heavy bin and kind of sum, every load issued first
@@ -599,68 +606,68 @@ __global__ __launch_bounds__(kTile) void k_place(KArgs a, PubArgs pub) {
             s_hpt[tid] = 0;
             s_hwt[tid] = 0;
         }
-    }
-    int wex = 0;
-    long long pex = 0;
-    if (heavy) {
-        // prefix inside the wave over the columns of the same heavy bin
+        if (heavy) {
+            // prefix inside the wave over the columns of the same heavy bin
 #pragma unroll 1
-        for (int c = 0; c < kHeavyBins; ++c) {
-            const bool mine = bin == BIN_SORT2 + c;
-            int wt = 0;
-            long long pt = 0;
-            if (ballot(mine)) {
-                const int nw = mine ? heavy_windows(op) : 0;
-                const long long p = mine ? op : 0;
-                const int wi = wave_incl_scan(nw);
-                const long long pi = wave_incl_scan64(p);
-                if (mine) {
-                    wex = wi - nw;
-                    pex = pi - p;
+            for (int c = 0; c < kHeavyBins; ++c) {
+                const bool mine = bin == BIN_SORT2 + c;
+                int wt = 0;
+                long long pt = 0;
+                if (ballot(mine)) {
+                    const int nw = mine ? heavy_windows(op) : 0;
+                    const long long p = mine ? op : 0;
+                    const int wi = wave_incl_scan(nw);
+                    const long long pi = wave_incl_scan64(p);
+                    if (mine) {
+                        wex = wi - nw;
+                        pex = pi - p;
+                    }
+                    wt = __builtin_amdgcn_readlane(wi, 63);
+                    pt = wave_last64(pi);
                 }
-                wt = __builtin_amdgcn_readlane(wi, 63);
-                pt = wave_last64(pi);
-            }
-            if (lane == 0) {
-                s_w[w][c] = wt;
-                s_p[w][c] = pt;
+                if (lane == 0) {
+                    s_w[w][c] = wt;
+                    s_p[w][c] = pt;
+                }
             }
         }
     }
     __syncthreads();
-    if (header && tid == 0) {
-        long long p = 0, q = 0;
-        if (heavy_sums)
-            for (int c = 0; c < kHeavyBins; ++c) {
-                p += s_hpt[c];
-                q += s_hwt[c];
-            }
-        place_header(a, terr, s_total, s_tot, s_max, p, q);
-    }
     if (header) {
+        if (w == 0) {
+            long long p = 0, q = 0;
+            if (heavy_sums)
+                for (int c = 0; c < kHeavyBins; ++c) {
+                    p += s_hpt[c];
+                    q += s_hwt[c];
+                }
+            place_header(a, 0, s_total, s_tot, s_max, p, q);
+        }
         publish_header(a, pub, tid, T);
         return;
     }
-    if (heavy && tid < kHeavyBins) {
-        long long p = s_hpb[tid], q = s_hwb[tid];
-        if (SELF)
-            for (int c = 0; c < tid; ++c) {  // the heavy bins before this one
-                p += s_hpt[c];
-                q += s_hwt[c];
-            }
+    if (heavy) {
+        if (tid < kHeavyBins) {
+            long long p = s_hpb[tid], q = s_hwb[tid];
+            if (SELF)
+                for (int c = 0; c < tid; ++c) {  // the heavy bins before this one
+                    p += s_hpt[c];
+                    q += s_hwt[c];
+                }
 #pragma unroll 1
-        for (int x = 0; x < NW; ++x) {
-            const long long pv = s_p[x][tid];
-            const int wv = s_w[x][tid];
-            s_p[x][tid] = p;
-            s_w[x][tid] = (int)q;
-            p += pv;
-            q += wv;
+            for (int x = 0; x < NW; ++x) {
+                const long long pv = s_p[x][tid];
+                const int wv = s_w[x][tid];
+                s_p[x][tid] = p;
+                s_w[x][tid] = (int)q;
+                p += pv;
+                q += wv;
+            }
         }
+        __syncthreads();
     }
-    __syncthreads();
     if (!in) return;
-    const int g = col0 + j0 + tid, at = s_cnt[w][bin] + rank;
+    const int g = col0 + j0 + tid, at = s_at[w][bin] + rank;
     a.binlist[at] = make_int4(g, bse.x, bse.y - bse.x, op);
     if (heavy && bin >= BIN_SORT2 && bin <= BIN_WSORT) {
         const int h = bin - BIN_SORT2, li = at - s_start[BIN_SORT2];
