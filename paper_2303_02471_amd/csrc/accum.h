@@ -893,46 +893,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KPL == 16 ? 
 }
 
 // ---------------------------------------------------------------- wavefront groups
-// Bin `bin` holds columns of at most S products; G = N / S of them per wave.
-// One wavefront per workgroup: waves share nothing.
+// Group gi of a bin of columns of at most S products: G = N / S of them.
 template <typename K, typename V, int KPL, int S, bool FILL, bool MULTI>
-__global__ __launch_bounds__(64) void k_acc_wave(KArgs a, int bin) {
+__device__ __forceinline__ void group_item(const KArgs &a, GroupLds<V, 64 * KPL, FILL> &L,
+                                           int bin_first, int bin_cols, int gi, int lane,
+                                           int &bad) {
     constexpr int N = 64 * KPL, G = N / S;
     static_assert(S <= N && (N % S) == 0 && N <= (1 << kKeyBits), "segments tile the buffer");
-    __shared__ GroupLds<V, N, FILL> L;
-    const BinRange br = bin_range<FILL>(a, bin, bin);
-    if (br.stop) return;
-    const int lane = threadIdx.x;
-    const int ngroups = ceil_div(br.count, G);
-    int bad = 0;
-    for (int gi = blockIdx.x; gi < ngroups; gi += gridDim.x) {
-        const int first = br.first + gi * G, ncol = min(G, br.count - gi * G);
-        int c0 = 0;
-        do {
-            // the columns from c0 on, lane c holding column c0 + c
-            int4 ent = lane < ncol - c0 ? a.binlist[first + c0 + lane] : make_int4(0, 0, 0, 0);
-            if (ballot(ent.w > S || ent.z > N)) {  // cannot happen for unchanged inputs
-                bad = 1;
-                break;
-            }
-            int nc = ncol - c0;
-            const Prob d = prob_of<MULTI>(a, ent.x);
-            if constexpr (MULTI) {
-                // a group may cross problems (bins are filled problem by
-                // problem): the columns of the first one's are an item
-                const unsigned long long other =
-                    ballot(lane < nc && (ent.x < d.col0 || ent.x >= d.col0 + d.n));
-                if (other) nc = __builtin_ctzll(other);
-                if (lane >= nc) ent = make_int4(0, 0, 0, 0);
-            }
-            wave_item<K, V, KPL, S, FILL>(a, d, L, ent, nc, lane, bad);
-            c0 += nc;
-        } while (MULTI && c0 < ncol);
-    }
-    // an output count other than the planned one: other inputs, or (a
-    // numeric phase run at a previous structure's positions) a redo
-    if (ballot(bad != 0) && lane == 0)
-        atomicOr(&a.hdr->err, a.spec_fill ? ERR_RETRY : ERR_GROUP);
+    const int first = bin_first + gi * G, ncol = min(G, bin_cols - gi * G);
+    int c0 = 0;
+    do {
+        // the columns from c0 on, lane c holding column c0 + c
+        int4 ent = lane < ncol - c0 ? a.binlist[first + c0 + lane] : make_int4(0, 0, 0, 0);
+        if (ballot(ent.w > S || ent.z > N)) {  // cannot happen for unchanged inputs
+            bad = 1;
+            break;
+        }
+        int nc = ncol - c0;
+        const Prob d = prob_of<MULTI>(a, ent.x);
+        if constexpr (MULTI) {
+            // a group may cross problems (bins are filled problem by
+            // problem): the columns of the first one's are an item
+            const unsigned long long other =
+                ballot(lane < nc && (ent.x < d.col0 || ent.x >= d.col0 + d.n));
+            if (other) nc = __builtin_ctzll(other);
+            if (lane >= nc) ent = make_int4(0, 0, 0, 0);
+        }
+        wave_item<K, V, KPL, S, FILL>(a, d, L, ent, nc, lane, bad);
+        c0 += nc;
+    } while (MULTI && c0 < ncol);
 }
 
 // ---------------------------------------------------------------- one column per lane
@@ -943,21 +932,20 @@ __global__ __launch_bounds__(64) void k_acc_wave(KArgs a, int bin) {
 // LDS slots. Keys (row << LB | position) are 32-bit while rows stay below
 // 2^(32 - LB) - 1.
 template <typename K, typename V, int L, bool FILL, bool MULTI>
-__global__ __launch_bounds__(64) void k_acc_lane(KArgs a, int bin) {
+__device__ __forceinline__ void lane_item(const KArgs &a, V *sval, int start, int cnt, int gi,
+                                          int lane, int &bad) {
     constexpr int LB = L <= 4 ? 2 : (L <= 8 ? 3 : 4);
     static_assert((1 << LB) == L, "L is 4, 8 or 16");
     constexpr K KMAX = KeyTraits<K>::kmax;
-    __shared__ V sval[FILL ? 64 * L : 1];
-    const BinRange br = bin_range<FILL>(a, bin, bin);
-    if (br.stop) return;
-    const int lane = threadIdx.x, start = br.first, cnt = br.count;
-    int bad = 0, badrow = 0, kmax = 0;
-    for (int ci = blockIdx.x * 64 + lane; ci < cnt; ci += gridDim.x * 64) {
+    int badrow = 0, kmax = 0;
+    const int ci = gi * 64 + lane;
+    do {  // (once; a lane that is done leaves it)
+        if (ci >= cnt) break;
         const int4 ent = a.binlist[start + ci];
         const int g = ent.x, bs = ent.y, nb = ent.z, op = ent.w;
         if (op > L || nb > L) {  // cannot happen for unchanged inputs
             bad = 1;
-            continue;
+            break;
         }
         // (the lanes' columns may belong to several problems)
         const Prob d = MULTI ? a.table[find_prob(a, g)] : a.single;
@@ -994,7 +982,7 @@ __global__ __launch_bounds__(64) void k_acc_lane(KArgs a, int bin) {
         }
         if (run != op) {  // entries do not add up to the product count
             bad = 1;
-            continue;
+            break;
         }
         // product p belongs to the entry after the ones ending at or before p
         int q[L];
@@ -1071,7 +1059,7 @@ __global__ __launch_bounds__(64) void k_acc_lane(KArgs a, int bin) {
         if (FILL) {
             if (nd != clen) {
                 bad = 1;
-                continue;
+                break;
             }
             gmem<int32_t> *cri = to_gmem(d.cri);
             gmem<V> *cv = to_gmem((V *)d.cv);
@@ -1092,17 +1080,70 @@ __global__ __launch_bounds__(64) void k_acc_lane(KArgs a, int bin) {
                 }
             }
         }
-    }
+    } while (false);
     if (ballot(badrow) && lane == 0) atomicOr(&a.hdr->err, ERR_CSC);
-    if (ballot(bad != 0) && lane == 0)
-        atomicOr(&a.hdr->err, FILL && a.spec_fill ? ERR_RETRY : ERR_GROUP);
-    if (!FILL || a.spec_fill) {
-#pragma unroll
-        for (int dd = 32; dd >= 1; dd >>= 1)
-            kmax = max(kmax, __builtin_amdgcn_ds_bpermute((lane ^ dd) << 2, kmax));
+    if ((!FILL || a.spec_fill) && ballot(kmax > 0)) {
+        kmax = __builtin_amdgcn_readlane(wave_incl_max(kmax), 63);
         if (lane == 0 && kmax > __atomic_load_n(&a.hdr->later_maxk, __ATOMIC_RELAXED))
             atomicMax(&a.hdr->later_maxk, kmax);
     }
+    wsync();
+}
+
+// ---------------------------------------------------------------- light columns
+// Columns of at most 256 products: the bins of `mask` (bit i: ESC sub-bin i),
+// largest first, in one launch. Sub-bins 0 and 1 (at most 4, 8 products) take
+// 64 columns an item, one per lane; sub-bin i >= 2 (at most 4 << i products)
+// 64 >> i columns in segments of 4 << i (measured: segments of 16 beat a lane
+// per column by 16%, segments of 8 lose by 14%). One wavefront per workgroup:
+// waves share nothing. The item's bin is found from the header's counts. With
+// a launch per bin the chip drained between them and the host paid 4 to 5 us
+// for each: whole product of a 1M-column power law 542 us, now 530, of a
+// 300k-column one (f32) 223, now 214, numeric phase of a 400k one 205, now 192.
+constexpr int kLightBins = kEscBins;
+__host__ __device__ constexpr int light_columns(int i) { return i < kLaneSubBins ? 64 : 64 >> i; }
+
+template <typename K, typename V, bool FILL, bool MULTI>
+__global__ __launch_bounds__(64) void k_acc_light(KArgs a, unsigned mask) {
+    __shared__ union {
+        GroupLds<V, 256, FILL> g;
+        V lanes[FILL ? 64 * 8 : 1];
+    } L;
+    cmem<Hdr> *h = (cmem<Hdr> *)a.hdr;
+    if ((h->err | (FILL ? h->cap_over : 0)) != 0) return;
+    const int lane = threadIdx.x;
+    int bad = 0;
+    for (int i = blockIdx.x;; i += gridDim.x) {
+        int gi = i, bin = -1, first = 0, cols = 0;
+#pragma unroll
+        for (int b = kLightBins - 1; b >= 0; --b) {
+            const int n = (mask >> b) & 1u ? h->bin_count[BIN_ESC0 + b] : 0;
+            const int items = (n + light_columns(b) - 1) / light_columns(b);
+            if (bin < 0) {
+                if (gi < items) {
+                    bin = b;
+                    cols = n;
+                    first = h->bin_start[BIN_ESC0 + b];
+                } else {
+                    gi -= items;
+                }
+            }
+        }
+        if (bin < 0) break;
+        switch (bin) {
+            case 0: lane_item<K, V, 4, FILL, MULTI>(a, L.lanes, first, cols, gi, lane, bad); break;
+            case 1: lane_item<K, V, 8, FILL, MULTI>(a, L.lanes, first, cols, gi, lane, bad); break;
+            case 2: group_item<K, V, 4, 16, FILL, MULTI>(a, L.g, first, cols, gi, lane, bad); break;
+            case 3: group_item<K, V, 4, 32, FILL, MULTI>(a, L.g, first, cols, gi, lane, bad); break;
+            case 4: group_item<K, V, 4, 64, FILL, MULTI>(a, L.g, first, cols, gi, lane, bad); break;
+            case 5: group_item<K, V, 4, 128, FILL, MULTI>(a, L.g, first, cols, gi, lane, bad); break;
+            default: group_item<K, V, 4, 256, FILL, MULTI>(a, L.g, first, cols, gi, lane, bad); break;
+        }
+    }
+    // an output count other than the planned one: other inputs, or (a
+    // numeric phase run at a previous structure's positions) a redo
+    if (ballot(bad != 0) && lane == 0)
+        atomicOr(&a.hdr->err, a.spec_fill ? ERR_RETRY : ERR_GROUP);
 }
 
 // ---------------------------------------------------------------- heavy columns
@@ -1368,42 +1409,48 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
 }
 
 // ---------------------------------------------------------------- launchers
-// ESC sub-bins 0 and 1 (at most 4, 8 products): one column per lane. ESC
-// sub-bin i >= 2 (at most 4 << i products): KPL = 4 (256 positions), segments
-// of 4 << i (measured: segments of 16 beat a lane per column by 16%, segments
-// of 8 lose by 14%). Sort bins 0 and 1 (at most 512, 1024 products): one
-// column per wave, KPL = 8, 16. Larger columns are heavy.
 template <bool MULTI, typename K, typename V, bool FILL>
-static hipError_t launch_wave_bin(const KArgs &a, int bin, int grid, hipStream_t s) {
-    const dim3 g(grid), t(64);
-    switch (bin) {
-        case BIN_ESC0 + 0: hipLaunchKernelGGL((k_acc_lane<K, V, 4, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_ESC0 + 1: hipLaunchKernelGGL((k_acc_lane<K, V, 8, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_ESC0 + 2: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 16, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_ESC0 + 3: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 32, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_ESC0 + 4: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 64, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_ESC0 + 5: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 128, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_ESC0 + 6: hipLaunchKernelGGL((k_acc_wave<K, V, 4, 256, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_SORT0 + 0: hipLaunchKernelGGL((k_acc_one<K, V, 8, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        case BIN_SORT0 + 1: hipLaunchKernelGGL((k_acc_one<K, V, 16, FILL, MULTI>), g, t, 0, s, a, bin); break;
-        default: return hipErrorInvalidValue;
-    }
+static hipError_t launch_light_k(const KArgs &a, unsigned mask, int items, hipStream_t s) {
+    hipLaunchKernelGGL((k_acc_light<K, V, FILL, MULTI>), dim3(items), dim3(64), 0, s, a, mask);
+    return hipGetLastError();
+}
+template <bool MULTI, typename K, typename V, bool FILL>
+static hipError_t launch_one_k(const KArgs &a, int bin, int items, hipStream_t s) {
+    if (bin == BIN_SORT0)
+        hipLaunchKernelGGL((k_acc_one<K, V, 8, FILL, MULTI>), dim3(items), dim3(64), 0, s, a, bin);
+    else
+        hipLaunchKernelGGL((k_acc_one<K, V, 16, FILL, MULTI>), dim3(items), dim3(64), 0, s, a, bin);
     return hipGetLastError();
 }
 
 template <bool MULTI>
-hipError_t launch_acc_wave_t(const KArgs &a, int bin, int items, bool wide, bool fill, bool f64,
-                           hipStream_t s) {
+hipError_t launch_acc_light_t(const KArgs &a, unsigned mask, int items, bool wide, bool fill,
+                              bool f64, hipStream_t s) {
     if (items <= 0) return hipSuccess;
-    if (!fill) {
-        return wide ? launch_wave_bin<MULTI, unsigned long long, float, false>(a, bin, items, s)
-                    : launch_wave_bin<MULTI, unsigned, float, false>(a, bin, items, s);
-    }
+    using W = unsigned long long;
+    if (!fill)
+        return wide ? launch_light_k<MULTI, W, float, false>(a, mask, items, s)
+                    : launch_light_k<MULTI, unsigned, float, false>(a, mask, items, s);
     if (f64)
-        return wide ? launch_wave_bin<MULTI, unsigned long long, double, true>(a, bin, items, s)
-                    : launch_wave_bin<MULTI, unsigned, double, true>(a, bin, items, s);
-    return wide ? launch_wave_bin<MULTI, unsigned long long, float, true>(a, bin, items, s)
-                : launch_wave_bin<MULTI, unsigned, float, true>(a, bin, items, s);
+        return wide ? launch_light_k<MULTI, W, double, true>(a, mask, items, s)
+                    : launch_light_k<MULTI, unsigned, double, true>(a, mask, items, s);
+    return wide ? launch_light_k<MULTI, W, float, true>(a, mask, items, s)
+                : launch_light_k<MULTI, unsigned, float, true>(a, mask, items, s);
+}
+
+template <bool MULTI>
+hipError_t launch_acc_one_t(const KArgs &a, int bin, int items, bool wide, bool fill, bool f64,
+                            hipStream_t s) {
+    if (items <= 0) return hipSuccess;
+    using W = unsigned long long;
+    if (!fill)
+        return wide ? launch_one_k<MULTI, W, float, false>(a, bin, items, s)
+                    : launch_one_k<MULTI, unsigned, float, false>(a, bin, items, s);
+    if (f64)
+        return wide ? launch_one_k<MULTI, W, double, true>(a, bin, items, s)
+                    : launch_one_k<MULTI, unsigned, double, true>(a, bin, items, s);
+    return wide ? launch_one_k<MULTI, W, float, true>(a, bin, items, s)
+                : launch_one_k<MULTI, unsigned, float, true>(a, bin, items, s);
 }
 
 template <bool MULTI>

@@ -294,14 +294,24 @@ hipError_t launch_later_runs(const KArgs &a, bool f64, long long n, hipStream_t 
 // fill = false: distinct rows per column (gnnz; window counts of heavy
 // columns); fill = true: rows and values of C. wide: 64-bit keys (rows of
 // 2^21 - 1 and more).
-int wave_bin_items(int bin, int ncols);
+// light: the ESC sub-bins of `mask` (columns of at most 256 products) in one
+// launch; one: bin SORT0 or SORT0 + 1 (at most 512, 1024), a wavefront each.
+int light_items(const int32_t *bin_count, unsigned mask);
 template <bool MULTI>
-hipError_t launch_acc_wave_t(const KArgs &a, int bin, int items, bool wide, bool fill, bool f64,
-                             hipStream_t s);
-inline hipError_t launch_acc_wave(const KArgs &a, int bin, int items, bool wide, bool fill,
-                                  bool f64, hipStream_t s) {
-    return a.nprob == 1 ? launch_acc_wave_t<false>(a, bin, items, wide, fill, f64, s)
-                        : launch_acc_wave_t<true>(a, bin, items, wide, fill, f64, s);
+hipError_t launch_acc_light_t(const KArgs &a, unsigned mask, int items, bool wide, bool fill,
+                              bool f64, hipStream_t s);
+template <bool MULTI>
+hipError_t launch_acc_one_t(const KArgs &a, int bin, int items, bool wide, bool fill, bool f64,
+                            hipStream_t s);
+inline hipError_t launch_acc_light(const KArgs &a, unsigned mask, int items, bool wide, bool fill,
+                                   bool f64, hipStream_t s) {
+    return a.nprob == 1 ? launch_acc_light_t<false>(a, mask, items, wide, fill, f64, s)
+                        : launch_acc_light_t<true>(a, mask, items, wide, fill, f64, s);
+}
+inline hipError_t launch_acc_one(const KArgs &a, int bin, int items, bool wide, bool fill,
+                                 bool f64, hipStream_t s) {
+    return a.nprob == 1 ? launch_acc_one_t<false>(a, bin, items, wide, fill, f64, s)
+                        : launch_acc_one_t<true>(a, bin, items, wide, fill, f64, s);
 }
 // global ESC with radix sort over groups of heavy columns (after the heavy
 // expansion); rowbits: bits of the largest row index

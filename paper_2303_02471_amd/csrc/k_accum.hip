@@ -4,17 +4,18 @@
 namespace spg {
 
 // (the other kind is instantiated in its own file)
-extern template hipError_t launch_acc_wave_t<true>(const KArgs &, int, int, bool, bool, bool,
-                                                   hipStream_t);
-extern template hipError_t launch_heavy_t<true>(const KArgs &, int, int, bool, bool, bool,
-                                                hipStream_t, bool, long long, int, int);
+extern template hipError_t launch_acc_light_t<true>(const KArgs &, unsigned, int, bool, bool, bool,
+                                               hipStream_t);
+extern template hipError_t launch_acc_one_t<true>(const KArgs &, int, int, bool, bool, bool, hipStream_t);
+extern template hipError_t launch_heavy_t<true>(const KArgs &, int, int, bool, bool, bool, hipStream_t,
+                                           bool, long long, int, int);
 
-// work items of a wave bin: 64 columns (one per lane: ESC sub-bins 0 and 1),
-// groups of columns (the other ESC sub-bins) or columns (sort bins)
-int wave_bin_items(int bin, int ncols) {
-    if (bin >= BIN_ESC0 && bin < BIN_ESC0 + kLaneSubBins) return ceil_div(ncols, 64);
-    if (bin >= BIN_ESC0 && bin < BIN_ESC0 + kEscBins) return ceil_div(ncols, 64 >> (bin - BIN_ESC0));
-    return ncols;
+// work items of the light bins of `mask` with these column counts
+int light_items(const int32_t *bin_count, unsigned mask) {
+    int n = 0;
+    for (int i = 0; i < kLightBins; ++i)
+        if ((mask >> i) & 1u) n += ceil_div(bin_count[BIN_ESC0 + i], light_columns(i));
+    return n;
 }
 
 // The heavy columns' launches one part at a time (the caller interleaves them
@@ -26,8 +27,10 @@ int heavy_parts(bool radix) { return radix ? 2 : 3; }
 // filling ones that follow it
 int heavy_first_part(bool radix, bool mapped) { return !radix && mapped ? 1 : 0; }
 
-template hipError_t launch_acc_wave_t<false>(const KArgs &, int, int, bool, bool, bool, hipStream_t);
+template hipError_t launch_acc_light_t<false>(const KArgs &, unsigned, int, bool, bool, bool,
+                                        hipStream_t);
+template hipError_t launch_acc_one_t<false>(const KArgs &, int, int, bool, bool, bool, hipStream_t);
 template hipError_t launch_heavy_t<false>(const KArgs &, int, int, bool, bool, bool, hipStream_t,
-                                          bool, long long, int, int);
+                                    bool, long long, int, int);
 
 }  // namespace spg

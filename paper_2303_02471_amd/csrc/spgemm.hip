@@ -902,13 +902,15 @@ spgemm_status ensure_lblock(spgemm_plan p, hipStream_t s) {
 }
 
 // The direct-gather accumulators of every bin, counting (fill = false) or
-// filling C, on three streams: the wavefront groups and lane bins of the
-// columns of at most 64 products on one side stream, the wavefront groups of
-// up to 256 and the one-column waves (up to 1024 products) on another, the
-// heavy columns (above 1024 products) on the caller's. The host takes
-// several microseconds per launch, so the order of the launches matters:
-// first every launch of the heavy chain but its last, then one launch per
-// stream in turn (each stream's first kernel early).
+// filling C, on up to three streams: the columns of at most 64 products, those
+// of at most 1024, and the heavy ones above. The first of these (heavy first)
+// that has work runs on the caller's stream, so one kind alone needs neither a
+// fork nor a join (a 500 x 500 grid's Laplacian squared, all columns of at most
+// 25 products: 127 us with its bins' two launches on a side stream, 106 with
+// their one launch on the caller's). The host takes several
+// microseconds per launch, so the order of the launches matters: first every
+// launch of the heavy chain but its last, then one launch per stream in turn
+// (each stream's first kernel early).
 struct LaunchQueue {
     const char *name;
     hipStream_t st;
@@ -926,42 +928,52 @@ hipError_t launch_direct_accumulators(spgemm_plan p, const KArgs &a, hipStream_t
     // fork and join cost more than the overlap gains
     const bool one = (p->flags & SPGEMM_ONE_STREAM) || h.total_op < kSmallProducts;
     if (!one && (e = ensure_side_streams(p))) return e;
-    auto on = [&](int i) { return one ? s : side(p, i, s); };
+    // kind 0: at most 64 products (or lane-per-column blocks), 1: heavy, 2: the others
+    const bool lbk = (p->flags & SPGEMM_LANE_BLOCKED) != 0;
+    unsigned light[2] = {0, 0};  // ESC sub-bins of kinds 0 and 2
+    for (int i = 0; i < kEscBins; ++i)
+        if (h.bin_count[BIN_ESC0 + i] && !(lbk && i < p->lb.nsub))
+            light[i < kEscSide0 ? 0 : 1] |= 1u << i;
+    int nlb = 0;  // columns in lane-per-column blocks
+    if (lbk)
+        for (int i = 0; i < p->lb.nsub; ++i) nlb += h.bin_count[BIN_ESC0 + i];
+    const int nheavy =
+        h.bin_count[BIN_SORT2] + h.bin_count[BIN_SORT3] + h.bin_count[BIN_WSORT];
+    bool work[3] = {light[0] != 0 || nlb > 0, nheavy > 0,
+                    light[1] != 0 || h.bin_count[BIN_SORT0] > 0 || h.bin_count[BIN_SORT0 + 1] > 0};
+    // the lane blocks' launch always runs: it leaves their histogram cleared
+    work[0] = work[0] || lbk;
+    // a small product's light columns are one launch
+    if (one) {
+        light[0] |= light[1];
+        light[1] = 0;
+    }
+    const int mine = work[1] ? 1 : (work[0] ? 0 : 2);  // the kind on the caller's stream
     unsigned used = 0;
     if (!one) {
-        for (int i = 0; i < kEscBins; ++i)
-            if (h.bin_count[BIN_ESC0 + i]) used |= i < kEscSide0 ? 1u : 2u;
-        for (int c = 0; c < 2; ++c)
-            if (h.bin_count[BIN_SORT0 + c]) used |= 2u;
+        if (work[0] && mine != 0) used |= 1u;
+        if (work[2] && mine != 2) used |= 2u;
     }
+    auto on = [&](int kind) {
+        return one || kind == mine || kind == 1 ? s : side(p, kind == 0 ? 0 : 1, s);
+    };
     if ((e = fork(p, s, used))) return e;
     LaunchQueue q[3] = {{fill ? "esc_numeric" : "esc_symbolic", on(0), {}},
                         {fill ? "heavy_numeric" : "heavy_symbolic", s, {}},
-                        {fill ? "wave_numeric" : "wave_symbolic", on(1), {}}};
-    // side stream 0: the lightest sub-bins as lane-per-column blocks (option),
-    // then the wavefront sub-bins from the largest down
-    const bool lbk = (p->flags & SPGEMM_LANE_BLOCKED) != 0;
+                        {fill ? "wave_numeric" : "wave_symbolic", on(2), {}}};
     if (lbk) {
-        int nl = 0;
-        for (int i = 0; i < p->lb.nsub; ++i) nl += h.bin_count[BIN_ESC0 + i];
         const bool spars = (p->flags & SPGEMM_LANE_SPARS) != 0;
         const hipStream_t se = q[0].st;
-        q[0].l.push_back([=, &a] { return launch_lane_blocked(a, p->lb, nl, p->lb_grid, spars, fill, f64, se); });
+        q[0].l.push_back([=, &a] { return launch_lane_blocked(a, p->lb, nlb, p->lb_grid, spars, fill, f64, se); });
     }
-    // (the sub-bins above 64 products go to side stream 1, below)
-    for (int i = std::min(kEscBins, kEscSide0) - 1; i >= 0; --i) {
-        if (lbk && i < p->lb.nsub) continue;
-        const int n = h.bin_count[BIN_ESC0 + i];
-        const hipStream_t se = q[0].st;
-        if (n)
-            q[0].l.push_back([=, &a] {
-                return launch_acc_wave(a, BIN_ESC0 + i, wave_bin_items(BIN_ESC0 + i, n), wide, fill,
-                                       f64, se);
-            });
-    }
-    // caller's stream: columns above 1024 products (bins SORT2, SORT3, WSORT)
-    const int nheavy =
-        h.bin_count[BIN_SORT2] + h.bin_count[BIN_SORT3] + h.bin_count[BIN_WSORT];
+    auto light_launch = [&](LaunchQueue &x, unsigned mask) {
+        if (!mask) return;
+        const int items = light_items(h.bin_count, mask);
+        const hipStream_t sl = x.st;
+        x.l.push_back([=, &a] { return launch_acc_light(a, mask, items, wide, fill, f64, sl); });
+    };
+    light_launch(q[0], light[0]);
+    // columns above 1024 products (bins SORT2, SORT3, WSORT)
     if (nheavy) {
         const bool radix = (p->flags & SPGEMM_RADIX_ESC) != 0;
         const int nwin = h.heavy_win, rowbits = p->rowbits;
@@ -972,23 +984,14 @@ hipError_t launch_direct_accumulators(spgemm_plan p, const KArgs &a, hipStream_t
                 return launch_heavy(a, nheavy, nwin, wide, fill, f64, s, radix, hp, rowbits, part);
             });
     }
-    // side stream 1: the one-column waves, 1024 products then 512, then the
-    // wavefront sub-bins above 64 products (the three streams then hold
-    // similar work on power-law inputs)
+    // the one-column waves, 1024 products then 512, then the groups above 64
+    // products (the three streams then hold similar work on power-law inputs)
     for (int c = 1; c >= 0; --c) {
         const int n = h.bin_count[BIN_SORT0 + c];
         const hipStream_t sw = q[2].st;
-        if (n) q[2].l.push_back([=, &a] { return launch_acc_wave(a, BIN_SORT0 + c, n, wide, fill, f64, sw); });
+        if (n) q[2].l.push_back([=, &a] { return launch_acc_one(a, BIN_SORT0 + c, n, wide, fill, f64, sw); });
     }
-    for (int i = kEscBins - 1; i >= kEscSide0; --i) {
-        const int n = h.bin_count[BIN_ESC0 + i];
-        const hipStream_t sw = q[2].st;
-        if (n)
-            q[2].l.push_back([=, &a] {
-                return launch_acc_wave(a, BIN_ESC0 + i, wave_bin_items(BIN_ESC0 + i, n), wide, fill,
-                                       f64, sw);
-            });
-    }
+    light_launch(q[2], light[1]);
     // on one stream the queues go one after the other (nothing to overlap;
     // each launch group's timing events then bracket only its own kernels)
     const bool interleave = !one;

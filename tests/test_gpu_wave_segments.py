@@ -127,3 +127,51 @@ def test_row_clusters(dtype):
     cp, ri, v = api.matmul(api.CscTensor.from_host(A), api.CscTensor.from_host(B)).to_host()
     assert_same_structure(cp, ri, ocp, ori, "clusters")
     assert_values_exact(v, ov, "clusters")
+
+
+@pytest.mark.parametrize("kinds", ["light", "groups", "waves", "light groups", "light waves heavy",
+                                   "light groups waves heavy"])
+@pytest.mark.parametrize("size", ["one stream", "streams"])
+def test_bins_share_launches(kinds, size):
+    """Every mix of the kinds of columns that are launched together, with a
+    bin's columns just below, at and just above whole work items, below and
+    above the product count from which the kinds run on streams of their own;
+    a kept plan then takes a B with other counts in every bin."""
+    print(f"[case] shared launches {kinds} {size}", flush=True)
+    counts = {"light": (4, 8, 16, 32, 64), "groups": (128, 256), "waves": (512, 1024),
+              "heavy": (1500, 5000)}
+    m = 8192
+    rng = np.random.default_rng(11)
+    lens = sorted({c // d for cs in counts.values() for c in cs for d in (1, 2)})
+    acols = [rng.permutation(m)[:z] for z in lens for _ in range(4)]
+    acp = np.concatenate([[0], np.cumsum([len(r) for r in acols])]).astype(np.int32)
+    A = gen.CSC(m, len(acols), acp, np.concatenate(acols).astype(np.int32),
+                rng.standard_normal(acp[-1]))
+
+    def b_matrix(shift):
+        cols = []
+        for kind in kinds.split():
+            for c in counts[kind]:
+                item = 64 if c <= 8 else max(1, 64 * 4 // c)
+                fill = 0 if size == "one stream" else (1 << 21) // (c * len(counts[kind]))
+                half = 4 * lens.index(c // 2)
+                for i in range(item * 2 + shift + fill):
+                    # two A columns of c / 2 rows, or one of them
+                    a, b = rng.choice(4, 2, replace=False)
+                    cols.append([half + a] if i % 9 == 8 and c > 4 else [half + a, half + b])
+        cols = [cols[i] for i in rng.permutation(len(cols))]
+        bcp = np.concatenate([[0], np.cumsum([len(b) for b in cols])]).astype(np.int32)
+        return gen.CSC(len(acols), len(cols), bcp, np.concatenate(cols).astype(np.int32),
+                       rng.standard_normal(bcp[-1]))
+
+    At = api.CscTensor.from_host(A)
+    plan = out = None
+    for shift in (-1, 0, 0, 1):
+        B = b_matrix(shift)
+        ocp, ori, ov = oracle.spgemm(A, B, "f64")
+        plan, *out, nnz = api.multiply(At, api.CscTensor.from_host(B), plan=plan, out=out)
+        torch.cuda.synchronize()
+        cpt, rit, vt = out
+        assert_same_structure(cpt.cpu().numpy(), rit[:nnz].cpu().numpy(), ocp, ori, kinds)
+        assert_values_exact(vt[:nnz].cpu().numpy(), ov, kinds)
+    plan.close()
