@@ -1164,22 +1164,41 @@ __global__ __launch_bounds__(kBlock) void k_win_map(KArgs a) {
 
 // Expansion of the heavy columns into the scratch: the row (and in FILL the
 // value A(i,k) B(k,j)) of every product, in Algorithm 1's order. One workgroup
-// per heavy column (grid-stride), its stored B entries 256 at a time.
+// per column of at most 4096 products, up to `split` per longer one (each a
+// range of its stored B entries, kExpandEntries or more; its first product's
+// position is the sum of the lengths before it), 256 entries at a time. On its
+// own it is bound by the longest workgroup's rounds of gathers (10k-column
+// power law, 21 heavy columns: 44 us; whole product 143, now 116), on a full
+// chip by the 128-byte lines its short A columns touch.
+constexpr int kExpandEntries = 64;
 template <typename V, bool FILL, bool MULTI>
-__global__ __launch_bounds__(kBlock) void k_heavy_expand(KArgs a) {
+__global__ __launch_bounds__(kBlock) void k_heavy_expand(KArgs a, int split) {
     __shared__ int s_acp[kBlock], s_eoff[kBlock], scan_tmp[kBlock / 64 + 1];
     __shared__ V s_bv[FILL ? kBlock : 1];
     const BinRange br = bin_range<FILL>(a, kHeavyBin, BIN_WSORT);
     if (br.stop) return;  // the same in every thread
     const int first = br.first, n = br.count;
     const int tid = threadIdx.x;
+    const int nlong = ((cmem<Hdr> *)a.hdr)->bin_count[BIN_WSORT];
+    const int items = nlong * split + n - nlong;
     int bad = 0, rowbad = 0;
     // largest columns first (the heavy list runs from small to large bins):
     // the longest workgroups start before the short ones
-    for (int lj = blockIdx.x; lj < n; lj += gridDim.x) {
+    for (int it = blockIdx.x; it < items; it += gridDim.x) {
+        const bool parted = it < nlong * split;
+        const int lj = parted ? it / split : it - nlong * (split - 1);
         const int li = n - 1 - lj;
         const int4 ent = a.binlist[first + li];
         const int bs = ent.y, nb = ent.z;
+        // its entries [b0, b1)
+        int b0 = 0, b1 = nb;
+        if (parted) {
+            const int parts = min(split, (nb + kExpandEntries - 1) / kExpandEntries);
+            const int per = (nb + parts - 1) / parts;
+            b0 = min(nb, it % split * per);
+            b1 = min(nb, b0 + per);
+            if (b0 == b1) continue;
+        }
         const Prob d = prob_of<MULTI>(a, ent.x);
         const long long base0 = a.hoff[li], end = base0 + ent.w;
         const int2 *__restrict__ Ep = a.E + d.ebase;
@@ -1187,11 +1206,21 @@ __global__ __launch_bounds__(kBlock) void k_heavy_expand(KArgs a) {
         const gmem<const V> *__restrict__ av = to_gmem((const V *)d.av);
         const gmem<const V> *__restrict__ bvp = to_gmem((const V *)d.bv);
         long long base = base0;
-        for (int bw = 0; bw < nb; bw += kBlock) {
+        if (b0 > 0) {
+            int before = 0, sum;
+            for (int t = tid; t < b0; t += kBlock) before += Ep[bs + t].y;
+            block_excl_scan(before, scan_tmp, sum);
+            base += sum;
+            if (base < base0) {  // (the lengths do not add up to the product count)
+                bad = 1;
+                continue;
+            }
+        }
+        for (int bw = b0; bw < b1; bw += kBlock) {
             const int t = bw + tid;
             int z = 0, as = 0;
             V bval = V(0);
-            if (t < nb) {
+            if (t < b1) {
                 const int2 e = Ep[bs + t];
                 as = e.x;
                 z = e.y;
@@ -1203,8 +1232,8 @@ __global__ __launch_bounds__(kBlock) void k_heavy_expand(KArgs a) {
             s_eoff[tid] = ex;
             if (FILL) s_bv[tid] = bval;
             __syncthreads();
-            const int nbw = min(kBlock, nb - bw);
-            if (base + Ew > end) {  // more products than planned: inputs changed
+            const int nbw = min(kBlock, b1 - bw);
+            if (Ew < 0 || base + Ew > end) {  // more products than planned: inputs changed
                 bad = 1;
                 __syncthreads();
                 break;
@@ -1456,13 +1485,23 @@ hipError_t launch_acc_one_t(const KArgs &a, int bin, int items, bool wide, bool 
 template <bool MULTI>
 hipError_t launch_heavy_t(const KArgs &a, int ncols, int nwin, bool wide, bool fill, bool f64,
                         hipStream_t s, bool radix, long long heavy_products, int rowbits,
-                        int part) {
+                        int part, int nlong) {
     if (ncols <= 0) return hipSuccess;
     const bool expand = radix ? part == 0 : part == 1;
     if (expand) {
-        if (!fill) hipLaunchKernelGGL((k_heavy_expand<float, false, MULTI>), dim3(ncols), dim3(kBlock), 0, s, a);
-        else if (f64) hipLaunchKernelGGL((k_heavy_expand<double, true, MULTI>), dim3(ncols), dim3(kBlock), 0, s, a);
-        else hipLaunchKernelGGL((k_heavy_expand<float, true, MULTI>), dim3(ncols), dim3(kBlock), 0, s, a);
+        // the long columns' workgroups end last where the heavy columns do not
+        // fill the chip (8 workgroups on each of 256 CUs): split by 4 (400k
+        // power law, 1.1k heavy columns, numeric phase: 190 us, split 172; by
+        // 8: 180). Where they do, the parts only cost (1M, 3.7k heavy columns:
+        // 532 us, split 534, by 8: 537)
+        const int split = ncols <= 2048 ? 4 : 1;
+        const int grid = ncols + nlong * (split - 1);
+        if (!fill) hipLaunchKernelGGL((k_heavy_expand<float, false, MULTI>), dim3(grid), dim3(kBlock), 0, s, a,
+                                      split);
+        else if (f64) hipLaunchKernelGGL((k_heavy_expand<double, true, MULTI>), dim3(grid), dim3(kBlock), 0, s, a,
+                                      split);
+        else hipLaunchKernelGGL((k_heavy_expand<float, true, MULTI>), dim3(grid), dim3(kBlock), 0, s, a,
+                                      split);
         return hipGetLastError();
     }
     if (radix) return part == 1 ? launch_esc_radix(a, heavy_products, rowbits, fill, f64, s) : hipSuccess;

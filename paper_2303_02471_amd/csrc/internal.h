@@ -339,7 +339,7 @@ hipError_t launch_lane_blocked(const KArgs &a, const LbArgs &lb, int ncols_hint,
                                bool spars, bool fill, bool f64, hipStream_t s);
 
 // heavy columns: windows, or (radix) the global radix ESC; heavy_products and
-// rowbits size the radix launch
+// rowbits size the radix launch, nlong is the columns above 4096 products
 // part 0 .. heavy_parts(radix) - 1 of the heavy columns' launches, in order;
 // a launch whose windows are mapped already starts at heavy_first_part
 int heavy_parts(bool radix);
@@ -347,15 +347,15 @@ int heavy_first_part(bool radix, bool mapped);
 template <bool MULTI>
 hipError_t launch_heavy_t(const KArgs &a, int ncols, int nwin, bool wide, bool fill, bool f64,
                           hipStream_t s, bool radix, long long heavy_products, int rowbits,
-                          int part);
+                          int part, int nlong);
 inline hipError_t launch_heavy(const KArgs &a, int ncols, int nwin, bool wide, bool fill, bool f64,
                                hipStream_t s, bool radix, long long heavy_products, int rowbits,
-                               int part) {
+                               int part, int nlong) {
     return a.nprob == 1
                ? launch_heavy_t<false>(a, ncols, nwin, wide, fill, f64, s, radix, heavy_products,
-                                       rowbits, part)
+                                       rowbits, part, nlong)
                : launch_heavy_t<true>(a, ncols, nwin, wide, fill, f64, s, radix, heavy_products,
-                                      rowbits, part);
+                                      rowbits, part, nlong);
 }
 inline int row_bits(int m) { return m <= 1 ? 0 : 32 - __builtin_clz((unsigned)(m - 1)); }
 // Backward view, built once per single-problem plan (see k_backward.hip).

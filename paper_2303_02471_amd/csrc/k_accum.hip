@@ -8,7 +8,7 @@ extern template hipError_t launch_acc_light_t<true>(const KArgs &, unsigned, int
                                                hipStream_t);
 extern template hipError_t launch_acc_one_t<true>(const KArgs &, int, int, bool, bool, bool, hipStream_t);
 extern template hipError_t launch_heavy_t<true>(const KArgs &, int, int, bool, bool, bool, hipStream_t,
-                                           bool, long long, int, int);
+                                           bool, long long, int, int, int);
 
 // work items of the light bins of `mask` with these column counts
 int light_items(const int32_t *bin_count, unsigned mask) {
@@ -31,6 +31,6 @@ template hipError_t launch_acc_light_t<false>(const KArgs &, unsigned, int, bool
                                         hipStream_t);
 template hipError_t launch_acc_one_t<false>(const KArgs &, int, int, bool, bool, bool, hipStream_t);
 template hipError_t launch_heavy_t<false>(const KArgs &, int, int, bool, bool, bool, hipStream_t,
-                                    bool, long long, int, int);
+                                    bool, long long, int, int, int);
 
 }  // namespace spg

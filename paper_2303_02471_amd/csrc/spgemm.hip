@@ -981,7 +981,8 @@ hipError_t launch_direct_accumulators(spgemm_plan p, const KArgs &a, hipStream_t
         for (int part = heavy_first_part(radix, fill || a.spec_total >= 0);
              part < heavy_parts(radix); ++part)
             q[1].l.push_back([=, &a] {
-                return launch_heavy(a, nheavy, nwin, wide, fill, f64, s, radix, hp, rowbits, part);
+                return launch_heavy(a, nheavy, nwin, wide, fill, f64, s, radix, hp, rowbits, part,
+                                    h.bin_count[BIN_WSORT]);
             });
     }
     // the one-column waves, 1024 products then 512, then the groups above 64

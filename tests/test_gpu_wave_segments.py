@@ -175,3 +175,37 @@ def test_bins_share_launches(kinds, size):
         assert_same_structure(cpt.cpu().numpy(), rit[:nnz].cpu().numpy(), ocp, ori, kinds)
         assert_values_exact(vt[:nnz].cpu().numpy(), ov, kinds)
     plan.close()
+
+
+@pytest.mark.parametrize("nb", [1, 63, 64, 65, 129, 255, 257, 1030])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_long_columns_in_parts(nb, dtype):
+    """Columns of more than 4096 products of nb stored B entries (a part of a
+    column takes at least 64 of them), among entries whose A columns are empty
+    or hold most of the products, beside columns that are not split."""
+    print(f"[case] long columns {nb} {dtype}", flush=True)
+    np_t = np.float64 if dtype == "f64" else np.float32
+    rng = np.random.default_rng(13)
+    m = 9000
+    lens = np.full(nb, 5000 // nb + 1)
+    lens[rng.permutation(nb)[:nb // 3]] = 0
+    lens[nb // 2] = 4097  # the count's bulk, in the middle part
+    lens = np.concatenate([lens, [1500, 700, 30]])
+    acp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ari = np.concatenate([rng.permutation(m)[:z] for z in lens]).astype(np.int32)
+    long = np.arange(nb)
+    cols = [long, [nb], long[::-1], [nb, nb + 1, nb + 2], rng.permutation(nb), [nb + 2],
+            np.arange(nb + 3)]
+    bcp = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
+    A = gen.CSC(m, len(lens), acp, ari, rng.standard_normal(len(ari)).astype(np_t))
+    B = gen.CSC(len(lens), len(cols), bcp, np.concatenate(cols).astype(np.int32),
+                rng.standard_normal(bcp[-1]).astype(np_t))
+    ocp, ori, ov = oracle.spgemm(A, B, dtype)
+    At, Bt = api.CscTensor.from_host(A), api.CscTensor.from_host(B)
+    plan, out = None, None
+    for _ in range(2):
+        plan, *out, nnz = api.multiply(At, Bt, plan=plan, out=out)
+        torch.cuda.synchronize()
+        assert_same_structure(out[0].cpu().numpy(), out[1][:nnz].cpu().numpy(), ocp, ori, nb)
+        assert_values_exact(out[2][:nnz].cpu().numpy(), ov, nb)
+    plan.close()
