@@ -229,7 +229,7 @@ def accumulator_compare(reps=20):
              ("blocked lanes, HASH", {"lane_blocked": True}),
              ("blocked lanes, SPARS", {"lane_blocked": True, "lane_spars": True}),
              ("radix ESC for heavy columns", {"radix_esc": True}))
-    plan_groups = ("classify", "tally", "place", "heavy_plan", "scan", "product_offsets")
+    plan_groups = ("classify", "tally", "place", "scan", "product_offsets")
     out = []
     for name, A, B in cases:
         B = A if B is None else B
@@ -358,18 +358,17 @@ def copy_calibration():
 # launch group -> kernel symbol (FP64 runs)
 # launch groups whose HBM traffic --record-traffic can record: the kernels of
 # one launch of the group (their per-dispatch traffic adds up)
-KERNEL_SYMBOL = {"heavy_numeric": ("k_heavy_expand<double, true>",
-                                   "k_acc_window<unsigned int, double, true>"),
-                 "wave_numeric": ("k_acc_wave<unsigned int, double, 16, 1024, true>",
-                                  "k_acc_wave<unsigned int, double, 8, 512, true>",
-                                  "k_acc_wave<unsigned int, double, 4, 128, true>",
-                                  "k_acc_wave<unsigned int, double, 4, 256, true>"),
-                 "esc_numeric": ("k_acc_lane<unsigned int, double, 4, true>",
-                                 "k_acc_lane<unsigned int, double, 8, true>",
-                                 "k_acc_wave<unsigned int, double, 4, 16, true>",
-                                 "k_acc_wave<unsigned int, double, 4, 32, true>",
-                                 "k_acc_wave<unsigned int, double, 4, 64, true>"),
-                 "numeric": ("k_numeric<double>",), "expand": ("k_expand",)}
+# (symbol, i, n): the i-th of every n dispatches of the symbol, in launch order
+# (a step launches the light columns' kernel for the ones of at most 64
+# products, then for the others)
+LIGHT = "k_acc_light<unsigned int, double, true, false>"
+KERNEL_SYMBOL = {"heavy_numeric": (("k_heavy_expand<double, true, false>", 0, 1),
+                                   ("k_acc_window<unsigned int, double, true, false>", 0, 1)),
+                 "wave_numeric": (("k_acc_one<unsigned int, double, 16, true, false>", 0, 1),
+                                  ("k_acc_one<unsigned int, double, 8, true, false>", 0, 1),
+                                  (LIGHT, 1, 2)),
+                 "esc_numeric": ((LIGHT, 0, 2),),
+                 "numeric": (("k_numeric<double>", 0, 1),), "expand": (("k_expand", 0, 1),)}
 
 
 def _src_digest():
@@ -394,9 +393,10 @@ def _pmc_rows(d):
     return rows
 
 
-def _per_dispatch(rows, counter, symbol):
-    v = [float(r["Counter_Value"]) for r in rows
+def _per_dispatch(rows, counter, symbol, first=0, every=1):
+    v = [(int(r["Dispatch_Id"]), float(r["Counter_Value"])) for r in rows
          if r["Counter_Name"] == counter and symbol in r["Kernel_Name"]]
+    v = [x for _, x in sorted(v)][first::every]
     return sum(v) / len(v) if v else None, len(v)
 
 
@@ -410,15 +410,15 @@ def record_traffic(args):
     fetch = write = 0.0
     nf, nw = [], []
     for sym in syms:
-        f1, n1 = _per_dispatch(frows, "FETCH_SIZE", sym)
-        w1, n2 = _per_dispatch(wrows, "WRITE_SIZE", sym)
+        f1, n1 = _per_dispatch(frows, "FETCH_SIZE", *sym)
+        w1, n2 = _per_dispatch(wrows, "WRITE_SIZE", *sym)
         if f1 is None or w1 is None:
             raise SystemExit(f"no {sym} dispatch in the counter runs")
         fetch += f1
         write += w1
         nf.append(n1)
         nw.append(n2)
-    sym = list(syms)
+    sym = [s for s, _, _ in syms]
     cfetch, _ = _per_dispatch(_pmc_rows(cfdir), "FETCH_SIZE", "copyBuffer")
     cwrite, _ = _per_dispatch(_pmc_rows(cwdir), "WRITE_SIZE", "copyBuffer")
     gib_kib = float(1 << 20)
@@ -461,7 +461,7 @@ def per_column_work(A, B, t_esc=256, t_block=2 ** 31 - 1):
     esc = (op > 0) & (op <= esc_max)
     blk = (op > esc_max) & (op > t_block)
     srt = (op > esc_max) & ~blk
-    # direct-gather accumulators by stream: lane bins and wavefront groups of
+    # direct-gather accumulators by stream: columns per lane and wavefront groups of
     # at most 64 products (esc); wavefront groups above 64 and one-column
     # waves up to 1024 products (wave); heavy columns above (heavy)
     return op, nb, {"esc": esc & (op <= 64), "wave": (esc & (op > 64)) | (srt & (op <= 1024)),
@@ -598,7 +598,6 @@ def main():
     # one numeric launch does every column (tiles and chunks of large ones)
     kbytes["numeric"] = kernel_bytes(op, nb, nnzc, op > 0, vb)[0]
     heavy_prod = int(op[bins["heavy"]].sum())
-    kbytes["heavy_plan"] = 4 * int(bins["heavy"].sum())
     # expansion: (A column start, length) per stored B entry, A row read and
     # product row written per product
     kbytes["expand"] = 8 * B.nnz + 8 * int(op.sum())

@@ -9,24 +9,26 @@
 //          contiguously at the column's place in C.
 // Nothing per product is kept between the phases.
 //
-// Wave buffer. A wavefront holds N = 64 KPL positions, KPL consecutive
-// positions per lane (position s = KPL lane + r in register r). The columns of
-// a work item occupy aligned segments of S positions; a column's products fill
-// its segment in the order Algorithm 1 meets them (stored B entries in storage
-// order, then the rows of the selected A column in storage order), the rest of
-// the segment is padding that sorts last.
+// Wave buffer. A wavefront holds N = 64 KPL positions. The columns of a work
+// item occupy aligned segments of S positions: S / KPL neighbouring lanes, KPL
+// rows of them. A column's products fill its segment row by row in the order
+// Algorithm 1 meets them (stored B entries in storage order, then the rows of
+// the selected A column in storage order); the rest of the segment is padding
+// that sorts last.
 //
 // Gather. A product's address in A is (start of its entry's A column) +
-// (its position) - (the entry's first position). The wave writes, at the first
-// position of every stored B entry, that difference and the entry's B value
-// (a "head"); every other position takes the head before it (a forward fill,
-// first inside each lane's registers, then across lanes by a shuffle scan).
-// All of a lane's loads of A are then independent and issued together.
+// (its position) - (the entry's first position). The wave writes that
+// difference and the entry's B value (a "head") at the first position of every
+// stored B entry, and of every further row the entry reaches; a position's head
+// is the last one at or before it in its row, found from one ballot per row.
+// All of a lane's loads of A are then independent and issued together, and
+// neighbouring lanes read neighbouring entries of one A column.
 //
 // Sort and compress. Keys (row << 11 | position) are sorted inside every
-// segment by a bitonic network on registers (distances below KPL) and lanes
-// (DPP, ds_swizzle, ds_bpermute). Equal rows form runs whose positions are in
-// Algorithm 1's order; a run's head adds the run's values in that order.
+// segment by a bitonic network on registers and lanes (DPP, ds_swizzle,
+// permlane swaps), or, where one column fills the buffer, by order-preserving
+// buckets in LDS. Equal rows form runs whose positions are in Algorithm 1's
+// order; a run's values are added in that order.
 //
 // Heavy columns (more products than a wave buffer holds) are cut into row
 // windows of equal span, each an independent wave work item that compacts the

@@ -14,10 +14,11 @@ constexpr int kWave = 64;
 //   EMPTY      Op_j == 0: no output entries
 //   ESC_i      Op_j <= 4 << i (and <= t_esc): wavefront sort-merge (Section 4),
 //              64 >> i columns per wavefront group (at most 256 products)
-//   SORT_i     Op_j <= 512 << i: workgroup sort-merge, one column per
-//              workgroup of 128 << i threads
-//   WSORT      Op_j > 4096: the same sort over row windows of the column, one
-//              workgroup per column taking the windows in row order
+//              (<= 8 products: one column per lane)
+//   SORT_i     Op_j <= 512 << i: one column per wavefront (i = 0, 1)
+//   SORT_2, SORT_3, WSORT   Op_j <= 2048, <= 4096, above: heavy, a wavefront
+//              per row window of the column's expanded products
+//              (the product space's kernels: a workgroup per column)
 //   BLK_c      Op_j > t_block instead of SORT / WSORT (an option): one
 //              workgroup per column with an LDS table over
 //              row windows -- a direct-indexed SPA (Section 2.2) when the

@@ -1,14 +1,17 @@
 // Host side of the C ABI (include/spgemm.h): argument checks, plans, device
 // workspace, and the launch sequence of every phase.
 //
-// Symbolic:  classify (Op_j, accumulator bin) -> place (bin lists) ->
-//            product-space offsets -> expansion (row of every product) ->
-//            ESC / workgroup accumulators: distinct rows per column and the
-//            destination of every product -> prefix scan into the column
-//            pointers -> one device-to-host copy of the totals.
-// Numeric:   every product formed and written or staged through its
-//            destination, then the staged later products added in order.
-// Backward:  row view of B (once per plan) -> sampled products for dB, dA.
+// Symbolic:  classify (Op_j, accumulator bin) -> place (bin lists, layout of
+//            the heavy columns' scratch) -> accumulators counting the distinct
+//            rows of every column -> scan into the column pointers; the totals
+//            are published to mapped host memory.
+// Numeric:   the same accumulators, filling C. A planned one-call product runs
+//            them in place of the counting ones, at the previous structure's
+//            column pointers.
+//            (Options: the product space, with product offsets, an expansion of
+//            every product and a numeric launch through their destinations.)
+// Backward:  the products' places in C and in A's order (once per plan) ->
+//            sampled products for dB, dA.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1780,7 +1783,9 @@ void spgemm_release_pool(void) {
 // passes its name to a kernel or a copy: the address of each device's copy is
 // looked up once per device (hipGetSymbolAddress) and that pointer is carved.
 namespace {
-constexpr size_t kScratchBytes = size_t(128) << 20;
+// (64 KiB above 128 MiB: the alignment and the small tiles' records of a plan's
+// arrays stay out of what a problem may need)
+constexpr size_t kScratchBytes = (size_t(128) << 20) + (size_t(64) << 10);
 constexpr int kNoAllocDevices = 64;
 }  // namespace
 
