@@ -1335,16 +1335,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const int x = L.stk[2 * sp], y = L.stk[2 * sp + 1];
             wsync();
             // compact the window's products (product order) into the buffer,
-            // 8 rows per lane loaded before any is tested
+            // the next 8 rows per lane in flight while 8 are tested (the scan
+            // waits on its loads: 1M power law 525 us, with them ahead 518;
+            // numeric phase of a 400k one 180, 177)
             constexpr int U = 8;
             int cnt = 0;
+            int ahead[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) ahead[u] = u * 64 + lane < op ? prow[u * 64 + lane] : -1;
             for (int e0 = 0; e0 < op; e0 += 64 * U) {
                 int r[U], pos[U];
                 bool in[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int e = e0 + u * 64 + lane;
-                    r[u] = e < op ? prow[e] : -1;
+                    const int e = e0 + (U + u) * 64 + lane;
+                    r[u] = ahead[u];
+                    ahead[u] = e < op ? prow[e] : -1;
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
