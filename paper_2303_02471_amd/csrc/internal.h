@@ -214,8 +214,10 @@ struct KArgs {
     int32_t win_cap;        // from an earlier call that finds more is redone
     // Numeric phase run at the column positions of the plan's previous
     // structure (single problem, before this call's counts are scanned): it
-    // also records every column's entry count, and a count that differs
-    // from the previous structure asks for a redo (ERR_RETRY).
+    // also records every column's entry count. A light column whose count is
+    // not its place's, a heavy one that outgrows its place and a window whose
+    // count changed ask for a redo (ERR_RETRY); columns without products are
+    // not met, so the host compares the totals as well.
     int32_t spec_fill;
     int32_t *save;          // second copy of a single problem's column pointers (NULL: none)
 };

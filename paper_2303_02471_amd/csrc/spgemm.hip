@@ -1192,7 +1192,8 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
     // A planned one-call product on a plan whose last structure is known runs
     // its numeric phase now, at that structure's column positions, counting
     // every column's entries as it goes; the scan then builds this call's
-    // column pointers from those counts. A count that differs asks for a redo.
+    // column pointers from those counts. A count or a total that differs asks
+    // for a redo.
     const bool speculate = p->direct && spec && fo && p->nprob == 1 && p->saved_ok &&
                            p->saved_n == p->ncols && p->saved_total <= fo->cap && p->ncols > 0;
     PubArgs pub{nullptr, 0, 0};
@@ -1274,6 +1275,14 @@ spgemm_status symbolic_pass(spgemm_plan p, hipStream_t s, const std::vector<int4
         std::memcpy(p->totals_host.data(), (char *)p->pinned + kHdrBytes, 8 * (size_t)p->nprob);
     if (err & (ERR_GROUP | ERR_RETRY)) return SPGEMM_ERR_CSC;
     if (err & ERR_NNZOVF) return SPGEMM_ERR_INDEX_OVERFLOW;
+    // The accumulators compare only columns that have products now: a light
+    // one fills its old place exactly, a heavy one fits in it, and one that is
+    // empty now is met by none. So equal totals are what makes every column
+    // equal to the previous structure's.
+    if (speculate && p->totals_host[0] != p->saved_total) {
+        *retry = true;
+        return SPGEMM_OK;
+    }
     // products beyond the first of their entry (the staged later products of
     // the product-space accumulators)
     long long nnz_all = 0;

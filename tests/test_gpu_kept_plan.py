@@ -1,0 +1,59 @@
+"""Kept plans that meet other structures, options and value types than the ones
+their last call left behind, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2303_02471_amd import inputs as gen
+from helpers import HAVE_GPU, assert_same_structure, assert_values_exact
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not HAVE_GPU, reason="needs an MI355X GPU")]
+
+if HAVE_GPU:
+    import torch
+    from paper_2303_02471_amd import api
+
+
+def _csc(nrows, cols, seed):
+    cp = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
+    ri = np.concatenate([np.asarray(c, np.int32) for c in cols]).astype(np.int32)
+    return gen.CSC(nrows, len(cols), cp, ri, np.random.default_rng(seed).uniform(-1, 1, len(ri)))
+
+
+def _kept(A, Bs, what):
+    """One-call products A x B of every B in turn on one plan and its arrays."""
+    At = api.CscTensor.from_host(A)
+    plan, out = None, None
+    for step, B in enumerate(Bs):
+        Bt = api.CscTensor.from_host(B)
+        plan, cp, ri, v, nnz = api.multiply(At, Bt, plan=plan, out=out)
+        out = (cp, ri, v)
+        torch.cuda.synchronize()
+        want = oracle.spgemm(A, B)
+        assert nnz == int(want[0][-1]), f"{what}, step {step}"
+        assert_same_structure(cp.cpu().numpy(), ri[:nnz].cpu().numpy(), want[0], want[1],
+                              f"{what}, step {step}")
+        assert_values_exact(v[:nnz].cpu().numpy(), want[2], f"{what}, step {step}")
+    plan.close()
+
+
+def test_columns_without_products_now():
+    """Products and stored entries as many as before, every column that has
+    products as long as its old place, and a column that had some has none."""
+    print("[case] kept plan: a column loses its products", flush=True)
+    A = _csc(3, [[0, 1, 2], [0, 1, 2]], 1)
+    B1, B2 = (_csc(2, c, 2) for c in ([[0], [1], [0, 1], []], [[], [0, 1], [0, 1], []]))
+    _kept(A, (B1, B1, B2, B2, B1), "empty")
+
+
+def test_heavy_column_in_a_longer_place():
+    """A heavy column that is shorter than the place it now stands in, with the
+    window counts of the column that was heavy before."""
+    print("[case] kept plan: heavy and light columns exchanged", flush=True)
+    rng = np.random.default_rng(3)
+    rows = rng.permutation(4000)[:40]
+    A = _csc(4000, [rows[:20]] * 60 + [rows[20:]], 4)
+    heavy, two, one = list(range(60)), [0, 60], [0, 1]  # 1200 products, 20 rows; 40, 20 of 40
+    B1, B2 = _csc(61, [heavy, two], 5), _csc(61, [one, heavy], 5)
+    _kept(A, (B1, B1, B2, B2, B1), "heavy")

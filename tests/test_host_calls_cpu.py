@@ -1,0 +1,145 @@
+"""What the library's host side queues, in which order and on which stream, on
+the CPU: libspgemm.so bound to a stub of the HIP runtime (host/hip_stub.c) whose
+kernels do nothing and whose header readings come from the test. Every scenario
+runs in a process of its own (the stub has to be there before any HIP runtime).
+"""
+import ctypes as C
+import importlib.util
+import os
+import re
+import shutil
+import subprocess
+import sys
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+# words of the device header (csrc/internal.h): columns per bin, errors, products
+BIN_EMPTY, BIN_ESC0, BIN_SORT2, BIN_WSORT = 0, 1, 10, 12
+W_ERR, W_TOTAL_OP, W_HEAVY_PROD, W_HEAVY_WIN, W_NNZ = 36, 40, 42, 44, 48
+ERR_RETRY = 32
+S1, S2, S3 = 0x1000, 0x2000, 0x3000
+
+
+class Host:
+    """The library on the stub, with one 4 x 4 problem's arrays."""
+
+    def __init__(self, stub):
+        self.stub = C.CDLL(stub, mode=C.RTLD_GLOBAL)
+        self.stub.stub_log.restype = C.c_char_p
+        spec = importlib.util.spec_from_file_location(
+            "_lib", os.path.join(ROOT, "paper_2303_02471_amd", "_lib.py"))
+        self.lib = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(self.lib)
+        self.L = self.lib.lib()
+        self.words = (C.c_uint32 * 4096).in_dll(self.stub, "stub_words")
+        self.room = (C.c_double * 4096)()
+        self.plan = C.c_void_p()
+        self.nnz = C.c_int64()
+
+    def at(self, i):
+        return C.addressof(self.room) + 512 * i
+
+    def header(self, bins, total_op, nnz, heavy=(0, 0), err=0):
+        for i in range(64):
+            self.words[i] = 0
+        for b, n in bins.items():
+            self.words[b] = n
+        self.words[W_ERR], self.words[W_TOTAL_OP] = err, total_op
+        self.words[W_HEAVY_PROD], self.words[W_HEAVY_WIN] = heavy
+        self.words[W_NNZ] = nnz
+
+    def csc(self, base, nnz=8):
+        return self.lib.Csc(4, 4, nnz, self.at(base), self.at(base + 1), self.at(base + 2))
+
+    def options(self, **kw):
+        o = self.lib.Options()
+        for k, v in kw.items():
+            setattr(o, k, v)
+        return C.byref(o)
+
+    def multiply(self, stream=S1, dtype=1, opts=None, capacity=400):
+        a, b = self.csc(0), self.csc(3)
+        return self.L.spgemm_multiply(C.byref(a), C.byref(b), dtype, opts, stream,
+                                      C.byref(self.plan), self.at(6), self.at(7), self.at(8),
+                                      capacity, C.byref(self.nnz))
+
+    def symbolic(self, stream=S1, dtype=1, opts=None):
+        a, b = self.csc(0), self.csc(3)
+        return self.L.spgemm_symbolic(C.byref(a), C.byref(b), dtype, opts, stream,
+                                      C.byref(self.plan), self.at(6), C.byref(self.nnz))
+
+    def numeric(self, stream):
+        return self.L.spgemm_numeric(self.plan, self.at(2), self.at(5), self.at(7), self.at(8), stream)
+
+    def log(self):
+        lines = self.stub.stub_log().decode().split("\n")[:-1]
+        self.stub.stub_clear()
+        return lines
+
+    def capture(self, stream):
+        C.c_void_p.in_dll(self.stub, "stub_capturing").value = stream
+
+    def fail(self, call, on, code):
+        (C.c_char * 64).in_dll(self.stub, "stub_fail_call").value = call.encode()
+        C.c_void_p.in_dll(self.stub, "stub_fail_on").value = on
+        C.c_int.in_dll(self.stub, "stub_fail_code").value = code
+
+
+def count(log, what):
+    return sum(1 for x in log if re.search(what, x))
+
+
+def first(log, what):
+    return next(i for i, x in enumerate(log) if re.search(what, x))
+
+
+SCENARIOS = {}
+
+
+def scenario(f):
+    SCENARIOS[f.__name__] = f
+    return f
+
+
+@scenario
+def other_total_at_the_previous_positions_is_redone(h):
+    """A product run at the previous structure's positions whose own total is
+    another one: no kernel compares the columns that are empty now, so the
+    totals decide, and the numeric phase runs again at the new positions."""
+    h.header({BIN_EMPTY: 1, BIN_ESC0: 3}, 12, 9)
+    assert h.multiply() == 0 and h.nnz.value == 9
+    h.log()
+    assert h.multiply() == 0 and h.nnz.value == 9
+    same = h.log()
+    assert count(same, "k_classify") == 1 and count(same, "k_acc_light") == 1
+    h.header({BIN_EMPTY: 2, BIN_ESC0: 2}, 12, 6)
+    assert h.multiply() == 0 and h.nnz.value == 6
+    log = h.log()
+    assert count(log, "k_classify") == 2, log
+    # the last numeric launch comes after the scan that made the new pointers
+    assert first(log[::-1], "k_acc_light") < first(log[::-1], "k_scan_small"), log
+
+
+if __name__ != "__main__":
+    import pytest
+
+    @pytest.fixture(scope="module")
+    def stub(tmp_path_factory):
+        if shutil.which("gcc") is None:
+            pytest.skip("needs gcc")
+        if not os.path.exists(os.path.join(ROOT, "paper_2303_02471_amd", "libspgemm.so")):
+            from paper_2303_02471_amd import build
+            build.build()
+        so = str(tmp_path_factory.mktemp("stub") / "libhip_stub.so")
+        subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so,
+                        os.path.join(HERE, "host", "hip_stub.c")], check=True)
+        return so
+
+    @pytest.mark.parametrize("name", sorted(SCENARIOS))
+    def test_host_calls(stub, name):
+        r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, name],
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+else:
+    SCENARIOS[sys.argv[2]](Host(sys.argv[1]))
