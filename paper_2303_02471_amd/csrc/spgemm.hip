@@ -1436,6 +1436,14 @@ static spgemm_status symbolic_common(int32_t count, const spgemm_csc *A, const s
     if (!p) return SPGEMM_ERR_NO_MEMORY;
     const bool fresh = (*plan_inout == nullptr);
     if (fresh) p->allocator = current_allocator();
+    // What a planned launch takes over from the last call (the heavy scratch's
+    // index arrays and window counts, the staging of the later products) was
+    // made for that call's options and, in the product space, value type.
+    constexpr uint32_t kKinds =
+        SPGEMM_LANE_HASH | SPGEMM_LANE_BLOCKED | SPGEMM_LANE_SPARS | SPGEMM_RADIX_ESC;
+    if (((p->flags ^ flags) & kKinds) || std::memcmp(&p->tune, &tune, sizeof(Tune)) != 0 ||
+        (p->dt != dt && !p->direct))
+        p->spec_ready = false;
     p->dt = dt;
     p->batched = batched;
     p->nprob = count;

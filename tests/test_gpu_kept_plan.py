@@ -57,3 +57,26 @@ def test_heavy_column_in_a_longer_place():
     heavy, two, one = list(range(60)), [0, 60], [0, 1]  # 1200 products, 20 rows; 40, 20 of 40
     B1, B2 = _csc(61, [heavy, two], 5), _csc(61, [one, heavy], 5)
     _kept(A, (B1, B1, B2, B2, B1), "heavy")
+
+
+def test_options_and_types_change_on_one_plan():
+    """Every accumulator choice after every other one, and both value types, on
+    one plan with columns of every size class."""
+    print("[case] kept plan: options and types change", flush=True)
+    A, B = gen.powerlaw(20000, seed=6)
+    opts = [{}, {"radix_esc": True}, {}, {"lane_hash": True}, {"t_block": -1}, {"lane_blocked": True},
+            {"radix_esc": True}, {"t_esc": 32}, {"t_block": -1}]
+    plan, out = None, {"f64": None, "f32": None}
+    for step in range(2 * len(opts)):
+        kw, dt = opts[step // 2], ("f64", "f32")[(step + step // 2) % 2]
+        np_t = np.float64 if dt == "f64" else np.float32
+        a, b = A.astype(np_t), B.astype(np_t)
+        want = oracle.spgemm(a, b, dt)
+        plan, cp, ri, v, nnz = api.multiply(api.CscTensor.from_host(a), api.CscTensor.from_host(b),
+                                            opts=api.options(**kw), plan=plan, out=out[dt])
+        out[dt] = (cp, ri, v)
+        torch.cuda.synchronize()
+        what = f"step {step} {kw} {dt}"
+        assert_same_structure(cp.cpu().numpy(), ri[:nnz].cpu().numpy(), want[0], want[1], what)
+        assert_values_exact(v[:nnz].cpu().numpy(), want[2], what)
+    plan.close()

@@ -121,6 +121,26 @@ def other_total_at_the_previous_positions_is_redone(h):
     assert first(log[::-1], "k_acc_light") < first(log[::-1], "k_scan_small"), log
 
 
+@scenario
+def other_options_take_the_pass_with_the_read_back(h):
+    """A planned launch runs on what the last call left; after a call with other
+    options (or, in the product space, another value type) the sizes are read
+    back and the scratch made first: two publications instead of one."""
+    lib = h.lib
+    default, radix = h.options(), h.options(flags=lib.SPGEMM_RADIX_ESC)
+    hashed = h.options(flags=lib.SPGEMM_LANE_HASH)
+    h.header({BIN_EMPTY: 2, BIN_SORT2: 2}, 3000, 100, heavy=(3000, 4))
+    steps = ((default, 1, 2), (default, 1, 1), (radix, 1, 2), (radix, 1, 1), (default, 1, 2),
+             (default, 1, 1), (default, 0, 1),  # (the direct scratch fits either type)
+             (hashed, 0, 2), (hashed, 0, 1), (hashed, 1, 2), (hashed, 1, 1),
+             (h.options(flags=lib.SPGEMM_LANE_HASH, t_split=-1), 1, 2), (default, 1, 2),
+             (h.options(flags=lib.SPGEMM_ONE_STREAM), 1, 1))
+    for i, (opts, dtype, passes) in enumerate(steps):
+        assert h.multiply(dtype=dtype, opts=opts) == 0, i
+        log = h.log()
+        assert count(log, r"^publish") == passes, (i, log)
+
+
 if __name__ != "__main__":
     import pytest
 
