@@ -59,6 +59,23 @@ def test_heavy_column_in_a_longer_place():
     _kept(A, (B1, B1, B2, B2, B1), "heavy")
 
 
+def test_windows_that_no_launch_has_counted():
+    """Many windows of few products, then few windows of more (the scratch is
+    laid out anew), then as many products in more windows than the second call
+    counted but no more than the first."""
+    print("[case] kept plan: more windows than were counted", flush=True)
+    rng = np.random.default_rng(7)
+    A = gen.uniform_z(5000, 25, seed=8, nrows=4000)
+
+    def B(*entries):  # entries of the first columns of 100
+        cols = [rng.permutation(5000)[:n] for n in entries] + [[]] * (100 - len(entries))
+        return _csc(5000, cols, 9)
+
+    B2, B3 = B(5000, 41), B(2581, *[41] * 60)
+    assert 25 * B2.nnz == 25 * B3.nnz
+    _kept(A, (B(*[41] * 100), B2, B2, B3, B3), "windows")
+
+
 def test_options_and_types_change_on_one_plan():
     """Every accumulator choice after every other one, and both value types, on
     one plan with columns of every size class."""
