@@ -435,7 +435,9 @@ __global__ __launch_bounds__(kTile) void k_place(KArgs a, PubArgs pub) {
     // column tid of the tile: its entries and product count load with its bin
     const int32_t *bcp = a.nprob == 1 ? a.single.bcp : a.table[pid].bcp;
     const bool in = tid < nt;
-    const int bin = in ? a.binw[col0 + j0 + tid] : -1;
+    // (a tile that found malformed input has written no bins: any number may
+    // stand there, and it counts into the LDS before the error is known)
+    const int bin = in ? (int)min((unsigned)a.binw[col0 + j0 + tid], (unsigned)NBINS - 1u) : -1;
     const int2a bse = in ? load_pair(bcp, j0 + tid) : int2a{0, 0};
     const int op = in ? a.op[col0 + j0 + tid] : 0;
     // row r of the records: bin r's columns per tile; the last row error bits.
