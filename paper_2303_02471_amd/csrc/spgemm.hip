@@ -1600,6 +1600,8 @@ spgemm_status spgemm_batched(int32_t count, const spgemm_csc *A_host, const spge
                     std::memcmp(p->table_dev_copy.data(), p->probs.data(),
                                 sizeof(Prob) * p->probs.size()) == 0;
         if (!same) {
+            // the plan's earlier work, possibly on another stream, still reads it
+            SPG_TRY(order_plan(p, s));
             if (spgemm_status st = wait_upload(p)) return st;
             std::memcpy(p->mirror.room(), p->probs.data(), sizeof(Prob) * p->nprob);
             if (spgemm_status st = upload_table(p, sizeof(Prob) * p->nprob, s)) return st;

@@ -97,3 +97,29 @@ def test_options_and_types_change_on_one_plan():
         assert_same_structure(cp.cpu().numpy(), ri[:nnz].cpu().numpy(), want[0], want[1], what)
         assert_values_exact(v[:nnz].cpu().numpy(), want[2], what)
     plan.close()
+
+
+def test_batched_values_on_two_streams():
+    """New value and output arrays on another stream right behind the last call:
+    each call's kernels meet their own problem table."""
+    print("[case] kept plan: batched numeric on two streams", flush=True)
+    mats = [(gen.uniform_z(30000, 12, seed=20 + i), gen.uniform_z(30000, 12, seed=30 + i))
+            for i in range(2)]
+    dev = [tuple(api.CscTensor.from_host(x) for x in m) for m in mats]
+    plan, cps, nnzs = api.batched_symbolic(dev)
+    sets = []
+    for scale in (1.0, 2.0, 4.0, 8.0):
+        pairs = [(api.CscTensor(a.nrows, a.ncols, a.colptr, a.rowidx, a.val * scale), b) for a, b in dev]
+        sets.append((scale, pairs, [torch.zeros(z, dtype=torch.int32, device="cuda") for z in nnzs],
+                     [torch.zeros(z, dtype=torch.float64, device="cuda") for z in nnzs]))
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for i, (_, pairs, ris, vs) in enumerate(sets):
+        api.batched_numeric(plan, pairs, ris, vs, stream=streams[i % 2])
+    torch.cuda.synchronize()
+    for p, (A, B) in enumerate(mats):
+        want = oracle.spgemm(A, B)
+        for scale, _, ris, vs in sets:
+            assert_same_structure(cps[p].cpu().numpy(), ris[p].cpu().numpy(), want[0], want[1], f"{scale}")
+            assert_values_exact(vs[p].cpu().numpy(), scale * want[2], f"{scale}")
+    plan.close()

@@ -72,6 +72,19 @@ class Host:
     def numeric(self, stream):
         return self.L.spgemm_numeric(self.plan, self.at(2), self.at(5), self.at(7), self.at(8), stream)
 
+    def batched(self, stream, values=None):
+        """Size query of two problems, or (values: their value arrays) numeric."""
+        a, b = self.csc(0), self.csc(3)
+        if values:
+            a.val, b.val = self.at(values), self.at(values + 1)
+        As, Bs = (self.lib.Csc * 2)(a, a), (self.lib.Csc * 2)(b, b)
+        two = (C.c_void_p * 2)
+        nnz = (C.c_int64 * 2)()
+        return self.L.spgemm_batched(2, As, Bs, 1, None, stream, C.byref(self.plan),
+                                     two(self.at(6), self.at(7)), nnz,
+                                     two(self.at(8), self.at(9)) if values else None,
+                                     two(self.at(10), self.at(11)) if values else None)
+
     def log(self):
         lines = self.stub.stub_log().decode().split("\n")[:-1]
         self.stub.stub_clear()
@@ -139,6 +152,21 @@ def other_options_take_the_pass_with_the_read_back(h):
         assert h.multiply(dtype=dtype, opts=opts) == 0, i
         log = h.log()
         assert count(log, r"^publish") == passes, (i, log)
+
+
+@scenario
+def batch_table_waits_for_the_plans_earlier_work(h):
+    """New value arrays on another stream: the copy over the problem table, which
+    the last call's kernels read, is ordered behind them."""
+    h.header({BIN_ESC0: 8}, 40, 15)
+    h.words[W_NNZ + 2] = 15  # the second problem's
+    assert h.batched(S1) == 0
+    assert h.batched(S1, values=12) == 0
+    h.log()
+    assert h.batched(S2, values=14) == 0
+    log = h.log()
+    assert first(log, f"record .* stream {S1:#x}") < first(log, f"wait stream {S2:#x}") \
+        < first(log, f"^copy .* stream {S2:#x}") < first(log, "k_acc_light"), log
 
 
 if __name__ != "__main__":
