@@ -1600,6 +1600,10 @@ spgemm_status spgemm_batched(int32_t count, const spgemm_csc *A_host, const spge
                     std::memcmp(p->table_dev_copy.data(), p->probs.data(),
                                 sizeof(Prob) * p->probs.size()) == 0;
         if (!same) {
+            // a graph's replays would copy what the upload room holds then
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            SPG_TRY(hipStreamIsCapturing(s, &cs));
+            if (cs != hipStreamCaptureStatusNone) return SPGEMM_ERR_HIP;
             // the plan's earlier work, possibly on another stream, still reads it
             SPG_TRY(order_plan(p, s));
             if (spgemm_status st = wait_upload(p)) return st;

@@ -169,6 +169,31 @@ def batch_table_waits_for_the_plans_earlier_work(h):
         < first(log, f"^copy .* stream {S2:#x}") < first(log, "k_acc_light"), log
 
 
+@scenario
+def batch_table_is_not_copied_inside_a_graph(h):
+    """Arrays other than the last call's, on a stream under capture: refused
+    (replays would copy from host memory that later calls write); the last
+    call's arrays queue kernels only, and the plan goes on as before."""
+    h.header({BIN_ESC0: 8}, 40, 15)
+    h.words[W_NNZ + 2] = 15
+    assert h.batched(S1) == 0
+    assert h.batched(S1, values=12) == 0
+    h.log()
+    h.capture(S2)
+    assert h.batched(S2, values=14) == 7
+    log = h.log()
+    assert not count(log, "^copy|^launch|^record"), log
+    h.capture(None)
+    assert h.batched(S1, values=12) == 0
+    assert not count(h.log(), "^copy .* kind 2")
+    h.capture(S2)
+    assert h.batched(S2, values=12) == 0
+    log = h.log()
+    assert count(log, "^launch") and not count(log, "^copy|^sync|^await"), log
+    h.capture(None)
+    assert h.batched(S1, values=14) == 0 and count(h.log(), "^copy .* kind 1") == 1
+
+
 if __name__ != "__main__":
     import pytest
 
