@@ -287,10 +287,11 @@ hipError_t acquire_sides(SideSet &x, int device) {
     return hipEventCreateWithFlags(&x.fork_ev, ef);
 }
 
-// The device writes no more to it and no copy reads it.
-void release_mirror(HostMirror &m) {
+// idle: the device writes no more to it and no copy reads it, so another plan
+// may have it.
+void release_mirror(HostMirror &m, bool idle) {
     if (!m.base) return;
-    if (12 * m.words + m.upload <= kPoolBytes) {
+    if (idle && 12 * m.words + m.upload <= kPoolBytes) {
         HostPool &hp = host_pool();
         std::lock_guard<std::mutex> lk(hp.mu);
         if (hp.mirrors.size() < kPoolMirrors) {
@@ -626,7 +627,7 @@ spgemm_status ensure_workspace(spgemm_plan p, hipStream_t s) {
             if (spgemm_status st = wait_upload(p)) return st;
             // nothing queued may still publish to the old one
             if (p->mirror.base) SPG_TRY(hipStreamSynchronize(s));
-            release_mirror(p->mirror);
+            release_mirror(p->mirror, true);
             if (spgemm_status st = acquire_mirror(p->mirror, p->device, words, room)) return st;
         }
         p->pinned = p->mirror.raw();
@@ -1778,10 +1779,12 @@ void spgemm_plan_destroy(spgemm_plan p) {
     dev_free(p, p->bt, s);
     dev_free(p, p->terms, s);
     dev_free(p, p->lbuf, s);
-    (void)hipStreamSynchronize(s);
+    // host memory that a publication or an upload may still reach goes to no
+    // other plan
+    bool idle = hipStreamSynchronize(s) == hipSuccess;
     release_sides(p->sides);
-    (void)wait_upload(p);
-    release_mirror(p->mirror);
+    idle &= wait_upload(p) == SPGEMM_OK;
+    release_mirror(p->mirror, idle);
     if (p->order_ev) (void)hipEventDestroy(p->order_ev);
     if (p->upload_done) (void)hipEventDestroy(p->upload_done);
     delete p;

@@ -194,6 +194,28 @@ def batch_table_is_not_copied_inside_a_graph(h):
     assert h.batched(S1, values=14) == 0 and count(h.log(), "^copy .* kind 1") == 1
 
 
+@scenario
+def host_memory_of_unfinished_work_is_not_pooled(h):
+    """A plan destroyed while its stream cannot be waited for: the next plan takes
+    other host memory. One destroyed in order hands its own on."""
+    h.header({BIN_ESC0: 4}, 12, 9)
+
+    def plan():
+        h.plan = C.c_void_p()
+        h.log()
+        assert h.multiply() == 0
+        return count(h.log(), "^hostalloc")
+
+    assert plan() == 1
+    h.L.spgemm_plan_destroy(h.plan)
+    assert plan() == 0
+    h.fail("hipStreamSynchronize", S1, 900)
+    h.L.spgemm_plan_destroy(h.plan)
+    h.fail("", None, 0)
+    assert plan() == 1
+    h.L.spgemm_plan_destroy(h.plan)
+
+
 if __name__ != "__main__":
     import pytest
 
