@@ -416,14 +416,21 @@ hipError_t order_after(spgemm_plan p, hipStream_t later, hipStream_t earlier) {
 }
 
 // Work queued on s from now on comes after the plan's earlier work. (A stream
-// being captured cannot wait for work outside its graph: there the caller
-// keeps the plan's other work apart from the graph's replays.)
+// being captured cannot wait for work outside its graph, nor another stream for
+// work that is only captured: there the caller keeps the plan's other work
+// apart from the graph's replays.)
 hipError_t order_plan(spgemm_plan p, hipStream_t s) {
     if (p->last_stream == s) return hipSuccess;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     hipError_t e = hipStreamIsCapturing(s, &st);
     if (e != hipSuccess || st != hipStreamCaptureStatusNone) return e;
-    return order_after(p, s, p->last_stream);
+    e = hipStreamIsCapturing(p->last_stream, &st);
+    if (e == hipSuccess && st != hipStreamCaptureStatusNone) return e;
+    if (e == hipSuccess && (e = order_after(p, s, p->last_stream)) == hipSuccess) return e;
+    // the last call's stream takes no event any more (its owner has destroyed
+    // it): what may be left of its work is waited for on the host
+    (void)hipGetLastError();
+    return hipDeviceSynchronize();
 }
 
 // Releases b (its last use is ordered before the end of stream `s`).

@@ -216,6 +216,28 @@ def host_memory_of_unfinished_work_is_not_pooled(h):
     h.L.spgemm_plan_destroy(h.plan)
 
 
+@scenario
+def last_calls_stream_is_gone_or_under_capture(h):
+    """The plan's last call ran on a stream that is destroyed since: the next
+    numeric call on another one waits for the device and goes on. Or its last
+    call was captured: nothing is recorded on the capturing stream."""
+    h.header({BIN_ESC0: 4}, 12, 9)
+    assert h.symbolic(S1) == 0
+    assert h.numeric(S2) == 0
+    h.log()
+    h.fail("hipEventRecord", S2, 400)
+    assert h.numeric(S1) == 0
+    log = h.log()
+    assert first(log, "^sync device") < first(log, "k_acc_light"), log
+    h.fail("", None, 0)
+    h.capture(S3)
+    assert h.numeric(S3) == 0
+    h.log()
+    assert h.numeric(S1) == 0
+    assert not count(h.log(), f"^record .* stream {S3:#x}")
+    h.capture(None)
+
+
 if __name__ != "__main__":
     import pytest
 
