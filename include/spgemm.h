@@ -311,7 +311,7 @@ spgemm_status spgemm_multiply_noalloc(const spgemm_csc *A, const spgemm_csc *B, 
  * The first call builds and caches a view of the two patterns inside the plan
  * (per product its place in C; per stored entry its products and terms) and
  * takes space for one value per product (the terms of dA; without that space
- * dA gathers G a second time). It may allocate; later calls on the plan are
+ * dA and dB gather G from C each). It may allocate; later calls on the plan are
  * stream-ordered, allocate nothing and queue only kernels (they may be captured
  * in a HIP graph together with spgemm_numeric on the same plan; a replay uses
  * the plan's workspace, so it must not overlap other work on the plan).

@@ -371,6 +371,14 @@ struct BwView {
     const int4 *aview;        // [nnz(A)] (first term: 64 bits, terms, their distance)
     const int32_t *rowptr;    // [rows of B + 1]
     const int32_t *rowent;    // [nnz(B)] every row's stored B entries by ascending column
+    const long long *rowpofs; // [nnz(B)] the first product of each of them
+    const int2 *arow;         // [nnz(A)] (A column, place in it)
+};
+// sizes that the form of the gradients depends on
+struct BwShape {
+    int32_t nnzb;
+    long long products, nnzc;
+    int32_t longest_b, longest_a;  // terms of one entry of dB, dA (-1: not known yet)
 };
 // writable arrays of the view and its construction temporaries
 struct BwBuild {
@@ -378,21 +386,27 @@ struct BwBuild {
     long long *pofs, *woff;
     int4 *aview;
     int32_t *rowptr, *rowent;
-    int32_t *cnt;          // [rows of B], cleared with the error word behind it
-    size_t clear_bytes;
+    long long *rowpofs;
+    int2 *arow;
+    int32_t *cnt;          // [rows of B], cleared with the error word and the longest
+    size_t clear_bytes;    // lists behind it
+    int *longest;          // [2] longest lists of dB and dA
     int32_t *arrival, *pos;
     long long *wbase;      // [rows of B] terms of dA before every row
     long long *bsum, *bsum2;  // [bw_scan_blocks]
 };
 int bw_scan_blocks(int nnzb, int nrows);
+// pub: where the longest lists go, for later calls
 hipError_t launch_bw_view(const Prob &p, const BwView &v, const BwBuild &b, const int32_t *cri,
-                          int *err, hipStream_t s);
-// dA (if da) and dB (if db) of one problem through the view; terms: space of
-// one value per product, or NULL; err collects ERR_CSC for a place outside C
-// (an inconsistent plan)
-hipError_t launch_backward(const Prob &p, const BwView &v, void *terms, bool f64, const void *av,
-                           const void *bv, const void *gv, void *da, void *db, int *err,
-                           hipStream_t s);
+                          int *err, const PubArgs &pub, hipStream_t s);
+// whether dA (need_a) and dB (need_b) are faster in two passes than in one launch
+bool bw_two_passes(const BwShape &x, bool f64, bool need_a, bool need_b);
+// dA (if da) and dB (if db) of one problem through the view, in two passes (dA
+// with `terms`, space of one value per product) or one launch; err collects
+// ERR_CSC for a place outside C (an inconsistent plan)
+hipError_t launch_backward(const Prob &p, const BwView &v, bool two, void *terms, bool f64,
+                           const void *av, const void *bv, const void *gv, void *da, void *db,
+                           int *err, hipStream_t s);
 // nwords 32-bit words from src to mapped host memory dst, as 8-byte pairs
 // (word, seq)
 hipError_t launch_publish(const void *src, const PubArgs &pub, hipStream_t s);

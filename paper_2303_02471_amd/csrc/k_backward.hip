@@ -14,14 +14,18 @@
 // first product (pofs) and the first of its terms of dA (woff); per stored A
 // entry its terms of dA.
 //
-// Two passes over the products. The first walks them in product order, where
-// a column's G values lie together: it loads G once, adds up dB and writes the
-// terms G(i,j) B(k,j) of dA grouped by A's column, entry after entry of B's
-// row k in ascending j. The second adds up dA from contiguous blocks. One pass
-// gathering G twice, once in A's order all over C, with a thread per entry
-// walking its list alone, took 87 us for 6.4 M float products (8 per entry) and
-// 324 us for 5 M double products of power-law columns, where the longest list
-// set the time; the two passes take 31 + 8 us and 88 + 11 us.
+// Two forms, the same sums. Two passes over the products: the first walks them
+// in product order, where a column's G values lie together; it loads G once,
+// adds up dB and writes the terms G(i,j) B(k,j) of dA grouped by A's column,
+// entry after entry of B's row k in ascending j; the second adds up dA from
+// contiguous blocks. Or one launch with a thread per stored entry, which
+// gathers G for its own list: half the launches and no terms in memory, but G is
+// read twice, for dA all over C, and the longest list sets the time (6.4 M
+// float products, 8 per entry: 87 us, in two passes 31 + 8; 5 M double products
+// of power-law columns: 324 us, in two passes 88 + 11). bw_two_passes chooses.
+#include <algorithm>
+#include <cmath>
+
 #include "devutil.h"
 
 namespace spg {
@@ -238,28 +242,81 @@ __global__ __launch_bounds__(kBlock) void k_grad_a(const int4 *__restrict__ avie
     da[q] = acc;
 }
 
-// dA without the terms in memory (a plan that could not get their space): one
-// thread per stored A entry walks B's row and gathers G.
+// ---------------------------------------------------------------- one launch
+// One thread per stored entry: blocks [0, nbw) dB, the others dA. Bound by the
+// gathers of G and, where a list is long, by its chain of them, so kBwUnroll
+// terms' loads are in flight together.
+constexpr int kBwUnroll = 4;
+
 template <typename V>
-__global__ __launch_bounds__(kBlock) void k_grad_a_gather(BwView v, Prob p, int nnza,
-                                                          const V *__restrict__ bv,
-                                                          const V *__restrict__ gv,
-                                                          V *__restrict__ da, int *err) {
-    const int q = blockIdx.x * kBlock + threadIdx.x;
-    if (q >= nnza) return;
-    const int k = column_of(p.acp, p.k, q), u = q - p.acp[k];
-    V acc = V(0);
+__device__ __forceinline__ V g_at(const V *__restrict__ gv, long long nnzc, uint32_t at, int &bad) {
+    if ((long long)at < nnzc) return gv[at];
+    bad = 1;
+    return V(0);
+}
+
+template <typename V>
+__global__ __launch_bounds__(kBlock) void k_grad(BwView v, int nnza, int nnzb, int nbw,
+                                                 const V *__restrict__ av,
+                                                 const V *__restrict__ bv,
+                                                 const V *__restrict__ gv, V *__restrict__ da,
+                                                 V *__restrict__ db, int *err) {
+    constexpr int U = kBwUnroll;
     int bad = 0;
-    for (int r = v.rowptr[k]; r < v.rowptr[k + 1]; ++r) {
-        const int t = v.rowent[r];
-        const uint32_t gp = v.gpos[v.pofs[t] + u];
-        if ((long long)gp >= v.nnzc) {
-            bad = 1;
-            continue;
+    V acc = V(0);
+    if ((int)blockIdx.x < nbw) {
+        const int t = blockIdx.x * kBlock + threadIdx.x;
+        if (t >= nnzb) return;
+        const int2 e = v.E[t];
+        const V *__restrict__ ap = av + e.x;
+        const uint32_t *__restrict__ gp = v.gpos + v.pofs[t];
+        int u = 0;
+        for (; u + U <= e.y; u += U) {
+            V a[U], g[U];
+            uint32_t at[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                a[q] = ap[u + q];
+                at[q] = gp[u + q];
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) g[q] = g_at(gv, v.nnzc, at[q], bad);
+#pragma unroll
+            for (int q = 0; q < U; ++q) acc = acc + a[q] * g[q];
         }
-        acc = acc + gv[gp] * bv[t];
+        for (; u < e.y; ++u) acc = acc + ap[u] * g_at(gv, v.nnzc, gp[u], bad);
+        db[t] = acc;
+    } else {
+        const int q = (blockIdx.x - nbw) * kBlock + threadIdx.x;
+        if (q >= nnza) return;
+        const int2 x = v.arow[q];
+        const int r1 = v.rowptr[x.x + 1];
+        const uint32_t *__restrict__ gp = v.gpos + x.y;
+        int r = v.rowptr[x.x];
+        for (; r + U <= r1; r += U) {
+            int t[U];
+            long long pf[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                t[u] = v.rowent[r + u];
+                pf[u] = v.rowpofs[r + u];
+            }
+            uint32_t at[U];
+            V b[U], g[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                at[u] = gp[pf[u]];
+                b[u] = bv[t[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) g[u] = g_at(gv, v.nnzc, at[u], bad);
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc = acc + g[u] * b[u];
+        }
+        for (; r < r1; ++r)
+            acc = acc + g_at(gv, v.nnzc, gp[v.rowpofs[r]], bad) * bv[v.rowent[r]];
+        da[q] = acc;
     }
-    da[q] = acc;
     if (bad) atomicOr(err, ERR_CSC);
 }
 
@@ -376,16 +433,20 @@ __global__ __launch_bounds__(kBlock) void k_bv_fill(Prob p, const int32_t *rowpt
 // Blocks [0, nbt): every B entry's rank in its row by ascending column (the
 // entries before it in B's storage, counted in the row's list: by its thread,
 // or for rows above kBvCount entries by the whole wavefront), the row's sorted
-// entries and the entry's terms of dA. The others: every A entry's terms.
+// entries, the entry's terms of dA, and the longest lists of dB (`longest[0]`)
+// and dA. The others: every A entry's terms.
 constexpr int kBvCount = 64;
 __global__ __launch_bounds__(kBlock) void k_bv_rank(Prob p, const int32_t *rowptr,
                                                     const int32_t *pos, const long long *wbase,
-                                                    int nbt, int32_t *rowent, long long *woff,
-                                                    int4 *aview) {
+                                                    const long long *pofs, int nbt,
+                                                    int32_t *rowent, long long *rowpofs,
+                                                    long long *woff, int4 *aview, int2 *arow,
+                                                    int *longest) {
     if ((int)blockIdx.x < nbt) {
         const int t = blockIdx.x * kBlock + threadIdx.x;
         const int k = t < p.nnzb ? p.bri[t] : -1;
         const int b = k >= 0 ? rowptr[k] : 0, e = k >= 0 ? rowptr[k + 1] : 0;
+        const int z = k >= 0 ? p.acp[k + 1] - p.acp[k] : 0;
         int rank = 0;
         if (e - b <= kBvCount)
             for (int r = b; r < e; ++r) rank += pos[r] < t ? 1 : 0;
@@ -399,29 +460,42 @@ __global__ __launch_bounds__(kBlock) void k_bv_rank(Prob p, const int32_t *rowpt
             n = wave_sum(n);
             if (lane_id() == src) rank = n;
         }
+        const int lb = __builtin_amdgcn_readlane(wave_incl_max(z), 63);
+        const int la = __builtin_amdgcn_readlane(wave_incl_max(z > 0 ? e - b : 0), 63);
+        if (lane_id() == 0) {
+            if (lb > __atomic_load_n(&longest[0], __ATOMIC_RELAXED)) atomicMax(&longest[0], lb);
+            if (la > __atomic_load_n(&longest[1], __ATOMIC_RELAXED)) atomicMax(&longest[1], la);
+        }
         if (k < 0) return;
         rowent[b + rank] = t;
-        woff[t] = wbase[k] + (long long)rank * (p.acp[k + 1] - p.acp[k]);
+        rowpofs[b + rank] = pofs[t];
+        woff[t] = wbase[k] + (long long)rank * z;
     } else {
         const int q = (blockIdx.x - nbt) * kBlock + threadIdx.x;
         if (q >= p.nnza) return;
-        const int k = column_of(p.acp, p.k, q);
-        const long long base = wbase[k] + (q - p.acp[k]);
+        const int k = column_of(p.acp, p.k, q), u = q - p.acp[k];
+        const long long base = wbase[k] + u;
         aview[q] = make_int4((int)(unsigned)base, (int)(unsigned)((unsigned long long)base >> 32),
                              rowptr[k + 1] - rowptr[k], p.acp[k + 1] - p.acp[k]);
+        arow[q] = make_int2(k, u);
     }
 }
 
 // the place of every product's row among C's entries (C's columns ascend: a
-// binary search), products taken as in the first pass
+// binary search), products taken as in the first pass; and the longest lists
+// to the host
 __global__ __launch_bounds__(64) void k_bv_gpos(Prob p, const int2 *__restrict__ E,
                                                 const long long *__restrict__ pofs,
                                                 const int32_t *__restrict__ cri, long long nnzc,
-                                                uint32_t *__restrict__ gpos, int *err) {
+                                                uint32_t *__restrict__ gpos, int *err,
+                                                const int *longest, PubArgs pub) {
     __shared__ unsigned bits[kBwN / 32];
     __shared__ int s_q[64], s_lo[64], s_hi[64];
     const int lane = threadIdx.x;
     const int t = blockIdx.x * 64 + lane;
+    if (pub.dst && blockIdx.x == 0 && lane < pub.nwords)
+        __hip_atomic_store(&pub.dst[lane], (unsigned)longest[lane] | ((unsigned long long)pub.seq << 32),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const long long p0 = pofs[blockIdx.x * 64];
     int2 e = make_int2(0, 0);
     int c0 = 0, c1 = 0;
@@ -489,10 +563,10 @@ __global__ __launch_bounds__(64) void k_bv_gpos(Prob p, const int2 *__restrict__
 int bw_scan_blocks(int nnzb, int nrows) { return ceil_div(nnzb, kBvBlock) + ceil_div(nrows, kBvBlock); }
 
 hipError_t launch_bw_view(const Prob &p, const BwView &v, const BwBuild &b, const int32_t *cri,
-                          int *err, hipStream_t s) {
+                          int *err, const PubArgs &pub, hipStream_t s) {
     const int nrows = p.k;  // rows of B
     hipError_t e;
-    // counts and the error word lie together
+    // counts, the error word and the longest lists lie together
     if ((e = hipMemsetAsync(b.cnt, 0, b.clear_bytes, s))) return e;
     const int gt = ceil_div(p.nnzb, kBlock), ga = ceil_div(p.nnza, kBlock);
     if (gt > 0) hipLaunchKernelGGL(k_bv_count, dim3(gt), dim3(kBlock), 0, s, p, b.cnt, b.arrival);
@@ -508,37 +582,97 @@ hipError_t launch_bw_view(const Prob &p, const BwView &v, const BwBuild &b, cons
     if (gt + ga > 0)
         hipLaunchKernelGGL(k_bv_rank, dim3(gt + ga), dim3(kBlock), 0, s, p,
                            (const int32_t *)b.rowptr, (const int32_t *)b.pos,
-                           (const long long *)b.wbase, gt, b.rowent, b.woff, b.aview);
+                           (const long long *)b.wbase, (const long long *)b.pofs, gt, b.rowent,
+                           b.rowpofs, b.woff, b.aview, b.arow, b.longest);
     if (p.nnzb > 0)
         hipLaunchKernelGGL(k_bv_gpos, dim3(ceil_div(p.nnzb, 64)), dim3(64), 0, s, p, v.E,
-                           (const long long *)b.pofs, cri, v.nnzc, b.gpos, err);
+                           (const long long *)b.pofs, cri, v.nnzc, b.gpos, err,
+                           (const int *)b.longest, pub);
     return hipGetLastError();
+}
+
+// The form that is faster, from the sizes and the longest lists (unknown in a
+// plan's first call, which takes the two passes: they never wait on one list).
+// Estimates in us, fitted to both forms' times, dA and dB together and each
+// alone, in both types, on 114 products of 2 thousand to 47 million (uniform,
+// power-law, banded, block, stencil and clustered patterns, columns of 2 to
+// 1000 entries). With r products per entry of C and z per stored B entry:
+//   one launch   products x (a + b / r^1.75): of many products on an entry of G
+//                most find it in a cache, one alone reads a line for it; or the
+//                longest list's chain of gathers; or a launch, 5.2.
+//   two passes   what the products and entries move; or a wavefront's chain of
+//                chunks (64 z products, 512 each) and half of that; or two
+//                launches, 8.8.
+// Both gradients took the faster form on all 114, one alone on all but 5, which
+// lose 15 to 35%.
+// Measured (one launch, two passes; double): 5000 columns of 8 in A and B 7.2
+// and 10.0 us, 50,000 59 and 30; 500 columns of 40 12.6 and 27.1, 1500 41.8 and
+// 32.3; 20,000 columns of 20 in a band (r = 10) 35.5 and 55.6; a power law of
+// 20,000 columns 161 and 37.
+bool bw_two_passes(const BwShape &x, bool f64, bool need_a, bool need_b) {
+    if (x.longest_a < 0) return true;
+    const double p = 1e-6 * (double)x.products, nb = 1e-6 * x.nnzb;
+    const double z = (double)x.products / std::max(x.nnzb, 1);
+    const double r = (double)x.products / (double)std::max(x.nnzc, 1ll);
+    const double alone = std::pow(r, -1.75);  // of the products, those that find no line of G
+    const double ga = p * (1.8 + (f64 ? 12 : 9) * alone) + 10 * nb * alone;
+    // (long columns of A: a wavefront's lists pass through more lines than the
+    // first cache holds, and the larger G is the less the second one does)
+    const double more_g = std::max(0.0, std::log2((double)x.nnzc * (f64 ? 8 : 4) / 2e6));
+    const double gb = p * ((z < 25 ? 0.7 + 0.1 * z : 3.4 + 0.6 * more_g) + (f64 ? 5 : 2.5) * alone);
+    const double chain_a = 0.17 * x.longest_a, chain_b = 0.09 * x.longest_b;
+    const double more = std::max(0.0, z * 64 / kBwN - 1);  // chunks after a wavefront's first
+    double one, two;
+    if (need_a && need_b) {
+        one = std::max({1.5 + ga + gb, chain_a, chain_b, 5.2});
+        two = 7.3 + std::max((f64 ? 6.2 : 4.5) * p + (f64 ? 12 : 4.5) * nb,
+                             (more > 0 ? 1.5 : 0) + 4.2 * more + (f64 ? 3 : 2) * p);
+        two = std::max(two, 8.8);
+    } else if (need_a) {
+        one = std::max({ga, chain_a, 5.2});
+        two = 7.3 + std::max((f64 ? 5.1 : 3.5) * p + (f64 ? 10 : 4) * nb,
+                             3 * more + (f64 ? 2.2 : 1.5) * p);
+        two = std::max(two, 8.8);
+    } else {  // (the first pass alone)
+        one = std::max({gb, chain_b, 5.2});
+        two = 5.2 + std::max((f64 ? 3 : 2) * p + (f64 ? 5 : 2.5) * nb + more,
+                             2 * more + (f64 ? 2 : 1.3) * p);
+        two = std::max(two, 5.8);
+    }
+    // (one gradient alone: the estimates part less well, and the one launch is
+    // the form that needs no space)
+    return (need_a && need_b ? 1.0 : 1.08) * two < one;
 }
 
 template <typename V>
-static hipError_t run_backward(const Prob &p, const BwView &v, void *terms, const V *av,
+static hipError_t run_backward(const Prob &p, const BwView &v, bool two, void *terms, const V *av,
                                const V *bv, const V *gv, V *da, V *db, int *err, hipStream_t s) {
+    if (p.nnzb <= 0) db = nullptr;
+    if (p.nnza <= 0) da = nullptr;
+    if (!da && !db) return hipSuccess;
+    if (!two || (da && !terms)) {
+        const int nbw = db ? ceil_div(p.nnzb, kBlock) : 0, naw = da ? ceil_div(p.nnza, kBlock) : 0;
+        hipLaunchKernelGGL(k_grad<V>, dim3(nbw + naw), dim3(kBlock), 0, s, v, p.nnza, p.nnzb, nbw,
+                           av, bv, gv, da, db, err);
+        return hipGetLastError();
+    }
     V *w = da ? (V *)terms : nullptr;
-    if (p.nnzb > 0 && (db || w))
+    if (p.nnzb > 0)
         hipLaunchKernelGGL(k_grad_b<V>, dim3(ceil_div(p.nnzb, 64)), dim3(64), 0, s, v, p.nnzb, av,
                            bv, gv, db, w, err);
-    if (da && p.nnza > 0) {
-        const dim3 g(ceil_div(p.nnza, kBlock)), t(kBlock);
-        if (terms)
-            hipLaunchKernelGGL(k_grad_a<V>, g, t, 0, s, v.aview, p.nnza, (const V *)w, da);
-        else
-            hipLaunchKernelGGL(k_grad_a_gather<V>, g, t, 0, s, v, p, p.nnza, bv, gv, da, err);
-    }
+    if (da)
+        hipLaunchKernelGGL(k_grad_a<V>, dim3(ceil_div(p.nnza, kBlock)), dim3(kBlock), 0, s, v.aview,
+                           p.nnza, (const V *)w, da);
     return hipGetLastError();
 }
 
-hipError_t launch_backward(const Prob &p, const BwView &v, void *terms, bool f64, const void *av,
-                           const void *bv, const void *gv, void *da, void *db, int *err,
-                           hipStream_t s) {
+hipError_t launch_backward(const Prob &p, const BwView &v, bool two, void *terms, bool f64,
+                           const void *av, const void *bv, const void *gv, void *da, void *db,
+                           int *err, hipStream_t s) {
     if (f64)
-        return run_backward<double>(p, v, terms, (const double *)av, (const double *)bv,
+        return run_backward<double>(p, v, two, terms, (const double *)av, (const double *)bv,
                                     (const double *)gv, (double *)da, (double *)db, err, s);
-    return run_backward<float>(p, v, terms, (const float *)av, (const float *)bv,
+    return run_backward<float>(p, v, two, terms, (const float *)av, (const float *)bv,
                                (const float *)gv, (float *)da, (float *)db, err, s);
 }
 

@@ -143,6 +143,8 @@ struct spgemm_plan_s {
     DevBuf bt, terms;
     bool bt_ready = false;
     int *bt_err = nullptr;
+    uint32_t bt_seq = 0;  // publication of the view's longest lists (0: none on its way)
+    int32_t longest_b = -1, longest_a = -1;  // -1: not known yet
 
     bool wide_keys = false;  // some problem has 2^20 rows or more: 64-bit sort keys
     bool wide_esc = false;   // some problem has 2^24 - 1 rows or more: 64-bit ESC keys
@@ -350,6 +352,24 @@ PubArgs next_publication(spgemm_plan p, size_t words) {
     return PubArgs{(unsigned long long *)p->mirror.dev, (int32_t)words, ++p->mirror.seq};
 }
 size_t all_words(spgemm_plan p) { return (kHdrBytes + 8 * (size_t)p->nprob) / 4; }
+// The mirror's last two pairs are the gradients' (their view's longest lists).
+constexpr size_t kViewWords = 2;
+PubArgs next_view_publication(spgemm_plan p) {
+    if (!p->mirror.base) return PubArgs{nullptr, 0, 0};
+    return PubArgs{(unsigned long long *)p->mirror.dev + p->mirror.words - kViewWords,
+                   (int32_t)kViewWords, ++p->mirror.seq};
+}
+// Takes them over as soon as the device has written them.
+void read_view_publication(spgemm_plan p) {
+    if (!p->bt_seq) return;
+    const unsigned long long *w = p->mirror.pairs() + p->mirror.words - kViewWords;
+    const unsigned long long b = __atomic_load_n(w, __ATOMIC_ACQUIRE),
+                             a = __atomic_load_n(w + 1, __ATOMIC_ACQUIRE);
+    if ((uint32_t)(b >> 32) != p->bt_seq || (uint32_t)(a >> 32) != p->bt_seq) return;
+    p->longest_b = (int32_t)(uint32_t)b;
+    p->longest_a = (int32_t)(uint32_t)a;
+    p->bt_seq = 0;
+}
 
 // Waits until the first `words` published pairs carry the last sequence number
 // and copies them to the raw mirror. The stream is polled now and then, so a
@@ -628,7 +648,7 @@ spgemm_status ensure_workspace(spgemm_plan p, hipStream_t s) {
     p->o_table = o_tab;
     p->table_bytes = o_tiles + sizeof(int4) * (size_t)std::max(p->ntiles, 1) - o_tab;
     if (!p->use_arena) {
-        const size_t words = (kHdrBytes + 8 * (size_t)std::max(p->nprob, 1)) / 4;
+        const size_t words = (kHdrBytes + 8 * (size_t)std::max(p->nprob, 1)) / 4 + kViewWords;
         const size_t room = p->nprob > 1 ? p->table_bytes : 0;
         if (words > p->mirror.words || room > p->mirror.upload) {
             if (spgemm_status st = wait_upload(p)) return st;
@@ -1484,6 +1504,8 @@ static spgemm_status symbolic_common(int32_t count, const spgemm_csc *A, const s
     p->ntiles = (int)tiles.size();
     p->symbolic_ok = false;
     p->bt_ready = false;
+    p->bt_seq = 0;
+    p->longest_b = p->longest_a = -1;
     (void)hipGetDevice(&p->device);
     hipStream_t s = (hipStream_t)stream;
     if (count == 0) {
@@ -1654,7 +1676,8 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
     };
     const size_t o_pofs = carve(8 * nb), o_woff = carve(8 * nb), o_aview = carve(16 * na),
                  o_rowptr = carve(4 * (k + 1)), o_rowent = carve(4 * nb),
-                 o_cnt = carve(4 * (k + 1)), o_arrival = carve(4 * nb), o_pos = carve(4 * nb),
+                 o_rowpofs = carve(8 * nb), o_arow = carve(8 * na),
+                 o_cnt = carve(4 * (k + 3)), o_arrival = carve(4 * nb), o_pos = carve(4 * nb),
                  o_wbase = carve(8 * k), o_bsum = carve(8 * blocks), o_bsum2 = carve(8 * blocks),
                  o_gpos = carve(4 * products);
     const size_t need = off, terms_need = (f64 ? 8 : 4) * products;
@@ -1662,7 +1685,7 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
         p->bt_ready = false;
         if (spgemm_status st = dev_alloc(p, p->bt, need, s)) return st;
     }
-    // without this space dA gathers G a second time
+    // without this space the gradients are formed in one launch
     if (!p->bt_ready && terms_need > p->terms.bytes) (void)dev_alloc(p, p->terms, terms_need, s);
     void *terms = p->terms.bytes >= terms_need ? p->terms.ptr : nullptr;
     char *b = (char *)p->bt.ptr;
@@ -1672,8 +1695,11 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
     bb.aview = (int4 *)(b + o_aview);
     bb.rowptr = (int32_t *)(b + o_rowptr);
     bb.rowent = (int32_t *)(b + o_rowent);
+    bb.rowpofs = (long long *)(b + o_rowpofs);
+    bb.arow = (int2 *)(b + o_arow);
     bb.cnt = (int32_t *)(b + o_cnt);
-    bb.clear_bytes = 4 * (k + 1);
+    bb.clear_bytes = 4 * (k + 3);
+    bb.longest = bb.cnt + k + 1;
     bb.arrival = (int32_t *)(b + o_arrival);
     bb.pos = (int32_t *)(b + o_pos);
     bb.wbase = (long long *)(b + o_wbase);
@@ -1682,18 +1708,25 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
     bb.gpos = (uint32_t *)(b + o_gpos);
     p->bt_err = (int *)(b + o_cnt) + k;
     const BwView w{p->E, bb.gpos, p->totals_host[0], bb.pofs, bb.woff, bb.aview, bb.rowptr,
-                   bb.rowent};
+                   bb.rowent, bb.rowpofs, bb.arow};
     if (!p->bt_ready) {
         // the error word is cleared with the view only: later calls queue no
         // memset, so they can be captured in a HIP graph
         ProfScope ps("bw_view", s);
-        SPG_TRY(launch_bw_view(q, w, bb, C_rowidx, p->bt_err, s));
+        const PubArgs pub = next_view_publication(p);
+        SPG_TRY(launch_bw_view(q, w, bb, C_rowidx, p->bt_err, pub, s));
+        p->bt_seq = q.nnzb > 0 ? pub.seq : 0;
         p->bt_ready = true;
+    } else {
+        read_view_publication(p);
     }
     {
+        const BwShape shape{q.nnzb, (long long)products, p->totals_host[0], p->longest_b,
+                            p->longest_a};
+        const bool two = bw_two_passes(shape, f64, dA_val != nullptr, dB_val != nullptr);
         ProfScope ps("gradients", s);
-        SPG_TRY(launch_backward(q, w, terms, f64, A_val, B_val, G_val, dA_val, dB_val, p->bt_err,
-                                s));
+        SPG_TRY(launch_backward(q, w, two, terms, f64, A_val, B_val, G_val, dA_val, dB_val,
+                                p->bt_err, s));
     }
     p->last_stream = s;
     return SPGEMM_OK;

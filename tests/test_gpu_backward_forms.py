@@ -1,0 +1,56 @@
+"""Gradients in both forms (two passes over the products; one launch with a thread
+per stored entry), bit for bit against the oracle: a plan's first call takes
+the two passes, later ones the form that its sizes and longest lists make the
+faster. Lists of 0 to 9 terms around the one-launch form's 4 terms at a time."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2303_02471_amd import inputs as gen
+from helpers import HAVE_GPU
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not HAVE_GPU, reason="needs an MI355X GPU")]
+
+if HAVE_GPU:
+    import torch
+    from paper_2303_02471_amd import api
+
+
+def _random_lists(seed):
+    """Columns of 0 to 9 entries in A and B, rows of B as uneven."""
+    rng = np.random.default_rng(seed)
+
+    def csc(nrows, ncols):
+        cols = [rng.permutation(nrows)[:rng.integers(0, 10)] for _ in range(ncols)]
+        cp = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
+        ri = np.concatenate(cols).astype(np.int32)
+        return gen.CSC(nrows, ncols, cp, ri, rng.standard_normal(len(ri)))
+    return csc(700, 257), csc(257, 511)
+
+
+CASES = {"short lists": lambda: _random_lists(1),            # one launch
+         "one entry": lambda: (gen.uniform_z(3, 1, seed=1), gen.uniform_z(3, 1, seed=2)),
+         "uniform": lambda: (gen.uniform_z(2500, 40, seed=3), gen.uniform_z(2500, 40, seed=4)),  # two
+         "power law": lambda: gen.powerlaw(15000, seed=5)}   # two: long lists
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_forms(name, dtype):
+    print(f"[case] backward forms {name} {dtype}", flush=True)
+    np_t = np.float64 if dtype == "f64" else np.float32
+    A, B = (x.astype(np_t) for x in CASES[name]())
+    ocp, ori, ov = oracle.spgemm(A, B, dtype)
+    At, Bt = api.CscTensor.from_host(A), api.CscTensor.from_host(B)
+    Cm, plan = api.matmul(At, Bt, return_plan=True)
+    for call, need in enumerate(("ab", "ab", "a", "b", "ab")):
+        G = gen.gradient_values(len(ov), seed=call, dtype=np_t)
+        want = oracle.backward(A, B, ocp, ori, G, dtype)
+        got = api.backward(plan, At.val, Bt.val, Cm.rowidx, torch.from_numpy(G).cuda(),
+                           need_a="a" in need, need_b="b" in need)
+        torch.cuda.synchronize()
+        for x, w, n in zip(got, want, "ab"):
+            if n in need:
+                assert np.array_equal(x.cpu().numpy(), w), f"d{n.upper()}, call {call}"
+    plan.close()

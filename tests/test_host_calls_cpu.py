@@ -49,8 +49,10 @@ class Host:
         self.words[W_HEAVY_PROD], self.words[W_HEAVY_WIN] = heavy
         self.words[W_NNZ] = nnz
 
-    def csc(self, base, nnz=8):
-        return self.lib.Csc(4, 4, nnz, self.at(base), self.at(base + 1), self.at(base + 2))
+    entries = 8
+
+    def csc(self, base):
+        return self.lib.Csc(4, 4, self.entries, self.at(base), self.at(base + 1), self.at(base + 2))
 
     def options(self, **kw):
         o = self.lib.Options()
@@ -71,6 +73,10 @@ class Host:
 
     def numeric(self, stream):
         return self.L.spgemm_numeric(self.plan, self.at(2), self.at(5), self.at(7), self.at(8), stream)
+
+    def backward(self, stream, da=True, db=True):
+        return self.L.spgemm_backward(self.plan, self.at(2), self.at(5), self.at(7), self.at(8),
+                                      self.at(9) if da else None, self.at(10) if db else None, stream)
 
     def batched(self, stream, values=None):
         """Size query of two problems, or (values: their value arrays) numeric."""
@@ -236,6 +242,37 @@ def last_calls_stream_is_gone_or_under_capture(h):
     assert h.numeric(S1) == 0
     assert not count(h.log(), f"^record .* stream {S3:#x}")
     h.capture(None)
+
+
+FORMS = {"one": ["k_gradI"], "two": ["k_grad_b", "k_grad_a"], "first pass": ["k_grad_b"]}
+
+
+def form(log):
+    launched = [n for n in ("k_gradI", "k_grad_b", "k_grad_a") if count(log, n)]
+    return next(k for k, v in FORMS.items() if v == launched)
+
+
+@scenario
+def gradients_take_the_faster_form(h):
+    """The first call takes the two passes; once the longest lists are known, a
+    few products on short lists take one launch, many or long lists two."""
+    cases = (  # products, nnz(C), longest lists of dB and dA, form
+        (40, 36, 8, 8, "one"),
+        (40, 36, 900, 8, "two"),        # one long A column
+        (40, 36, 8, 900, "two"),        # one long B row
+        (3_000_000, 2_900_000, 8, 8, "two"),
+        (3_000_000, 300_000, 8, 8, "one"))  # ten products on every entry of C
+    h.entries = 400_000
+    for products, nnz, zb, za, want in cases:
+        h.header({BIN_ESC0: 4}, products, nnz)
+        h.plan = C.c_void_p()
+        assert h.symbolic(S1) == 0
+        h.words[0], h.words[1] = zb, za
+        h.log()
+        assert h.backward(S1) == 0 and form(h.log()) == "two"
+        assert h.backward(S1) == 0
+        got = form(h.log())
+        assert got == want, (products, zb, za, got)
 
 
 if __name__ != "__main__":
