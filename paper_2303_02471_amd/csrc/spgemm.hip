@@ -1723,7 +1723,15 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
     {
         const BwShape shape{q.nnzb, (long long)products, p->totals_host[0], p->longest_b,
                             p->longest_a};
-        const bool two = bw_two_passes(shape, f64, dA_val != nullptr, dB_val != nullptr);
+        bool two = bw_two_passes(shape, f64, dA_val != nullptr, dB_val != nullptr);
+        if (two && dA_val) {
+            // the terms belong to the plan and are written: a captured call,
+            // whose replays may meet other gradients of the plan, only reads
+            // the view
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            SPG_TRY(hipStreamIsCapturing(s, &cs));
+            two = cs == hipStreamCaptureStatusNone;
+        }
         ProfScope ps("gradients", s);
         SPG_TRY(launch_backward(q, w, two, terms, f64, A_val, B_val, G_val, dA_val, dB_val,
                                 p->bt_err, s));

@@ -54,3 +54,67 @@ def test_forms(name, dtype):
             if n in need:
                 assert np.array_equal(x.cpu().numpy(), w), f"d{n.upper()}, call {call}"
     plan.close()
+
+
+def _setup(A, B, grads):
+    ocp, ori, ov = oracle.spgemm(A, B)
+    At, Bt = api.CscTensor.from_host(A), api.CscTensor.from_host(B)
+    Cm, plan = api.matmul(At, Bt, return_plan=True)
+    Gs = [gen.gradient_values(len(ov), seed=40 + i, dtype=np.float64) for i in range(grads)]
+    want = [oracle.backward(A, B, ocp, ori, G) for G in Gs]
+    dev = [torch.from_numpy(G).cuda() for G in Gs]
+    api.backward(plan, At.val, Bt.val, Cm.rowidx, dev[0])  # builds the view
+    torch.cuda.synchronize()
+    return At, Bt, Cm, plan, dev, want
+
+
+def _equal(got, want, what):
+    for x, w, n in zip(got, want, "AB"):
+        assert np.array_equal(x.cpu().numpy(), w), f"{what}: d{n}"
+
+
+def test_two_streams():
+    """Gradients of one plan on two streams without a wait between them."""
+    print("[case] backward on two streams", flush=True)
+    At, Bt, Cm, plan, dev, want = _setup(*gen.powerlaw(60000, seed=7), 6)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for s in streams:
+        s.wait_stream(torch.cuda.current_stream())
+    outs = [(torch.zeros_like(At.val), torch.zeros_like(Bt.val)) for _ in dev]
+    torch.cuda.synchronize()
+    for i, (G, out) in enumerate(zip(dev, outs)):
+        api.backward(plan, At.val, Bt.val, Cm.rowidx, G, out=out, stream=streams[i % 2])
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        _equal(out, want[i], f"call {i}")
+    plan.close()
+
+
+def test_replays_beside_other_gradients():
+    """Replays of captured gradients on one stream while eager ones of the same
+    plan run on another."""
+    print("[case] captured backward beside eager backward", flush=True)
+    At, Bt, Cm, plan, dev, want = _setup(*gen.powerlaw(60000, seed=8), 5)
+    outs = [(torch.zeros_like(At.val), torch.zeros_like(Bt.val)) for _ in dev]
+    s, other = torch.cuda.Stream(), torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(g, stream=s):
+            api.backward(plan, At.val, Bt.val, Cm.rowidx, dev[0], out=outs[0])
+    torch.cuda.synchronize()
+    for r in range(3):
+        for o in outs:
+            o[0].zero_(), o[1].zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            g.replay()
+        for i in range(1, len(dev)):
+            api.backward(plan, At.val, Bt.val, Cm.rowidx, dev[i], out=outs[i], stream=other)
+            if i == 2:
+                with torch.cuda.stream(s):
+                    g.replay()
+        torch.cuda.synchronize()
+        for i, o in enumerate(outs):
+            _equal(o, want[i], f"round {r}, gradient {i}")
+    plan.close()

@@ -275,6 +275,22 @@ def gradients_take_the_faster_form(h):
         assert got == want, (products, zb, za, got)
 
 
+@scenario
+def captured_gradients_only_read_the_view(h):
+    """Many products: two passes through the plan's terms, but not in a call under
+    capture, whose replays may run beside other gradients of the plan."""
+    h.entries = 400_000
+    h.header({BIN_ESC0: 4}, 3_000_000, 2_900_000)
+    assert h.symbolic(S1) == 0 and h.backward(S1) == 0 and h.backward(S1) == 0
+    assert form(h.log()) == "two"
+    h.capture(S2)
+    assert h.backward(S2) == 0 and form(h.log()) == "one"
+    assert h.backward(S2, db=False) == 0 and form(h.log()) == "one"
+    assert h.backward(S2, da=False) == 0 and form(h.log()) == "first pass"
+    h.capture(None)
+    assert h.backward(S1) == 0 and form(h.log()) == "two"
+
+
 if __name__ != "__main__":
     import pytest
 
