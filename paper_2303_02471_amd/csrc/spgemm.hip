@@ -142,6 +142,7 @@ struct spgemm_plan_s {
     // backward: the view, and one value per product (the terms of dA)
     DevBuf bt, terms;
     bool bt_ready = false;
+    bool terms_tried = false;  // their space has been asked for since the symbolic phase
     int *bt_err = nullptr;
     uint32_t bt_seq = 0;  // publication of the view's longest lists (0: none on its way)
     int32_t longest_b = -1, longest_a = -1;  // -1: not known yet
@@ -1505,6 +1506,7 @@ static spgemm_status symbolic_common(int32_t count, const spgemm_csc *A, const s
     p->symbolic_ok = false;
     p->bt_ready = false;
     p->bt_seq = 0;
+    p->terms_tried = false;
     p->longest_b = p->longest_a = -1;
     (void)hipGetDevice(&p->device);
     hipStream_t s = (hipStream_t)stream;
@@ -1680,14 +1682,11 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
                  o_cnt = carve(4 * (k + 3)), o_arrival = carve(4 * nb), o_pos = carve(4 * nb),
                  o_wbase = carve(8 * k), o_bsum = carve(8 * blocks), o_bsum2 = carve(8 * blocks),
                  o_gpos = carve(4 * products);
-    const size_t need = off, terms_need = (f64 ? 8 : 4) * products;
+    const size_t need = off;
     if (need > p->bt.bytes) {
         p->bt_ready = false;
         if (spgemm_status st = dev_alloc(p, p->bt, need, s)) return st;
     }
-    // without this space the gradients are formed in one launch
-    if (!p->bt_ready && terms_need > p->terms.bytes) (void)dev_alloc(p, p->terms, terms_need, s);
-    void *terms = p->terms.bytes >= terms_need ? p->terms.ptr : nullptr;
     char *b = (char *)p->bt.ptr;
     BwBuild bb{};
     bb.pofs = (long long *)(b + o_pofs);
@@ -1732,6 +1731,13 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
             SPG_TRY(hipStreamIsCapturing(s, &cs));
             two = cs == hipStreamCaptureStatusNone;
         }
+        const size_t terms_need = (f64 ? 8 : 4) * products;
+        if (two && dA_val && !p->terms_tried) {
+            // once: without this space dA is formed in the one launch
+            p->terms_tried = true;
+            if (terms_need > p->terms.bytes) (void)dev_alloc(p, p->terms, terms_need, s);
+        }
+        void *terms = p->terms.bytes >= terms_need ? p->terms.ptr : nullptr;
         ProfScope ps("gradients", s);
         SPG_TRY(launch_backward(q, w, two, terms, f64, A_val, B_val, G_val, dA_val, dB_val,
                                 p->bt_err, s));

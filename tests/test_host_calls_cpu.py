@@ -291,6 +291,22 @@ def captured_gradients_only_read_the_view(h):
     assert h.backward(S1) == 0 and form(h.log()) == "two"
 
 
+@scenario
+def terms_take_space_when_da_is_asked_for(h):
+    """The space of one value per product: not for dB alone, nor under capture,
+    and once."""
+    h.entries, products = 400_000, 3_000_000
+    h.header({BIN_ESC0: 4}, products, 2_900_000)
+    assert h.symbolic(S1) == 0
+    terms = f"^alloc {8 * products} "
+    for da, stream, want in ((False, S1, 0), (False, S1, 0), (True, S2, 0), (True, S1, 1), (True, S1, 0)):
+        h.capture(S2 if stream == S2 else None)
+        h.log()
+        assert h.backward(stream, da=da) == 0
+        assert count(h.log(), terms) == want, (da, stream)
+    h.capture(None)
+
+
 if __name__ != "__main__":
     import pytest
 
