@@ -476,10 +476,20 @@ hipError_t launch_numeric(const KArgs &a, bool f64, int first, int nbig, int max
     if (nwg <= 0) return hipSuccess;
     if (nwg > 0x7fffffffll) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nwg);
+    // Tiles alone: four workgroups to a compute unit, by LDS that none of them
+    // uses; more of them push each other's columns of A and C out of the caches
+    // (4000 columns of 30, double: 58.6 us with four, 63.0 with the five that
+    // the registers allow; 3000 of 40 101.9 and 111.0). Beside the chunks of
+    // large columns, which wait on few long lists, every one that fits (power
+    // law of 100,000 columns 47.3 and 43.5).
+    constexpr unsigned kUnused = 24 << 10, kLds = 160 << 10;
+    static_assert(4 * (sizeof(NumericSmem<double>) + kUnused) <= kLds, "four fit");
+    static_assert(5 * (sizeof(NumericSmem<float>) + kUnused) > kLds, "five do not");
+    const unsigned unused = nchunk ? 0 : kUnused;
     if (f64)
-        hipLaunchKernelGGL((k_numeric<double>), grid, dim3(kBlock), 0, s, a, first, nbig, (int)nchunk);
+        hipLaunchKernelGGL((k_numeric<double>), grid, dim3(kBlock), unused, s, a, first, nbig, (int)nchunk);
     else
-        hipLaunchKernelGGL((k_numeric<float>), grid, dim3(kBlock), 0, s, a, first, nbig, (int)nchunk);
+        hipLaunchKernelGGL((k_numeric<float>), grid, dim3(kBlock), unused, s, a, first, nbig, (int)nchunk);
     return hipGetLastError();
 }
 

@@ -66,11 +66,11 @@ err_t __hipPopCallConfiguration(dim3_t *g, dim3_t *b, size_t *lds, stream_t *s) 
     return 0;
 }
 err_t hipLaunchKernel(const void *fun, dim3_t g, dim3_t b, void **args, size_t lds, stream_t s) {
-    (void)b; (void)lds;
+    (void)b;
     const char *name = "?";
     for (int i = 0; i < nkernels; ++i)
         if (kernels[i].fun == fun) name = kernels[i].name;
-    note("launch %s stream %p blocks %u", name, s, g.x);
+    note("launch %s stream %p blocks %u lds %zu", name, s, g.x, lds);
     /* the argument that says where the header goes */
     static const struct { const char *name; int arg; } pubs[] = {
         {"k_place", 1}, {"k_scan_small", 2}, {"k_scan_down", 4}, {"k_publish", 1}, {"k_bv_gpos", 8}};

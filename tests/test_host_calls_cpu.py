@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 
 # words of the device header (csrc/internal.h): columns per bin, errors, products
 BIN_EMPTY, BIN_ESC0, BIN_SORT2, BIN_WSORT = 0, 1, 10, 12
-W_ERR, W_TOTAL_OP, W_HEAVY_PROD, W_HEAVY_WIN, W_NNZ = 36, 40, 42, 44, 48
+W_ERR, W_CHUNKS, W_TOTAL_OP, W_HEAVY_PROD, W_HEAVY_WIN, W_NNZ = 36, 38, 40, 42, 44, 48
 ERR_RETRY = 32
 S1, S2, S3 = 0x1000, 0x2000, 0x3000
 
@@ -305,6 +305,22 @@ def terms_take_space_when_da_is_asked_for(h):
         assert h.backward(stream, da=da) == 0
         assert count(h.log(), terms) == want, (da, stream)
     h.capture(None)
+
+
+@scenario
+def numeric_tiles_alone_leave_room_in_the_caches(h):
+    """The product space's numeric launch: unused LDS keeps tiles alone to four
+    workgroups a compute unit (160 KB), not those beside chunks of large columns."""
+    opts = h.options(flags=h.lib.SPGEMM_LANE_HASH)
+    for bins, chunks in (({BIN_ESC0: 4}, 0), ({BIN_ESC0: 3, BIN_WSORT: 1}, 2)):
+        h.plan = C.c_void_p()
+        h.header(bins, 12000, 9000)
+        h.words[W_CHUNKS] = chunks
+        assert h.symbolic(S1, opts=opts) == 0
+        h.log()
+        assert h.numeric(S1) == 0
+        lds = [int(re.search(r"lds (\d+)", x).group(1)) for x in h.log() if "k_numeric" in x]
+        assert len(lds) == 1 and (lds[0] > 0) == (chunks == 0), (bins, lds)
 
 
 if __name__ != "__main__":
