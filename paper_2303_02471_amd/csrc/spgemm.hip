@@ -22,6 +22,7 @@
 #include <mutex>
 #include <new>
 #include <optional>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/spgemm.h"
@@ -228,15 +229,36 @@ struct ProfScope {
 // them); spgemm_release_pool frees them. Every access holds the mutex; an
 // object belongs to one plan at a time.
 constexpr size_t kPoolSets = 4, kPoolMirrors = 4, kPoolBytes = 1u << 20;
+template <typename T, size_t N>
+struct Idle {
+    T kept[N] = {};
+    size_t n = 0;
+    bool put(const T &x) {
+        if (n == N) return false;
+        kept[n++] = x;
+        return true;
+    }
+    template <typename Pred>
+    bool take(T &x, Pred fits) {
+        for (size_t i = 0; i < n; ++i)
+            if (fits(kept[i])) {
+                x = kept[i];
+                kept[i] = kept[--n];
+                kept[n] = T{};
+                return true;
+            }
+        return false;
+    }
+};
+// (of fixed size: handing an object back from a destructor allocates nothing,
+// and no static destructor ends it)
 struct HostPool {
     std::mutex mu;
-    std::vector<SideSet> sets;
-    std::vector<HostMirror> mirrors;
+    Idle<SideSet, kPoolSets> sets;
+    Idle<HostMirror, kPoolMirrors> mirrors;
 };
-HostPool &host_pool() {
-    static HostPool *pool = new HostPool;  // outlives every static destructor
-    return *pool;
-}
+HostPool g_pool;
+static_assert(std::is_trivially_destructible<HostPool>::value, "plans may outlive static objects");
 
 void destroy_sides(SideSet &x) {
     for (int i = 0; i < SideSet::kSide; ++i) {
@@ -256,10 +278,8 @@ void release_sides(SideSet &x) {
     bool ok = true;
     for (int i = 0; i < SideSet::kSide; ++i) ok &= hipStreamSynchronize(x.side[i]) == hipSuccess;
     if (ok) {
-        HostPool &hp = host_pool();
-        std::lock_guard<std::mutex> lk(hp.mu);
-        if (hp.sets.size() < kPoolSets) {
-            hp.sets.push_back(x);
+        std::lock_guard<std::mutex> lk(g_pool.mu);
+        if (g_pool.sets.put(x)) {
             x = SideSet{};
             return;
         }
@@ -269,14 +289,9 @@ void release_sides(SideSet &x) {
 
 hipError_t acquire_sides(SideSet &x, int device) {
     {
-        HostPool &hp = host_pool();
-        std::lock_guard<std::mutex> lk(hp.mu);
-        for (size_t i = 0; i < hp.sets.size(); ++i)
-            if (hp.sets[i].device == device) {
-                x = hp.sets[i];
-                hp.sets.erase(hp.sets.begin() + (long)i);
-                return hipSuccess;
-            }
+        std::lock_guard<std::mutex> lk(g_pool.mu);
+        if (g_pool.sets.take(x, [&](const SideSet &k) { return k.device == device; }))
+            return hipSuccess;
     }
     hipError_t e;
     // the fork and join events only order streams of this device: a
@@ -295,10 +310,8 @@ hipError_t acquire_sides(SideSet &x, int device) {
 void release_mirror(HostMirror &m, bool idle) {
     if (!m.base) return;
     if (idle && 12 * m.words + m.upload <= kPoolBytes) {
-        HostPool &hp = host_pool();
-        std::lock_guard<std::mutex> lk(hp.mu);
-        if (hp.mirrors.size() < kPoolMirrors) {
-            hp.mirrors.push_back(m);
+        std::lock_guard<std::mutex> lk(g_pool.mu);
+        if (g_pool.mirrors.put(m)) {
             m = HostMirror{};
             return;
         }
@@ -309,16 +322,11 @@ void release_mirror(HostMirror &m, bool idle) {
 
 spgemm_status acquire_mirror(HostMirror &m, int device, size_t words, size_t upload) {
     {
-        HostPool &hp = host_pool();
-        std::lock_guard<std::mutex> lk(hp.mu);
-        for (size_t i = 0; i < hp.mirrors.size(); ++i) {
-            const HostMirror &x = hp.mirrors[i];
-            if (x.device == device && x.words >= words && x.upload >= upload) {
-                m = x;
-                hp.mirrors.erase(hp.mirrors.begin() + (long)i);
-                return SPGEMM_OK;
-            }
-        }
+        std::lock_guard<std::mutex> lk(g_pool.mu);
+        if (g_pool.mirrors.take(m, [&](const HostMirror &k) {
+                return k.device == device && k.words >= words && k.upload >= upload;
+            }))
+            return SPGEMM_OK;
     }
     auto up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     m = HostMirror{};
@@ -1847,12 +1855,11 @@ void spgemm_plan_destroy(spgemm_plan p) {
 void spgemm_batch_plan_destroy(spgemm_batch_plan p) { spgemm_plan_destroy(p); }
 
 void spgemm_release_pool(void) {
-    HostPool &hp = host_pool();
-    std::lock_guard<std::mutex> lk(hp.mu);
-    for (SideSet &x : hp.sets) destroy_sides(x);
-    for (HostMirror &m : hp.mirrors) (void)hipHostFree(m.base);
-    hp.sets.clear();
-    hp.mirrors.clear();
+    std::lock_guard<std::mutex> lk(g_pool.mu);
+    SideSet x;
+    HostMirror m;
+    while (g_pool.sets.take(x, [](const SideSet &) { return true; })) destroy_sides(x);
+    while (g_pool.mirrors.take(m, [](const HostMirror &) { return true; })) (void)hipHostFree(m.base);
 }
 
 }  // extern "C"

@@ -323,6 +323,35 @@ def numeric_tiles_alone_leave_room_in_the_caches(h):
         assert len(lds) == 1 and (lds[0] > 0) == (chunks == 0), (bins, lds)
 
 
+@scenario
+def pool_is_bounded_and_given_back(h):
+    """Six plans end: the host memory of four is kept, the rest freed; four new
+    plans take it, and spgemm_release_pool frees what is idle."""
+    h.header({BIN_ESC0: 4}, 12, 9)
+
+    def plans(n):
+        made = []
+        for _ in range(n):
+            h.plan = C.c_void_p()
+            assert h.multiply() == 0
+            made.append(h.plan)
+        return made, count(h.log(), "^hostalloc")
+
+    def end(made):
+        for p in made:
+            h.L.spgemm_plan_destroy(p)
+        return count(h.log(), "^hostfree")
+
+    six, allocated = plans(6)
+    assert allocated == 6 and end(six) == 2
+    four, allocated = plans(4)
+    assert allocated == 0 and end(four) == 0
+    h.L.spgemm_release_pool()
+    assert count(h.log(), "^hostfree") == 4
+    one, allocated = plans(1)
+    assert allocated == 1 and end(one) == 0
+
+
 if __name__ != "__main__":
     import pytest
 
