@@ -388,12 +388,12 @@ struct BwBuild {
     int32_t *rowptr, *rowent;
     long long *rowpofs;
     int2 *arow;
-    int32_t *cnt;          // [rows of B], cleared with the error word and the longest
-    size_t clear_bytes;    // lists behind it
-    int *longest;          // [2] longest lists of dB and dA
+    int32_t *cnt;          // [rows of B], cleared with the error word behind it
+    size_t clear_bytes;
     int32_t *arrival, *pos;
     long long *wbase;      // [rows of B] terms of dA before every row
     long long *bsum, *bsum2;  // [bw_scan_blocks]
+    int2 *blong;              // [bw_scan_blocks]
 };
 int bw_scan_blocks(int nnzb, int nrows);
 // pub: where the longest lists go, for later calls

@@ -330,18 +330,23 @@ __global__ __launch_bounds__(kBlock) void k_bv_count(Prob p, int32_t *cnt, int32
 // Prefix sums in two launches. Blocks [0, nbt): the lengths of the A columns
 // that the stored B entries select (pofs); the others, over B's rows k: the
 // entries before (rowptr) and the terms of dA before (wbase, deg_k z_k each).
+// The last block also finds the longest lists of dB (z_k) and dA (deg_k), from
+// the blocks' own, and publishes them. (A device-wide maximum by atomics, one a
+// wavefront, took 20 us for 180,000 entries: all of them meet in one word.)
 struct BvScan {
     const int2 *E;
     int nnzb, nrows, nbt;
     const int32_t *cnt, *acp;
     long long *bsum, *bsum2;  // per block: pofs or wbase sums; rowptr sums
+    int2 *blong;              // per block: longest lists of dB, dA
     long long *pofs, *wbase;
     int32_t *rowptr;
 };
 constexpr int kBvPer = 4, kBvBlock = kBvPer * kBlock;
 
 __device__ __forceinline__ void bv_items(const BvScan &a, int b, long long (&x)[kBvPer],
-                                         long long (&y)[kBvPer]) {
+                                         long long (&y)[kBvPer], int2 &most) {
+    most = make_int2(0, 0);
 #pragma unroll
     for (int u = 0; u < kBvPer; ++u) {
         x[u] = y[u] = 0;
@@ -351,8 +356,11 @@ __device__ __forceinline__ void bv_items(const BvScan &a, int b, long long (&x)[
         } else {
             const int k = (b - a.nbt) * kBvBlock + threadIdx.x * kBvPer + u;
             if (k < a.nrows) {
+                const int z = a.acp[k + 1] - a.acp[k];
                 y[u] = a.cnt[k];
-                x[u] = y[u] * (a.acp[k + 1] - a.acp[k]);
+                x[u] = y[u] * z;
+                if (y[u] > 0) most.x = max(most.x, z);
+                if (y[u] > 0 && z > 0) most.y = max(most.y, (int)y[u]);
             }
         }
     }
@@ -360,8 +368,10 @@ __device__ __forceinline__ void bv_items(const BvScan &a, int b, long long (&x)[
 
 __global__ __launch_bounds__(kBlock) void k_bv_sums(BvScan a) {
     __shared__ long long s[2][kBlock / 64];
+    __shared__ int2 s_most[kBlock / 64];
     long long x[kBvPer], y[kBvPer], sx = 0, sy = 0;
-    bv_items(a, blockIdx.x, x, y);
+    int2 most;
+    bv_items(a, blockIdx.x, x, y, most);
 #pragma unroll
     for (int u = 0; u < kBvPer; ++u) {
         sx += x[u];
@@ -369,32 +379,56 @@ __global__ __launch_bounds__(kBlock) void k_bv_sums(BvScan a) {
     }
     sx = wave_sum64(sx);
     sy = wave_sum64(sy);
-    if ((threadIdx.x & 63) == 0) {
+    most.x = wave_incl_max(most.x);
+    most.y = wave_incl_max(most.y);
+    if ((threadIdx.x & 63) == 63) {
         s[0][threadIdx.x >> 6] = sx;
         s[1][threadIdx.x >> 6] = sy;
+        s_most[threadIdx.x >> 6] = most;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         sx = sy = 0;
+        most = make_int2(0, 0);
         for (int q = 0; q < kBlock / 64; ++q) {
             sx += s[0][q];
             sy += s[1][q];
+            most.x = max(most.x, s_most[q].x);
+            most.y = max(most.y, s_most[q].y);
         }
         a.bsum[blockIdx.x] = sx;
         a.bsum2[blockIdx.x] = sy;
+        a.blong[blockIdx.x] = most;
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_bv_scan(BvScan a) {
+__global__ __launch_bounds__(kBlock) void k_bv_scan(BvScan a, PubArgs pub) {
     __shared__ long long tmp[kBlock / 64 + 1];
     const int b = blockIdx.x, first = b < a.nbt ? 0 : a.nbt;
+    if (pub.dst && b == (int)gridDim.x - 1 && threadIdx.x < 64) {
+        int2 most = make_int2(0, 0);
+        for (int q = a.nbt + (int)threadIdx.x; q <= b; q += 64) {
+            most.x = max(most.x, a.blong[q].x);
+            most.y = max(most.y, a.blong[q].y);
+        }
+        most.x = wave_incl_max(most.x);
+        most.y = wave_incl_max(most.y);
+        if (threadIdx.x == 63) {
+            const unsigned long long tag = (unsigned long long)pub.seq << 32;
+            __hip_atomic_store(&pub.dst[0], (unsigned)most.x | tag, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&pub.dst[1], (unsigned)most.y | tag, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
     long long bx = 0, by = 0;  // sums of the earlier blocks of the same list
     for (int q = first + threadIdx.x; q < b; q += kBlock) {
         bx += a.bsum[q];
         by += a.bsum2[q];
     }
     long long x[kBvPer], y[kBvPer], sx = 0, sy = 0, tx, ty;
-    bv_items(a, b, x, y);
+    int2 most;
+    bv_items(a, b, x, y, most);
 #pragma unroll
     for (int u = 0; u < kBvPer; ++u) {
         sx += x[u];
@@ -433,20 +467,17 @@ __global__ __launch_bounds__(kBlock) void k_bv_fill(Prob p, const int32_t *rowpt
 // Blocks [0, nbt): every B entry's rank in its row by ascending column (the
 // entries before it in B's storage, counted in the row's list: by its thread,
 // or for rows above kBvCount entries by the whole wavefront), the row's sorted
-// entries, the entry's terms of dA, and the longest lists of dB (`longest[0]`)
-// and dA. The others: every A entry's terms.
+// entries and the entry's terms of dA. The others: every A entry's terms.
 constexpr int kBvCount = 64;
 __global__ __launch_bounds__(kBlock) void k_bv_rank(Prob p, const int32_t *rowptr,
                                                     const int32_t *pos, const long long *wbase,
                                                     const long long *pofs, int nbt,
                                                     int32_t *rowent, long long *rowpofs,
-                                                    long long *woff, int4 *aview, int2 *arow,
-                                                    int *longest) {
+                                                    long long *woff, int4 *aview, int2 *arow) {
     if ((int)blockIdx.x < nbt) {
         const int t = blockIdx.x * kBlock + threadIdx.x;
         const int k = t < p.nnzb ? p.bri[t] : -1;
         const int b = k >= 0 ? rowptr[k] : 0, e = k >= 0 ? rowptr[k + 1] : 0;
-        const int z = k >= 0 ? p.acp[k + 1] - p.acp[k] : 0;
         int rank = 0;
         if (e - b <= kBvCount)
             for (int r = b; r < e; ++r) rank += pos[r] < t ? 1 : 0;
@@ -460,16 +491,10 @@ __global__ __launch_bounds__(kBlock) void k_bv_rank(Prob p, const int32_t *rowpt
             n = wave_sum(n);
             if (lane_id() == src) rank = n;
         }
-        const int lb = __builtin_amdgcn_readlane(wave_incl_max(z), 63);
-        const int la = __builtin_amdgcn_readlane(wave_incl_max(z > 0 ? e - b : 0), 63);
-        if (lane_id() == 0) {
-            if (lb > __atomic_load_n(&longest[0], __ATOMIC_RELAXED)) atomicMax(&longest[0], lb);
-            if (la > __atomic_load_n(&longest[1], __ATOMIC_RELAXED)) atomicMax(&longest[1], la);
-        }
         if (k < 0) return;
         rowent[b + rank] = t;
         rowpofs[b + rank] = pofs[t];
-        woff[t] = wbase[k] + (long long)rank * z;
+        woff[t] = wbase[k] + (long long)rank * (p.acp[k + 1] - p.acp[k]);
     } else {
         const int q = (blockIdx.x - nbt) * kBlock + threadIdx.x;
         if (q >= p.nnza) return;
@@ -482,20 +507,15 @@ __global__ __launch_bounds__(kBlock) void k_bv_rank(Prob p, const int32_t *rowpt
 }
 
 // the place of every product's row among C's entries (C's columns ascend: a
-// binary search), products taken as in the first pass; and the longest lists
-// to the host
+// binary search), products taken as in the first pass
 __global__ __launch_bounds__(64) void k_bv_gpos(Prob p, const int2 *__restrict__ E,
                                                 const long long *__restrict__ pofs,
                                                 const int32_t *__restrict__ cri, long long nnzc,
-                                                uint32_t *__restrict__ gpos, int *err,
-                                                const int *longest, PubArgs pub) {
+                                                uint32_t *__restrict__ gpos, int *err) {
     __shared__ unsigned bits[kBwN / 32];
     __shared__ int s_q[64], s_lo[64], s_hi[64];
     const int lane = threadIdx.x;
     const int t = blockIdx.x * 64 + lane;
-    if (pub.dst && blockIdx.x == 0 && lane < pub.nwords)
-        __hip_atomic_store(&pub.dst[lane], (unsigned)longest[lane] | ((unsigned long long)pub.seq << 32),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const long long p0 = pofs[blockIdx.x * 64];
     int2 e = make_int2(0, 0);
     int c0 = 0, c1 = 0;
@@ -566,15 +586,15 @@ hipError_t launch_bw_view(const Prob &p, const BwView &v, const BwBuild &b, cons
                           int *err, const PubArgs &pub, hipStream_t s) {
     const int nrows = p.k;  // rows of B
     hipError_t e;
-    // counts, the error word and the longest lists lie together
+    // counts and the error word lie together
     if ((e = hipMemsetAsync(b.cnt, 0, b.clear_bytes, s))) return e;
     const int gt = ceil_div(p.nnzb, kBlock), ga = ceil_div(p.nnza, kBlock);
     if (gt > 0) hipLaunchKernelGGL(k_bv_count, dim3(gt), dim3(kBlock), 0, s, p, b.cnt, b.arrival);
     BvScan sc{v.E, p.nnzb, nrows, ceil_div(p.nnzb, kBvBlock), b.cnt, p.acp,
-              b.bsum, b.bsum2, b.pofs, b.wbase, b.rowptr};
+              b.bsum, b.bsum2, b.blong, b.pofs, b.wbase, b.rowptr};
     if (const int nb = bw_scan_blocks(p.nnzb, nrows)) {
         hipLaunchKernelGGL(k_bv_sums, dim3(nb), dim3(kBlock), 0, s, sc);
-        hipLaunchKernelGGL(k_bv_scan, dim3(nb), dim3(kBlock), 0, s, sc);
+        hipLaunchKernelGGL(k_bv_scan, dim3(nb), dim3(kBlock), 0, s, sc, pub);
     }
     if (gt > 0)
         hipLaunchKernelGGL(k_bv_fill, dim3(gt), dim3(kBlock), 0, s, p, (const int32_t *)b.rowptr,
@@ -583,11 +603,10 @@ hipError_t launch_bw_view(const Prob &p, const BwView &v, const BwBuild &b, cons
         hipLaunchKernelGGL(k_bv_rank, dim3(gt + ga), dim3(kBlock), 0, s, p,
                            (const int32_t *)b.rowptr, (const int32_t *)b.pos,
                            (const long long *)b.wbase, (const long long *)b.pofs, gt, b.rowent,
-                           b.rowpofs, b.woff, b.aview, b.arow, b.longest);
+                           b.rowpofs, b.woff, b.aview, b.arow);
     if (p.nnzb > 0)
         hipLaunchKernelGGL(k_bv_gpos, dim3(ceil_div(p.nnzb, 64)), dim3(64), 0, s, p, v.E,
-                           (const long long *)b.pofs, cri, v.nnzc, b.gpos, err,
-                           (const int *)b.longest, pub);
+                           (const long long *)b.pofs, cri, v.nnzc, b.gpos, err);
     return hipGetLastError();
 }
 

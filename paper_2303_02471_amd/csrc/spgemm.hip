@@ -1687,8 +1687,9 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
     const size_t o_pofs = carve(8 * nb), o_woff = carve(8 * nb), o_aview = carve(16 * na),
                  o_rowptr = carve(4 * (k + 1)), o_rowent = carve(4 * nb),
                  o_rowpofs = carve(8 * nb), o_arow = carve(8 * na),
-                 o_cnt = carve(4 * (k + 3)), o_arrival = carve(4 * nb), o_pos = carve(4 * nb),
+                 o_cnt = carve(4 * (k + 1)), o_arrival = carve(4 * nb), o_pos = carve(4 * nb),
                  o_wbase = carve(8 * k), o_bsum = carve(8 * blocks), o_bsum2 = carve(8 * blocks),
+                 o_blong = carve(8 * blocks),
                  o_gpos = carve(4 * products);
     const size_t need = off;
     if (need > p->bt.bytes) {
@@ -1705,13 +1706,13 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
     bb.rowpofs = (long long *)(b + o_rowpofs);
     bb.arow = (int2 *)(b + o_arow);
     bb.cnt = (int32_t *)(b + o_cnt);
-    bb.clear_bytes = 4 * (k + 3);
-    bb.longest = bb.cnt + k + 1;
+    bb.clear_bytes = 4 * (k + 1);
     bb.arrival = (int32_t *)(b + o_arrival);
     bb.pos = (int32_t *)(b + o_pos);
     bb.wbase = (long long *)(b + o_wbase);
     bb.bsum = (long long *)(b + o_bsum);
     bb.bsum2 = (long long *)(b + o_bsum2);
+    bb.blong = (int2 *)(b + o_blong);
     bb.gpos = (uint32_t *)(b + o_gpos);
     p->bt_err = (int *)(b + o_cnt) + k;
     const BwView w{p->E, bb.gpos, p->totals_host[0], bb.pofs, bb.woff, bb.aview, bb.rowptr,
@@ -1722,7 +1723,7 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
         ProfScope ps("bw_view", s);
         const PubArgs pub = next_view_publication(p);
         SPG_TRY(launch_bw_view(q, w, bb, C_rowidx, p->bt_err, pub, s));
-        p->bt_seq = q.nnzb > 0 ? pub.seq : 0;
+        p->bt_seq = q.k > 0 ? pub.seq : 0;
         p->bt_ready = true;
     } else {
         read_view_publication(p);

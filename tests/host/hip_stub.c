@@ -73,7 +73,7 @@ err_t hipLaunchKernel(const void *fun, dim3_t g, dim3_t b, void **args, size_t l
     note("launch %s stream %p blocks %u lds %zu", name, s, g.x, lds);
     /* the argument that says where the header goes */
     static const struct { const char *name; int arg; } pubs[] = {
-        {"k_place", 1}, {"k_scan_small", 2}, {"k_scan_down", 4}, {"k_publish", 1}, {"k_bv_gpos", 8}};
+        {"k_place", 1}, {"k_scan_small", 2}, {"k_scan_down", 4}, {"k_publish", 1}, {"k_bv_scan", 1}};
     for (unsigned i = 0; i < sizeof pubs / sizeof pubs[0]; ++i) {
         if (!strstr(name, pubs[i].name)) continue;
         const pub_t *p = args[pubs[i].arg];
