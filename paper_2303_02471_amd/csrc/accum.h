@@ -26,7 +26,7 @@
 //
 // Sort and compress. Keys (row << 11 | position) are sorted inside every
 // segment by a bitonic network on registers and lanes (DPP, ds_swizzle,
-// permlane swaps), or, where one column fills the buffer, by order-preserving
+// ds_bpermute), or, where one column fills the buffer, by order-preserving
 // buckets in LDS. Equal rows form runs whose positions are in Algorithm 1's
 // order; a run's values are added in that order.
 //
@@ -106,12 +106,6 @@ template <>
 struct KeyTraits<unsigned long long> {
     static constexpr unsigned long long kmax = ~0ull;
 };
-
-// value of `v` in the lane `d` below (lanes below d read their own)
-__device__ __forceinline__ int shfl_up_i(int v, int d) {
-    const int l = lane_id();
-    return __builtin_amdgcn_ds_bpermute((l >= d ? l - d : l) << 2, v);
-}
 
 // Median of three unsigned 32-bit values where c is 0 (the smaller of x and
 // y) or all ones (the larger): one v_med3_u32 takes a compare-exchange's side
@@ -270,6 +264,13 @@ __device__ __forceinline__ void seg_sort(K (&key)[KPL], int lane_in) {
 // row) leaves the keys as they were, for the network. The waves were bound by
 // the network's vector instructions: 1024-product waves of a batch 384 -> 357
 // us, counting 214 -> 172 us (with the smaller buffer below 341 and 140 us).
+// What the attempt costs where it is given up, numeric phases, against the
+// network alone: 20,000 columns of a band of 20, 23 and 30 (10 to 15 products a
+// row) 42 and 37, 85 and 74, 86 and 77 us, blocks of 32 79 and 61, a 27-point
+// stencil squared 114 and 100, rows drawn by u^4 26 and 24. What it gains where
+// the rows spread: 10,000 columns of 22 24.3 and 25.4, 4096 of 40 64 and 68,
+// windows on clusters, bands and blocks (narrow, so their rows spread) 104 and
+// 112, 386 and 416, 496 and 527.
 //   key: all ones where there is none; rows in [lo, lo + span); buf: 64 KPL
 //   words.
 constexpr int kBucketMax = 12;

@@ -114,8 +114,6 @@ __device__ __forceinline__ int wave_incl_max(int v) {
     return v;
 }
 
-__device__ __forceinline__ int wave_bcast(int v, int src) { return shfl_idx(v, src); }
-
 // 64-bit prefix sum (values and sums of 0 .. 2^63 - 1) over the wavefront, and
 // its last value: three scans of 21-bit pieces, whose sums stay below 2^27
 __device__ __forceinline__ long long wave_incl_scan64(long long v) {

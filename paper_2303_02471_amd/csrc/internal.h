@@ -107,7 +107,7 @@ struct Hdr {
     int32_t big_chunks;                // most kChunkB-entry chunks of a column above t_split
     int32_t cap_over;                  // nnz(C) exceeds the output capacity of a one-call product
     unsigned long long total_op;
-    unsigned long long heavy_prod;     // products of the heavy columns (bins SORT3, WSORT)
+    unsigned long long heavy_prod;     // products of the heavy columns (SORT2, SORT3, WSORT)
     int32_t heavy_win;                 // row windows of the heavy columns
     int32_t pad_;
 };
@@ -200,7 +200,7 @@ struct KArgs {
     int32_t *lpid;          // [later_n] problem
     int32_t *lkc;           // [later_n] occurrence index k
     void *lv;               // [later_n] value (V)
-    // Heavy columns of the direct-gather accumulators (bins SORT3 and WSORT,
+    // Heavy columns of the direct-gather accumulators (bins SORT2, SORT3 and WSORT,
     // adjacent in the bin list, position li among them): first product in the
     // heavy scratch, first row window, and the scratch itself.
     long long *hoff;        // [heavy columns]

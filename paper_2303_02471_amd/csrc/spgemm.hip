@@ -731,21 +731,6 @@ int esc_groups(const Hdr &h) {
     return g;
 }
 
-int device_cus() {
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            cus <= 0)
-            cus = 256;
-    }
-    return cus;
-}
-
-// One launch per accumulator kind, each with one wavefront (sort-merge) or
-// one workgroup (dense, hash) per work item; the grids come from the bin sizes
-// on the host.
 hipError_t ensure_side_streams(spgemm_plan p) {
     return p->sides.fork_ev ? hipSuccess : acquire_sides(p->sides, p->device);
 }
