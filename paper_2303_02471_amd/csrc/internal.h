@@ -401,10 +401,13 @@ hipError_t launch_bw_view(const Prob &p, const BwView &v, const BwBuild &b, cons
                           int *err, const PubArgs &pub, hipStream_t s);
 // whether dA (need_a) and dB (need_b) are faster in two passes than in one launch
 bool bw_two_passes(const BwShape &x, bool f64, bool need_a, bool need_b);
-// dA (if da) and dB (if db) of one problem through the view, in two passes (dA
-// with `terms`, space of one value per product) or one launch; err collects
-// ERR_CSC for a place outside C (an inconsistent plan)
-hipError_t launch_backward(const Prob &p, const BwView &v, bool two, void *terms, bool f64,
+// dA (if da) and dB (if db) of one problem through the view: in one launch; in
+// two passes (terms: space of one value per product, where dA is wanted); or
+// apart, the first pass for dB and the one launch for dA, where two passes would
+// be faster but have no terms to write. err collects ERR_CSC for a place outside
+// C (an inconsistent plan).
+enum class BwForm { one, two, apart };
+hipError_t launch_backward(const Prob &p, const BwView &v, BwForm form, void *terms, bool f64,
                            const void *av, const void *bv, const void *gv, void *da, void *db,
                            int *err, hipStream_t s);
 // nwords 32-bit words from src to mapped host memory dst, as 8-byte pairs

@@ -664,34 +664,39 @@ bool bw_two_passes(const BwShape &x, bool f64, bool need_a, bool need_b) {
 }
 
 template <typename V>
-static hipError_t run_backward(const Prob &p, const BwView &v, bool two, void *terms, const V *av,
-                               const V *bv, const V *gv, V *da, V *db, int *err, hipStream_t s) {
+static hipError_t run_backward(const Prob &p, const BwView &v, BwForm form, void *terms,
+                               const V *av, const V *bv, const V *gv, V *da, V *db, int *err,
+                               hipStream_t s) {
     if (p.nnzb <= 0) db = nullptr;
     if (p.nnza <= 0) da = nullptr;
-    if (!da && !db) return hipSuccess;
-    if (!two || (da && !terms)) {
-        const int nbw = db ? ceil_div(p.nnzb, kBlock) : 0, naw = da ? ceil_div(p.nnza, kBlock) : 0;
+    const int nb = ceil_div(p.nnzb, kBlock), na = ceil_div(p.nnza, kBlock);
+    if (form != BwForm::one) {
+        V *w = da && form == BwForm::two ? (V *)terms : nullptr;
+        if (p.nnzb > 0 && (db || w))
+            hipLaunchKernelGGL(k_grad_b<V>, dim3(ceil_div(p.nnzb, 64)), dim3(64), 0, s, v, p.nnzb,
+                               av, bv, gv, db, w, err);
+        db = nullptr;
+        if (da && w) {
+            hipLaunchKernelGGL(k_grad_a<V>, dim3(na), dim3(kBlock), 0, s, v.aview, p.nnza,
+                               (const V *)w, da);
+            da = nullptr;
+        }
+    }
+    if (da || db) {
+        const int nbw = db ? nb : 0, naw = da ? na : 0;
         hipLaunchKernelGGL(k_grad<V>, dim3(nbw + naw), dim3(kBlock), 0, s, v, p.nnza, p.nnzb, nbw,
                            av, bv, gv, da, db, err);
-        return hipGetLastError();
     }
-    V *w = da ? (V *)terms : nullptr;
-    if (p.nnzb > 0)
-        hipLaunchKernelGGL(k_grad_b<V>, dim3(ceil_div(p.nnzb, 64)), dim3(64), 0, s, v, p.nnzb, av,
-                           bv, gv, db, w, err);
-    if (da)
-        hipLaunchKernelGGL(k_grad_a<V>, dim3(ceil_div(p.nnza, kBlock)), dim3(kBlock), 0, s, v.aview,
-                           p.nnza, (const V *)w, da);
     return hipGetLastError();
 }
 
-hipError_t launch_backward(const Prob &p, const BwView &v, bool two, void *terms, bool f64,
+hipError_t launch_backward(const Prob &p, const BwView &v, BwForm form, void *terms, bool f64,
                            const void *av, const void *bv, const void *gv, void *da, void *db,
                            int *err, hipStream_t s) {
     if (f64)
-        return run_backward<double>(p, v, two, terms, (const double *)av, (const double *)bv,
+        return run_backward<double>(p, v, form, terms, (const double *)av, (const double *)bv,
                                     (const double *)gv, (double *)da, (double *)db, err, s);
-    return run_backward<float>(p, v, two, terms, (const float *)av, (const float *)bv,
+    return run_backward<float>(p, v, form, terms, (const float *)av, (const float *)bv,
                                (const float *)gv, (float *)da, (float *)db, err, s);
 }
 

@@ -1716,24 +1716,30 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
     {
         const BwShape shape{q.nnzb, (long long)products, p->totals_host[0], p->longest_b,
                             p->longest_a};
-        bool two = bw_two_passes(shape, f64, dA_val != nullptr, dB_val != nullptr);
-        if (two && dA_val) {
-            // the terms belong to the plan and are written: a captured call,
-            // whose replays may meet other gradients of the plan, only reads
-            // the view
-            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-            SPG_TRY(hipStreamIsCapturing(s, &cs));
-            two = cs == hipStreamCaptureStatusNone;
+        BwForm form = BwForm::one;
+        void *terms = nullptr;
+        if (bw_two_passes(shape, f64, dA_val != nullptr, dB_val != nullptr)) {
+            form = BwForm::two;
+            if (dA_val) {
+                // the terms belong to the plan and are written: a captured call,
+                // whose replays may meet other gradients of the plan, only
+                // reads the view. Their space is asked for once.
+                hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+                SPG_TRY(hipStreamIsCapturing(s, &cs));
+                const size_t terms_need = (f64 ? 8 : 4) * products;
+                if (cs == hipStreamCaptureStatusNone) {
+                    if (!p->terms_tried && terms_need > p->terms.bytes)
+                        (void)dev_alloc(p, p->terms, terms_need, s);
+                    p->terms_tried = true;
+                    if (p->terms.bytes >= terms_need) terms = p->terms.ptr;
+                }
+                if (!terms)
+                    form = dB_val && bw_two_passes(shape, f64, false, true) ? BwForm::apart
+                                                                            : BwForm::one;
+            }
         }
-        const size_t terms_need = (f64 ? 8 : 4) * products;
-        if (two && dA_val && !p->terms_tried) {
-            // once: without this space dA is formed in the one launch
-            p->terms_tried = true;
-            if (terms_need > p->terms.bytes) (void)dev_alloc(p, p->terms, terms_need, s);
-        }
-        void *terms = p->terms.bytes >= terms_need ? p->terms.ptr : nullptr;
         ProfScope ps("gradients", s);
-        SPG_TRY(launch_backward(q, w, two, terms, f64, A_val, B_val, G_val, dA_val, dB_val,
+        SPG_TRY(launch_backward(q, w, form, terms, f64, A_val, B_val, G_val, dA_val, dB_val,
                                 p->bt_err, s));
     }
     p->last_stream = s;
