@@ -311,12 +311,15 @@ spgemm_status spgemm_multiply_noalloc(const spgemm_csc *A, const spgemm_csc *B, 
  * The first call builds and caches a view of the two patterns inside the plan
  * (per product its place in C; per stored entry its products and terms). The
  * first that asks for dA may take space for one value per product (the terms of
- * dA; without that space dA and dB gather G from C each). Both may allocate;
- * later calls on the plan are stream-ordered, allocate nothing and queue only
- * kernels. They may be captured in a HIP graph, together with spgemm_numeric on
- * the same plan: captured gradients only read the view, so their replays may
- * overlap other gradients of the plan; a replay of spgemm_numeric uses the
- * plan's workspace and must not overlap other products on the plan.
+ * dA; without that space dA gathers G from C). Both may allocate; later calls on
+ * the plan are stream-ordered, allocate nothing and queue only kernels. They may
+ * be captured in a HIP graph, together with spgemm_numeric on the same plan; the
+ * replays come after the plan's calls made before the capture. A captured call
+ * that uses the terms' space keeps it (up to four of them, until the plan is
+ * destroyed; the next call that asks for dA may take new space), so replays of
+ * captured gradients may overlap other gradients of the plan; a replay of
+ * spgemm_numeric uses the plan's workspace and must not overlap other products
+ * on the plan.
  */
 spgemm_status spgemm_backward(spgemm_plan plan, const void *A_val, const void *B_val,
                               const int32_t *C_rowidx, const void *G_val,

@@ -144,6 +144,10 @@ struct spgemm_plan_s {
     DevBuf bt, terms;
     bool bt_ready = false;
     bool terms_tried = false;  // their space has been asked for since the symbolic phase
+    // terms of captured calls, which no other call uses
+    static constexpr int kCaptured = 4;
+    DevBuf captured[kCaptured];
+    int ncaptured = 0;
     int *bt_err = nullptr;
     uint32_t bt_seq = 0;  // publication of the view's longest lists (0: none on its way)
     int32_t longest_b = -1, longest_a = -1;  // -1: not known yet
@@ -1721,17 +1725,23 @@ spgemm_status spgemm_backward(spgemm_plan p, const void *A_val, const void *B_va
         if (bw_two_passes(shape, f64, dA_val != nullptr, dB_val != nullptr)) {
             form = BwForm::two;
             if (dA_val) {
-                // the terms belong to the plan and are written: a captured call,
-                // whose replays may meet other gradients of the plan, only
-                // reads the view. Their space is asked for once.
+                const size_t terms_need = (f64 ? 8 : 4) * products;
                 hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
                 SPG_TRY(hipStreamIsCapturing(s, &cs));
-                const size_t terms_need = (f64 ? 8 : 4) * products;
                 if (cs == hipStreamCaptureStatusNone) {
+                    // asked for once
                     if (!p->terms_tried && terms_need > p->terms.bytes)
                         (void)dev_alloc(p, p->terms, terms_need, s);
                     p->terms_tried = true;
                     if (p->terms.bytes >= terms_need) terms = p->terms.ptr;
+                } else if (p->terms.bytes >= terms_need && p->ncaptured < p->kCaptured) {
+                    // The terms are written, and replays may run beside other
+                    // gradients of the plan: the captured call keeps this
+                    // space for the plan's life, the next call asks for its own.
+                    p->captured[p->ncaptured++] = p->terms;
+                    terms = p->terms.ptr;
+                    p->terms = DevBuf{};
+                    p->terms_tried = false;
                 }
                 if (!terms)
                     form = dB_val && bw_two_passes(shape, f64, false, true) ? BwForm::apart
@@ -1832,6 +1842,7 @@ void spgemm_plan_destroy(spgemm_plan p) {
     dev_free(p, p->ws, s);
     dev_free(p, p->bt, s);
     dev_free(p, p->terms, s);
+    for (int i = 0; i < p->ncaptured; ++i) dev_free(p, p->captured[i], s);
     dev_free(p, p->lbuf, s);
     // host memory that a publication or an upload may still reach goes to no
     // other plan

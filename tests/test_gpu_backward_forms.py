@@ -91,29 +91,29 @@ def test_two_streams():
 
 
 def test_replays_beside_other_gradients():
-    """Replays of captured gradients on one stream while eager ones of the same
-    plan run on another."""
+    """Replays of gradients captured twice (with the terms' space, and without
+    any left) on streams of their own while eager ones of the same plan run on
+    another."""
     print("[case] captured backward beside eager backward", flush=True)
-    At, Bt, Cm, plan, dev, want = _setup(*gen.powerlaw(60000, seed=8), 5)
+    At, Bt, Cm, plan, dev, want = _setup(*gen.powerlaw(60000, seed=8), 6)
     outs = [(torch.zeros_like(At.val), torch.zeros_like(Bt.val)) for _ in dev]
-    s, other = torch.cuda.Stream(), torch.cuda.Stream()
-    g = torch.cuda.CUDAGraph()
-    s.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(s):
-        with torch.cuda.graph(g, stream=s):
-            api.backward(plan, At.val, Bt.val, Cm.rowidx, dev[0], out=outs[0])
+    streams, other = [torch.cuda.Stream(), torch.cuda.Stream()], torch.cuda.Stream()
+    graphs = [torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()]
+    for g, s, G, out in zip(graphs, streams, dev, outs):
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            with torch.cuda.graph(g, stream=s):
+                api.backward(plan, At.val, Bt.val, Cm.rowidx, G, out=out)
     torch.cuda.synchronize()
     for r in range(3):
         for o in outs:
             o[0].zero_(), o[1].zero_()
         torch.cuda.synchronize()
-        with torch.cuda.stream(s):
-            g.replay()
-        for i in range(1, len(dev)):
-            api.backward(plan, At.val, Bt.val, Cm.rowidx, dev[i], out=outs[i], stream=other)
-            if i == 2:
+        for i in range(2, len(dev)):
+            for g, s in zip(graphs, streams):
                 with torch.cuda.stream(s):
                     g.replay()
+            api.backward(plan, At.val, Bt.val, Cm.rowidx, dev[i], out=outs[i], stream=other)
         torch.cuda.synchronize()
         for i, o in enumerate(outs):
             _equal(o, want[i], f"round {r}, gradient {i}")

@@ -277,20 +277,29 @@ def gradients_take_the_faster_form(h):
 
 
 @scenario
-def captured_gradients_only_read_the_view(h):
-    """Many products: two passes through the plan's terms, but not in a call under
-    capture, whose replays may run beside other gradients of the plan: there dB
+def captured_gradients_share_no_terms(h):
+    """Many products: two passes through the plan's terms. A call under capture,
+    whose replays may run beside other gradients of the plan, keeps the space it
+    finds and the next call takes its own; without any, or after the fourth, dB
     keeps its pass, which writes no terms, and dA is formed in one launch."""
-    h.entries = 400_000
-    h.header({BIN_ESC0: 4}, 3_000_000, 2_900_000)
-    assert h.symbolic(S1) == 0 and h.backward(S1) == 0 and h.backward(S1) == 0
-    assert form(h.log()) == "two"
-    h.capture(S2)
-    assert h.backward(S2) == 0 and form(h.log()) == "apart"
-    assert h.backward(S2, db=False) == 0 and form(h.log()) == "one"
-    assert h.backward(S2, da=False) == 0 and form(h.log()) == "first pass"
-    h.capture(None)
-    assert h.backward(S1) == 0 and form(h.log()) == "two"
+    h.entries, products = 400_000, 3_000_000
+    h.header({BIN_ESC0: 4}, products, 2_900_000)
+    terms = f"^alloc {8 * products} "
+    assert h.symbolic(S1) == 0
+    for i in range(6):
+        h.log()
+        assert h.backward(S1) == 0
+        log = h.log()
+        assert form(log) == "two" and count(log, terms) == (1 if i < 5 else 0), i
+        h.capture(S2)
+        assert h.backward(S2, da=False) == 0 and form(h.log()) == "first pass"
+        for again in range(2):
+            assert h.backward(S2) == 0
+            log = h.log()
+            assert form(log) == ("two" if i < 4 and again == 0 else "apart"), (i, again)
+            assert not count(log, "^alloc|^sync|^await"), log
+        assert h.backward(S2, db=False) == 0 and form(h.log()) == "one"
+        h.capture(None)
 
 
 @scenario
@@ -301,7 +310,8 @@ def terms_take_space_when_da_is_asked_for(h):
     h.header({BIN_ESC0: 4}, products, 2_900_000)
     assert h.symbolic(S1) == 0
     terms = f"^alloc {8 * products} "
-    for da, stream, want in ((False, S1, 0), (False, S1, 0), (True, S2, 0), (True, S1, 1), (True, S1, 0)):
+    for da, stream, want in ((False, S1, 0), (False, S1, 0), (True, S2, 0), (True, S1, 1), (True, S1, 0),
+                             (True, S2, 0), (True, S1, 1), (True, S1, 0)):
         h.capture(S2 if stream == S2 else None)
         h.log()
         assert h.backward(stream, da=da) == 0
