@@ -1315,20 +1315,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         const int *__restrict__ prow = a.hrow + hb;
         const V *__restrict__ pval = FILL ? (const V *)a.hval + hb : nullptr;
         // output position of the window: the entries of the earlier windows
-        int out = 0, c0 = 0, clen = 0;
+        int out = 0;
         if (FILL) {
-            const int2a cp = load_pair(d.ccp, j);
             for (int q = lane; q < w; q += 64) out += a.wcnt[wb + q];
             out = wave_sum(out);
-            c0 = cp.x;
-            clen = cp.y - c0;
-            // a launch at a previous structure's positions may meet windows
-            // that no launch has counted: any number stands there
-            if (out < 0 || out > clen) {
+            // A launch at a previous structure's positions may meet windows that
+            // no launch has counted, where any number stands: below zero it is
+            // refused here, beyond the column where an entry would be written.
+            if (out < 0) {
                 bad = 1;
                 continue;
             }
         }
+        int c0 = 0;
+        if (FILL) c0 = d.ccp[j];
         const int m = d.m;
         int sp = 0;
         if (lane == 0) {
@@ -1405,7 +1405,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                         acc = firstp ? V(0) + pval[e] : acc + pval[e];
                         firstp = false;
                     }
-                    if (total >= clen - out) bad = 1;
+                    if (total >= d.ccp[j + 1] - c0 - out) bad = 1;
                     else {
                         d.cri[c0 + out + total] = x;
                         ((V *)d.cv)[c0 + out + total] = acc;
@@ -1431,6 +1431,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                                                        L.mem, lane);
             const int runs = o.total;
             if constexpr (FILL) {
+                const int clen = d.ccp[j + 1] - c0;
                 if (total + runs > clen - out) bad = 1;
                 else one_emit<K, V, KPL>(d, key, v, o, (long long)c0 + out + total, L.mem, lane);
             }

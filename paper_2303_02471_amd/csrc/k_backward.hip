@@ -11,8 +11,8 @@
 // times the u-th entry of A's column bri[t]. A view built once per plan
 // records, in product order, the place of every product's G(i,j) among C's
 // entries (gpos, by binary search of C's sorted rows); per stored B entry its
-// first product (pofs) and the first of its terms of dA (woff); per stored A
-// entry its terms of dA.
+// first product (pofs) and the first of its terms of dA (woff), and the entries
+// of every row of B by ascending column; per stored A entry its terms of dA.
 //
 // Two forms, the same sums. Two passes over the products: the first walks them
 // in product order, where a column's G values lie together; it loads G once,
@@ -23,6 +23,8 @@
 // read twice, for dA all over C, and the longest list sets the time (6.4 M
 // float products, 8 per entry: 87 us, in two passes 31 + 8; 5 M double products
 // of power-law columns: 324 us, in two passes 88 + 11). bw_two_passes chooses.
+// Where it asks for two passes but the terms have no space, dB keeps its pass and
+// dA is formed in the one launch.
 #include <algorithm>
 #include <cmath>
 
