@@ -31,7 +31,9 @@
  * workspace (from the allocator of spgemm_set_allocator, by default
  * stream-ordered hipMallocAsync) and frees it in spgemm_plan_destroy. A plan
  * may be used on another stream than its last call's: the new call is
- * ordered after the plan's earlier work without a host wait.
+ * ordered after the plan's earlier work without a host wait (a numeric or
+ * gradient call waits for the device if that stream has been destroyed since;
+ * captured calls and their replays are kept apart by the caller).
  *
  * Errors: every call returns a status code; nothing aborts or throws across
  * the ABI. On error, outputs are unspecified. Input checks that keep every
